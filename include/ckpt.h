@@ -119,7 +119,10 @@ int ckpt_eval_peak(const int64_t *d, const uint8_t *mask, const ckpt_layout *lay
  * (0 and every sum of a contiguous range inside d_1..d_{n-1}) the least
  * checkpoint memory c_s whose segments all fit in s, by the recurrence of
  * Equation (T); the answer is min_s (s + c_s) with d_0 and d_n checkpoints.
- * n <= CKPT_CUBIC_MAX_LAYERS.
+ * n <= CKPT_CUBIC_MAX_LAYERS.  For chains of up to 256 layers the minimum is
+ * found without running the recurrence for every budget (c_s does not grow with
+ * s, so a few evaluated budgets settle the others; the results are the same);
+ * ckpt_solve_cubic_costs runs it for each one.
  * Canonical result: budget_out[c] is the smallest optimal budget value s*;
  * the set is built from position n by taking, each time, the smallest
  * feasible predecessor of minimal value.
@@ -150,8 +153,8 @@ int ckpt_solve_cubic(const int64_t *d, const ckpt_layout *layout, uint8_t *mask_
  * are solved without pruning.
  * evaluated_out [out] `batch` int64 or NULL: the number of budgets whose
  * recurrence was run (sampled ones counted again when they run a second time),
- * times n the recurrence cells actually evaluated; ckpt_solve_cubic always
- * runs n(n-1)/2 + 1.  Other arguments and workspace as for ckpt_solve_cubic. */
+ * times n the recurrence cells actually evaluated; without pruning it is
+ * n(n-1)/2 + 1.  Other arguments and workspace as for ckpt_solve_cubic. */
 int ckpt_solve_cubic_pruned(const int64_t *d, const ckpt_layout *layout, uint8_t *mask_out,
                             int64_t *peak_out, int64_t *budget_out, int64_t *evaluated_out,
                             int32_t *status_out, void *ws, size_t ws_bytes, void *hip_stream);

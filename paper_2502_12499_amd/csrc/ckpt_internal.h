@@ -85,6 +85,17 @@ __device__ inline uint32_t wave_min_u32(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// Lexicographic minimum of (a, b) over the wave; every lane gets the result.  Both values are
+// non-negative wherever this is used (costs, budgets, indices, kInf), so they order as unsigned:
+// the smallest a, then the smallest b among the lanes that hold it.
+__device__ inline void wave_min_pair(int64_t &a, int64_t &b)
+{
+    const uint64_t am = wave_min_u64((uint64_t)a);
+    const uint64_t bm = wave_min_u64((uint64_t)a == am ? (uint64_t)b : ~0ull);
+    a = (int64_t)am;
+    b = (int64_t)bm;
+}
+
 // ---- eval_peak ---------------------------------------------------------------
 hipError_t launch_eval_peak(const int64_t *d, const uint8_t *mask, int64_t batch, int n, Strides st,
                             int objective, int64_t *peak_out, int32_t *status_out, hipStream_t stream);
@@ -119,6 +130,11 @@ hipError_t launch_solve_cubic(const int64_t *d, int64_t batch, int n, Strides st
                               int64_t *peak_out, int64_t *budget_out, int32_t *status_out, bool pruned,
                               int64_t *evaluated_out, int64_t *trace_s, int64_t *trace_cost, void *ws,
                               hipStream_t stream);
+// the unpruned call without the costs, for chains of up to kSearchMaxLayers layers; ws: 256 + 4 * batch bytes
+constexpr int kSearchMaxLayers = 256;
+hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
+                               int64_t *peak_out, int64_t *budget_out, int32_t *status_out, void *ws,
+                               hipStream_t stream);
 // entries per chain of the two trace arrays: one per lane of the chain's waves of 64 budgets
 int64_t cubic_trace_len(int n);
 

@@ -8,6 +8,9 @@
 // the answer is min_s (s + c_s) over the budgets s = 0 and s = P[b] - P[a-1],
 // 1 <= a <= b <= n-1.
 //
+// Chains of up to kSearchMaxLayers layers take the search of cubic_search.hip instead, except where the call
+// asks for the cost or the number of the budgets it runs (ckpt_solve_cubic_costs, _pruned).
+//
 // Kernels, all on the caller's stream, in this order (from 1024 layers on, links
 // and slices share one launch: neither needs the other):
 //   prologue  one wave per chain: validates the sizes, builds P by a wave scan,
@@ -230,17 +233,6 @@ __host__ CubicWs carve_cubic(void *ws, int64_t batch, int n)
 __device__ inline int64_t shfl_i64(int64_t v, int src) { return __shfl(v, src, kWave); }
 __device__ inline int64_t shfl_xor_i64(int64_t v, int m) { return __shfl_xor(v, m, kWave); }
 __device__ inline int64_t shfl_up_i64(int64_t v, int d) { return __shfl_up(v, d, kWave); }
-
-// Lexicographic minimum of (a, b) over the wave; every lane gets the result.  Both values are
-// non-negative wherever this is used (costs, budgets, indices, kInf), so they order as unsigned:
-// the smallest a, then the smallest b among the lanes that hold it.
-__device__ inline void wave_min_pair(int64_t &a, int64_t &b)
-{
-    const uint64_t am = wave_min_u64((uint64_t)a);
-    const uint64_t bm = wave_min_u64((uint64_t)a == am ? (uint64_t)b : ~0ull);
-    a = (int64_t)am;
-    b = (int64_t)bm;
-}
 
 // ---- prologue ---------------------------------------------------------------
 
@@ -2097,6 +2089,10 @@ hipError_t launch_solve_cubic(const int64_t *d, int64_t batch, int n, Strides st
                               hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
+    // (the limit: the search keeps 4 or 8 bytes per position for each of its 64 points in LDS; at 256 layers that is
+    // 74 or 148 KB of the CU's 160)
+    if (n <= kSearchMaxLayers && !pruned && !trace_s)
+        return launch_cubic_search(d, batch, n, st, mask_out, peak_out, budget_out, status_out, ws, stream);
     pruned = pruned && n >= kPruneFromLayers;
     CubicWs w = carve_cubic(ws, batch, n);
     const int64_t K = num_budgets(n);

@@ -1,0 +1,71 @@
+"""ckpt_solve_cubic on the lengths and sizes where its search over the budgets changes form, against the
+oracle: blocks of eight positions, slices of 64, 32- and 64-bit arithmetic, prefix sums beyond 32 bits,
+repeated budgets, ties, batches on both sides of the split into two launches."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_12499_amd import binding as B
+from paper_2502_12499_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(d, chain_major=False):
+    dc = inputs.chain_major(d)
+    t = torch.from_numpy(dc if chain_major else np.ascontiguousarray(d)).cuda()
+    mask, peak, budget, status = B.ckpt_solve_cubic(t, chain_major=chain_major)
+    torch.cuda.synchronize()
+    want_peak, want_mask, want_s = oracle.batch_solve_static(dc)
+    got = mask.cpu().numpy()
+    assert (status.cpu().numpy() == 0).all()
+    assert np.array_equal(peak.cpu().numpy(), want_peak)
+    assert np.array_equal(budget.cpu().numpy(), want_s)
+    assert np.array_equal(got if chain_major else got.T, want_mask)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 7, 8, 9, 16, 63, 64, 65, 127, 128, 129, 255, 256])
+def test_lengths_and_kinds_of_sizes(n):
+    rng = np.random.default_rng(n)
+    b = 24 if n <= 65 else 4
+    print(f"cubic search: n = {n}", flush=True)
+    check(inputs.uniform_aligned_chains(n, n, b, 256, 32768), chain_major=n % 2 == 1)
+    check(inputs.log_uniform_chains(n, n, b))                                    # sums beyond 32 bits
+    check(rng.integers(1, (1 << 62) // (n + 2), size=(n + 1, b)).astype(np.int64))  # 64-bit arithmetic
+    check(rng.integers(1, 4, size=(n + 1, b)).astype(np.int64))                  # ties, few values
+    check((1 << rng.integers(0, 40, size=(n + 1, b))).astype(np.int64))          # one layer outweighs the rest
+    check(np.arange(1, n + 2, dtype=np.int64)[:, None].repeat(2, 1))
+    alternating = np.ones((n + 1, 2), dtype=np.int64)
+    alternating[::2, 0] = 1000003
+    alternating[1::2, 1] = 999999937
+    check(alternating)
+
+
+@pytest.mark.parametrize("batch", [1023, 1024, 1600])
+def test_batches_on_both_sides_of_the_split(batch):
+    d = inputs.uniform_aligned_chains(3, 20, batch, 256, 32768)
+    wide = np.random.default_rng(batch).integers(1, 1 << 50, size=(21, batch)).astype(np.int64)
+    d[:, ::7] = wide[:, ::7]                                                     # every seventh needs 64 bits
+    check(d)
+
+
+def test_bad_chains_are_reported_alone():
+    d = inputs.uniform_aligned_chains(4, 30, 1100, 256, 32768)
+    dc = inputs.chain_major(d)
+    want_peak, want_mask, want_s = oracle.batch_solve_static(dc)
+    d[5, 3] = 0
+    d[:, 700] = (1 << 62) + 1
+    d[30, 1099] = -1
+    for batch in (800, 1100):
+        mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d[:, :batch])).cuda())
+        torch.cuda.synchronize()
+        bad = np.array([c for c in (3, 700, 1099) if c < batch])
+        ok = np.setdiff1d(np.arange(batch), bad)
+        st = status.cpu().numpy()
+        assert (st[ok] == 0).all() and st[bad].tolist() == [3, 4, 3][:len(bad)]
+        assert (peak.cpu().numpy()[bad] == -1).all() and (budget.cpu().numpy()[bad] == -1).all()
+        assert not mask.cpu().numpy()[:, bad].any()
+        assert np.array_equal(peak.cpu().numpy()[ok], want_peak[ok])
+        assert np.array_equal(budget.cpu().numpy()[ok], want_s[ok])
+        assert np.array_equal(mask.cpu().numpy().T[ok], want_mask[ok])
