@@ -274,8 +274,8 @@ int ckpt_solve_quadratic(const int64_t *d, const ckpt_layout *layout, uint8_t *m
  *       workspace itself (from pageable host memory these are the slowest
  *       steps of a call on a large batch).  With a device copy the lengths are
  *       counted and checked on the device and offsets_host is not read (it may
- *       be NULL), except by ckpt_ragged_solve_cubic, which launches length by
- *       length and always plans on the host.
+ *       be NULL), except by ckpt_ragged_solve_cubic, which always plans on the
+ *       host.
  *   ws: ckpt_ragged_workspace_bytes(which, offsets_host, batch) bytes, 256-byte
  *       aligned; it receives the counts of the lengths, the table of groups
  *       (the chains of one length), the chains' places grouped by length

@@ -135,6 +135,15 @@ constexpr int kSearchMaxLayers = 256;
 hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
                                int64_t *peak_out, int64_t *budget_out, int32_t *status_out, void *ws,
                                hipStream_t stream);
+// The same for a ragged batch whose chains all have up to kSearchMaxLayers layers, on the flat arrays
+// themselves.  A launch per class of lengths (its LDS is that of the longest chain in it); longest[k]: the
+// longest chain of class k, 0 if it has none.  count: one value, list: `batch` values of scratch.
+constexpr int kSearchClasses = 4;
+inline int search_class_limit(int k) { return 32 << k; }
+static_assert((32 << (kSearchClasses - 1)) == kSearchMaxLayers, "the last class ends where the search does");
+hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch, const int *longest,
+                                      uint8_t *mask_out, int64_t *peak_out, int64_t *budget_out, int32_t *status_out,
+                                      int32_t *count, int32_t *list, hipStream_t stream);
 // entries per chain of the two trace arrays: one per lane of the chain's waves of 64 budgets
 int64_t cubic_trace_len(int n);
 

@@ -717,6 +717,39 @@ __global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t 
     }
 }
 
+// The chains of a ragged batch that have n_lo .. n_hi layers, each where it lies in the flat array.
+template <bool WIDE>
+__global__ __launch_bounds__(kWave) void cubic_search_ragged_kernel(const int64_t *__restrict__ d,
+                                                                    const int64_t *__restrict__ off, int n_lo, int n_hi,
+                                                                    uint8_t *__restrict__ mask_out,
+                                                                    int64_t *__restrict__ peak_out,
+                                                                    int64_t *__restrict__ budget_out,
+                                                                    int32_t *__restrict__ status_out, SearchWs w)
+{
+    const int64_t c = blockIdx.x, o = off[c], n = off[c + 1] - o - 1;
+    if (n < n_lo || n > n_hi) return;
+    const bool done = search_one<true, WIDE>(d + o, 1, (int)n, mask_out + o, 1, peak_out + c,
+                                             budget_out ? budget_out + c : nullptr,
+                                             status_out ? status_out + c : nullptr);
+    if (!WIDE && !done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
+}
+
+__global__ __launch_bounds__(kWave) void cubic_search_ragged_wide_kernel(const int64_t *__restrict__ d,
+                                                                         const int64_t *__restrict__ off,
+                                                                         uint8_t *__restrict__ mask_out,
+                                                                         int64_t *__restrict__ peak_out,
+                                                                         int64_t *__restrict__ budget_out,
+                                                                         int32_t *__restrict__ status_out, SearchWs w)
+{
+    const int count = *w.count;
+    for (int item = blockIdx.x; item < count; item += gridDim.x) {
+        const int64_t c = w.list[item], o = off[c], n = off[c + 1] - o - 1;
+        (void)search_one<false, true>(d + o, 1, (int)n, mask_out + o, 1, peak_out + c,
+                                      budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr);
+        __syncthreads();
+    }
+}
+
 constexpr int kMaxDevices = 64;
 std::atomic<bool> search_lds_raised[kMaxDevices];
 
@@ -730,7 +763,9 @@ hipError_t raise_search_lds_limit()
     if (search_lds_raised[dev].load(std::memory_order_acquire)) return hipSuccess;
     const int most = (int)search_lds_bytes(kSearchMaxLayers, 8);
     for (const void *f : {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
-                          (const void *)cubic_search_wide_kernel}) {
+                          (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel<true>,
+                          (const void *)cubic_search_ragged_kernel<false>,
+                          (const void *)cubic_search_ragged_wide_kernel}) {
         e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most);
         if (e != hipSuccess) return e;
     }
@@ -766,6 +801,35 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
         hipLaunchKernelGGL(cubic_search_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(n, 8), stream, d,
                            n, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch, const int *longest,
+                                      uint8_t *mask_out, int64_t *peak_out, int64_t *budget_out, int32_t *status_out,
+                                      int32_t *count, int32_t *list, hipStream_t stream)
+{
+    if (batch == 0) return hipSuccess;
+    const hipError_t e = raise_search_lds_limit();
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)batch), block(kWave);
+    const SearchWs w{count, list};
+    const bool wide = batch < kSearchSplitFrom;
+    if (!wide) hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
+    int all = 0;
+    for (int k = kSearchClasses - 1; k >= 0; --k) {  // the longest chains first
+        const int n = longest[k], below = k > 0 ? search_class_limit(k - 1) + 1 : 1;
+        if (n == 0) continue;
+        all = all > n ? all : n;
+        if (wide)
+            hipLaunchKernelGGL(cubic_search_ragged_kernel<true>, grid, block, search_lds_bytes(n, 8), stream, d,
+                               offsets_dev, below, n, mask_out, peak_out, budget_out, status_out, w);
+        else
+            hipLaunchKernelGGL(cubic_search_ragged_kernel<false>, grid, block, search_lds_bytes(n, 4), stream, d,
+                               offsets_dev, below, n, mask_out, peak_out, budget_out, status_out, w);
+    }
+    if (!wide)
+        hipLaunchKernelGGL(cubic_search_ragged_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(all, 8),
+                           stream, d, offsets_dev, mask_out, peak_out, budget_out, status_out, w);
     return hipGetLastError();
 }
 

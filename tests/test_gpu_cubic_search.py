@@ -69,3 +69,30 @@ def test_bad_chains_are_reported_alone():
         assert np.array_equal(peak.cpu().numpy()[ok], want_peak[ok])
         assert np.array_equal(budget.cpu().numpy()[ok], want_s[ok])
         assert np.array_equal(mask.cpu().numpy().T[ok], want_mask[ok])
+
+
+@pytest.mark.parametrize("batch,offsets_on_device", [(300, False), (1500, True)])
+def test_ragged_batches_of_short_chains(batch, offsets_on_device):
+    """Every class of lengths, both arithmetics, a bad chain among them."""
+    rng = np.random.default_rng(batch)
+    lengths = np.concatenate([np.array([1, 2, 32, 33, 64, 65, 128, 129, 256]), rng.integers(1, 40, size=batch - 9)])
+    rng.shuffle(lengths)
+    d, _, off = inputs.ragged_batch(batch, lengths)
+    for c in range(0, batch, 5):                                                 # 64-bit arithmetic
+        d[off[c]:off[c + 1]] = rng.integers(1, 1 << 52, size=off[c + 1] - off[c])
+    want_peak, want_mask, want_s = oracle.ragged_solve_static(d, off)
+    bad = batch // 2
+    d[off[bad]] = -5
+    t = torch.from_numpy(d).cuda()
+    mask, peak, budget, status = B.ckpt_ragged_solve_cubic(
+        t, off, offsets_dev=torch.from_numpy(off).cuda() if offsets_on_device else None)
+    torch.cuda.synchronize()
+    ok = np.arange(batch) != bad
+    st = status.cpu().numpy()
+    assert (st[ok] == 0).all() and st[bad] == 3
+    assert np.array_equal(peak.cpu().numpy()[ok], want_peak[ok]) and peak.cpu().numpy()[bad] == -1
+    assert np.array_equal(budget.cpu().numpy()[ok], want_s[ok]) and budget.cpu().numpy()[bad] == -1
+    got = mask.cpu().numpy()
+    keep = np.ones(len(d), dtype=bool)
+    keep[off[bad]:off[bad + 1]] = False
+    assert np.array_equal(got[keep], want_mask[keep]) and not got[~keep].any()
