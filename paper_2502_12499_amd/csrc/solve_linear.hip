@@ -57,6 +57,7 @@
 #include "ckpt_internal.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace ckpt {
 namespace {
@@ -76,7 +77,8 @@ struct LinearWs {
 
 // Full-capacity state of one chain: qM, qT, recD (int64), qJ, recK, nxt (int32), padded to 256 bytes.
 __host__ __device__ inline size_t stack_bytes(int n) { return (((size_t)n + 1) * 36 + 255) / 256 * 256; }
-__host__ __device__ inline size_t lds_stack_bytes(int n) { return ((size_t)n + 1) * 32; }
+// In LDS positions are 16-bit, and nxt lies there too: the call that allocates nothing has no room for it elsewhere.
+__host__ __device__ inline size_t lds_stack_bytes(int n) { return ((size_t)n + 1) * 30; }
 
 __host__ LinearWs carve_linear(void *ws, int64_t batch, int n)
 {
@@ -700,14 +702,15 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
 {
     const int count = w.count[1];
     const size_t n1 = (size_t)n_all + 1;
-    char *base = w.scratch + (size_t)blockIdx.x * stack_bytes(n_all);
-    int32_t *nxt = (int32_t *)(base + n1 * 32);
-    if (LDS_STACKS) base = (char *)lin_lds;
+    typedef std::conditional_t<LDS_STACKS, uint16_t, int32_t> Pos;
+    static_assert(kLdsStackMaxN < 65536, "positions in LDS");
+    char *base = LDS_STACKS ? (char *)lin_lds : w.scratch + (size_t)blockIdx.x * stack_bytes(n_all);
     int64_t *qM = (int64_t *)base;
     int64_t *qT = qM + n1;
     int64_t *recD = qT + n1;
-    int32_t *qJ = (int32_t *)(recD + n1);
-    int32_t *recK = qJ + n1;
+    Pos *qJ = (Pos *)(recD + n1);
+    Pos *recK = qJ + n1;
+    Pos *nxt = recK + n1;
 
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
         if (threadIdx.x != 0) continue;
@@ -728,7 +731,7 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
         bool bad_size = x <= 0;
         bool ovf = false;
         int64_t dmax = x;
-        qJ[0] = n;
+        qJ[0] = (Pos)n;
         qM[0] = x;
         qT[0] = 0;
         int hd = 0, pt = 0;    // Q occupies slots 0..hd, crossover at pt
@@ -752,7 +755,7 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
             while (top >= 0 && recD[top] <= di) --top;
             ++top;
             recD[top] = di;
-            recK[top] = i;
+            recK[top] = (Pos)i;
             if (rp > top) rp = top;
 
             while (pt < hd) {
@@ -774,11 +777,11 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
                 }
             }
             Mi = di + best;
-            nxt[i] = nx;
+            nxt[i] = (Pos)nx;
 
             while (hd > pt && qM[hd] >= Mi) --hd;
             ++hd;
-            qJ[hd] = i;
+            qJ[hd] = (Pos)i;
             qM[hd] = Mi;
             qT[hd] = Ti;
         }

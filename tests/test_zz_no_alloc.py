@@ -60,3 +60,21 @@ def test_limits_are_host_errors():
     assert lib.ckpt_solve_linear_noalloc(fake, ctypes.byref(over_batch), fake, fake, None, None) == 2
     assert lib.ckpt_solve_linear_noalloc(fake, ctypes.byref(over_n), fake, fake, None, None) == 2
     assert lib.ckpt_solve_linear_noalloc(None, ctypes.byref(B.Layout(4, 8, 1, 4)), fake, fake, None, None) == 1
+
+
+def test_the_last_kernel_at_the_largest_batch():
+    """With the largest batch the lists fill the library's array to its end: chains that go through both
+    lists (sizes that are not positive, found after most of the chain) must not need room behind them."""
+    n, batch = 24, 1048576
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    d = torch.randint(256, 32769, (n + 1, batch), generator=gen, device=DEV, dtype=torch.int64) * 4096
+    bad = torch.arange(0, batch, 100003, device=DEV)
+    d[0, bad] = 0
+    want = B.ckpt_solve_linear(d)
+    mask, peak, status = torch.full_like(want[0], 7), torch.full_like(want[1], -5), torch.full_like(want[2], -5)
+    torch.cuda.synchronize()
+    B.ckpt_solve_linear_noalloc(d, mask, peak, status)
+    torch.cuda.synchronize()
+    assert int((want[2] != 0).sum()) == len(bad)
+    same(want, (mask, peak, status))
