@@ -162,15 +162,27 @@ struct RaggedGroupDev {
     int64_t stage_off;
     int64_t pitch;
     int32_t tiles_x;  // tiles across the chains: ceil(count / 64)
-    int32_t pad;
+    int32_t linear_first;  // the linear solver's first wave of the group: it numbers its waves on its own
 };
 
 // The sums over the groups laid out so far (all of them at the end); `bad` is set by the device's
 // count of the lengths when an offset is out of range.
 struct RaggedTotals {
     int32_t n_groups, bad, max_layers, pad;
-    int64_t chains, waves, tiles, tiles2, staged;
+    int64_t chains, waves, linear_waves, tiles, tiles2, staged;
 };
+
+// Groups whose chains the linear solver gives a wave each instead of a lane each: few chains (they would fill a
+// handful of waves) and long ones (whose lane-per-chain form takes 660 ns a position, four times what a wave per
+// chain takes; 65,536 chains with sixteen of 1,001 layers among them: 0.70 ms -> 0.30 ms).
+__host__ __device__ inline bool ragged_wave_per_chain(int n, int64_t count)
+{
+    return n > 256 && n <= 4095 && count <= 1024;
+}
+__host__ __device__ inline int64_t ragged_linear_waves(int n, int64_t count)
+{
+    return ragged_wave_per_chain(n, count) ? count : (count + 63) / 64;
+}
 
 // Elements from one position to the next in a group's staging: rows start on 256 bytes for groups
 // of 32 chains or more, on 64 bytes for smaller ones (a lone long chain is not blown up 32 times).
@@ -193,12 +205,13 @@ __host__ __device__ inline RaggedGroupDev ragged_next_group(RaggedTotals &t, int
     g.stage_off = t.staged;
     g.pitch = ragged_pitch(many);
     g.tiles_x = (int32_t)((many + 63) / 64);
-    g.pad = 0;
+    g.linear_first = (int32_t)t.linear_waves;
     *tile_first2 = t.tiles2;
     t.n_groups += 1;
     t.max_layers = n;
     t.chains += many;
     t.waves += (many + 63) / 64;
+    t.linear_waves += ragged_linear_waves(n, many);
     t.tiles += (int64_t)g.tiles_x * ((n + 1 + 63) / 64);
     t.tiles2 += (int64_t)g.tiles_x * ((2 * n + 2 + 63) / 64);
     t.staged += ((int64_t)(n + 1) * g.pitch + 31) / 32 * 32;  // the next group starts on 256 bytes
@@ -212,6 +225,15 @@ __device__ inline int ragged_group_of_wave(const RaggedGroupDev *g, int n_groups
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if ((int64_t)g[mid].wave_first <= wave) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+__device__ inline int ragged_group_of_linear_wave(const RaggedGroupDev *g, int n_groups, int64_t wave)
+{
+    int lo = 0, hi = n_groups - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if ((int64_t)g[mid].linear_first <= wave) lo = mid; else hi = mid - 1;
     }
     return lo;
 }

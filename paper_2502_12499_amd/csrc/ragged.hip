@@ -66,69 +66,117 @@ __global__ __launch_bounds__(kCountThreads) void ragged_count_kernel(const int64
     }
 }
 
-// Exclusive prefix sum of one value per thread over the workgroup (kCountThreads threads);
-// `wave_sum` is LDS for one value per wave.
-__device__ inline int64_t block_exclusive_sum(int64_t v, int64_t *wave_sum)
+// Exclusive prefix sums of N values per thread over the workgroup (kCountThreads threads), and their totals.
+constexpr int kSums = 7;
+__device__ inline void block_exclusive_sums(int64_t (&v)[kSums], int64_t (&total)[kSums],
+                                            int64_t (&wave_sum)[kCountThreads / kWave][kSums])
 {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    int64_t incl = v;
+    int64_t incl[kSums];
 #pragma unroll
+    for (int q = 0; q < kSums; ++q) incl[q] = v[q];
+#pragma unroll 1
     for (int s = 1; s < kWave; s <<= 1) {
-        const int64_t up = __shfl_up(incl, s, kWave);
-        if (lane >= s) incl += up;
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) {
+            const int64_t up = __shfl_up(incl[q], s, kWave);
+            if (lane >= s) incl[q] += up;
+        }
     }
     __syncthreads();  // (the previous call's readers are done with wave_sum)
-    if (lane == kWave - 1) wave_sum[wave] = incl;
+    if (lane == kWave - 1) {
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) wave_sum[wave][q] = incl[q];
+    }
     __syncthreads();
-    int64_t before = 0;
-    for (int k = 0; k < wave; ++k) before += wave_sum[k];
-    return before + incl - v;
+    int64_t before[kSums] = {};
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) total[q] = 0;
+#pragma unroll 1
+    for (int k = 0; k < kCountThreads / kWave; ++k) {
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) {
+            const int64_t x = wave_sum[k][q];
+            before[q] += k < wave ? x : 0;
+            total[q] += x;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kSums; ++q) v[q] = before[q] + incl[q] - v[q];
 }
 
-// One workgroup: thread t takes the lengths t*span+1 .. (t+1)*span, first adds up what its groups
-// contribute to the totals, then, knowing the totals of the threads before it, writes their
-// descriptors.  The last thread's totals are the call's.
+// One workgroup: the lengths in tiles of kCountThreads, a length per thread.  Most of the 65,535 possible lengths do
+// not occur, so the tiles that hold none are found first (every thread reads its length of every tile, all
+// loads in flight) and passed over; in a tile that holds some, every thread adds up what its group
+// contributes to the totals and, knowing the totals before it, writes the group's descriptor.  (A
+// thread per stretch of 64 lengths, each walked twice, took 65 us; this takes 16.)
 __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint32_t *__restrict__ hist, int max_layers,
                                                                       RaggedGroupDev *__restrict__ groups,
                                                                       int64_t *__restrict__ tile_first2,
                                                                       RaggedTotals *__restrict__ totals)
 {
-    __shared__ int64_t wave_sum[kCountThreads / kWave];
+    __shared__ int64_t wave_sum[kCountThreads / kWave][kSums];
+    __shared__ unsigned long long used;  // bit k: some length of tile k occurs
     __shared__ int longest;
-    if (threadIdx.x == 0) longest = 0;
-    const int span = (max_layers + kCountThreads - 1) / kCountThreads;
-    const int n_lo = (int)threadIdx.x * span + 1, n_hi = min(n_lo + span - 1, max_layers);
-    RaggedTotals mine = {};
-    for (int n = n_lo; n <= n_hi; ++n) {
-        const int64_t many = hist[n];
-        int64_t unused;
-        if (many) (void)ragged_next_group(mine, n, many, &unused);
+    constexpr int kTiles = (CKPT_MAX_LAYERS + kCountThreads - 1) / kCountThreads;
+    static_assert(kTiles <= 64, "one bit per tile");
+    if (threadIdx.x == 0) {
+        longest = 0;
+        used = 0;
     }
-    RaggedTotals t = {};
-    t.n_groups = (int32_t)block_exclusive_sum(mine.n_groups, wave_sum);
-    t.chains = block_exclusive_sum(mine.chains, wave_sum);
-    t.waves = block_exclusive_sum(mine.waves, wave_sum);
-    t.tiles = block_exclusive_sum(mine.tiles, wave_sum);
-    t.tiles2 = block_exclusive_sum(mine.tiles2, wave_sum);
-    t.staged = block_exclusive_sum(mine.staged, wave_sum);
-    for (int n = n_lo; n <= n_hi; ++n) {
-        const int64_t many = hist[n];
-        if (!many) continue;
-        const int at = t.n_groups;
-        int64_t first2;
-        groups[at] = ragged_next_group(t, n, many, &first2);
-        tile_first2[at] = first2;
-    }
-    if (mine.n_groups) atomicMax(&longest, mine.max_layers);
     __syncthreads();
-    if (threadIdx.x == kCountThreads - 1) {
-        totals->n_groups = t.n_groups;
+    unsigned long long mine = 0;
+#pragma unroll 16
+    for (int k = 0; k < kTiles; ++k) {  // (a load behind a branch would wait for the one before it)
+        const int n = 1 + k * kCountThreads + (int)threadIdx.x;
+        const bool some = hist[n <= max_layers ? n : max_layers] != 0 && n <= max_layers;
+        mine |= some ? 1ull << k : 0;
+    }
+    if (mine) {
+        atomicOr(&used, mine);
+        atomicMax(&longest, 1 + (63 - __clzll(mine)) * kCountThreads + (int)threadIdx.x);
+    }
+    __syncthreads();
+    RaggedTotals at = {};  // the totals before the tile
+    for (unsigned long long todo = used; todo != 0; todo &= todo - 1) {
+        const int n = 1 + (__ffsll(todo) - 1) * kCountThreads + (int)threadIdx.x;
+        const int64_t many = n <= max_layers ? hist[n] : 0;
+        RaggedTotals one = {};
+        int64_t first2;
+        if (many) (void)ragged_next_group(one, n, many, &first2);
+        int64_t v[kSums] = {one.n_groups, one.chains, one.waves, one.linear_waves, one.tiles, one.tiles2, one.staged};
+        int64_t all[kSums];
+        block_exclusive_sums(v, all, wave_sum);
+        if (many) {
+            RaggedTotals t = {};
+            t.n_groups = at.n_groups + (int32_t)v[0];
+            t.chains = at.chains + v[1];
+            t.waves = at.waves + v[2];
+            t.linear_waves = at.linear_waves + v[3];
+            t.tiles = at.tiles + v[4];
+            t.tiles2 = at.tiles2 + v[5];
+            t.staged = at.staged + v[6];
+            const int slot = t.n_groups;
+            groups[slot] = ragged_next_group(t, n, many, &first2);
+            tile_first2[slot] = first2;
+        }
+        at.n_groups += (int32_t)all[0];
+        at.chains += all[1];
+        at.waves += all[2];
+        at.linear_waves += all[3];
+        at.tiles += all[4];
+        at.tiles2 += all[5];
+        at.staged += all[6];
+    }
+    if (threadIdx.x == 0) {
+        totals->n_groups = at.n_groups;
         totals->max_layers = longest;
-        totals->chains = t.chains;
-        totals->waves = t.waves;
-        totals->tiles = t.tiles;
-        totals->tiles2 = t.tiles2;
-        totals->staged = t.staged;
+        totals->chains = at.chains;
+        totals->waves = at.waves;
+        totals->linear_waves = at.linear_waves;
+        totals->tiles = at.tiles;
+        totals->tiles2 = at.tiles2;
+        totals->staged = at.staged;
     }
 }
 
@@ -417,7 +465,7 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
     if (which == CKPT_CALL_EVAL_PEAK) {
         e = launch_eval_peak_ragged(sd, smask, groups, n_groups, p.t.waves, batch, objective, speak, sstatus, stream);
     } else if (which == CKPT_CALL_SOLVE_LINEAR) {
-        e = launch_solve_linear_ragged(sd, groups, n_groups, p.t.waves, batch, p.t.max_layers, smask, speak, sstatus,
+        e = launch_solve_linear_ragged(sd, groups, n_groups, p.t.linear_waves, batch, p.t.max_layers, smask, speak, sstatus,
                                        base + w.inner, stream);
     } else if (which == CKPT_CALL_EVAL_TIMELINE) {
         e = launch_eval_timeline_ragged(sd, smask, groups, n_groups, p.t.waves, objective, swide, sstatus, stream);

@@ -38,7 +38,7 @@ int ragged_check_totals(const RaggedTotals &t, int64_t batch)
 {
     // a padded staging is at most 8 times the sizes themselves (one chain to a group everywhere);
     // launches are 32-bit
-    if (t.chains != batch || t.staged > INT64_MAX / 64 || t.tiles2 > 0x7fffffffLL || t.waves > 0x7fffffffLL)
+    if (t.chains != batch || t.staged > INT64_MAX / 64 || t.tiles2 > 0x7fffffffLL || t.waves > 0x7fffffffLL || t.linear_waves > 0x7fffffffLL)
         return CKPT_ERR_SHAPE;
     return CKPT_OK;
 }

@@ -59,6 +59,9 @@
 #include <atomic>
 #include <type_traits>
 
+// v_writelane_b32 (the compiler has an intrinsic for it, but no builtin)
+extern "C" __device__ int ckpt_write_lane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
 namespace ckpt {
 namespace {
 
@@ -534,28 +537,6 @@ __global__ __launch_bounds__(kWave) void linear_ring_kernel(const int64_t *__res
                                gridDim.x, 0, ring);
 }
 
-// Every group of a ragged call in one launch: a wave looks up the group its 64 chains belong to
-// and solves them where that group is staged, with the step log in registers if the group's
-// chains have up to kLogMaxLayers layers (a wave-uniform branch: long and short groups run side by
-// side on the chip).  Results go to the chains' places.
-__global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t *__restrict__ d_stage,
-                                                                   const RaggedGroupDev *__restrict__ groups,
-                                                                   int n_groups, uint8_t *__restrict__ mask_stage,
-                                                                   int64_t *__restrict__ peak_stage,
-                                                                   int32_t *__restrict__ status_stage, LinearWs w)
-{
-    __shared__ __attribute__((aligned(4096))) uint32_t ring[kPlanes][kRing][kWave];
-    const RaggedGroupDev g = groups[ragged_group_of_wave(groups, n_groups, blockIdx.x)];
-    const unsigned waves = (unsigned)((g.count + kWave - 1) / kWave);
-    const unsigned block = blockIdx.x - (unsigned)g.wave_first;
-    if (g.n <= kLogMaxLayers)
-        linear_ring_wave<true>(d_stage + g.stage_off, g.count, g.n, 1, g.pitch, mask_stage + g.stage_off,
-                               peak_stage + g.first, status_stage + g.first, w, block, waves, g.first, ring);
-    else
-        linear_ring_wave<false>(d_stage + g.stage_off, g.count, g.n, 1, g.pitch, mask_stage + g.stage_off,
-                                peak_stage + g.first, status_stage + g.first, w, block, waves, g.first, ring);
-}
-
 // ---------------------------------------------------------------------------
 // wide kernel: one lane per chain deferred by the ring kernel, 64-bit values
 // ---------------------------------------------------------------------------
@@ -690,21 +671,16 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
 
 extern __shared__ __align__(16) unsigned char lin_lds[];
 
-// n_all: the chains' length, or in a ragged call (`groups`) the longest one, for which the stacks
-// are laid out; a listed number is then a chain's place among all chains, as in the wide kernel.
-template <bool LDS_STACKS>
-__global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__restrict__ d, int n_all,
-                                                            int64_t cstride, int64_t pstride_all,
-                                                            uint8_t *__restrict__ mask_out,
-                                                            int64_t *__restrict__ peak_out,
-                                                            int32_t *__restrict__ status_out, LinearWs w,
-                                                            const RaggedGroupDev *__restrict__ groups, int n_groups)
+
+__device__ inline int uniform_bits(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// One chain by one lane: the recurrence with stacks of full capacity.  `base`: room for the stacks and the steps
+// of a chain of n_room layers.
+template <typename Pos>
+__device__ void list_chain(const int64_t *__restrict__ dp, const int n, const int64_t pstride, uint8_t *__restrict__ mp,
+                           int64_t *__restrict__ peak_out, int32_t *__restrict__ status_out, char *base, const int n_room)
 {
-    const int count = w.count[1];
-    const size_t n1 = (size_t)n_all + 1;
-    typedef std::conditional_t<LDS_STACKS, uint16_t, int32_t> Pos;
-    static_assert(kLdsStackMaxN < 65536, "positions in LDS");
-    char *base = LDS_STACKS ? (char *)lin_lds : w.scratch + (size_t)blockIdx.x * stack_bytes(n_all);
+    const size_t n1 = (size_t)n_room + 1;
     int64_t *qM = (int64_t *)base;
     int64_t *qT = qM + n1;
     int64_t *recD = qT + n1;
@@ -712,9 +688,103 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
     Pos *recK = qJ + n1;
     Pos *nxt = recK + n1;
 
+    int64_t x = dp[(int64_t)n * pstride];
+    bool bad_size = x <= 0;
+    bool ovf = false;
+    int64_t dmax = x;
+    qJ[0] = (Pos)n;
+    qM[0] = x;
+    qT[0] = 0;
+    int hd = 0, pt = 0;    // Q occupies slots 0..hd, crossover at pt
+    int top = -1, rp = 0;  // records occupy slots 0..top
+    uint64_t T = 0;        // T(i)
+    int64_t dnext = x;     // d_{i+1}
+    int64_t Mi = x;
+
+    for (int i = n - 1; i >= 0; --i) {
+        const int64_t di = dp[(int64_t)i * pstride];
+        bad_size |= di <= 0;
+        dmax = di > dmax ? di : dmax;
+        T += (uint64_t)dnext;
+        ovf |= T > (uint64_t)INT64_MAX;
+        dnext = di;
+        if (bad_size | ovf) continue;  // keep scanning for errors, skip the work
+        ovf |= (T + (uint64_t)di + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // bounds M(i) and every U(i,j)
+        if (ovf) continue;
+        const int64_t Ti = (int64_t)T;
+
+        while (top >= 0 && recD[top] <= di) --top;
+        ++top;
+        recD[top] = di;
+        recK[top] = (Pos)i;
+        if (rp > top) rp = top;
+
+        while (pt < hd) {
+            const int e = pt + 1;
+            const int je = qJ[e];
+            int r = rp;
+            while (recK[r] >= je) ++r;  // the top record has k = i < je
+            if (Ti - qT[e] + recD[r] < qM[e]) break;
+            pt = e;
+            rp = r;
+        }
+        int64_t best = Ti - qT[pt] + recD[rp];  // U(i, j_pt)
+        int nx = qJ[pt];
+        if (pt < hd) {
+            const int64_t Mp = qM[pt + 1];
+            if (Mp <= best) {
+                best = Mp;
+                nx = qJ[pt + 1];
+            }
+        }
+        Mi = di + best;
+        nxt[i] = (Pos)nx;
+
+        while (hd > pt && qM[hd] >= Mi) --hd;
+        ++hd;
+        qJ[hd] = (Pos)i;
+        qM[hd] = Mi;
+        qT[hd] = Ti;
+    }
+    ovf |= (T + (uint64_t)dnext + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // sum(d) + max(d)
+
+    int32_t status = CKPT_OK;
+    if (bad_size) status = CKPT_ERR_SIZE;
+    else if (ovf) status = CKPT_ERR_OVERFLOW;
+    if (status_out) *status_out = status;
+    *peak_out = status == CKPT_OK ? Mi : -1;
+    if (status != CKPT_OK) {
+        for (int k = 0; k <= n; ++k) mp[(int64_t)k * pstride] = 0;
+        return;
+    }
+    int cur = 0;
+    for (int k = 0; k <= n; ++k) {
+        const bool on = k == cur;
+        mp[(int64_t)k * pstride] = on ? 1 : 0;
+        if (on && k < n) cur = nxt[k];
+    }
+}
+
+// n_all: the chains' length, or in a ragged call (`groups`) the longest one, for which the stacks
+// are laid out; a listed number is then a chain's place among all chains, as in the wide kernel.
+// flagged: 0, or the number of chains of a batch in which the wave kernel marked those left (w.list[c] != 0).
+template <bool LDS_STACKS>
+__global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__restrict__ d, int n_all,
+                                                            int64_t cstride, int64_t pstride_all,
+                                                            uint8_t *__restrict__ mask_out,
+                                                            int64_t *__restrict__ peak_out,
+                                                            int32_t *__restrict__ status_out, LinearWs w,
+                                                            const RaggedGroupDev *__restrict__ groups, int n_groups,
+                                                            int flagged)
+{
+    if (threadIdx.x != 0) return;
+    const int count = flagged ? flagged : w.count[1];
+    typedef std::conditional_t<LDS_STACKS, uint16_t, int32_t> Pos;
+    static_assert(kLdsStackMaxN < 65536, "positions in LDS");
+    char *const base = LDS_STACKS ? (char *)lin_lds : w.scratch + (size_t)blockIdx.x * stack_bytes(n_all);
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
-        if (threadIdx.x != 0) continue;
-        const int64_t c = w.list2[item];
+        if (flagged && w.list[item] == 0) continue;
+        const int64_t c = flagged ? item : w.list2[item];
         int n = n_all;
         int64_t pstride = pstride_all;
         const int64_t *dp = d + c * cstride;
@@ -726,84 +796,219 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
             dp = d + g.stage_off + (c - g.first);
             mp = mask_out + g.stage_off + (c - g.first);
         }
-
-        int64_t x = dp[(int64_t)n * pstride];
-        bool bad_size = x <= 0;
-        bool ovf = false;
-        int64_t dmax = x;
-        qJ[0] = (Pos)n;
-        qM[0] = x;
-        qT[0] = 0;
-        int hd = 0, pt = 0;    // Q occupies slots 0..hd, crossover at pt
-        int top = -1, rp = 0;  // records occupy slots 0..top
-        uint64_t T = 0;        // T(i)
-        int64_t dnext = x;     // d_{i+1}
-        int64_t Mi = x;
-
-        for (int i = n - 1; i >= 0; --i) {
-            const int64_t di = dp[(int64_t)i * pstride];
-            bad_size |= di <= 0;
-            dmax = di > dmax ? di : dmax;
-            T += (uint64_t)dnext;
-            ovf |= T > (uint64_t)INT64_MAX;
-            dnext = di;
-            if (bad_size | ovf) continue;  // keep scanning for errors, skip the work
-            ovf |= (T + (uint64_t)di + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // bounds M(i) and every U(i,j)
-            if (ovf) continue;
-            const int64_t Ti = (int64_t)T;
-
-            while (top >= 0 && recD[top] <= di) --top;
-            ++top;
-            recD[top] = di;
-            recK[top] = (Pos)i;
-            if (rp > top) rp = top;
-
-            while (pt < hd) {
-                const int e = pt + 1;
-                const int je = qJ[e];
-                int r = rp;
-                while (recK[r] >= je) ++r;  // the top record has k = i < je
-                if (Ti - qT[e] + recD[r] < qM[e]) break;
-                pt = e;
-                rp = r;
-            }
-            int64_t best = Ti - qT[pt] + recD[rp];  // U(i, j_pt)
-            int nx = qJ[pt];
-            if (pt < hd) {
-                const int64_t Mp = qM[pt + 1];
-                if (Mp <= best) {
-                    best = Mp;
-                    nx = qJ[pt + 1];
-                }
-            }
-            Mi = di + best;
-            nxt[i] = (Pos)nx;
-
-            while (hd > pt && qM[hd] >= Mi) --hd;
-            ++hd;
-            qJ[hd] = (Pos)i;
-            qM[hd] = Mi;
-            qT[hd] = Ti;
-        }
-        ovf |= (T + (uint64_t)dnext + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // sum(d) + max(d)
-
-        int32_t status = CKPT_OK;
-        if (bad_size) status = CKPT_ERR_SIZE;
-        else if (ovf) status = CKPT_ERR_OVERFLOW;
-        if (status_out) status_out[c] = status;
-        peak_out[c] = status == CKPT_OK ? Mi : -1;
-        if (status != CKPT_OK) {
-            for (int k = 0; k <= n; ++k) mp[(int64_t)k * pstride] = 0;
-            continue;
-        }
-        int cur = 0;
-        for (int k = 0; k <= n; ++k) {
-            const bool on = k == cur;
-            mp[(int64_t)k * pstride] = on ? 1 : 0;
-            if (on && k < n) cur = nxt[k];
-        }
+        list_chain<Pos>(dp, n, pstride, mp, peak_out + c, status_out ? status_out + c : nullptr, base, n_all);
     }
 }
+
+// ---------------------------------------------------------------------------
+// wave kernel: one wave per chain
+// ---------------------------------------------------------------------------
+
+__device__ inline uint32_t get_lane(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ inline uint64_t get_lane(uint64_t v, int lane)
+{
+    return ((uint64_t)get_lane((uint32_t)(v >> 32), lane) << 32) | get_lane((uint32_t)v, lane);
+}
+__device__ inline uint32_t put_lane(uint32_t v, uint32_t x, int lane)
+{
+    return (uint32_t)ckpt_write_lane((int)x, lane, (int)v);
+}
+__device__ inline uint64_t put_lane(uint64_t v, uint64_t x, int lane)
+{
+    return ((uint64_t)put_lane((uint32_t)(v >> 32), (uint32_t)(x >> 32), lane) << 32) |
+           put_lane((uint32_t)v, (uint32_t)x, lane);
+}
+
+// The recurrence of one chain with the live entries of Q in the lanes of a wave: slot p of the stack in
+// lane p % 64, with M(j), A(j), T(j), R(i, j) and j.  Every live entry raises its own R with d_i, so nothing is
+// folded when the crossover moves, and the two loops of the algorithm are a compare each: the entries that
+// satisfy U(i,j) >= M(j) are the ones from pt on towards the head, those that M(i) dominates the ones from the
+// head down, and a bit count of the lanes says how far either pointer moves.  Sizes come from `load` (scaled);
+// the chosen step of every position goes to nxt.  Returns false if more than 64 entries are live.
+template <typename U, class Load>
+__device__ __forceinline__ bool wave_steps(const Load load, const int n, uint16_t *nxt, U &result)
+{
+    const int lane = threadIdx.x % kWave;
+    U dprev = get_lane(load(n), 0);
+    U M = dprev, A = dprev, Tj = 0, R = 0, T = 0, Mi = dprev;  // (Q = {n} in lane 0)
+    uint32_t J = (uint32_t)n;
+    uint64_t live = 1;
+    int pt = 0, hd = 0;
+    int most = 0;  // live entries, less one: looked at once per 64 steps (an overfull stack only spoils values)
+    U rows = load(n - 1 - lane);
+    for (int ihi = n - 1; ihi >= 0; ihi -= kWave) {
+        const U ahead = load(ihi - kWave - lane);  // (positions below 0 repeat position 0 and are not used)
+        const int many = ihi + 1 < kWave ? ihi + 1 : kWave;
+        uint32_t steps = 0;
+        for (int k = 0; k < many; ++k) {
+            const U di = get_lane(rows, k);
+            T += dprev;
+            dprev = di;
+            R = R > di ? R : di;
+            const U X = R + T;
+            const uint64_t sat = __builtin_amdgcn_ballot_w64(X >= A) & live;  // the entry at pt always is
+            pt += (int)__popcll((unsigned long long)sat) - 1;
+            const int at = pt & (kWave - 1), cand = (pt + 1) & (kWave - 1);
+            live = (live & ~sat) | (1ull << at);
+            const U u = X - Tj, v = u > M ? u : M;                            // max(M(j), U(i, j))
+            const U vp = get_lane(v, at), vc = get_lane(v, cand);
+            const bool take = pt != hd && vc <= vp;                           // ties go to the lower index
+            Mi = di + (take ? vc : vp);
+            steps = put_lane(steps, get_lane(J, take ? cand : at), k);
+            const uint64_t drop = __builtin_amdgcn_ballot_w64(M >= Mi) & live;
+            hd += 1 - (int)__popcll((unsigned long long)drop);
+            most = hd - pt > most ? hd - pt : most;
+            const int top = hd & (kWave - 1);
+            live = (live & ~drop) | (1ull << top);
+            M = put_lane(M, Mi, top);
+            A = put_lane(A, Mi + T, top);
+            Tj = put_lane(Tj, T, top);
+            R = put_lane(R, (U)0, top);
+            J = put_lane(J, (uint32_t)(ihi - k), top);
+        }
+        if (most >= kWave) return false;
+        if (lane < many) nxt[ihi - lane] = (uint16_t)steps;
+        rows = ahead;
+    }
+    result = Mi;
+    return true;
+}
+
+// Bytes of LDS for the steps of a chain.
+__host__ __device__ inline size_t wave_lds_bytes(int n) { return ((size_t)n + 1) * 2; }
+
+// One chain, its results included; false (with nothing written) if it is left to the list kernel.
+__device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const int n, const int64_t pstride,
+                                           uint8_t *__restrict__ mp, int64_t *__restrict__ peak_out,
+                                           int32_t *__restrict__ status_out, unsigned char *lds)
+{
+    const int lane = threadIdx.x % kWave;
+    // the chain once over: validity, the trailing zeros its sizes share, their sum and largest
+    uint64_t bits = 0, sum = 0, high = 0, mx = 0;
+    bool bad = false;
+    for (int k0 = 0; k0 <= n; k0 += 4 * kWave) {
+        int64_t x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = dp[(int64_t)min(k0 + u * kWave + lane, n) * pstride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = k0 + u * kWave + lane <= n;
+            bad |= x[u] <= 0;
+            bits |= (uint64_t)x[u];
+            sum += in ? (uint64_t)x[u] : 0;
+            high += in ? (uint64_t)x[u] >> 32 : 0;
+            mx = (uint64_t)x[u] > mx ? (uint64_t)x[u] : mx;
+        }
+    }
+#pragma unroll
+    for (int m = kWave / 2; m >= 1; m >>= 1) {
+        bits |= (uint64_t)__shfl_xor((long long)bits, m, kWave);
+        sum += (uint64_t)__shfl_xor((long long)sum, m, kWave);
+        high += (uint64_t)__shfl_xor((long long)high, m, kWave);
+    }
+    mx = ~wave_min_u64(~mx);
+    // (high below 2^31: the sum stays below 2^63 + 2^48)
+    const bool ovf = high >= (1ull << 31) || sum + mx > (uint64_t)INT64_MAX;
+    const int32_t status = __any(bad) ? CKPT_ERR_SIZE : (ovf ? CKPT_ERR_OVERFLOW : CKPT_OK);
+    uint16_t *const nxt = (uint16_t *)lds;
+    int64_t peak = -1;
+    if (status == CKPT_OK) {
+        const int sh = uniform_bits(__ffsll((unsigned long long)bits) - 1);
+        const auto at = [&](int k) -> uint64_t { return (uint64_t)dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
+        bool done;
+        if (((sum + mx) >> sh) < (1ull << 30)) {
+            uint32_t m0;
+            done = wave_steps<uint32_t>([&](int k) { return (uint32_t)at(k); }, n, nxt, m0);
+            peak = (int64_t)((uint64_t)m0 << sh);
+        } else {
+            uint64_t m0;
+            done = wave_steps<uint64_t>(at, n, nxt, m0);
+            peak = (int64_t)(m0 << sh);
+        }
+        if (!done) return false;
+    }
+    // The set: 64 positions at a time, their steps in the lanes, and from one checkpoint to the next by reading a lane
+    // (an LDS read per checkpoint costs three times as much).
+    __syncthreads();
+    const int none = n + 2 * kWave;
+    int cur = status == CKPT_OK ? 0 : none;
+    for (int b = 0; b <= n; b += kWave) {
+        const int steps = status == CKPT_OK ? nxt[min(b + lane, n - 1)] : 0;
+        uint64_t set = 0;
+        while (cur < b + kWave) {
+            set |= 1ull << (cur - b);
+            cur = cur == n ? none : __builtin_amdgcn_readlane(steps, cur - b);
+        }
+        if (b + lane <= n) mp[(int64_t)(b + lane) * pstride] = (uint8_t)((set >> lane) & 1ull);
+    }
+    if (lane == 0) {
+        *peak_out = peak;
+        if (status_out) *status_out = status;
+    }
+    return true;
+}
+
+// Every group of a ragged call in one launch: a wave looks up the group its 64 chains belong to
+// and solves them where that group is staged, with the step log in registers if the group's
+// chains have up to kLogMaxLayers layers (a wave-uniform branch: long and short groups run side by
+// side on the chip), or one chain of the group as the wave kernel does (ragged_wave_per_chain).  The last groups,
+// the longest chains, start first.  Results go to the chains' places.
+__global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t *__restrict__ d_stage,
+                                                                   const RaggedGroupDev *__restrict__ groups,
+                                                                   int n_groups, uint8_t *__restrict__ mask_stage,
+                                                                   int64_t *__restrict__ peak_stage,
+                                                                   int32_t *__restrict__ status_stage, LinearWs w)
+{
+    __shared__ __attribute__((aligned(4096))) uint32_t ring[kPlanes][kRing][kWave];
+    const unsigned wave = gridDim.x - 1 - blockIdx.x;
+    const RaggedGroupDev g = groups[ragged_group_of_linear_wave(groups, n_groups, wave)];
+    const unsigned waves = (unsigned)((g.count + kWave - 1) / kWave);
+    const unsigned block = wave - (unsigned)g.linear_first;
+    if (ragged_wave_per_chain(g.n, g.count)) {
+        static_assert(sizeof(ring) >= 2 * (4095 + 1), "the wave's LDS for the longest of these chains");
+        const int64_t at = g.stage_off + block, c = g.first + (int64_t)block;
+        const bool done = wave_chain(d_stage + at, g.n, g.pitch, mask_stage + at, peak_stage + c, status_stage + c,
+                                     (unsigned char *)ring);
+        if (!done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
+    } else if (g.n <= kLogMaxLayers)
+        linear_ring_wave<true>(d_stage + g.stage_off, g.count, g.n, 1, g.pitch, mask_stage + g.stage_off,
+                               peak_stage + g.first, status_stage + g.first, w, block, waves, g.first, ring);
+    else
+        linear_ring_wave<false>(d_stage + g.stage_off, g.count, g.n, 1, g.pitch, mask_stage + g.stage_off,
+                                peak_stage + g.first, status_stage + g.first, w, block, waves, g.first, ring);
+}
+
+// Few chains: a wave each.  A lane-per-chain wave alone on its SIMD takes 330 ns a position (660 ns beyond 256
+// layers); here the step is a chain of about 35 instructions, half of them scalar, and takes 150 ns (32 bits):
+// one chain of 152 layers 57 us -> 27 us, 997 chains of 1,001 layers 672 us -> 158 us.  What bounds it is that chain:
+// a position needs the one before it.
+// OWN_LIST: a chain of more than 64 live entries is done by list_chain in the same LDS at once; else it is
+// marked in w.list and left to linear_list_kernel.
+template <bool OWN_LIST>
+__global__ __launch_bounds__(kWave) void linear_wave_kernel(const int64_t *__restrict__ d, int n, int64_t cstride,
+                                                            int64_t pstride, uint8_t *__restrict__ mask_out,
+                                                            int64_t *__restrict__ peak_out,
+                                                            int32_t *__restrict__ status_out, LinearWs w)
+{
+    const int64_t c = blockIdx.x;
+    const int64_t *dp = d + c * cstride;
+    uint8_t *mp = mask_out + c * cstride;
+    int32_t *st = status_out ? status_out + c : nullptr;
+    const bool done = wave_chain(dp, n, pstride, mp, peak_out + c, st, lin_lds);
+    if (threadIdx.x != 0) return;
+    if (OWN_LIST) {
+        if (!done) list_chain<uint16_t>(dp, n, pstride, mp, peak_out + c, st, (char *)lin_lds, n);
+    } else {
+        w.list[c] = done ? 0 : 1;
+    }
+}
+
+// A wave per chain up to this many chains: beyond, the lanes of the ring kernel do more per instruction.  4,096 chains
+// of aligned sizes: 30 us against 46 us at 64 layers, 110 against 158 us at 256, 403 against 660 us at 1,001;
+// the times grow with the number of chains here and stay there (unaligned sizes: 37 against 152 us at 64 layers).
+__host__ inline int64_t wave_max_batch(int n) { return n <= kLogMaxLayers ? 4096 : 6144; }
+constexpr int kWaveMaxLayers = 16383;    // 32 KB of LDS
+constexpr int kOwnListMaxLayers = 511;   // 15 KB of LDS for the stacks, kept free for a case that hardly happens
 
 }  // namespace
 
@@ -848,11 +1053,37 @@ hipError_t launch_solve_linear_noalloc(const int64_t *d, int64_t batch, int n, S
     return launch_solve_linear(d, batch, n, st, mask_out, peak_out, status_out, ptr, stream);
 }
 
+namespace {
+void launch_list(const int64_t *d, int n, Strides st, uint8_t *mask_out, int64_t *peak_out, int32_t *status_out,
+                 const LinearWs &w, unsigned grid, int flagged, hipStream_t stream)
+{
+    if (n <= kLdsStackMaxN)
+        hipLaunchKernelGGL(linear_list_kernel<true>, dim3(grid), dim3(kWave), lds_stack_bytes(n), stream, d, n,
+                           st.chain, st.pos, mask_out, peak_out, status_out, w, (const RaggedGroupDev *)nullptr, 0,
+                           flagged);
+    else
+        hipLaunchKernelGGL(linear_list_kernel<false>, dim3(grid), dim3(kWave), 0, stream, d, n, st.chain, st.pos,
+                           mask_out, peak_out, status_out, w, (const RaggedGroupDev *)nullptr, 0, flagged);
+}
+}  // namespace
+
 hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
                                int64_t *peak_out, int32_t *status_out, void *ws, hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
     LinearWs w = carve_linear(ws, batch, n);
+    const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
+    if (batch <= wave_max_batch(n) && n <= kWaveMaxLayers) {
+        if (n <= kOwnListMaxLayers) {
+            hipLaunchKernelGGL(linear_wave_kernel<true>, dim3((unsigned)batch), dim3(kWave), lds_stack_bytes(n), stream, d,
+                               n, st.chain, st.pos, mask_out, peak_out, status_out, w);
+            return hipGetLastError();
+        }
+        hipLaunchKernelGGL(linear_wave_kernel<false>, dim3((unsigned)batch), dim3(kWave), wave_lds_bytes(n), stream, d, n,
+                           st.chain, st.pos, mask_out, peak_out, status_out, w);
+        launch_list(d, n, st, mask_out, peak_out, status_out, w, lgrid, (int)batch, stream);
+        return hipGetLastError();
+    }
     const unsigned grid = (unsigned)((batch + kWave - 1) / kWave);
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, stream, w);
     if (st.chain <= kRingMaxChainStride)
@@ -869,13 +1100,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     hipLaunchKernelGGL(linear_wide_kernel, dim3((unsigned)(wide_blocks < kWideBlocks ? wide_blocks : kWideBlocks)),
                        dim3(kWave), 0, stream, d, n, st.chain, st.pos, mask_out, peak_out, status_out, w,
                        (const RaggedGroupDev *)nullptr, 0);
-    const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
-    if (n <= kLdsStackMaxN)
-        hipLaunchKernelGGL(linear_list_kernel<true>, dim3(lgrid), dim3(kWave), lds_stack_bytes(n), stream, d, n,
-                           st.chain, st.pos, mask_out, peak_out, status_out, w, (const RaggedGroupDev *)nullptr, 0);
-    else
-        hipLaunchKernelGGL(linear_list_kernel<false>, dim3(lgrid), dim3(kWave), 0, stream, d, n, st.chain, st.pos,
-                           mask_out, peak_out, status_out, w, (const RaggedGroupDev *)nullptr, 0);
+    launch_list(d, n, st, mask_out, peak_out, status_out, w, lgrid, 0, stream);
     return hipGetLastError();
 }
 
@@ -895,10 +1120,10 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
     const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
     if (max_layers <= kLdsStackMaxN)
         hipLaunchKernelGGL(linear_list_kernel<true>, dim3(lgrid), dim3(kWave), lds_stack_bytes(max_layers), stream,
-                           d_stage, max_layers, 1, 0, mask_stage, peak_stage, status_stage, w, groups, n_groups);
+                           d_stage, max_layers, 1, 0, mask_stage, peak_stage, status_stage, w, groups, n_groups, 0);
     else
         hipLaunchKernelGGL(linear_list_kernel<false>, dim3(lgrid), dim3(kWave), 0, stream, d_stage, max_layers, 1, 0,
-                           mask_stage, peak_stage, status_stage, w, groups, n_groups);
+                           mask_stage, peak_stage, status_stage, w, groups, n_groups, 0);
     return hipGetLastError();
 }
 

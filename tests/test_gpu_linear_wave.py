@@ -1,0 +1,101 @@
+"""ckpt_solve_linear where a chain gets a wave of its own: lengths around the 64 rows a wave holds and the
+limits of its launches, 32- and 64-bit arithmetic, more than 64 live entries, batches on both sides of the
+rule, against the oracle; and such groups inside a ragged batch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_12499_amd import binding as B
+from paper_2502_12499_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(d, chain_major=False):
+    dc = inputs.chain_major(d)
+    t = torch.from_numpy(dc if chain_major else np.ascontiguousarray(d)).cuda()
+    mask, peak, status = B.ckpt_solve_linear(t, chain_major=chain_major)
+    torch.cuda.synchronize()
+    want_peak, want_mask = oracle.batch_solve_dynamic(dc)
+    got = mask.cpu().numpy()
+    assert (status.cpu().numpy() == 0).all()
+    assert np.array_equal(peak.cpu().numpy(), want_peak)
+    assert np.array_equal(got if chain_major else got.T, want_mask)
+
+
+def live_entries(n):
+    """Sizes that keep many entries of the queue alive: one large layer at the far end, tiny ones before it, so that
+    the value function falls along the chain while no crossover is reached."""
+    d = np.ones((n + 1, 1), dtype=np.int64)
+    d[1:, 0] = np.arange(n, 0, -1)
+    d[n, 0] = 1
+    d[n - 1, 0] = 1 << 40
+    return d
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 511, 512, 700])
+def test_lengths_and_kinds_of_sizes(n):
+    rng = np.random.default_rng(n)
+    print(f"linear, a wave per chain: n = {n}", flush=True)
+    check(inputs.uniform_aligned_chains(n, n, 9, 256, 32768), chain_major=n % 2 == 1)
+    check(inputs.log_uniform_chains(n, n, 9))
+    check(rng.integers(1, (1 << 62) // (n + 2), size=(n + 1, 5)).astype(np.int64))
+    check(rng.integers(1, 4, size=(n + 1, 5)).astype(np.int64))
+    check(np.full((n + 1, 2), 3, dtype=np.int64))
+    check(np.arange(1, n + 2, dtype=np.int64)[:, None].repeat(2, 1))
+    check(np.arange(n + 1, 0, -1, dtype=np.int64)[:, None].repeat(2, 1))
+    check((1 << rng.integers(0, 40, size=(n + 1, 5))).astype(np.int64))
+    if n > 1:
+        check(live_entries(n))
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 3000])
+def test_long_chains(n):
+    check(inputs.uniform_aligned_chains(n, n, 2, 256, 32768))
+    check(live_entries(n))
+
+
+@pytest.mark.parametrize("batch", [4096, 4097])
+def test_batches_on_both_sides_of_the_rule(batch):
+    d = inputs.uniform_aligned_chains(3, 40, batch, 256, 32768)
+    d[:, ::9] += 1
+    check(d)
+
+
+def test_bad_chains_are_reported_alone():
+    for n in (100, 600):
+        d = inputs.uniform_aligned_chains(4, n, 12, 256, 32768)
+        want_peak, want_mask = oracle.batch_solve_dynamic(inputs.chain_major(d))
+        d[n, 2] = 0
+        d[:, 7] = (1 << 62) + 3
+        d[0, 11] = -4
+        mask, peak, status = B.ckpt_solve_linear(torch.from_numpy(d).cuda())
+        torch.cuda.synchronize()
+        ok = np.array([c for c in range(12) if c not in (2, 7, 11)])
+        st = status.cpu().numpy()
+        assert (st[ok] == 0).all() and st[[2, 7, 11]].tolist() == [3, 4, 3]
+        assert (peak.cpu().numpy()[[2, 7, 11]] == -1).all() and not mask.cpu().numpy()[:, [2, 7, 11]].any()
+        assert np.array_equal(peak.cpu().numpy()[ok], want_peak[ok])
+        assert np.array_equal(mask.cpu().numpy().T[ok], want_mask[ok])
+
+
+def test_long_groups_of_a_ragged_batch():
+    """Groups on both sides of the rule (257 and 4095 layers get waves, 256 and 4096 lanes), with chains that
+    leave either kind, lengths counted on the host and on the device."""
+    rng = np.random.default_rng(1)
+    lengths = np.concatenate([np.array([256, 257, 257, 1001, 4095, 4096, 300, 300, 300]),
+                              rng.choice([5, 24, 300], size=200)])
+    rng.shuffle(lengths)
+    d, _, off = inputs.ragged_batch(6, lengths)
+    for c in range(0, len(lengths), 3):
+        d[off[c]:off[c + 1]] += 1
+    for c in np.nonzero(lengths == 300)[0][:3]:
+        d[off[c]:off[c + 1]] = live_entries(300)[:, 0]
+    want_peak, want_mask = oracle.ragged_solve_dynamic(d, off)
+    for off_dev in (None, torch.from_numpy(off).cuda()):
+        mask, peak, status = B.ckpt_ragged_solve_linear(torch.from_numpy(d).cuda(), off, offsets_dev=off_dev)
+        torch.cuda.synchronize()
+        assert (status.cpu().numpy() == 0).all()
+        assert np.array_equal(peak.cpu().numpy(), want_peak)
+        assert np.array_equal(mask.cpu().numpy(), want_mask)
