@@ -119,10 +119,10 @@ int ckpt_eval_peak(const int64_t *d, const uint8_t *mask, const ckpt_layout *lay
  * (0 and every sum of a contiguous range inside d_1..d_{n-1}) the least
  * checkpoint memory c_s whose segments all fit in s, by the recurrence of
  * Equation (T); the answer is min_s (s + c_s) with d_0 and d_n checkpoints.
- * n <= CKPT_CUBIC_MAX_LAYERS.  For chains of up to 256 layers the minimum is
- * found without running the recurrence for every budget (c_s does not grow with
- * s, so a few evaluated budgets settle the others; the results are the same);
- * ckpt_solve_cubic_costs runs it for each one.
+ * n <= CKPT_CUBIC_MAX_LAYERS.  The minimum is found without running the
+ * recurrence for every budget (c_s does not grow with s, so a few evaluated
+ * budgets settle the others; the results are the same); ckpt_solve_cubic_costs
+ * runs it for each one.
  * Canonical result: budget_out[c] is the smallest optimal budget value s*;
  * the set is built from position n by taking, each time, the smallest
  * feasible predecessor of minimal value.
@@ -132,8 +132,8 @@ int ckpt_solve_cubic(const int64_t *d, const ckpt_layout *layout, uint8_t *mask_
                      int64_t *peak_out, int64_t *budget_out, int32_t *status_out,
                      void *ws, size_t ws_bytes, void *hip_stream);
 
-/* The same result as ckpt_solve_cubic, without running the recurrence for
- * budgets that cannot be optimal.  Any cost s + c_s that has been reached
+/* The same result as ckpt_solve_cubic, by running the recurrence for every
+ * budget but those that bounds rule out beforehand.  Any cost s + c_s that has been reached
  * bounds the optimum from above (UB).  From above: c_s >= d_0 + d_n for every
  * budget (both ends are checkpoints), so a budget s > UB - d_0 - d_n costs more
  * than UB.  From below: with m interior checkpoints the other interior layers

@@ -50,13 +50,6 @@ __device__ inline uint64_t dpp_min_step_u64(uint64_t v)
     return o < v ? o : v;
 }
 
-template <int CTRL, int ROW_MASK>
-__device__ inline uint32_t dpp_min_step_u32(uint32_t v)
-{
-    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROW_MASK, 0xf, false);
-    return o < v ? o : v;
-}
-
 // Minimum over the wave, returned to every lane.  Shifts by 1, 2, 4, 8 inside
 // each row of 16 lanes leave the row's minimum in its last lane; lane 15 is
 // then broadcast into row 1 and lane 47 into row 3, lane 31 into rows 2 and 3,
@@ -74,14 +67,24 @@ __device__ inline uint64_t wave_min_u64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// (one instruction a step: a lane without a source keeps its value; the value a DPP source reads must be two wait
+// states old)
 __device__ inline uint32_t wave_min_u32(uint32_t v)
 {
-    v = dpp_min_step_u32<kDppRowShr1, 0xf>(v);
-    v = dpp_min_step_u32<kDppRowShr2, 0xf>(v);
-    v = dpp_min_step_u32<kDppRowShr4, 0xf>(v);
-    v = dpp_min_step_u32<kDppRowShr8, 0xf>(v);
-    v = dpp_min_step_u32<kDppRowBcast15, 0xa>(v);
-    v = dpp_min_step_u32<kDppRowBcast31, 0xc>(v);
+    asm("s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_min_u32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+        "s_nop 0"
+        : "+v"(v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
@@ -135,6 +138,11 @@ constexpr int kSearchMaxLayers = 256;
 hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
                                int64_t *peak_out, int64_t *budget_out, int32_t *status_out, void *ws,
                                hipStream_t stream);
+// ... and for longer ones; ws: cubic_search_long_bytes() bytes
+size_t cubic_search_long_bytes(int64_t batch, int n);
+hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
+                                    int64_t *peak_out, int64_t *budget_out, int32_t *status_out, void *ws,
+                                    hipStream_t stream);
 // The same for a ragged batch whose chains all have up to kSearchMaxLayers layers, on the flat arrays
 // themselves.  A launch per class of lengths (its LDS is that of the longest chain in it); longest[k]: the
 // longest chain of class k, 0 if it has none.  count: one value, list: `batch` values of scratch.

@@ -399,73 +399,78 @@ __device__ inline uint64_t select_lanes(uint64_t off, uint64_t on, uint64_t mask
 // before it is larger or gone.  The lanes hold three neighbouring slices of 64 positions in registers and slide
 // along the chain: Z, the positions before, A, where the next cells are, and B, whose prefix sums are
 // under way; a window that reaches back beyond Z is finished from the values parked in F.
-// What bounds it is the chain of dependent instructions of a head (about 50, half of them scalar); a form that
-// kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips.
+// What bounds it is the chain of dependent instructions of a head (about 50, half of them scalar, eight to nine
+// cycles each); a form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips.
 // P: prefix sums, P[n] below 2^31 or 2^63; F: room for n + 1 values; RECORD: head[j], the predecessor of j, is
-// written for j = 1..n.
-template <typename U, bool RECORD, typename H>
-__device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F, H *head)
+// written for j = 1..n.  stop(F(h)) is asked once per slice; when it says so the pass ends with F(h), which F_s(n)
+// is not below.
+struct NeverStop {
+    template <typename U>
+    __device__ bool operator()(U) const { return false; }
+};
+template <typename U, bool RECORD, typename H, class Stop = NeverStop>
+__device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F, H *head, Stop stop = Stop())
 {
-    typedef std::make_signed_t<U> I;
     constexpr U kMax = std::numeric_limits<U>::max();
     const int lane = threadIdx.x % kWave;
     // P at position k, and P[k - 1], what cell k compares (past n: larger than anything, so the cell ends the head)
     auto at = [&](int k) -> U { return P[k < n ? k : n]; };
     auto before = [&](int k) -> U { return k > n ? kMax : P[k > 0 ? k - 1 : 0]; };
     int base = 0;                          // A holds the positions base + lane
-    U PZ = 0, FZ = kMax, PA = at(lane), QA = before(lane), PB = at(kWave + lane), QB = before(kWave + lane);
+    // per position: P + s (a window of sums ending in x begins where this reaches x), the size, P before, F
+    U SZ = 0, FZ = kMax, PA = at(lane), QA = before(lane), PB = at(kWave + lane), QB = before(kWave + lane);
+    U SA = PA + s, DA = PA - QA;
     U FA = PA;                             // (F(0) = P[0] in lane 0)
     int HA = 0;
-    int h = 0, t = 1;                      // t: the next cell, relative to base (1..64)
-    U fh = uniform_lane_u(PA, 0), Ph = fh;
+    int h = 0, t = 1;                      // t: the next cell, relative to base (0..63)
+    U fh = uniform_lane_u(PA, 0), Sh = fh + s;
     for (;;) {
         // the cells from t on, as if h stayed for all of them (a later head overwrites them)
-        const uint64_t from = t < kWave ? ~0ull << t : 0ull;
-        FA = select_lanes(FA, (PA - QA) + fh, from);
+        const uint64_t from = ~0ull << t;
+        FA = select_lanes(FA, DA + fh, from);
         if (RECORD) HA = (int)select_lanes((uint32_t)HA, (uint32_t)h, from);
-        const uint64_t out = __builtin_amdgcn_ballot_w64(QA > Ph + s) & from;
+        const uint64_t out = __builtin_amdgcn_ballot_w64(QA > Sh) & from;
         if (out == 0) {
             // h outlasts A: slide
+            if (stop(fh)) return fh;
             F[base + lane] = FA;
             if (RECORD) head[base + lane] = (H)HA;
             base += kWave;
             t = 0;
-            PZ = PA; FZ = FA;
+            SZ = SA; FZ = FA;
             PA = PB; QA = QB;
+            SA = PA + s; DA = PA - QA;
             PB = at(base + kWave + lane);
             QB = before(base + kWave + lane);
             continue;
         }
         const int e = __ffsll((unsigned long long)out) - 1;  // the first cell that does not see h
-        if (base + e > n) {
+        if (__builtin_expect(base + e > n, 0)) {
             if (RECORD && base + lane <= n) head[base + lane] = (H)HA;
             // (t = 0 and cell n the last of the slice before: its value is in Z)
             return n >= base ? uniform_lane_u(FA, n - base) : uniform_lane_u(FZ, kWave - 1);
         }
-        // The window of e: P[i] >= P[e - 1] - s, i < e; h and what lies before it are out by themselves.
+        // The window of e: P[i] + s >= P[e - 1], i < e; h and what lies before it are out by themselves.  (Before the
+        // first slide Z holds no positions: its values are the largest there are.)
         const U Pe = uniform_lane_u(QA, e);
-        const U low = (I)(Pe - s) > 0 ? Pe - s : 0;
-        const uint64_t wa = __builtin_amdgcn_ballot_w64(PA >= low) & ((1ull << e) - 1ull);
-        const uint64_t wz = base > 0 ? __builtin_amdgcn_ballot_w64(PZ >= low) : 0ull;
+        const uint64_t wa = __builtin_amdgcn_ballot_w64(SA >= Pe) & ~(~0ull << e);
+        const uint64_t wz = __builtin_amdgcn_ballot_w64(SZ >= Pe);
         const U va = select_lanes(kMax, FA, wa), vz = select_lanes(kMax, FZ, wz);
-        U mn;
-        if constexpr (sizeof(U) == 4) mn = wave_min_u32(va < vz ? va : vz); else mn = wave_min_u64(va < vz ? va : vz);
-        const uint64_t ea = __builtin_amdgcn_ballot_w64(FA == mn) & wa;
-        const uint64_t ez = __builtin_amdgcn_ballot_w64(FZ == mn) & wz;
+        if constexpr (sizeof(U) == 4) fh = wave_min_u32(va < vz ? va : vz); else fh = wave_min_u64(va < vz ? va : vz);
+        const uint64_t ea = __builtin_amdgcn_ballot_w64(FA == fh) & wa;
+        const uint64_t ez = __builtin_amdgcn_ballot_w64(FZ == fh) & wz;
         const int sa = __ffsll((unsigned long long)ea) - 1, sz = __ffsll((unsigned long long)ez) - 1;
         const bool in_z = ez != 0;
-        const U pa = uniform_lane_u(PA, sa & 63), pz = uniform_lane_u(PZ, sz & 63);
-        h = in_z ? base - kWave + sz : base + sa;
-        Ph = in_z ? pz : pa;
-        fh = mn;
+        const U pa = uniform_lane_u(SA, sa & 63), pz = uniform_lane_u(SZ, sz & 63);
+        if (RECORD) h = in_z ? base - kWave + sz : base + sa;
+        Sh = in_z ? pz : pa;
         t = e;
-        if ((wz & 1ull) != 0 && base > kWave) {
+        if (__builtin_expect((wz & 1ull) != 0 && base > kWave, 0)) {
             // the whole of Z lies in the window: the parked values before it
             for (int top = base - kWave - 1; top >= 0; top -= kWave) {
-                const int i = top - lane, ic = i > 0 ? i : 0;
-                const U pi = P[ic];
-                const uint64_t in = __builtin_amdgcn_ballot_w64(pi >= low) & (top < kWave - 1 ? (2ull << top) - 1ull : ~0ull);
-                const U fi = F[ic];
+                const int i = top - lane;          // (top is 63 or more)
+                const U si = P[i] + s, fi = F[i];
+                const uint64_t in = __builtin_amdgcn_ballot_w64(si >= Pe);
                 const U v = select_lanes(kMax, fi, in);
                 U m;
                 if constexpr (sizeof(U) == 4) m = wave_min_u32(v); else m = wave_min_u64(v);
@@ -473,7 +478,7 @@ __device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F,
                     fh = m;
                     const int far = 63 - __clzll((unsigned long long)(__builtin_amdgcn_ballot_w64(fi == m) & in));
                     h = top - far;
-                    Ph = uniform_lane_u(pi, far);
+                    Sh = uniform_lane_u(si, far);
                 }
                 if (in != ~0ull) break;
             }
@@ -830,6 +835,649 @@ hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_d
     if (!wide)
         hipLaunchKernelGGL(cubic_search_ragged_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(all, 8),
                            stream, d, offsets_dev, mask_out, peak_out, budget_out, status_out, w);
+    return hipGetLastError();
+}
+
+namespace {
+
+// ---------------------------------------------------------------------------
+// long chains: one wave per point, the points of a round on the whole chip
+// ---------------------------------------------------------------------------
+//
+//   table      one workgroup per chain: checks, prefix sums divided by the unit that all sizes are multiples
+//              of (their common power of two; their greatest common divisor where that still leaves more
+//              than 31 bits: the sizes of a network share its batch size), a first bound
+//   round x 2  `points` waves per chain evaluate a point each, cutting the open intervals evenly
+//   close x 2  (after each) takes the best cost and lists the intervals that stay open
+//   list       a thread per start: the budgets inside the open intervals, each value once (a table of the
+//              values seen keeps most repeated ones out)
+//   finish     a wave per listed budget, and one for the best point so far; each keeps the set of its best
+//   result     the best of the waves, its set spread to bytes
+// After two rounds of 1,024 points one to twenty budgets are left on every kind of chain tried, so `finish` takes
+// one pass; it takes whatever is left.  A call is bound by three passes in a row, one after another, each as long as
+// its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves stops: a
+// small s would have a head at every cell.
+// Measured, with every budget evaluated in brackets: one chain of 4,096 aligned layers 312 us (1,650), of 1,001 of a
+// network 467 (1,200 to 1,490); two of 3,115 aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484
+// (118,000); 1,000 of 300 600 (3,710), unrounded 685 (34,000).
+constexpr int kOpenMax = 128;       // open intervals kept (more are joined)
+constexpr int kSeenSlots = 1024;    // table of values seen
+constexpr int kMostPoints = 1024;   // of a round, per chain
+constexpr int kTableThreads = 1024;
+constexpr int kTablePer = (CKPT_CUBIC_MAX_LAYERS + 1 + kTableThreads - 1) / kTableThreads;
+constexpr int kBounds = kTableThreads / kWave;
+
+struct LongMeta {
+    int32_t status;
+    int32_t narrow;      // 1: 32-bit values
+    uint64_t unit;       // the sizes were divided by this
+    uint64_t ub;         // the best cost known (a bound, then costs); lowered while a round runs
+    uint64_t ends;       // d_0 + d_n
+    uint64_t best_cost;  // of the evaluated points (~0: none)
+    uint64_t best_s;
+    int32_t open[2];     // intervals before round 0 / 1 ...
+    int32_t left;        // ... and after the rounds
+    int32_t listed;      // budgets in the list
+};
+struct Open {
+    int64_t lo, hi;      // lo < s <= hi
+    uint64_t c;          // F_s(n) is at least this for all of them
+    int32_t first;       // number of its first point
+    int32_t pad;
+};
+struct Point {
+    int64_t prev, s;
+    uint64_t c;          // F_s(n), or with `exact` 0 a value it is not below
+    int64_t exact;
+};
+struct LongWs {
+    LongMeta *meta;      // [batch]
+    Open *open;          // [batch][3][kOpenMax] before round 0, before round 1, after it
+    Point *point;        // [batch][points]
+    uint64_t *seen;      // [batch][kSeenSlots]
+    uint64_t *found;     // [batch][finish_waves][2] best cost and its s of a finish wave
+    uint64_t *set;       // [batch][finish_waves][n / 64 + 1] and its set, a bit a layer
+    uint32_t *list;      // [batch][K] start << 13 | end
+    char *P;             // [batch][n + 1] uint64_t (uint32_t in the same bytes when narrow)
+};
+static_assert(CKPT_CUBIC_MAX_LAYERS < (1 << 13), "a start and an end in 26 bits");
+
+// Points per chain and round: the chip's SIMDs twice over between the chains, within 64 .. 1,024 (512 below 512
+// layers, which a workspace has room for).
+__host__ __device__ inline int long_points(int64_t batch, int n)
+{
+    const int most = n < 512 ? kMostPoints / 2 : kMostPoints;
+    const int64_t share = batch >= 32 ? 64 : 2048 / batch;
+    return (int)(share < most ? share : most) / kWave * kWave;
+}
+__host__ __device__ inline int64_t long_budgets(int n) { return (int64_t)n * (n - 1) / 2 + 1; }
+
+// Waves per chain that evaluate what the rounds leave: as many as points, up to 512.
+__host__ __device__ inline int finish_waves(int64_t batch, int n)
+{
+    const int points = long_points(batch, n);
+    return points < 512 ? points : n < 512 ? 256 : 512;
+}
+
+__host__ size_t carve_long(void *ws, int64_t batch, int n, LongWs *w)
+{
+    size_t at = 0;
+    char *base = (char *)ws;
+    const size_t B = (size_t)batch;
+    auto take = [&](size_t bytes) { char *here = base + at; at += align_up(bytes); return here; };
+    w->meta = (LongMeta *)take(B * sizeof(LongMeta));
+    w->open = (Open *)take(B * 3 * kOpenMax * sizeof(Open));
+    const size_t points = B * (size_t)long_points(batch, n) * sizeof(Point);
+    const size_t sets = B * (size_t)finish_waves(batch, n) * ((size_t)n / kWave + 1) * 8;
+    w->point = (Point *)take(points > sets ? points : sets);
+    w->set = (uint64_t *)w->point;  // (the rounds are over when the first set is written)
+    w->seen = (uint64_t *)take(B * kSeenSlots * 8);
+    w->found = (uint64_t *)take(B * (size_t)finish_waves(batch, n) * 16);
+    w->list = (uint32_t *)take(B * (size_t)long_budgets(n) * 4);
+    w->P = take(B * ((size_t)n + 1) * 8);
+    return at;
+}
+
+// ---- table ----
+
+// The smallest over the workgroup, for every thread.
+__device__ inline uint64_t block_min(uint64_t v, uint64_t *room)
+{
+    v = wave_min_u64(v);
+    __syncthreads();
+    if (threadIdx.x % kWave == 0) room[threadIdx.x / kWave] = v;
+    __syncthreads();
+    v = room[threadIdx.x % (kTableThreads / kWave)];
+    static_assert(kTableThreads / kWave <= kWave, "one wave holds the waves' values");
+    return wave_min_u64(v);
+}
+
+__global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64_t *__restrict__ d, int n, int64_t cstride,
+                                                                     int64_t pstride, int points, int waves, LongWs w)
+{
+    constexpr int kWaves = kTableThreads / kWave;
+    __shared__ uint64_t room[kWaves], part[5][kWaves];
+    __shared__ float bound_of[kBounds];
+    __shared__ uint64_t ends2[2];
+    float *const prefix = (float *)search_lds;  // [n + 1]
+    const int64_t c = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int64_t *dp = d + c * cstride;
+    const int per = (n + kTableThreads) / kTableThreads, k0 = tid * per;  // a thread takes `per` sizes in a row
+    uint64_t x[kTablePer];
+    uint64_t bits = 0, high = 0, sum = 0, mx = 0, bad = 0;
+#pragma unroll
+    for (int q = 0; q < kTablePer; ++q) x[q] = q < per && k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
+    for (int k = tid; k < kSeenSlots; k += kTableThreads) w.seen[c * kSeenSlots + k] = 0;
+    for (int k = tid; k < 2 * waves; k += kTableThreads) w.found[c * 2 * waves + k] = ~0ull;
+#pragma unroll
+    for (int q = 0; q < kTablePer; ++q) {
+        bad |= (q < per && k0 + q <= n && (int64_t)x[q] <= 0) ? 1 : 0;
+        bits |= x[q];
+        high += x[q] >> 32;
+        sum += x[q];
+        mx = x[q] > mx ? x[q] : mx;
+    }
+#pragma unroll
+    for (int k = kWave / 2; k >= 1; k >>= 1) {
+        bits |= (uint64_t)__shfl_xor((long long)bits, k, kWave);
+        high += (uint64_t)__shfl_xor((long long)high, k, kWave);
+        sum += (uint64_t)__shfl_xor((long long)sum, k, kWave);
+    }
+    mx = ~wave_min_u64(~mx);
+    bad = __any(bad != 0) ? 1 : 0;
+    if (lane == 0) {
+        part[0][wave] = bits; part[1][wave] = high; part[2][wave] = sum; part[3][wave] = mx; part[4][wave] = bad;
+    }
+    __syncthreads();
+    bits = high = sum = mx = bad = 0;
+    for (int k = 0; k < kWaves; ++k) {
+        bits |= part[0][k];
+        high += part[1][k];
+        sum += part[2][k];
+        mx = part[3][k] > mx ? part[3][k] : mx;
+        bad |= part[4][k];
+    }
+    LongMeta m = {};
+    m.status = bad ? CKPT_ERR_SIZE
+                   : (high >= (1ull << 31) || sum + mx > (uint64_t)INT64_MAX) ? CKPT_ERR_OVERFLOW : CKPT_OK;
+    if (m.status != CKPT_OK) {
+        if (tid == 0) w.meta[c] = m;
+        return;
+    }
+    uint64_t unit = bits & (0 - bits);
+    if ((sum + mx) / unit >= (1ull << 31)) {
+        // Euclid on all sizes at once: the smallest remainder of any size takes the divisor's place until none is left
+        uint64_t g = mx;
+#pragma unroll
+        for (int q = 0; q < kTablePer; ++q) g = x[q] != 0 && x[q] < g ? x[q] : g;
+        g = block_min(g, room);
+        for (int turn = 0; turn < 12 && g > unit; ++turn) {  // (not settled by then: small divisors do not help)
+            uint64_t r = ~0ull;
+#pragma unroll
+            for (int q = 0; q < kTablePer; ++q) {
+                const uint64_t rest = x[q] % g;
+                r = rest != 0 && rest < r ? rest : r;
+            }
+            r = block_min(r, room);
+            if (r == ~0ull) {
+                unit = g;
+                break;
+            }
+            g = r;
+        }
+    }
+    m.unit = unit;
+    m.narrow = (sum + mx) / unit < (1ull << 31);
+    const bool pow2 = (unit & (unit - 1)) == 0;
+    const int shift = __ffsll((unsigned long long)unit) - 1;
+    uint64_t *const P64 = (uint64_t *)w.P + c * (n + 1);
+    uint32_t *const P32 = (uint32_t *)P64;
+    uint64_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < kTablePer; ++q) {
+        x[q] = pow2 ? x[q] >> shift : x[q] / unit;
+        mine += x[q];
+    }
+    const uint64_t incl = wave_scan_u64(mine);
+    __syncthreads();
+    if (lane == kWave - 1) room[wave] = incl;
+    __syncthreads();
+    uint64_t run = incl - mine, total = 0;
+    for (int k = 0; k < kWaves; ++k) {
+        run += k < wave ? room[k] : 0;
+        total += room[k];
+    }
+#pragma unroll
+    for (int q = 0; q < kTablePer; ++q) {
+        const int k = k0 + q;
+        if (q >= per || k > n) break;
+        run += x[q];
+        if (m.narrow) P32[k] = (uint32_t)run; else P64[k] = run;
+        prefix[k] = (float)run;
+        if (k == 0) ends2[0] = x[q];
+        if (k == n) ends2[1] = x[q];
+    }
+    __syncthreads();
+    // A bound: for 16 segment lengths (one to a wave) a checkpoint wherever the interior prefix sums pass a
+    // multiple of the length.  What lies between two of them adds up to the length at most; the floats' errors are
+    // covered by raising the result.
+    const uint64_t ends = ends2[0] + ends2[1], all = total - ends;
+    {
+        const float p0 = prefix[0], length = fmaxf((float)all * exp2f(-0.5f * (float)(wave + 1)), 1.0f);
+        const float inv = 1.0f / length;
+        float kept = 0.0f;
+        for (int i = 1 + lane; i < n; i += kWave) {
+            const float a = prefix[i - 1] - p0, b = prefix[i] - p0;
+            kept += floorf(a * inv) != floorf(b * inv) ? b - a : 0.0f;
+        }
+#pragma unroll
+        for (int k = kWave / 2; k >= 1; k >>= 1) kept += __shfl_xor(kept, k, kWave);
+        // (a checkpoint's size comes from a difference of rounded sums: up to 2^-23 of the whole for each)
+        if (lane == 0) bound_of[wave] = (kept + length) * (1.0f + 1.0f / 512.0f) + (float)all * (float)n * 0x1p-22f;
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    float low = bound_of[0];
+    for (int k = 1; k < kBounds; ++k) low = fminf(low, bound_of[k]);
+    uint64_t ub = ends + (uint64_t)(double)low + 1;
+    ub = ub < total ? ub : total;
+    m.ub = ub;
+    m.ends = ends;
+    m.best_cost = total <= ub ? total : ~0ull;  // s = 0: every layer a checkpoint
+    m.best_s = 0;
+    const uint64_t span = all < ub - ends ? all : ub - ends;
+    m.open[0] = span > 0 ? 1 : 0;
+    w.open[c * 3 * kOpenMax] = Open{0, (int64_t)span, 0, 0, 0};
+    w.meta[c] = m;
+}
+
+// ---- rounds ----
+
+// What a wave reads while others write: past the L1 cache and the XCD's own L2.
+template <typename T>
+__device__ inline T shared_load(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Point g of a round: the interval that holds it and its place there.
+__device__ inline void point_of(const Open *open, int count, int points, int g, int64_t &prev, int64_t &s)
+{
+    const int lane = threadIdx.x;
+    int at = -1;
+    for (int k0 = 0; k0 < count; k0 += kWave)
+        at += (int)__popcll((unsigned long long)__builtin_amdgcn_ballot_w64(k0 + lane < count && open[k0 + lane].first <= g));
+    const Open o = open[at];
+    const int next = at + 1 < count ? open[at + 1].first : points;
+    const int64_t many = next - o.first, t = g - o.first, wide = o.hi - o.lo;
+    const int64_t part = wide / many, rest = wide % many;
+    prev = o.lo + part * t + rest * t / many;
+    s = o.lo + part * (t + 1) + rest * (t + 1) / many;
+}
+
+// A chain's point, evaluated: F_s(n), or less if it stopped (`exact` false then); RECORD: `head` as in wave_cost.
+template <typename U, bool RECORD>
+__device__ __forceinline__ uint64_t long_cost(const LongWs &w, const LongMeta *meta, const int64_t c, const int n,
+                                              const int64_t prev, const int64_t s, bool &exact, uint16_t *head)
+{
+    const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
+    exact = true;
+    // No s above prev can be optimal once F(h) is above what the best cost leaves beside it.  (The best cost is read a
+    // slice ahead: it comes from memory, past the caches.)
+    uint64_t ahead = shared_load(&meta->ub);
+    auto stop = [&](U fh) -> bool {
+        const uint64_t ub = ahead;
+        ahead = shared_load(&meta->ub);
+        const bool out = (int64_t)(ub - (uint64_t)fh) <= prev;
+        if (out) exact = false;
+        return out;
+    };
+    return (uint64_t)wave_cost<U, RECORD>(P, n, (U)s, (U *)search_lds, head, stop);
+}
+
+__global__ __launch_bounds__(kWave) void search_round_kernel(int n, int points, int round, LongWs w)
+{
+    const int64_t c = blockIdx.y;
+    LongMeta *meta = w.meta + c;
+    const int count = meta->open[round];
+    if (meta->status != CKPT_OK || count == 0) return;  // (the same for all waves of the chain: nothing to close)
+    const int lane = threadIdx.x, g = blockIdx.x;
+    int64_t prev, s;
+    point_of(w.open + (c * 3 + round) * kOpenMax, count, points, g, prev, s);
+    Point p{prev, s, ~0ull, 0};
+    if (s > prev) {
+        bool exact;
+        p.c = meta->narrow ? long_cost<uint32_t, false>(w, meta, c, n, prev, s, exact, nullptr)
+                           : long_cost<uint64_t, false>(w, meta, c, n, prev, s, exact, nullptr);
+        p.exact = exact;
+        if (exact && lane == 0) atomicMin((unsigned long long *)&meta->ub, (unsigned long long)(p.c + (uint64_t)s));
+    }
+    if (lane == 0) w.point[c * points + g] = p;
+}
+
+// The end of a round, one wave per chain: the best of the points, and the intervals that stay open under the best
+// cost.  (A launch of its own: as the work of the round's last wave it took a device-wide fence in every wave, 36 ns
+// of the whole chip each, 2.2 of 2.3 ms for 1,000 chains of 300 layers.)
+__global__ __launch_bounds__(kWave) void search_close_kernel(int points, int round, LongWs w)
+{
+    const int64_t c = blockIdx.x;
+    LongMeta *meta = w.meta + c;
+    if (meta->status != CKPT_OK || meta->open[round] == 0) return;
+    const int lane = threadIdx.x;
+    // (all loads in flight together: read where they are used, this took 12 us)
+    const int per = points / kWave;  // consecutive points of a lane
+    const Point *pt = w.point + c * points + lane * per;
+    Point q[kMostPoints / kWave];
+#pragma unroll
+    for (int k = 0; k < kMostPoints / kWave; ++k) q[k] = pt[k < per ? k : 0];
+    uint64_t cost = ~0ull, at = ~0ull;
+#pragma unroll
+    for (int k = 0; k < kMostPoints / kWave; ++k) {
+        const int64_t prev = q[k].prev, s = q[k].s;
+        const uint64_t pc = q[k].c + (uint64_t)s;
+        if (k < per && q[k].exact != 0 && s > prev && (pc < cost || (pc == cost && (uint64_t)s < at))) {
+            cost = pc;
+            at = (uint64_t)s;
+        }
+    }
+    const uint64_t best = wave_min_u64(cost), best_at = wave_min_u64(cost == best ? at : ~0ull);
+    uint64_t bc = meta->best_cost, bs = meta->best_s;
+    if (best < bc || (best == bc && best_at < bs)) {
+        bc = best;
+        bs = best_at;
+    }
+    const uint64_t known = meta->ub, ub = known < bc ? known : bc;
+    // the open parts; joined from the kOpenMax-th on
+    uint64_t width = 0;
+    int many = 0;
+#pragma unroll
+    for (int k = 0; k < kMostPoints / kWave; ++k) {
+        const int64_t prev = q[k].prev, s = q[k].s;
+        const uint64_t pc = q[k].c;
+        const int64_t last = q[k].exact != 0 ? s - 1 : s;
+        const int64_t top = pc > ub ? -1 : last < (int64_t)(ub - pc) ? last : (int64_t)(ub - pc);
+        if (k < per && top > prev) {
+            width += (uint64_t)(top - prev);
+            ++many;
+        }
+    }
+    int incl = many;
+#pragma unroll
+    for (int k = 1; k < kWave; k <<= 1) {
+        const int o = __shfl_up(incl, k, kWave);
+        if (lane >= k) incl += o;
+    }
+    const int count = __builtin_amdgcn_readlane(incl, kWave - 1);
+    Open *out = w.open + (c * 3 + round + 1) * kOpenMax;
+    int slot = incl - many;
+    int64_t tail_lo = INT64_MAX, tail_hi = -1;
+    uint64_t tail_c = ~0ull;
+#pragma unroll
+    for (int k = 0; k < kMostPoints / kWave; ++k) {
+        const int64_t prev = q[k].prev, s = q[k].s;
+        const uint64_t pc = q[k].c;
+        const int64_t last = q[k].exact != 0 ? s - 1 : s;
+        const int64_t top = pc > ub ? -1 : last < (int64_t)(ub - pc) ? last : (int64_t)(ub - pc);
+        if (k >= per || top <= prev) continue;
+        if (slot < kOpenMax - 1) {
+            out[slot] = Open{prev, top, pc, 0, 0};
+        } else {
+            tail_lo = prev < tail_lo ? prev : tail_lo;
+            tail_hi = top > tail_hi ? top : tail_hi;
+            tail_c = pc < tail_c ? pc : tail_c;
+        }
+        ++slot;
+    }
+    int kept = count;
+    if (count >= kOpenMax) {
+        kept = kOpenMax;
+        tail_lo = (int64_t)wave_min_u64((uint64_t)tail_lo);
+        tail_c = wave_min_u64(tail_c);
+        tail_hi = (int64_t)(~wave_min_u64(~(uint64_t)(tail_hi + 1)) - 1);
+        if (lane == 0) out[kOpenMax - 1] = Open{tail_lo, tail_hi, tail_c, 0, 0};
+    }
+    __syncthreads();
+    // points for the next round: one each, the others by width
+    if (round == 0 && kept > 0) {
+        const float whole = [&] {
+            float v = (float)width;
+#pragma unroll
+            for (int k = kWave / 2; k >= 1; k >>= 1) v += __shfl_xor(v, k, kWave);
+            return v;
+        }();
+        int given = 0;
+        const int spare = points > kept ? points - kept : 0;
+        for (int k0 = 0; k0 < kept; k0 += kWave) {
+            const int k = k0 + lane;
+            int mine = 0;
+            if (k < kept) {
+                const float part = (float)(out[k].hi - out[k].lo) / whole * (float)spare * 0.9999f;
+                mine = 1 + (part > 0.0f ? (part < (float)spare ? (int)part : spare) : 0);
+            }
+            int sum = mine;
+#pragma unroll
+            for (int j = 1; j < kWave; j <<= 1) {
+                const int o = __shfl_up(sum, j, kWave);
+                if (lane >= j) sum += o;
+            }
+            if (k < kept) out[k].first = given + sum - mine;
+            given += __builtin_amdgcn_readlane(sum, kWave - 1);
+        }
+    }
+    if (lane == 0) {
+        meta->best_cost = bc;
+        meta->best_s = bs;
+        meta->ub = ub;
+        if (round == 0) meta->open[1] = kept; else meta->left = kept;
+    }
+}
+
+// ---- the budgets that are left ----
+
+constexpr int kListThreads = 256;
+template <typename U>
+__device__ __forceinline__ void list_start(const LongWs &w, LongMeta *meta, const Open *open, const int count,
+                                           const int64_t c, const int n, const int a, const uint64_t lowest,
+                                           const uint64_t highest)
+{
+    const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
+    const uint64_t pa = P[a];
+    int lo = a + 1, hi = n;  // the first end with P[x] - P[a] > lowest
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if ((uint64_t)P[mid] - pa > lowest) hi = mid; else lo = mid + 1;
+    }
+    for (int x = lo; x < n; ++x) {
+        const uint64_t sv = (uint64_t)P[x] - pa;
+        if (sv > highest) break;
+        bool in = false;
+        for (int k = 0; k < count && !in; ++k) in = (int64_t)sv > open[k].lo && (int64_t)sv <= open[k].hi;
+        if (!in) continue;
+        // (sv > 0: it lies above an interval's lower end; an empty slot is 0)
+        unsigned slot = (unsigned)((sv * 0x9E3779B97F4A7C15ull) >> 54);
+        static_assert(kSeenSlots == 1024, "ten bits of the product");
+        bool fresh = true;
+        for (int probe = 0; probe < 8; ++probe, slot = (slot + 1) % kSeenSlots) {
+            const uint64_t was = atomicCAS((unsigned long long *)w.seen + c * kSeenSlots + slot, 0ull,
+                                           (unsigned long long)sv);
+            if (was == sv) fresh = false;
+            if (was == sv || was == 0) break;
+        }
+        if (fresh) w.list[c * long_budgets(n) + atomicAdd(&meta->listed, 1)] = (uint32_t)a << 13 | (uint32_t)x;
+    }
+}
+
+__global__ __launch_bounds__(kListThreads) void search_list_kernel(int n, LongWs w)
+{
+    __shared__ Open open[kOpenMax];
+    const int64_t c = blockIdx.y;
+    LongMeta *meta = w.meta + c;
+    const int count = meta->left;
+    if (meta->status != CKPT_OK || count == 0) return;
+    for (int k = threadIdx.x; k < count; k += kListThreads) open[k] = w.open[(c * 3 + 2) * kOpenMax + k];
+    __syncthreads();
+    int64_t lowest = open[0].lo, highest = open[0].hi;
+    for (int k = 1; k < count; ++k) {
+        lowest = open[k].lo < lowest ? open[k].lo : lowest;
+        highest = open[k].hi > highest ? open[k].hi : highest;
+    }
+    const int a = (int)blockIdx.x * kListThreads + (int)threadIdx.x;
+    if (a >= n - 1) return;
+    if (meta->narrow)
+        list_start<uint32_t>(w, meta, open, count, c, n, a, (uint64_t)lowest, (uint64_t)highest);
+    else
+        list_start<uint64_t>(w, meta, open, count, c, n, a, (uint64_t)lowest, (uint64_t)highest);
+}
+
+// Bytes of F in LDS, before the heads.
+__host__ __device__ inline size_t long_f_bytes(int n) { return ((size_t)n + 1 + kWave) * 8; }
+
+// A wave per budget, its set recorded on the way (a pass of its own for the set of the best took
+// 143 us at 1,001 layers of a network and 85 at 4,096 aligned ones; recording makes a pass 7 to 20 % longer).  The last wave of
+// a chain takes the best point of the rounds besides: its set is not known yet.
+__global__ __launch_bounds__(kWave) void search_finish_kernel(int n, LongWs w)
+{
+    const int64_t c = blockIdx.y;
+    LongMeta *meta = w.meta + c;
+    if (meta->status != CKPT_OK) return;
+    const int lane = threadIdx.x, words = n / kWave + 1;
+    uint16_t *const head = (uint16_t *)(search_lds + long_f_bytes(n));
+    uint64_t *const mine = w.found + (c * gridDim.x + blockIdx.x) * 2;
+    uint64_t *const set = w.set + (c * gridDim.x + blockIdx.x) * words;
+    uint64_t cost = ~0ull, at = ~0ull;
+    const int listed = meta->listed, more = meta->best_cost != ~0ull ? 1 : 0;
+    for (int item = blockIdx.x; item < listed + more; item += gridDim.x) {
+        uint64_t s = meta->best_s;
+        if (item < listed) {
+            const uint32_t both = w.list[c * long_budgets(n) + item];
+            const int a = (int)(both >> 13), x = (int)(both & 8191u);
+            const uint64_t *P64 = (const uint64_t *)w.P + c * (n + 1);
+            const uint32_t *P32 = (const uint32_t *)P64;
+            s = meta->narrow ? (uint64_t)(P32[x] - P32[a]) : P64[x] - P64[a];
+        }
+        bool exact;
+        const uint64_t v = meta->narrow ? long_cost<uint32_t, true>(w, meta, c, n, (int64_t)s - 1, (int64_t)s, exact, head)
+                                        : long_cost<uint64_t, true>(w, meta, c, n, (int64_t)s - 1, (int64_t)s, exact, head);
+        if (!exact || v + s > cost || (v + s == cost && s > at)) continue;
+        uint64_t known = 0;
+        if (lane == 0) known = atomicMin((unsigned long long *)&meta->ub, (unsigned long long)(v + s));
+        known = uniform_lane_u(known, 0);
+        if (v + s > known) continue;
+        cost = v + s;
+        at = s;
+        // The set, from n back to 0, 64 positions at a time: their predecessors in the lanes, one after the other.
+        __syncthreads();
+        int cur = n;
+        for (int word = words - 1; word >= 0; --word) {
+            const int b = word * kWave, pred = head[b + lane <= n ? b + lane : n];
+            uint64_t bits = 0;
+            while (cur >= b) {
+                bits |= 1ull << (cur - b);
+                cur = cur == 0 ? -1 : __builtin_amdgcn_readlane(pred, cur - b);
+            }
+            if (lane == 0) set[word] = bits;
+        }
+        if (lane == 0) {
+            mine[0] = cost;
+            mine[1] = at;
+        }
+        __syncthreads();
+    }
+}
+
+// ---- results ----
+
+__global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int waves, int64_t cstride, int64_t pstride,
+                                                                     uint8_t *__restrict__ mask_out,
+                                                                     int64_t *__restrict__ peak_out,
+                                                                     int64_t *__restrict__ budget_out,
+                                                                     int32_t *__restrict__ status_out, LongWs w)
+{
+    const int64_t c = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const LongMeta m = w.meta[c];
+    uint8_t *mp = mask_out + c * cstride;
+    if (tid == 0 && status_out) status_out[c] = m.status;
+    if (m.status != CKPT_OK) {
+        for (int k = tid; k <= n; k += kListThreads) mp[(int64_t)k * pstride] = 0;
+        if (tid == 0) {
+            peak_out[c] = -1;
+            if (budget_out) budget_out[c] = -1;
+        }
+        return;
+    }
+    // (each wave by itself: the smallest cost, of those the smallest s, and a wave of the finish that found it)
+    uint64_t cost = ~0ull, at = ~0ull;
+    int by = 0;
+    for (int k = lane; k < waves; k += kWave) {
+        const uint64_t fc = w.found[(c * waves + k) * 2], fs = w.found[(c * waves + k) * 2 + 1];
+        if (fc < cost || (fc == cost && fs < at)) {
+            cost = fc;
+            at = fs;
+            by = k;
+        }
+    }
+    const uint64_t best = wave_min_u64(cost), s = wave_min_u64(cost == best ? at : ~0ull);
+    by = (int)wave_min_u32(cost == best && at == s ? (uint32_t)by : ~0u);
+    const uint64_t *set = w.set + (c * waves + by) * (n / kWave + 1);
+    for (int k = tid; k <= n; k += kListThreads)
+        mp[(int64_t)k * pstride] = (uint8_t)((set[k / kWave] >> (k % kWave)) & 1ull);
+    if (tid == 0) {
+        peak_out[c] = (int64_t)(best * m.unit);
+        if (budget_out) budget_out[c] = (int64_t)(s * m.unit);
+    }
+}
+
+std::atomic<bool> long_lds_raised[kMaxDevices];
+constexpr size_t kLongLds = ((size_t)CKPT_CUBIC_MAX_LAYERS + 1 + kWave) * 10;  // F and the heads
+
+hipError_t raise_long_lds_limit()
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (long_lds_raised[dev].load(std::memory_order_acquire)) return hipSuccess;
+    for (const void *f : {(const void *)search_round_kernel, (const void *)search_finish_kernel}) {
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLongLds);
+        if (e != hipSuccess) return e;
+    }
+    long_lds_raised[dev].store(true, std::memory_order_release);
+    return hipSuccess;
+}
+
+}  // namespace
+
+size_t cubic_search_long_bytes(int64_t batch, int n)
+{
+    LongWs w;
+    return carve_long(nullptr, batch, n, &w);
+}
+
+hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
+                                    int64_t *peak_out, int64_t *budget_out, int32_t *status_out, void *ws,
+                                    hipStream_t stream)
+{
+    if (batch == 0) return hipSuccess;
+    if (batch > 65535) return hipErrorInvalidConfiguration;
+    const size_t f_lds = long_f_bytes(n), set_lds = ((size_t)n + 1 + kWave) * 10;
+    if (set_lds > 65536) {
+        const hipError_t e = raise_long_lds_limit();
+        if (e != hipSuccess) return e;
+    }
+    LongWs w;
+    (void)carve_long(ws, batch, n, &w);
+    const int points = long_points(batch, n), waves = finish_waves(batch, n);
+    const unsigned B = (unsigned)batch;
+    hipLaunchKernelGGL(search_table_kernel, dim3(B), dim3(kTableThreads), ((size_t)n + 1) * 4, stream, d, n, st.chain,
+                       st.pos, points, waves, w);
+    for (int round = 0; round < 2; ++round) {
+        hipLaunchKernelGGL(search_round_kernel, dim3((unsigned)points, B), dim3(kWave), f_lds, stream, n, points, round, w);
+        hipLaunchKernelGGL(search_close_kernel, dim3(B), dim3(kWave), 0, stream, points, round, w);
+    }
+    hipLaunchKernelGGL(search_list_kernel, dim3((unsigned)((n + kListThreads - 1) / kListThreads), B), dim3(kListThreads),
+                       0, stream, n, w);
+    hipLaunchKernelGGL(search_finish_kernel, dim3((unsigned)waves, B), dim3(kWave), set_lds, stream, n, w);
+    hipLaunchKernelGGL(search_result_kernel, dim3(B), dim3(kListThreads), 0, stream, n, waves, st.chain, st.pos, mask_out,
+                       peak_out, budget_out, status_out, w);
     return hipGetLastError();
 }
 

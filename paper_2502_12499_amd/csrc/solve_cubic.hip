@@ -8,8 +8,9 @@
 // the answer is min_s (s + c_s) over the budgets s = 0 and s = P[b] - P[a-1],
 // 1 <= a <= b <= n-1.
 //
-// Chains of up to kSearchMaxLayers layers take the search of cubic_search.hip instead, except where the call
-// asks for the cost or the number of the budgets it runs (ckpt_solve_cubic_costs, _pruned).
+// ckpt_solve_cubic itself takes the search of cubic_search.hip, but for batches of more than 65,535 chains beyond
+// kSearchMaxLayers layers; the kernels here serve those and the calls that ask for the cost or the number of the
+// budgets they run (ckpt_solve_cubic_costs, _pruned).
 //
 // Kernels, all on the caller's stream, in this order (from 1024 layers on, links
 // and slices share one launch: neither needs the other):
@@ -2093,6 +2094,9 @@ hipError_t launch_solve_cubic(const int64_t *d, int64_t batch, int n, Strides st
     // 74 or 148 KB of the CU's 160)
     if (n <= kSearchMaxLayers && !pruned && !trace_s)
         return launch_cubic_search(d, batch, n, st, mask_out, peak_out, budget_out, status_out, ws, stream);
+    // (the limit: a chain is a row of a grid's y extent)
+    if (!pruned && !trace_s && batch <= 65535 && cubic_search_long_bytes(batch, n) <= cubic_workspace_bytes(batch, n))
+        return launch_cubic_search_long(d, batch, n, st, mask_out, peak_out, budget_out, status_out, ws, stream);
     pruned = pruned && n >= kPruneFromLayers;
     CubicWs w = carve_cubic(ws, batch, n);
     const int64_t K = num_budgets(n);

@@ -96,3 +96,55 @@ def test_ragged_batches_of_short_chains(batch, offsets_on_device):
     keep = np.ones(len(d), dtype=bool)
     keep[off[bad]:off[bad + 1]] = False
     assert np.array_equal(got[keep], want_mask[keep]) and not got[~keep].any()
+
+
+def network(n, seed):
+    """Layer sizes of a bottleneck network: every size a multiple of the batch size, many sums repeated."""
+    rng = np.random.default_rng(seed)
+    batch, width, pixels = int(rng.integers(9, 250)), 16 * int(rng.integers(1, 5)), 8 * int(rng.integers(7, 29))
+    ends = np.sort(rng.integers(2, n, size=3))
+    sizes = [batch * 12 * (2 * pixels) ** 2, batch * 4 * width * pixels ** 2]
+    for k in range(2, n):
+        stage = int(np.searchsorted(ends, k, side="right"))
+        w, hw = width << stage, max(pixels >> stage, 1)
+        sizes.append(batch * 4 * (4 * w if k % 3 == 1 else w) * hw * hw)
+    sizes.append(batch * 4000)
+    return np.array(sizes, dtype=np.int64)[:, None]
+
+
+@pytest.mark.parametrize("n", [257, 319, 320, 321, 511, 512, 640])
+def test_long_chains(n):
+    """One wave per point: slices of 64 positions, windows that reach back beyond two of them, the
+    greatest common divisor, 32- and 64-bit values."""
+    rng = np.random.default_rng(n)
+    print(f"cubic search, long chains: n = {n}", flush=True)
+    check(inputs.uniform_aligned_chains(n, n, 3, 256, 32768), chain_major=n % 2 == 1)
+    check(inputs.log_uniform_chains(n, n, 2))
+    check(network(n, n))
+    check(rng.integers(1, (1 << 62) // (n + 2), size=(n + 1, 1)).astype(np.int64))
+    check(rng.integers(1, 4, size=(n + 1, 2)).astype(np.int64))
+    check(np.full((n + 1, 1), 3 << 40, dtype=np.int64))
+    check((1 << rng.integers(0, 40, size=(n + 1, 1))).astype(np.int64))
+    check(np.arange(n + 1, 0, -1, dtype=np.int64)[:, None].copy())
+    heavy_ends = np.ones((n + 1, 1), dtype=np.int64)                             # one window over hundreds of layers
+    heavy_ends[n // 2] = 1 << 30
+    check(heavy_ends)
+
+
+@pytest.mark.parametrize("batch", [2, 33])
+def test_batches_of_long_chains(batch):
+    d = inputs.uniform_aligned_chains(7, 270, batch, 256, 32768)
+    d[:, 1] = inputs.log_uniform_chains(8, 270, 1)[:, 0]
+    want_peak, want_mask, want_s = oracle.batch_solve_static(inputs.chain_major(d))
+    if batch > 2:
+        d[100, 5] = 0
+    mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d)).cuda())
+    torch.cuda.synchronize()
+    ok = np.arange(batch) != 5
+    assert status.cpu().numpy().tolist() == [0 if k else 3 for k in ok]
+    assert np.array_equal(peak.cpu().numpy()[ok], want_peak[ok])
+    assert np.array_equal(budget.cpu().numpy()[ok], want_s[ok])
+    assert np.array_equal(mask.cpu().numpy().T[ok], want_mask[ok])
+    if batch > 2:
+        assert peak[5] == -1 and budget[5] == -1 and not mask[:, 5].any()
+
