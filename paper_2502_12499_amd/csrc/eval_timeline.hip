@@ -17,20 +17,23 @@
 //
 // A backward stage needs something from each side of position i: the part of
 // its segment below i (running sums from the pass itself) and the part above,
-// max or sum of d_i..d_{nx-1}.  The kernel walks the chain once, upwards, in
+// max or sum of d_i..d_{nx-1}; Algorithm 2's stages also contain the sum of ALL
+// checkpoints.  Chains of up to kTwiceMaxLayers layers are divided among the
+// waves of a workgroup, which hold their rows in registers: see
+// eval_timeline_parts_kernel.  Both objectives then read 9(n+1) bytes and write
+// 16(n+1) per chain (beyond kOnceMaxLayers layers the chain is read twice),
+// which is what the stages themselves have to move.
+// Longer chains, the groups of a ragged call, and under Algorithm 3 large
+// batches of more than kOnceMaxLayers layers take the walk (timeline_walk), a
+// lane per chain: it walks the chain once, upwards, in
 // chunks of kChunk rows held in registers, with the next chunk already loaded
 // and the one after it in flight.  For a chunk it first finds what lies above
 // the chunk's last row (it scans the next chunk's registers up to the first
 // checkpoint; while some lane of the wave has found none, the wave goes on
 // with the rows in flight and then with eight further rows at a time),
 // then sweeps the chunk downwards in registers to get the part above every
-// row, then upwards to write both stages of every row.  Algorithm 3's stages
-// need nothing else, so that objective reads 9(n+1) bytes and writes 16(n+1)
-// per chain, which is what the method itself has to move.  Algorithm 2's
-// stages all contain the sum of ALL checkpoints, which is only known at the
-// end of the chain, so that objective passes over the chain once more
-// beforehand; chains of up to 160 layers whose sizes fit 31 bits are left in
-// LDS by that pass, and the walk reads them from there.
+// row, then upwards to write both stages of every row.  For Algorithm 2 it
+// passes over the chain once more beforehand, to add up the checkpoints.
 #include "ckpt_internal.h"
 
 namespace ckpt {
@@ -38,19 +41,25 @@ namespace {
 
 constexpr int kBlock = 64;
 constexpr int kChunk = 8;
-// Under Algorithm 2 the chains of up to this many layers are kept in LDS between the two passes
-// (256 bytes per row and wave: 40 KB at most, so that four waves still fit a CU; with fewer the
-// kernel is slower than reading the chain twice: 2.8 ms against 2.0 ms at n = 256).
-constexpr int kLdsRowsMaxLayers = 160;
+// The parts of a chain.  32 rows are 112 registers a lane, so that four waves fit a SIMD: with 64 (two waves) and 16
+// (seven) 1,048,576 chains of 256 layers take as long within 5 %, 997 chains of 300 layers 23 us instead of 18.
+constexpr int kPartRows = 32, kPartWaves = 16;
+constexpr int kOnceMaxLayers = kPartRows * kPartWaves, kTwiceMaxLayers = 2 * kOnceMaxLayers;
+// Under Algorithm 3 the walk reads a chain once: beyond kOnceMaxLayers layers it is the faster one when its waves fill
+// the chip (1,001 layers: 50,000 chains 551 us against 456 of the parts, 200,000 chains 1.08 ms against 1.52).
+constexpr int64_t kTwiceMaxBatch = 49152;
+extern __shared__ __align__(16) uint64_t timeline_parts[];
 
-// The walk up the chain that writes both stages of every row.  ld(r) and lm(r) give the size and
-// the mask byte of row r, 1 <= r <= n (from memory, or from the copy the first pass left in LDS).
-template <int OBJ, class LD, class LM>
-__device__ __forceinline__ void timeline_walk(const LD ld, const LM lm, const int n, const int64_t x0,
-                                              const bool bad_mask, const uint64_t ckpt_all,
-                                              int64_t *__restrict__ op, const int64_t opstride,
+// The walk up the chain that writes both stages of every row.
+template <int OBJ>
+__device__ __forceinline__ void timeline_walk(const int64_t *__restrict__ dp, const uint8_t *__restrict__ mp,
+                                              const int64_t pstride, const int n, const bool bad_mask,
+                                              const uint64_t ckpt_all, int64_t *__restrict__ op, const int64_t opstride,
                                               int32_t *__restrict__ status_out, const int64_t c)
 {
+    auto ld = [&](int r) -> int64_t { return dp[(int64_t)r * pstride]; };
+    auto lm = [&](int r) -> uint8_t { return mp[(int64_t)r * pstride]; };
+    const int64_t x0 = dp[0];
     const int64_t last = 2 * (int64_t)n + 1;
     // the part of a segment above a row: its largest size (Algorithm 3) or its sum (Algorithm 2).
     // Sums are unsigned so that an invalid chain cannot trip signed overflow.
@@ -182,26 +191,17 @@ __device__ __forceinline__ void timeline_walk(const LD ld, const LM lm, const in
 }
 
 // The timeline of chain c of a batch laid out by the strides (the lanes of a wave call it together).
-// LDS_ROWS (Algorithm 2 only; `rows` is LDS for n x 64 words): the pass that adds up the checkpoints
-// leaves row r >= 1 of each lane's chain in rows[r-1][lane] as size | mask << 31, and if every size
-// of every chain of the wave is below 2^31 the walk reads the chain from there instead of from
-// memory a second time.
-template <int OBJ, bool LDS_ROWS>
+template <int OBJ>
 __device__ __forceinline__ void eval_timeline_chain(const int64_t *__restrict__ d, const uint8_t *__restrict__ mask,
                                                     int64_t batch, int n, int64_t cstride, int64_t pstride,
                                                     int64_t *__restrict__ out, int64_t ocstride, int64_t opstride,
-                                                    int32_t *__restrict__ status_out, const int64_t c, uint32_t *rows)
+                                                    int32_t *__restrict__ status_out, const int64_t c)
 {
-    static_assert(!LDS_ROWS || OBJ == CKPT_OBJ_STATIC, "only Algorithm 2 reads the chain twice");
     if (c >= batch) return;
     const int64_t *dp = d + c * cstride;
     const uint8_t *mp = mask + c * cstride;
-    int64_t *op = out + c * ocstride;
-    const int lane = threadIdx.x % kBlock;
 
-    const int64_t x0 = dp[0];
     uint64_t ckpt_all = 0;  // sum of all checkpoints (Algorithm 2 only)
-    bool narrow = true;
     if (OBJ == CKPT_OBJ_STATIC) {
         // both loads of a row are issued whatever the mask says, so that sixteen rows are in flight
 #pragma unroll 16
@@ -209,24 +209,10 @@ __device__ __forceinline__ void eval_timeline_chain(const int64_t *__restrict__ 
             const uint8_t on = mp[(int64_t)k * pstride];
             const int64_t x = dp[(int64_t)k * pstride];
             ckpt_all += on ? (uint64_t)x : 0;
-            if (LDS_ROWS && k >= 1) {
-                rows[(k - 1) * kBlock + lane] = (uint32_t)x | (on ? 0x80000000u : 0u);
-                narrow &= ((uint64_t)x >> 31) == 0;
-            }
         }
     }
     const bool bad_mask = mp[0] == 0 || mp[(int64_t)n * pstride] == 0;
-    auto ld_mem = [&](int r) -> int64_t { return dp[(int64_t)r * pstride]; };
-    auto lm_mem = [&](int r) -> uint8_t { return mp[(int64_t)r * pstride]; };
-    if (LDS_ROWS) {
-        if (__builtin_amdgcn_ballot_w64(!narrow) == 0) {
-            auto ld_lds = [&](int r) -> int64_t { return (int64_t)(rows[(r - 1) * kBlock + lane] & 0x7fffffffu); };
-            auto lm_lds = [&](int r) -> uint8_t { return (uint8_t)(rows[(r - 1) * kBlock + lane] >> 31); };
-            timeline_walk<OBJ>(ld_lds, lm_lds, n, x0, bad_mask, ckpt_all, op, opstride, status_out, c);
-            return;
-        }
-    }
-    timeline_walk<OBJ>(ld_mem, lm_mem, n, x0, bad_mask, ckpt_all, op, opstride, status_out, c);
+    timeline_walk<OBJ>(dp, mp, pstride, n, bad_mask, ckpt_all, out + c * ocstride, opstride, status_out, c);
 }
 
 template <int OBJ>
@@ -237,23 +223,237 @@ __global__ __launch_bounds__(kBlock) void eval_timeline_kernel(const int64_t *__
                                                                int64_t opstride, int32_t *__restrict__ status_out)
 {
     const int64_t c = (int64_t)xcd_paired_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    eval_timeline_chain<OBJ, false>(d, mask, batch, n, cstride, pstride, out, ocstride, opstride, status_out, c,
-                                    nullptr);
+    eval_timeline_chain<OBJ>(d, mask, batch, n, cstride, pstride, out, ocstride, opstride, status_out, c);
 }
 
-// Algorithm 2 for chains short enough that a wave's 64 chains fit in LDS four times per CU (n words
-// per lane, launched with n * 256 bytes of dynamic LDS): the chain is read from memory once.
-extern __shared__ __align__(16) uint32_t timeline_rows[];
-__global__ __launch_bounds__(kBlock) void eval_timeline_static_lds_kernel(const int64_t *__restrict__ d,
-                                                                          const uint8_t *__restrict__ mask,
-                                                                          int64_t batch, int n, int64_t cstride,
-                                                                          int64_t pstride, int64_t *__restrict__ out,
-                                                                          int64_t ocstride, int64_t opstride,
-                                                                          int32_t *__restrict__ status_out)
+// The rows of 64 chains are divided into parts among the waves of a workgroup.  A wave holds its part in registers, all
+// loads in flight at once, and sums it up; the parts' summaries meet in LDS; then each wave writes the stages of its own
+// rows: what a row needs from outside its part is a few values per chain.  Up to kOnceMaxLayers layers a wave has one
+// part and reads it once (TWICE = false); beyond, each has two, read again to write their stages.
+// Bound by memory: 1,048,576 chains of 256 layers move 6.75 GB in 1.38 to 1.41 ms, 4.8 to 4.9 TB/s, what a large copy
+// reaches (Algorithm 2 by the walk, which reads every chain twice: 1.97 ms).  With few chains, by one memory latency a
+// pass: 997 chains of 300 layers 18 us (116), one of 152 layers 17 (35), 997 of 1,001 layers 72 (371).
+// (Loads that bypass the caches: 2 % faster at that size, up to 40 % slower where the sizes fit the memory-side cache.)
+struct Part {
+    int64_t x[kPartRows];
+    uint8_t on[kPartRows];
+    int first, rows;
+    __device__ __forceinline__ Part(int q, int per, int n) : first(1 + q * per), rows(min(per, n - q * per)) {}
+};
+struct Stages {
+    int64_t *op;
+    int64_t opstride, last;
+    uint64_t ckpt_all;
+};
+
+template <int OBJ>
+__device__ __forceinline__ uint64_t timeline_join(uint64_t acc, uint64_t v)
 {
-    const int64_t c = (int64_t)xcd_paired_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    eval_timeline_chain<CKPT_OBJ_STATIC, true>(d, mask, batch, n, cstride, pstride, out, ocstride, opstride, status_out,
-                                               c, timeline_rows);
+    return OBJ == CKPT_OBJ_STATIC ? acc + v : (v > acc ? v : acc);
+}
+
+// Eight rows at a time; rows past the part's end re-read its last one.
+__device__ __forceinline__ void part_load(Part &p, const int64_t *__restrict__ dp, const uint8_t *__restrict__ mp,
+                                          const int64_t pstride)
+{
+#pragma unroll
+    for (int b = 0; b < kPartRows; b += 8) {
+        if (b >= p.rows) break;
+#pragma unroll
+        for (int u = b; u < b + 8; ++u) {
+            const int64_t r = p.first + (u < p.rows ? u : p.rows - 1);
+            p.on[u] = mp[r * pstride];
+            p.x[u] = dp[r * pstride];
+        }
+    }
+}
+
+// The mask of a part, a bit a row.
+__device__ __forceinline__ uint32_t part_bits(const Part &p)
+{
+    uint32_t on = 0;
+#pragma unroll
+    for (int b = 0; b < kPartRows; b += 8) {
+        if (b >= p.rows) break;
+#pragma unroll
+        for (int u = b; u < b + 8; ++u) on |= (uint32_t)(p.on[u] != 0) << u;
+    }
+    return on;
+}
+
+// Both stages of a part's rows.  below, seg, segmax, prev: of the rows before it; acc: what lies above it.
+template <int OBJ>
+__device__ __forceinline__ void part_write(const Part &p, const uint32_t on, const Stages &o, uint64_t below, uint64_t seg,
+                                           int64_t segmax, int64_t prev, uint64_t acc)
+{
+    // what lies above the last row of each eight
+    uint64_t above8[kPartRows / 8];
+#pragma unroll
+    for (int b = kPartRows - 8; b >= 0; b -= 8) {
+        above8[b / 8] = acc;
+        if (b >= p.rows || b == 0) continue;
+#pragma unroll
+        for (int u = b + 7; u >= b; --u)
+            if (u < p.rows) acc = ((on >> u) & 1u) ? 0 : timeline_join<OBJ>(acc, (uint64_t)p.x[u]);
+    }
+#pragma unroll
+    for (int b = 0; b < kPartRows; b += 8) {
+        if (b >= p.rows) break;
+        uint64_t above[8];
+        acc = above8[b / 8];
+#pragma unroll
+        for (int u = b + 7; u >= b; --u) {
+            if (u < p.rows) acc = ((on >> u) & 1u) ? 0 : timeline_join<OBJ>(acc, (uint64_t)p.x[u]);
+            above[u - b] = acc;
+        }
+#pragma unroll
+        for (int u = b; u < b + 8; ++u) {
+            if (u >= p.rows) break;
+            const int64_t i = p.first + u, x = p.x[u];
+            __builtin_nontemporal_store((int64_t)(below + (uint64_t)x + (uint64_t)prev), o.op + i * o.opstride);
+            uint64_t back;
+            if (OBJ == CKPT_OBJ_STATIC)
+                back = o.ckpt_all + seg + above[u - b];
+            else
+                back = below + seg + (uint64_t)x + ((uint64_t)segmax > above[u - b] ? (uint64_t)segmax : above[u - b]);
+            __builtin_nontemporal_store((int64_t)back, o.op + (o.last - i) * o.opstride);
+            const bool ck = (on >> u) & 1u;
+            below += ck ? (uint64_t)x : 0;
+            seg = ck ? 0 : seg + (uint64_t)x;
+            if (OBJ != CKPT_OBJ_STATIC) segmax = ck || x > segmax ? x : segmax;
+            prev = ck ? 0 : x;
+        }
+    }
+}
+
+enum { kCkpt, kTail, kTailMax, kHead, kTotal, kLargest, kPrev, kPartWords };  // a part's summary in LDS, [word][part][lane]
+enum : uint32_t { kHas = 1, kBadSize = 2, kOverflow = 4, kBadMask = 8 };      // and its flags behind them, [part][lane]
+size_t parts_lds_bytes(int parts) { return (size_t)parts * kBlock * (kPartWords * 8 + 4); }
+
+template <int OBJ, bool TWICE>
+__global__ __launch_bounds__(kBlock *kPartWaves) void eval_timeline_parts_kernel(
+    const int64_t *__restrict__ d, const uint8_t *__restrict__ mask, int64_t batch, int n, int parts, int64_t cstride,
+    int64_t pstride, int64_t *__restrict__ out, int64_t ocstride, int64_t opstride, int32_t *__restrict__ status_out)
+{
+    const int lane = threadIdx.x % kBlock, waves = blockDim.x / kBlock;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBlock);
+    const int64_t chain = (int64_t)xcd_paired_block(blockIdx.x, gridDim.x) * kBlock + lane;
+    const int64_t c = chain < batch ? chain : batch - 1;  // (lanes past the batch repeat the last chain, writing nothing)
+    const int64_t *dp = d + c * cstride;
+    const uint8_t *mp = mask + c * cstride;
+    const int per = (n + parts - 1) / parts;  // rows 1 + q * per .. of part q
+    uint32_t *const flags = (uint32_t *)(timeline_parts + (size_t)kPartWords * parts * kBlock);
+    auto word = [&](int field, int q) -> uint64_t & { return timeline_parts[(field * parts + q) * kBlock + lane]; };
+
+    const int64_t x0 = dp[0];
+    auto sum_up = [&](const Part &p, const uint32_t on, const int q) {
+        uint64_t ckpt = 0, tail = 0, head = 0, total = 0;
+        int64_t tail_max = 0, largest = 0, prev = 0;
+        uint32_t f = 0;
+#pragma unroll
+        for (int b = 0; b < kPartRows; b += 8) {
+            if (b >= p.rows) break;
+#pragma unroll
+            for (int u = b; u < b + 8; ++u) {
+                if (u >= p.rows) break;
+                const int64_t x = p.x[u];
+                const bool ck = (on >> u) & 1u;
+                f |= x <= 0 ? kBadSize : 0;
+                total += (uint64_t)x;
+                f |= total > (uint64_t)INT64_MAX ? kOverflow : 0;
+                largest = x > largest ? x : largest;
+                f |= ck ? kHas : 0;
+                head = (f & kHas) ? head : timeline_join<OBJ>(head, (uint64_t)x);
+                ckpt += ck ? (uint64_t)x : 0;
+                tail = ck ? 0 : tail + (uint64_t)x;
+                if (OBJ != CKPT_OBJ_STATIC) tail_max = ck || x > tail_max ? x : tail_max;
+                prev = ck ? 0 : x;
+            }
+        }
+        if (q == 0) f |= (x0 <= 0 ? kBadSize : 0) | (mp[0] == 0 ? kBadMask : 0);
+        if (q == parts - 1) f |= (on >> (p.rows - 1)) & 1u ? 0 : kBadMask;
+        word(kCkpt, q) = ckpt;
+        word(kTail, q) = tail;
+        if (OBJ != CKPT_OBJ_STATIC) word(kTailMax, q) = (uint64_t)tail_max;
+        word(kHead, q) = head;
+        word(kTotal, q) = total;
+        word(kLargest, q) = (uint64_t)largest;
+        word(kPrev, q) = (uint64_t)prev;
+        flags[q * kBlock + lane] = f;
+    };
+    int64_t *op = out + c * ocstride;
+    Stages o{op, opstride, 2 * (int64_t)n + 1, 0};
+    auto write = [&](const Part &p, const uint32_t on, const int mine) {
+        uint64_t below = (uint64_t)x0, seg = 0, acc = 0, total = (uint64_t)x0;
+        int64_t segmax = x0, prev = 0, largest = x0;
+        uint32_t seen = 0;
+        bool open = true;
+        o.ckpt_all = (uint64_t)x0;
+        for (int q = 0; q < parts; ++q) {
+            const uint32_t f = flags[q * kBlock + lane];
+            const uint64_t ck = word(kCkpt, q);
+            o.ckpt_all += ck;
+            if (q < mine) {
+                below += ck;
+                seg = (f & kHas) ? word(kTail, q) : seg + word(kTail, q);
+                if (OBJ != CKPT_OBJ_STATIC) {
+                    const int64_t m = (int64_t)word(kTailMax, q);
+                    segmax = (f & kHas) || m > segmax ? m : segmax;
+                }
+                if (q == mine - 1) prev = (int64_t)word(kPrev, q);
+            } else if (q > mine) {
+                if (open) acc = timeline_join<OBJ>(acc, word(kHead, q));
+                open = open && !(f & kHas);
+            }
+            // (the sum of the parts so far and a part are at most INT64_MAX each, or the flag is up)
+            total += word(kTotal, q);
+            seen |= f | (total > (uint64_t)INT64_MAX ? kOverflow : 0);
+            const int64_t m = (int64_t)word(kLargest, q);
+            largest = m > largest ? m : largest;
+        }
+        if (total + (uint64_t)largest > (uint64_t)INT64_MAX) seen |= kOverflow;
+        const int32_t status = (seen & kBadSize)    ? CKPT_ERR_SIZE
+                               : (seen & kOverflow) ? CKPT_ERR_OVERFLOW
+                               : (seen & kBadMask)  ? CKPT_ERR_MASK
+                                                    : CKPT_OK;
+        if (chain >= batch) return;
+        if (mine == 0) {
+            op[0] = status == CKPT_OK ? x0 : -1;
+            op[o.last * opstride] = status == CKPT_OK ? x0 : -1;
+            if (status_out) status_out[c] = status;
+        }
+        if (status == CKPT_OK) {
+            part_write<OBJ>(p, on, o, below, seg, segmax, prev, acc);
+        } else {
+            for (int64_t i = p.first; i < p.first + p.rows; ++i) {
+                op[i * opstride] = -1;
+                op[(o.last - i) * opstride] = -1;
+            }
+        }
+    };
+
+    if constexpr (TWICE) {
+#pragma unroll 1
+        for (int q = wave; q < parts; q += waves) {
+            Part p(q, per, n);
+            part_load(p, dp, mp, pstride);
+            sum_up(p, part_bits(p), q);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int q = wave; q < parts; q += waves) {
+            Part p(q, per, n);
+            part_load(p, dp, mp, pstride);
+            write(p, part_bits(p), q);
+        }
+    } else {
+        Part p(wave, per, n);
+        part_load(p, dp, mp, pstride);
+        const uint32_t on = part_bits(p);
+        sum_up(p, on, wave);
+        __syncthreads();
+        write(p, on, wave);
+    }
 }
 
 // Every group of a ragged call in one launch: a wave looks up the group its 64 chains belong to and
@@ -268,8 +468,8 @@ __global__ __launch_bounds__(kBlock) void eval_timeline_ragged_kernel(const int6
 {
     const RaggedGroupDev g = groups[ragged_group_of_wave(groups, n_groups, blockIdx.x)];
     const int64_t c = ((int64_t)blockIdx.x - g.wave_first) * kBlock + threadIdx.x;
-    eval_timeline_chain<OBJ, false>(d_stage + g.stage_off, mask_stage + g.stage_off, g.count, g.n, 1, g.pitch,
-                                    wide_stage + 2 * g.stage_off, 1, g.pitch, status_stage + g.first, c, nullptr);
+    eval_timeline_chain<OBJ>(d_stage + g.stage_off, mask_stage + g.stage_off, g.count, g.n, 1, g.pitch,
+                                    wide_stage + 2 * g.stage_off, 1, g.pitch, status_stage + g.first, c);
 }
 
 // Checkpoint sets that do not depend on the sizes: the two ends only, every
@@ -307,10 +507,26 @@ hipError_t launch_eval_timeline(const int64_t *d, const uint8_t *mask, int64_t b
 {
     if (batch == 0) return hipSuccess;
     const unsigned grid = (unsigned)((batch + kBlock - 1) / kBlock);
-    if (objective == CKPT_OBJ_STATIC && n <= kLdsRowsMaxLayers)
-        hipLaunchKernelGGL(eval_timeline_static_lds_kernel, dim3(grid), dim3(kBlock), (size_t)n * kBlock * 4, stream, d,
-                           mask, batch, n, st.chain, st.pos, out, out_st.chain, out_st.pos, status_out);
-    else if (objective == CKPT_OBJ_STATIC)
+    if (n <= kOnceMaxLayers || (n <= kTwiceMaxLayers && (objective == CKPT_OBJ_STATIC || batch <= kTwiceMaxBatch))) {
+        const int parts = (n + kPartRows - 1) / kPartRows, waves = parts < kPartWaves ? parts : kPartWaves;
+        const size_t lds = parts_lds_bytes(parts);
+        auto go = [&](auto kernel) -> hipError_t {
+            if (lds > 65536) {  // beyond the default limit for dynamic LDS
+                const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                         (int)lds);
+                if (e != hipSuccess) return e;
+            }
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kBlock), lds, stream, d, mask, batch, n, parts, st.chain,
+                               st.pos, out, out_st.chain, out_st.pos, status_out);
+            return hipGetLastError();
+        };
+        if (objective == CKPT_OBJ_STATIC)
+            return parts <= kPartWaves ? go(eval_timeline_parts_kernel<CKPT_OBJ_STATIC, false>)
+                                       : go(eval_timeline_parts_kernel<CKPT_OBJ_STATIC, true>);
+        return parts <= kPartWaves ? go(eval_timeline_parts_kernel<CKPT_OBJ_DYNAMIC, false>)
+                                   : go(eval_timeline_parts_kernel<CKPT_OBJ_DYNAMIC, true>);
+    }
+    if (objective == CKPT_OBJ_STATIC)
         hipLaunchKernelGGL(eval_timeline_kernel<CKPT_OBJ_STATIC>, dim3(grid), dim3(kBlock), 0, stream, d, mask,
                            batch, n, st.chain, st.pos, out, out_st.chain, out_st.pos, status_out);
     else

@@ -55,6 +55,60 @@ def test_timeline_sizes_on_both_sides_of_31_bits():
         check_timeline(d, m)
 
 
+# A part of a chain is 32 rows, a workgroup has up to 16 waves with one part each (512 layers) or two (1,024).
+@pytest.mark.parametrize("n", [8, 9, 31, 32, 33, 63, 65, 97, 161, 511, 512, 513, 1000, 1023, 1024, 1025])
+def test_timeline_divided_chains(n):
+    batch = 64 + 7
+    say(f"eval_timeline n={n}: chains in parts")
+    d = inputs.log_uniform_chains(41, n, batch)
+    m = inputs.bernoulli_masks(41, n, batch)
+    m[1:n, 1::3] = 0                                    # segments that span parts; one checkpoint somewhere in some
+    for c in range(1, batch, 6):
+        m[1 + (c * 37) % n, c] = 1
+    check_timeline(d, m)
+
+
+@pytest.mark.parametrize("n", [33, 512, 700])
+def test_timeline_divided_chains_data_errors(n):
+    d = np.full((n + 1, 70), 1000, dtype=np.int64)
+    m = np.ones((n + 1, 70), dtype=np.uint8)
+    d[n // 2, 1] = 0
+    d[0, 2] = -5
+    d[n, 3] = -1
+    d[[0, n // 2, n], 4] = 1 << 61                      # 3 * 2^61 and the largest again pass 2^63 - 1
+    d[[n // 2, n], 5] = (1 << 61) - n * 1000            # these do not
+    d[[0, 1, n], 6] = (1 << 62) + 1                     # the sum passes 2^63 within and between parts
+    m[0, 7] = 0
+    m[n, 69] = 0
+    m[n, 2] = 0                                         # (a bad size comes before a bad mask)
+    want = np.zeros(70, dtype=np.int32)
+    want[[1, 2, 3]] = 3                               # CKPT_ERR_SIZE
+    want[[4, 6]] = 4                                  # CKPT_ERR_OVERFLOW
+    want[[7, 69]] = 5                                 # CKPT_ERR_MASK
+    ok = want == 0
+    say(f"eval_timeline n={n}: data errors in any part")
+    for obj in (B.OBJ_STATIC, B.OBJ_DYNAMIC):
+        tl, status = B.ckpt_eval_timeline(to_dev(d), to_dev(m), obj)
+        tl = tl.cpu().numpy().T
+        assert np.array_equal(status.cpu().numpy(), want)
+        assert (tl[~ok] == -1).all()
+        assert np.array_equal(tl[ok], oracle.batch_timeline(inputs.chain_major(d[:, ok]), inputs.chain_major(m[:, ok]), obj))
+
+
+@pytest.mark.parametrize("batch", [49152, 49153])
+def test_timeline_large_batch_of_long_chains(batch):
+    """Under Algorithm 3 larger batches beyond 512 layers walk the chain instead: both give what a small batch does."""
+    n = 513
+    d = np.tile(inputs.log_uniform_chains(43, n, 64), (1, batch // 64 + 1))[:, :batch]
+    m = np.tile(inputs.bernoulli_masks(43, n, 64), (1, batch // 64 + 1))[:, :batch]
+    say(f"eval_timeline n={n} batch={batch}")
+    tl, status = B.ckpt_eval_timeline(to_dev(d), to_dev(m), B.OBJ_DYNAMIC)
+    assert not status.any()
+    want = to_dev(oracle.batch_timeline(inputs.chain_major(d[:, :64]), inputs.chain_major(m[:, :64]), B.OBJ_DYNAMIC).T)
+    for c0 in range(0, batch, 64):
+        assert torch.equal(tl[:, c0:c0 + 64], want[:, :min(64, batch - c0)])
+
+
 def test_timeline_fixed_sets():
     say("eval_timeline: VGG-19 with the paper's sets, the extreme sets")
     d = inputs.vgg19_chain()
