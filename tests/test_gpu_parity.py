@@ -127,6 +127,51 @@ def test_eval_peak_batches(batch, n):
     check_eval(d, m, chain_major=True)
 
 
+# From 32 layers on a workgroup's waves share 64 chains: up to 16 in batches of up to 16,384, 8 up to 131,072, and
+# from 128 layers on 4 up to 262,144; a wave has at least eight rows.
+@pytest.mark.parametrize("n", [31, 32, 33, 39, 40, 127, 128, 129, 257, 1000])
+def test_eval_peak_divided_chains(n):
+    batch = 64 + 7
+    say(f"eval_peak n={n}: chains divided among waves")
+    d = inputs.log_uniform_chains(12, n, batch)
+    m = inputs.bernoulli_masks(12, n, batch)
+    m[1:n, 1::3] = 0                                    # segments across parts; one checkpoint somewhere in some
+    for c in range(1, batch, 6):
+        m[1 + (c * 37) % n, c] = 1
+    check_eval(d, m)
+    check_eval(d, m, chain_major=True)
+    d[n // 2, 1] = 0                                    # a bad size, an overflow, open ends: in any part
+    d[n, 2] = -1
+    d[[0, n // 2, n], 3] = 1 << 61
+    d[[n // 2, n], 4] = (1 << 61) - (1 << 40)
+    m[0, 5] = m[n, 6] = m[n, 2] = 0
+    ok = np.ones(batch, dtype=bool)
+    ok[[1, 2, 3, 5, 6]] = False
+    for obj in (0, 1):
+        peak, status = B.ckpt_eval_peak(to_dev(d), to_dev(m), obj)
+        torch.cuda.synchronize()
+        assert np_(status)[:7].tolist() == [0, 3, 3, 4, 0, 5, 5] and not np_(status)[7:].any()
+        assert (np_(peak)[~ok] == -1).all()
+        assert np.array_equal(np_(peak)[ok], oracle.batch_peak(inputs.chain_major(d[:, ok]), inputs.chain_major(m[:, ok]), obj))
+
+
+@pytest.mark.parametrize("batch,n", [(16384, 40), (16385, 40), (131072, 40), (131073, 40), (131073, 130), (262145, 130)])
+def test_eval_peak_batches_around_the_rule(batch, n):
+    say(f"eval_peak batch={batch} n={n}")
+    d64, m64 = inputs.log_uniform_chains(13, n, 64), inputs.bernoulli_masks(13, n, 64)
+    d = to_dev(d64).repeat(1, batch // 64 + 1)[:, :batch].contiguous()
+    m = to_dev(m64).repeat(1, batch // 64 + 1)[:, :batch].contiguous()
+    for obj in (0, 1):
+        want = oracle.batch_peak(inputs.chain_major(d64), inputs.chain_major(m64), obj)
+        want = np.tile(want, batch // 64 + 1)[:batch]
+        peak, status = B.ckpt_eval_peak(d, m, obj)
+        torch.cuda.synchronize()
+        assert not np_(status).any() and np.array_equal(np_(peak), want)
+        both, _ = B.ckpt_eval_peak(d, m, B.OBJ_BOTH)
+        torch.cuda.synchronize()
+        assert np.array_equal(np_(both)[obj], want)
+
+
 def test_eval_peak_fixed_sets_and_paper_sets():
     d = inputs.vgg19_chain()
     for positions in ([3, 6, 24], [5, 10, 15, 20, 24], [2, 4, 6, 9, 11, 14, 16, 19, 21, 23, 24], [24],

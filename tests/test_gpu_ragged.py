@@ -110,6 +110,18 @@ def test_one_large_group_beside_small_ones():
     check_linear(d, off)
 
 
+@pytest.mark.parametrize("batch", [131072, 131073])
+def test_peaks_on_both_sides_of_the_rule_for_small_calls(batch):
+    """Up to 2,048 times 64 chains a workgroup of eight waves takes 64 chains, beyond it one wave."""
+    d, m, off = inputs.ragged_batch(15, np.full(batch, 2))
+    say(f"ragged peaks, {batch} chains")
+    for obj in (B.OBJ_STATIC, B.OBJ_DYNAMIC):
+        peak, status = B.ckpt_ragged_eval_peak(to_dev(d), to_dev(m), off, obj)
+        torch.cuda.synchronize()
+        assert (np_(status) == 0).all()
+        assert np.array_equal(np_(peak), oracle.ragged_peak(d, m, off, obj)), f"objective {obj}"
+
+
 def test_chain_with_a_bad_size_is_reported_alone():
     lengths = [15, 24, 15, 3]
     d, m, off = inputs.ragged_batch(15, lengths)
