@@ -861,7 +861,6 @@ namespace {
 // network 467 (1,200 to 1,490); two of 3,115 aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484
 // (118,000); 1,000 of 300 600 (3,710), unrounded 685 (34,000).
 constexpr int kOpenMax = 128;       // open intervals kept (more are joined)
-constexpr int kSeenSlots = 1024;    // table of values seen
 constexpr int kMostPoints = 1024;   // of a round, per chain
 constexpr int kTableThreads = 1024;
 constexpr int kTablePer = (CKPT_CUBIC_MAX_LAYERS + 1 + kTableThreads - 1) / kTableThreads;
@@ -894,7 +893,7 @@ struct LongWs {
     LongMeta *meta;      // [batch]
     Open *open;          // [batch][3][kOpenMax] before round 0, before round 1, after it
     Point *point;        // [batch][points]
-    uint64_t *seen;      // [batch][kSeenSlots]
+    uint64_t *seen;      // [batch][seen_slots] values listed
     uint64_t *found;     // [batch][finish_waves][2] best cost and its s of a finish wave
     uint64_t *set;       // [batch][finish_waves][n / 64 + 1] and its set, a bit a layer
     uint32_t *list;      // [batch][K] start << 13 | end
@@ -903,20 +902,22 @@ struct LongWs {
 static_assert(CKPT_CUBIC_MAX_LAYERS < (1 << 13), "a start and an end in 26 bits");
 
 // Points per chain and round: the chip's SIMDs twice over between the chains, within 64 .. 1,024 (512 below 512
-// layers, which a workspace has room for).
+// layers, 256 up to 256, which a workspace has room for).
 __host__ __device__ inline int long_points(int64_t batch, int n)
 {
-    const int most = n < 512 ? kMostPoints / 2 : kMostPoints;
+    const int most = n <= 256 ? kMostPoints / 4 : n < 512 ? kMostPoints / 2 : kMostPoints;
     const int64_t share = batch >= 32 ? 64 : 2048 / batch;
     return (int)(share < most ? share : most) / kWave * kWave;
 }
+// (up to 1,024: ten bits of a product)
+__host__ __device__ inline int seen_slots(int n) { return n <= 256 ? 256 : 1024; }
 __host__ __device__ inline int64_t long_budgets(int n) { return (int64_t)n * (n - 1) / 2 + 1; }
 
 // Waves per chain that evaluate what the rounds leave: as many as points, up to 512.
 __host__ __device__ inline int finish_waves(int64_t batch, int n)
 {
     const int points = long_points(batch, n);
-    return points < 512 ? points : n < 512 ? 256 : 512;
+    return n <= 256 ? 64 : points < 512 ? points : n < 512 ? 256 : 512;
 }
 
 __host__ size_t carve_long(void *ws, int64_t batch, int n, LongWs *w)
@@ -931,7 +932,7 @@ __host__ size_t carve_long(void *ws, int64_t batch, int n, LongWs *w)
     const size_t sets = B * (size_t)finish_waves(batch, n) * ((size_t)n / kWave + 1) * 8;
     w->point = (Point *)take(points > sets ? points : sets);
     w->set = (uint64_t *)w->point;  // (the rounds are over when the first set is written)
-    w->seen = (uint64_t *)take(B * kSeenSlots * 8);
+    w->seen = (uint64_t *)take(B * (size_t)seen_slots(n) * 8);
     w->found = (uint64_t *)take(B * (size_t)finish_waves(batch, n) * 16);
     w->list = (uint32_t *)take(B * (size_t)long_budgets(n) * 4);
     w->P = take(B * ((size_t)n + 1) * 8);
@@ -968,7 +969,7 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
     uint64_t bits = 0, high = 0, sum = 0, mx = 0, bad = 0;
 #pragma unroll
     for (int q = 0; q < kTablePer; ++q) x[q] = q < per && k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
-    for (int k = tid; k < kSeenSlots; k += kTableThreads) w.seen[c * kSeenSlots + k] = 0;
+    for (int k = tid; k < seen_slots(n); k += kTableThreads) w.seen[c * seen_slots(n) + k] = 0;
     for (int k = tid; k < 2 * waves; k += kTableThreads) w.found[c * 2 * waves + k] = ~0ull;
 #pragma unroll
     for (int q = 0; q < kTablePer; ++q) {
@@ -1279,6 +1280,7 @@ __device__ __forceinline__ void list_start(const LongWs &w, LongMeta *meta, cons
                                            const uint64_t highest)
 {
     const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
+    const int slots = seen_slots(n);
     const uint64_t pa = P[a];
     int lo = a + 1, hi = n;  // the first end with P[x] - P[a] > lowest
     while (lo < hi) {
@@ -1292,11 +1294,10 @@ __device__ __forceinline__ void list_start(const LongWs &w, LongMeta *meta, cons
         for (int k = 0; k < count && !in; ++k) in = (int64_t)sv > open[k].lo && (int64_t)sv <= open[k].hi;
         if (!in) continue;
         // (sv > 0: it lies above an interval's lower end; an empty slot is 0)
-        unsigned slot = (unsigned)((sv * 0x9E3779B97F4A7C15ull) >> 54);
-        static_assert(kSeenSlots == 1024, "ten bits of the product");
+        unsigned slot = (unsigned)((sv * 0x9E3779B97F4A7C15ull) >> 54) % slots;
         bool fresh = true;
-        for (int probe = 0; probe < 8; ++probe, slot = (slot + 1) % kSeenSlots) {
-            const uint64_t was = atomicCAS((unsigned long long *)w.seen + c * kSeenSlots + slot, 0ull,
+        for (int probe = 0; probe < 8; ++probe, slot = (slot + 1) % slots) {
+            const uint64_t was = atomicCAS((unsigned long long *)w.seen + c * slots + slot, 0ull,
                                            (unsigned long long)sv);
             if (was == sv) fresh = false;
             if (was == sv || was == 0) break;

@@ -2084,19 +2084,28 @@ hipError_t raise_links_lds_limit()
 
 }  // namespace
 
+constexpr int kWavePerPointFrom = 128;
+constexpr int64_t kWavePerPointMaxBatch = 512;
+
 hipError_t launch_solve_cubic(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out,
                               int64_t *peak_out, int64_t *budget_out, int32_t *status_out, bool pruned,
                               int64_t *evaluated_out, int64_t *trace_s, int64_t *trace_cost, void *ws,
                               hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
-    // (the limit: the search keeps 4 or 8 bytes per position for each of its 64 points in LDS; at 256 layers that is
-    // 74 or 148 KB of the CU's 160)
+    // Two forms of the search.  A lane per point up to kSearchMaxLayers layers: it keeps 4 or 8 bytes per position for
+    // each of its 64 points in LDS, at 256 layers 74 or 148 KB of the CU's 160.  A wave per point beyond (a chain is a
+    // row of a grid's y extent), and for few chains of more than 128 layers, which leave the other form's chip idle:
+    // one unrounded chain of 256 layers 260 us and 89, of 130 layers 103 and 81; 512 of 256 layers 700 and 355, aligned
+    // 440 and 326; 1,024 aligned ones of 180 layers 328 and 470.  (From about 104 to 141 layers on, by the
+    // batch, it finds room in the workspace.)
+    const bool wave_per_point = !pruned && !trace_s && batch <= (n <= kSearchMaxLayers ? kWavePerPointMaxBatch : 65535) &&
+                                n > kWavePerPointFrom &&
+                                cubic_search_long_bytes(batch, n) <= cubic_workspace_bytes(batch, n);
+    if (wave_per_point)
+        return launch_cubic_search_long(d, batch, n, st, mask_out, peak_out, budget_out, status_out, ws, stream);
     if (n <= kSearchMaxLayers && !pruned && !trace_s)
         return launch_cubic_search(d, batch, n, st, mask_out, peak_out, budget_out, status_out, ws, stream);
-    // (the limit: a chain is a row of a grid's y extent)
-    if (!pruned && !trace_s && batch <= 65535 && cubic_search_long_bytes(batch, n) <= cubic_workspace_bytes(batch, n))
-        return launch_cubic_search_long(d, batch, n, st, mask_out, peak_out, budget_out, status_out, ws, stream);
     pruned = pruned && n >= kPruneFromLayers;
     CubicWs w = carve_cubic(ws, batch, n);
     const int64_t K = num_budgets(n);

@@ -148,3 +148,17 @@ def test_batches_of_long_chains(batch):
     if batch > 2:
         assert peak[5] == -1 and budget[5] == -1 and not mask[:, 5].any()
 
+
+
+# Up to 256 layers a wave takes a point in batches of up to 512 chains of more than 128 layers where the workspace has
+# the room (from 128 to 141 layers on), else a lane does: both forms at the same lengths.
+@pytest.mark.parametrize("n", [128, 129, 136, 141, 142, 200, 255, 256])
+def test_both_forms_of_the_search(n):
+    for batch in (1, 2, 8):
+        check(inputs.uniform_aligned_chains(n, n, batch, 256, 32768))
+        check(inputs.log_uniform_chains(n + 1, n, batch), chain_major=True)
+
+
+@pytest.mark.parametrize("batch", [512, 513])
+def test_both_forms_around_the_largest_batch(batch):
+    check(inputs.uniform_aligned_chains(5, 150, batch, 1, 4))
