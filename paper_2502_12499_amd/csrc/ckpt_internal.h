@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -97,6 +98,26 @@ __device__ inline void wave_min_pair(int64_t &a, int64_t &b)
     const uint64_t bm = wave_min_u64((uint64_t)a == am ? (uint64_t)b : ~0ull);
     a = (int64_t)am;
     b = (int64_t)bm;
+}
+
+// ---- a first bound for the cubic search ------------------------------------------------------------
+//
+// For a segment length, a checkpoint wherever the interior prefix sums pass a multiple of it: what lies between two of
+// them adds up to the length at most, so checkpoints + length bounds the optimum from above.  In floats, on prefix
+// sums of the INTERIOR sizes: the size in front is subtracted as an integer first (in a float it would swallow interior
+// sizes 2^24 times smaller), and no sum that is rounded exceeds `all`, the sum of the interior sizes.
+__host__ __device__ inline float bound_prefix(uint64_t prefix, uint64_t first) { return (float)(prefix - first); }
+// What layer i adds to the checkpoints: before, at: bound_prefix at i - 1 and i; inv: 1 / length.
+__host__ __device__ inline float bound_layer(float before, float at, float inv)
+{
+    return floorf(before * inv) != floorf(at * inv) ? at - before : 0.0f;
+}
+// The cost from the sum of those over the n - 1 interior layers, without the sizes at the ends.  A difference of two
+// rounded prefix sums is off by up to 2^-24 of `all` for each, on either side of a checkpoint, and the 1/512 covers the
+// roundings of their sum, of the length and of its reciprocal.
+__host__ __device__ inline float bound_cost(float kept, float length, uint64_t all, int n)
+{
+    return (kept + length) * (1.0f + 1.0f / 512.0f) + (float)all * (float)n * 0x1p-22f;
 }
 
 // ---- eval_peak ---------------------------------------------------------------

@@ -960,7 +960,7 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
     __shared__ uint64_t room[kWaves], part[5][kWaves];
     __shared__ float bound_of[kBounds];
     __shared__ uint64_t ends2[2];
-    float *const prefix = (float *)search_lds;  // [n + 1]
+    float *const prefix = (float *)search_lds;  // [n + 1] of the interior sizes
     const int64_t c = blockIdx.x;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int64_t *dp = d + c * cstride;
@@ -1043,6 +1043,7 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
     const uint64_t incl = wave_scan_u64(mine);
     __syncthreads();
     if (lane == kWave - 1) room[wave] = incl;
+    if (tid == 0) ends2[0] = x[0];
     __syncthreads();
     uint64_t run = incl - mine, total = 0;
     for (int k = 0; k < kWaves; ++k) {
@@ -1055,27 +1056,20 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
         if (q >= per || k > n) break;
         run += x[q];
         if (m.narrow) P32[k] = (uint32_t)run; else P64[k] = run;
-        prefix[k] = (float)run;
-        if (k == 0) ends2[0] = x[q];
+        prefix[k] = bound_prefix(run, ends2[0]);
         if (k == n) ends2[1] = x[q];
     }
     __syncthreads();
-    // A bound: for 16 segment lengths (one to a wave) a checkpoint wherever the interior prefix sums pass a
-    // multiple of the length.  What lies between two of them adds up to the length at most; the floats' errors are
-    // covered by raising the result.
+    // a bound from 16 segment lengths, one to a wave (see bound_prefix)
     const uint64_t ends = ends2[0] + ends2[1], all = total - ends;
     {
-        const float p0 = prefix[0], length = fmaxf((float)all * exp2f(-0.5f * (float)(wave + 1)), 1.0f);
+        const float length = fmaxf((float)all * exp2f(-0.5f * (float)(wave + 1)), 1.0f);
         const float inv = 1.0f / length;
         float kept = 0.0f;
-        for (int i = 1 + lane; i < n; i += kWave) {
-            const float a = prefix[i - 1] - p0, b = prefix[i] - p0;
-            kept += floorf(a * inv) != floorf(b * inv) ? b - a : 0.0f;
-        }
+        for (int i = 1 + lane; i < n; i += kWave) kept += bound_layer(prefix[i - 1], prefix[i], inv);
 #pragma unroll
         for (int k = kWave / 2; k >= 1; k >>= 1) kept += __shfl_xor(kept, k, kWave);
-        // (a checkpoint's size comes from a difference of rounded sums: up to 2^-23 of the whole for each)
-        if (lane == 0) bound_of[wave] = (kept + length) * (1.0f + 1.0f / 512.0f) + (float)all * (float)n * 0x1p-22f;
+        if (lane == 0) bound_of[wave] = bound_cost(kept, length, all, n);
     }
     __syncthreads();
     if (tid != 0) return;

@@ -5,6 +5,7 @@
 // rejected before any 64-bit product can wrap.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -91,6 +92,35 @@ int ragged_plan_on_device(const int64_t *offsets_dev, int64_t batch, int max_lay
     return rc;
 }
 }  // namespace ckpt
+
+// The first bound of the cubic search (csrc/ckpt_internal.h) for every segment length the kernel tries, against the exact
+// cost of the set that its cuts make: never below it, and within its stated slack above.  Returns the least bound.
+static uint64_t bound_of_chain(const int64_t *d, int n)
+{
+    uint64_t all = 0, least = ~0ull;
+    for (int k = 1; k < n; ++k) all += (uint64_t)d[k];
+    for (int w = 0; w < 16; ++w) {
+        const float length = fmaxf((float)all * exp2f(-0.5f * (float)(w + 1)), 1.0f), inv = 1.0f / length;
+        uint64_t run = (uint64_t)d[0], checkpoints = 0, seg = 0, longest = 0;
+        float kept = 0.0f, before = ckpt::bound_prefix(run, (uint64_t)d[0]);
+        for (int i = 1; i < n; ++i) {
+            run += (uint64_t)d[i];
+            const float at = ckpt::bound_prefix(run, (uint64_t)d[0]);
+            kept += ckpt::bound_layer(before, at, inv);
+            const bool cut = floorf(before * inv) != floorf(at * inv);
+            checkpoints += cut ? (uint64_t)d[i] : 0;
+            seg = cut ? 0 : seg + (uint64_t)d[i];
+            longest = seg > longest ? seg : longest;
+            before = at;
+        }
+        const uint64_t bound = (uint64_t)(double)ckpt::bound_cost(kept, length, all, n) + 1;
+        if (bound < checkpoints + longest) return 0;
+        const double exact = (double)checkpoints + (double)length;
+        if ((double)bound > exact * 1.01 + (double)all * n * 0x1p-21 + 2.0) return 0;
+        least = bound < least ? bound : least;
+    }
+    return least;
+}
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "host_driver: %s failed at line %d\n", #c, __LINE__); std::exit(1); } } while (0)
 
@@ -199,6 +229,33 @@ int main()
         CHECK(ckpt_ragged_workspace_bytes(CKPT_CALL_EVAL_TIMELINE, offs, many) > (size_t)many * 12);
         std::free(offs);
         CHECK(ckpt::launches == 10);
+    }
+    // the first bound of the cubic search: sizes of several kinds, and the same for every size in front and at the end
+    {
+        static int64_t chain[8192];
+        uint64_t seed = 88172645463325252ull;
+        for (const int n : {2, 3, 64, 142, 257, 300, 1001, 4096, 8191}) {
+            for (int kind = 0; kind < 5; ++kind) {
+                for (int k = 0; k <= n; ++k) {
+                    seed ^= seed << 13; seed ^= seed >> 7; seed ^= seed << 17;
+                    const int64_t r = (int64_t)(seed >> 20);
+                    chain[k] = kind == 0 ? 100 : kind == 1 ? 1 + r % 1000000 : kind == 2 ? (int64_t)1 << r % 40 : kind == 3 ? 1 + r % 3
+                                                                                                : 1 + r % ((big >> 1) / (n + 1));
+                    if (kind == 1 && k == n / 2) chain[k] = 1000000000000000;
+                }
+                chain[0] = chain[n] = 1;
+                const uint64_t plain = bound_of_chain(chain, n);
+                CHECK(plain > 0);
+                for (const int shift : {20, 24, 34, 40, 43, 50, 61}) {
+                    chain[0] = (int64_t)1 << shift;
+                    chain[n] = 1;
+                    CHECK(bound_of_chain(chain, n) == plain);
+                    chain[0] = 1;
+                    chain[n] = (int64_t)1 << shift;
+                    CHECK(bound_of_chain(chain, n) == plain);
+                }
+            }
+        }
     }
     for (int s = -1; s < 10; ++s) CHECK(ckpt_status_string(s) != nullptr);
     std::printf("host_driver ok\n");

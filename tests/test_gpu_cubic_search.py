@@ -131,6 +131,24 @@ def test_long_chains(n):
     check(heavy_ends)
 
 
+@pytest.mark.parametrize("n", [64, 142, 200, 257, 300, 640])
+def test_sizes_at_the_ends_that_outweigh_the_rest(n):
+    """The size in front, or the last one, 2^20 to 2^50 times the interior sizes: neither is part of any budget."""
+    rng = np.random.default_rng(n)
+    columns = []
+    for k in (0, n):
+        for shift in (24, 34, 40, 43, 50, 61):
+            for kind in range(3):
+                x = [np.full(n + 1, 100), rng.integers(1, 1000001, size=n + 1), rng.integers(1, 4, size=n + 1)][kind]
+                x = x.astype(np.int64)
+                x[k] = 1 << shift
+                columns.append(x)
+    d = np.stack(columns, axis=1)
+    check(d)
+    for c in (6, 7, 24):                                                         # one chain: more points to a round
+        check(d[:, c:c + 1])
+
+
 @pytest.mark.parametrize("batch", [2, 33])
 def test_batches_of_long_chains(batch):
     d = inputs.uniform_aligned_chains(7, 270, batch, 256, 32768)
