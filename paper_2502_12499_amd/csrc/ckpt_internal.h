@@ -22,6 +22,15 @@ struct Strides {
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
+// Whether sum(d) + max(d) is beyond INT64_MAX, for kernels that add the sizes of a chain up in no particular order.
+// `sum` is their sum modulo 2^64, `high` that of their upper halves: from 2^31 on the sum is at least 2^63, and below
+// that it is less than 2^63 + 2^48, so it has not wrapped.  (The sum and the largest size together may wrap: one
+// size near INT64_MAX beside small ones.)
+__host__ __device__ inline bool chain_overflows(uint64_t sum, uint64_t high, uint64_t largest)
+{
+    return high >= (1ull << 31) || sum > (uint64_t)INT64_MAX || largest > (uint64_t)INT64_MAX - sum;
+}
+
 // Workgroups are handed to the eight XCDs of the chip in turn, and each XCD has its own L2.  A
 // one-wave workgroup of a lane-per-chain kernel touches 64 bytes of a mask row, half a 128-byte
 // line; its neighbour, which holds the other half, would run on the next XCD and fetch the line

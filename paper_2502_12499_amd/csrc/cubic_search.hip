@@ -621,7 +621,6 @@ __device__ __forceinline__ bool search_one(const int64_t *__restrict__ dp, const
         mx = sum[q] > mx ? sum[q] : mx;
         high += sum[q] >> 32;
     }
-    // sum(d) + max(d) > INT64_MAX: the high halves alone reach 2^31, or the sum (below 2^64 then) does
     high = lane63_u64(wave_scan_u64(high));
     mx = ~wave_min_u64(~mx);
 #pragma unroll
@@ -637,8 +636,7 @@ __device__ __forceinline__ bool search_one(const int64_t *__restrict__ dp, const
         base = lane63_u64(sum[q]);
     }
     __syncthreads();
-    const bool ovf = high >= (1ull << 31) || base + mx > (uint64_t)INT64_MAX;
-    const int32_t status = __any(bad) ? CKPT_ERR_SIZE : (ovf ? CKPT_ERR_OVERFLOW : CKPT_OK);
+    const int32_t status = __any(bad) ? CKPT_ERR_SIZE : chain_overflows(base, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
     int64_t cost = -1, budget = -1;
     uint32_t on = 0;
     if (status == CKPT_OK) {
@@ -1000,8 +998,7 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
         bad |= part[4][k];
     }
     LongMeta m = {};
-    m.status = bad ? CKPT_ERR_SIZE
-                   : (high >= (1ull << 31) || sum + mx > (uint64_t)INT64_MAX) ? CKPT_ERR_OVERFLOW : CKPT_OK;
+    m.status = bad ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
     if (m.status != CKPT_OK) {
         if (tid == 0) w.meta[c] = m;
         return;

@@ -257,6 +257,25 @@ int main()
             }
         }
     }
+    // the overflow test of the kernels that add up a chain's sizes in any order, against 128-bit sums: one large size
+    // (INT64_MAX down to what just fits, and half of it) among small ones, at every place, and many large ones
+    for (const int n : {1, 2, 3, 64, 300, 65535}) {
+        for (const uint64_t large : {(uint64_t)big, (uint64_t)big - 1, (uint64_t)big - 0x80000000u, (uint64_t)big - 0x200000000u,
+                                     (uint64_t)(big - n) / 2, (uint64_t)(big - n) / 2 + 1, (uint64_t)big / (n + 1), (uint64_t)1 << 62}) {
+            for (const uint64_t other : {(uint64_t)1, (uint64_t)1000000, (uint64_t)0xffffffffu, large}) {
+                uint64_t sum = 0, high = 0, most = 0;
+                __int128 whole = 0;
+                for (int k = 0; k <= n; ++k) {
+                    const uint64_t x = k == n / 2 ? large : other;
+                    sum += x;
+                    high += x >> 32;
+                    most = x > most ? x : most;
+                    whole += (__int128)x;
+                }
+                CHECK(ckpt::chain_overflows(sum, high, most) == (whole + (__int128)most > (__int128)big));
+            }
+        }
+    }
     for (int s = -1; s < 10; ++s) CHECK(ckpt_status_string(s) != nullptr);
     std::printf("host_driver ok\n");
     return 0;

@@ -71,6 +71,44 @@ def test_bad_chains_are_reported_alone():
         assert np.array_equal(mask.cpu().numpy().T[ok], want_mask[ok])
 
 
+def one_large_size(n):
+    """Chains (n+1, 16) of small sizes with one near the largest 64-bit value, and whether sum(d) + max(d) still fits:
+    the large size in front, inside and at the end; up to half of the largest value it does."""
+    top = (1 << 63) - 1
+    columns = []
+    for k in (0, 1, n // 2, n):
+        for large in (top, top - (1 << 31), (top - n) // 2 + 1, (top - n) // 2):
+            x = np.ones(n + 1, dtype=np.int64)
+            x[k] = large
+            columns.append(x)
+    d = np.stack(columns, axis=1)
+    fits = [sum(map(int, x)) + int(x.max()) <= top for x in columns]
+    assert fits.count(True) == 4
+    return d, np.array(fits)
+
+
+@pytest.mark.parametrize("n", [2, 3, 64, 142, 200, 257, 300])
+@pytest.mark.parametrize("batch", [16, 1040])
+def test_one_size_near_the_largest_value(n, batch):
+    """sum(d) + max(d) wraps around 2^64 for some of these chains."""
+    if batch > 16 and n > 64:
+        batch = 528                                                              # (a lane per point up to 256 layers)
+    d, fits = one_large_size(n)
+    d = np.tile(d, (1, batch // 16))
+    fits = np.tile(fits, batch // 16)
+    print(f"one large size: n = {n}, batch = {batch}", flush=True)
+    good = np.where(fits[None, :], d, 1)
+    want_peak, want_mask, want_s = oracle.batch_solve_static(inputs.chain_major(np.ascontiguousarray(good[:, :16])))
+    mask, peak, budget, status = (t.cpu().numpy() for t in B.ckpt_solve_cubic(torch.from_numpy(d).cuda()))
+    assert status.tolist() == [0 if f else 4 for f in fits]
+    for c in range(batch):
+        if fits[c]:
+            assert peak[c] == want_peak[c % 16] and budget[c] == want_s[c % 16]
+            assert np.array_equal(mask[:, c], want_mask[c % 16])
+        else:
+            assert peak[c] == -1 and budget[c] == -1 and not mask[:, c].any()
+
+
 @pytest.mark.parametrize("batch,offsets_on_device", [(300, False), (1500, True)])
 def test_ragged_batches_of_short_chains(batch, offsets_on_device):
     """Every class of lengths, both arithmetics, a bad chain among them."""
