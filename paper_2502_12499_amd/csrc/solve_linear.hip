@@ -946,9 +946,7 @@ __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const
         high += (uint64_t)__shfl_xor((long long)high, m, kWave);
     }
     mx = ~wave_min_u64(~mx);
-    // (high below 2^31: the sum stays below 2^63 + 2^48)
-    const bool ovf = high >= (1ull << 31) || sum + mx > (uint64_t)INT64_MAX;
-    const int32_t status = __any(bad) ? CKPT_ERR_SIZE : (ovf ? CKPT_ERR_OVERFLOW : CKPT_OK);
+    const int32_t status = __any(bad) ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
     uint16_t *const nxt = (uint16_t *)lds;
     int64_t peak = -1;
     if (status == CKPT_OK) {

@@ -8,6 +8,7 @@ import torch
 import oracle
 from paper_2502_12499_amd import binding as B
 from paper_2502_12499_amd import inputs
+from test_gpu_cubic_search import one_large_size
 
 pytestmark = pytest.mark.gpu
 
@@ -78,6 +79,35 @@ def test_bad_chains_are_reported_alone():
         assert (peak.cpu().numpy()[[2, 7, 11]] == -1).all() and not mask.cpu().numpy()[:, [2, 7, 11]].any()
         assert np.array_equal(peak.cpu().numpy()[ok], want_peak[ok])
         assert np.array_equal(mask.cpu().numpy().T[ok], want_mask[ok])
+
+
+def check_one_large_size(results, d, fits):
+    """d: chains of equal length, the first sixteen of them over and over."""
+    mask, peak, status = results
+    good = np.ascontiguousarray(np.where(fits[None, :], d, 1)[:, :16])
+    want_peak, want_mask = oracle.batch_solve_dynamic(inputs.chain_major(good))
+    assert status.tolist() == [0 if f else 4 for f in fits]
+    for c in range(d.shape[1]):
+        if fits[c]:
+            assert peak[c] == want_peak[c % 16] and np.array_equal(mask[:, c], want_mask[c % 16])
+        else:
+            assert peak[c] == -1 and not mask[:, c].any()
+
+
+@pytest.mark.parametrize("n", [2, 3, 64, 200, 511, 512, 700])
+def test_one_size_near_the_largest_value(n):
+    """sum(d) + max(d) wraps around 2^64 for some of these chains."""
+    d, fits = one_large_size(n)
+    print(f"linear, one large size: n = {n}", flush=True)
+    check_one_large_size([t.cpu().numpy() for t in B.ckpt_solve_linear(torch.from_numpy(d).cuda())], d, fits)
+
+
+def test_one_size_near_the_largest_value_in_a_ragged_batch():
+    d, fits = one_large_size(300)
+    flat = torch.from_numpy(np.ascontiguousarray(d.T).reshape(-1)).cuda()
+    off = np.arange(17, dtype=np.int64) * 301
+    mask, peak, status = (t.cpu().numpy() for t in B.ckpt_ragged_solve_linear(flat, off))
+    check_one_large_size((mask.reshape(16, 301).T, peak, status), d, fits)
 
 
 def test_long_groups_of_a_ragged_batch():
