@@ -68,6 +68,15 @@ namespace {
 constexpr int kRing = 16;        // slots per lane in each ring
 constexpr int kChunk = 8;        // rows in flight per lane
 constexpr int kListBlocks = 1024;
+
+// Whether T(i) + d_i + max(d), which bounds M(i) and every U(i,j), is beyond INT64_MAX, T(i) itself not being so.  (The
+// three may wrap together: T + d_i alone is below 2^64, with a largest size near INT64_MAX the sum of all is not.)
+__device__ inline bool value_overflows(uint64_t T, int64_t di, int64_t dmax)
+{
+    const uint64_t room = (uint64_t)INT64_MAX - T;
+    return (uint64_t)di > room || (uint64_t)dmax > room - (uint64_t)di;
+}
+
 constexpr int kLdsStackMaxN = 2047;
 
 struct LinearWs {
@@ -615,7 +624,7 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
             T += (uint64_t)dnext;
             dnext = di;
             out |= T > (uint64_t)INT64_MAX;
-            if (!out) out |= (T + (uint64_t)di + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // bounds M(i), every U(i,j)
+            if (!out) out |= value_overflows(T, di, dmax);
             if (out) return;
             const int64_t Ti = (int64_t)T;
             Rp = di > Rp ? di : Rp;
@@ -748,7 +757,7 @@ __device__ void list_chain(const int64_t *__restrict__ dp, const int n, const in
         ovf |= T > (uint64_t)INT64_MAX;
         dnext = di;
         if (bad_size | ovf) continue;  // keep scanning for errors, skip the work
-        ovf |= (T + (uint64_t)di + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // bounds M(i) and every U(i,j)
+        ovf |= value_overflows(T, di, dmax);
         if (ovf) continue;
         const int64_t Ti = (int64_t)T;
 
@@ -785,7 +794,7 @@ __device__ void list_chain(const int64_t *__restrict__ dp, const int n, const in
         qM[hd] = Mi;
         qT[hd] = Ti;
     }
-    ovf |= (T + (uint64_t)dnext + (uint64_t)dmax) > (uint64_t)INT64_MAX;  // sum(d) + max(d)
+    if (!ovf) ovf = value_overflows(T, dnext, dmax);  // sum(d) + max(d)
 
     int32_t status = CKPT_OK;
     if (bad_size) status = CKPT_ERR_SIZE;

@@ -102,6 +102,14 @@ def test_one_size_near_the_largest_value(n):
     check_one_large_size([t.cpu().numpy() for t in B.ckpt_solve_linear(torch.from_numpy(d).cuda())], d, fits)
 
 
+@pytest.mark.parametrize("n,batch", [(3, 4112), (64, 4160), (300, 6160), (20000, 16)])
+def test_one_size_near_the_largest_value_a_lane_per_chain(n, batch):
+    d, fits = one_large_size(n)
+    d, fits = np.tile(d, (1, batch // 16)), np.tile(fits, batch // 16)
+    print(f"linear, one large size: n = {n}, batch = {batch}", flush=True)
+    check_one_large_size([t.cpu().numpy() for t in B.ckpt_solve_linear(torch.from_numpy(d).cuda())], d, fits)
+
+
 def test_one_size_near_the_largest_value_in_a_ragged_batch():
     d, fits = one_large_size(300)
     flat = torch.from_numpy(np.ascontiguousarray(d.T).reshape(-1)).cuda()
