@@ -401,9 +401,11 @@ __device__ inline uint64_t select_lanes(uint64_t off, uint64_t on, uint64_t mask
 // under way; a window that reaches back beyond Z is finished from the values parked in F.
 // What bounds it is the chain of dependent instructions of a head (about 50, half of them scalar, eight to nine
 // cycles each); a form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips.
-// P: prefix sums, P[n] below 2^31 or 2^63; F: room for n + 1 values; RECORD: head[j], the predecessor of j, is
-// written for j = 1..n.  stop(F(h)) is asked once per slice; when it says so the pass ends with F(h), which F_s(n)
-// is not below.
+// P: prefix sums, P[n] below 2^31 or 2^63; F (and head): room for n + 1 + kWave values; RECORD: head[j], the
+// predecessor of j, is written for j = 1..n.  stop(F(h)) is asked once per slice; when it says so the pass ends with
+// F(h), which F_s(n) is not below.  The pass ends whatever the sums are: a new head keeps the cell it was chosen for,
+// seen or not (on sums that ascend it always sees it; a test for an empty window took 5 % of a call), and a slice past
+// the last cell ends the pass with the largest value of the type.
 struct NeverStop {
     template <typename U>
     __device__ bool operator()(U) const { return false; }
@@ -422,21 +424,22 @@ __device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F,
     U SA = PA + s, DA = PA - QA;
     U FA = PA;                             // (F(0) = P[0] in lane 0)
     int HA = 0;
-    int h = 0, t = 1;                      // t: the next cell, relative to base (0..63)
+    int h = 0;
+    uint64_t from = ~1ull, test = ~1ull;   // the lanes of the head's cells, and of those that may end it
     U fh = uniform_lane_u(PA, 0), Sh = fh + s;
     for (;;) {
-        // the cells from t on, as if h stayed for all of them (a later head overwrites them)
-        const uint64_t from = ~0ull << t;
+        // as if h stayed for all of its cells (a later head overwrites them)
         FA = select_lanes(FA, DA + fh, from);
         if (RECORD) HA = (int)select_lanes((uint32_t)HA, (uint32_t)h, from);
-        const uint64_t out = __builtin_amdgcn_ballot_w64(QA > Sh) & from;
+        const uint64_t out = __builtin_amdgcn_ballot_w64(QA > Sh) & test;
         if (out == 0) {
             // h outlasts A: slide
             if (stop(fh)) return fh;
             F[base + lane] = FA;
             if (RECORD) head[base + lane] = (H)HA;
             base += kWave;
-            t = 0;
+            if (__builtin_expect(base > n + 1, 0)) return kMax;
+            from = test = ~0ull;
             SZ = SA; FZ = FA;
             PA = PB; QA = QB;
             SA = PA + s; DA = PA - QA;
@@ -447,13 +450,15 @@ __device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F,
         const int e = __ffsll((unsigned long long)out) - 1;  // the first cell that does not see h
         if (__builtin_expect(base + e > n, 0)) {
             if (RECORD && base + lane <= n) head[base + lane] = (H)HA;
-            // (t = 0 and cell n the last of the slice before: its value is in Z)
+            // (no cell in A yet and cell n the last of the slice before: its value is in Z)
             return n >= base ? uniform_lane_u(FA, n - base) : uniform_lane_u(FZ, kWave - 1);
         }
         // The window of e: P[i] + s >= P[e - 1], i < e; h and what lies before it are out by themselves.  (Before the
         // first slide Z holds no positions: its values are the largest there are.)
         const U Pe = uniform_lane_u(QA, e);
-        const uint64_t wa = __builtin_amdgcn_ballot_w64(SA >= Pe) & ~(~0ull << e);
+        from = ~0ull << e;
+        test = from << 1;
+        const uint64_t wa = __builtin_amdgcn_ballot_w64(SA >= Pe) & ~from;
         const uint64_t wz = __builtin_amdgcn_ballot_w64(SZ >= Pe);
         const U va = select_lanes(kMax, FA, wa), vz = select_lanes(kMax, FZ, wz);
         if constexpr (sizeof(U) == 4) fh = wave_min_u32(va < vz ? va : vz); else fh = wave_min_u64(va < vz ? va : vz);
@@ -464,9 +469,8 @@ __device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F,
         const U pa = uniform_lane_u(SA, sa & 63), pz = uniform_lane_u(SZ, sz & 63);
         if (RECORD) h = in_z ? base - kWave + sz : base + sa;
         Sh = in_z ? pz : pa;
-        t = e;
-        if (__builtin_expect((wz & 1ull) != 0 && base > kWave, 0)) {
-            // the whole of Z lies in the window: the parked values before it
+        if (__builtin_expect((wz & 1ull) != 0, 0)) {
+            // the whole of Z lies in the window: the parked values before it, if there are any
             for (int top = base - kWave - 1; top >= 0; top -= kWave) {
                 const int i = top - lane;          // (top is 63 or more)
                 const U si = P[i] + s, fi = F[i];
@@ -534,9 +538,10 @@ __device__ __forceinline__ void solve_short(const uint64_t (&sum)[kSearchPer], c
     (void)wave_cost<uint64_t, true>(full, n, (uint64_t)bs, F, head);
     __syncthreads();
     bits = 0;
-    for (int j = n;; j = head[j]) {
+    for (int j = n, next;; j = next) {
         if ((j & (kWave - 1)) == lane) bits |= 1u << (j / kWave);
-        if (j == 0) break;
+        next = head[j];
+        if (j == 0 || next >= j) break;
     }
     cost = (int64_t)((uint64_t)bc << shift);
     budget = (int64_t)((uint64_t)bs << shift);
@@ -1122,7 +1127,9 @@ __device__ __forceinline__ uint64_t long_cost(const LongWs &w, const LongMeta *m
         if (out) exact = false;
         return out;
     };
-    return (uint64_t)wave_cost<U, RECORD>(P, n, (U)s, (U *)search_lds, head, stop);
+    const U v = wave_cost<U, RECORD>(P, n, (U)s, (U *)search_lds, head, stop);
+    exact = exact && v != std::numeric_limits<U>::max();
+    return (uint64_t)v;
 }
 
 __global__ __launch_bounds__(kWave) void search_round_kernel(int n, int points, int round, LongWs w)
@@ -1387,16 +1394,8 @@ __global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int 
     const int tid = threadIdx.x, lane = tid % kWave;
     const LongMeta m = w.meta[c];
     uint8_t *mp = mask_out + c * cstride;
-    if (tid == 0 && status_out) status_out[c] = m.status;
-    if (m.status != CKPT_OK) {
-        for (int k = tid; k <= n; k += kListThreads) mp[(int64_t)k * pstride] = 0;
-        if (tid == 0) {
-            peak_out[c] = -1;
-            if (budget_out) budget_out[c] = -1;
-        }
-        return;
-    }
-    // (each wave by itself: the smallest cost, of those the smallest s, and a wave of the finish that found it)
+    // (each wave by itself: the smallest cost, of those the smallest s, and a wave of the finish that found it; what
+    // the table left in `found` of a bad chain is not looked at)
     uint64_t cost = ~0ull, at = ~0ull;
     int by = 0;
     for (int k = lane; k < waves; k += kWave) {
@@ -1409,6 +1408,17 @@ __global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int 
     }
     const uint64_t best = wave_min_u64(cost), s = wave_min_u64(cost == best ? at : ~0ull);
     by = (int)wave_min_u32(cost == best && at == s ? (uint32_t)by : ~0u);
+    // (a checked chain has a best point; if there is none all the same, no set has been written)
+    const int32_t status = m.status == CKPT_OK && best == ~0ull ? CKPT_ERR_DEVICE : m.status;
+    if (tid == 0 && status_out) status_out[c] = status;
+    if (status != CKPT_OK) {
+        for (int k = tid; k <= n; k += kListThreads) mp[(int64_t)k * pstride] = 0;
+        if (tid == 0) {
+            peak_out[c] = -1;
+            if (budget_out) budget_out[c] = -1;
+        }
+        return;
+    }
     const uint64_t *set = w.set + (c * waves + by) * (n / kWave + 1);
     for (int k = tid; k <= n; k += kListThreads)
         mp[(int64_t)k * pstride] = (uint8_t)((set[k / kWave] >> (k % kWave)) & 1ull);
