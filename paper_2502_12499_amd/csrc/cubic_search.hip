@@ -470,7 +470,9 @@ __device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F,
         if (RECORD) h = in_z ? base - kWave + sz : base + sa;
         Sh = in_z ? pz : pa;
         if (__builtin_expect((wz & 1ull) != 0, 0)) {
-            // the whole of Z lies in the window: the parked values before it, if there are any
+            // the whole of Z lies in the window: the parked values before it, if there are any (other lanes stored
+            // them: the fence keeps the compiler from moving the loads up; it costs no instruction)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             for (int top = base - kWave - 1; top >= 0; top -= kWave) {
                 const int i = top - lane;          // (top is 63 or more)
                 const U si = P[i] + s, fi = F[i];
