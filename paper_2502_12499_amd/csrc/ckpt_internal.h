@@ -8,6 +8,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <initializer_list>
+
 #include "../../include/ckpt.h"
 
 namespace ckpt {
@@ -21,6 +24,27 @@ struct Strides {
 };
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
+
+// Dynamic LDS beyond 64 KB has to be allowed per kernel and device.  The limit is state that all host threads share, so
+// it is raised once, to the most that any call of the kernels asks for, and not to what the present call does.
+// `raised`: a flag per device, of the calling file.
+constexpr int kMaxDevices = 64;
+constexpr size_t kDefaultLdsLimit = 65536;
+inline hipError_t raise_lds_limit(std::atomic<bool> (&raised)[kMaxDevices], std::initializer_list<const void *> kernels,
+                                  size_t most)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (raised[dev].load(std::memory_order_acquire)) return hipSuccess;
+    for (const void *f : kernels) {
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        if (e != hipSuccess) return e;
+    }
+    raised[dev].store(true, std::memory_order_release);
+    return hipSuccess;
+}
 
 // Whether sum(d) + max(d) is beyond INT64_MAX, for kernels that add the sizes of a chain up in no particular order.
 // `sum` is their sum modulo 2^64, `high` that of their upper halves: from 2^31 on the sum is at least 2^63, and below

@@ -14,7 +14,6 @@
 //   3. When few budgets lie in them (each is the difference of two prefix sums: found by bisection,
 //      the starts across the lanes) those are evaluated, and that is the end; else the
 //      intervals are cut into smaller ones at new points, and so on.
-#include <atomic>
 #include <limits>
 #include <type_traits>
 
@@ -760,27 +759,16 @@ __global__ __launch_bounds__(kWave) void cubic_search_ragged_wide_kernel(const i
     }
 }
 
-constexpr int kMaxDevices = 64;
 std::atomic<bool> search_lds_raised[kMaxDevices];
 
-// Once per device: the longest of these chains need more dynamic LDS than the default limit.
+// (the longest of these chains need more than the default)
 hipError_t raise_search_lds_limit()
 {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (search_lds_raised[dev].load(std::memory_order_acquire)) return hipSuccess;
-    const int most = (int)search_lds_bytes(kSearchMaxLayers, 8);
-    for (const void *f : {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
-                          (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel<true>,
-                          (const void *)cubic_search_ragged_kernel<false>,
-                          (const void *)cubic_search_ragged_wide_kernel}) {
-        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-        if (e != hipSuccess) return e;
-    }
-    search_lds_raised[dev].store(true, std::memory_order_release);
-    return hipSuccess;
+    return raise_lds_limit(search_lds_raised,
+                           {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
+                            (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel<true>,
+                            (const void *)cubic_search_ragged_kernel<false>, (const void *)cubic_search_ragged_wide_kernel},
+                           search_lds_bytes(kSearchMaxLayers, 8));
 }
 
 // From this many chains on the launch has LDS for 32-bit arithmetic only, twice the waves on a CU, and the
@@ -795,7 +783,7 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
                                hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
-    if (search_lds_bytes(n, 8) > 65536) {
+    if (search_lds_bytes(n, 8) > kDefaultLdsLimit) {
         const hipError_t e = raise_search_lds_limit();
         if (e != hipSuccess) return e;
     }
@@ -1435,17 +1423,7 @@ constexpr size_t kLongLds = ((size_t)CKPT_CUBIC_MAX_LAYERS + 1 + kWave) * 10;  /
 
 hipError_t raise_long_lds_limit()
 {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (long_lds_raised[dev].load(std::memory_order_acquire)) return hipSuccess;
-    for (const void *f : {(const void *)search_round_kernel, (const void *)search_finish_kernel}) {
-        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLongLds);
-        if (e != hipSuccess) return e;
-    }
-    long_lds_raised[dev].store(true, std::memory_order_release);
-    return hipSuccess;
+    return raise_lds_limit(long_lds_raised, {(const void *)search_round_kernel, (const void *)search_finish_kernel}, kLongLds);
 }
 
 }  // namespace
@@ -1463,7 +1441,7 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
     if (batch == 0) return hipSuccess;
     if (batch > 65535) return hipErrorInvalidConfiguration;
     const size_t f_lds = long_f_bytes(n), set_lds = ((size_t)n + 1 + kWave) * 10;
-    if (set_lds > 65536) {
+    if (set_lds > kDefaultLdsLimit) {
         const hipError_t e = raise_long_lds_limit();
         if (e != hipSuccess) return e;
     }

@@ -499,6 +499,8 @@ __global__ __launch_bounds__(kBlock) void select_baseline_kernel(int64_t batch, 
     }
 }
 
+std::atomic<bool> parts_lds_raised[kMaxDevices];
+
 }  // namespace
 
 hipError_t launch_eval_timeline(const int64_t *d, const uint8_t *mask, int64_t batch, int n, Strides st,
@@ -511,9 +513,11 @@ hipError_t launch_eval_timeline(const int64_t *d, const uint8_t *mask, int64_t b
         const int parts = (n + kPartRows - 1) / kPartRows, waves = parts < kPartWaves ? parts : kPartWaves;
         const size_t lds = parts_lds_bytes(parts);
         auto go = [&](auto kernel) -> hipError_t {
-            if (lds > 65536) {  // beyond the default limit for dynamic LDS
-                const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                         (int)lds);
+            if (lds > kDefaultLdsLimit) {  // (two parts to a wave)
+                const hipError_t e = raise_lds_limit(parts_lds_raised,
+                                                     {(const void *)eval_timeline_parts_kernel<CKPT_OBJ_STATIC, true>,
+                                                      (const void *)eval_timeline_parts_kernel<CKPT_OBJ_DYNAMIC, true>},
+                                                     parts_lds_bytes(kTwiceMaxLayers / kPartRows));
                 if (e != hipSuccess) return e;
             }
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kBlock), lds, stream, d, mask, batch, n, parts, st.chain,

@@ -2062,24 +2062,13 @@ int64_t cubic_trace_len(int n) { return waves_per_chain(n) * kWave; }
 
 namespace {
 
-// Once per device: the links kernel of long chains needs more dynamic LDS than the default limit.
-constexpr int kMaxDevices = 64;
 std::atomic<bool> links_lds_raised[kMaxDevices];
 
+// (the tables of long chains need more than the default)
 hipError_t raise_links_lds_limit()
 {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (links_lds_raised[dev].load(std::memory_order_acquire)) return hipSuccess;
-    e = hipFuncSetAttribute((const void *)cubic_links_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)links_lds_bytes(CKPT_CUBIC_MAX_LAYERS));
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)cubic_prepare_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)links_lds_bytes(CKPT_CUBIC_MAX_LAYERS));
-    if (e == hipSuccess) links_lds_raised[dev].store(true, std::memory_order_release);
-    return e;
+    return raise_lds_limit(links_lds_raised, {(const void *)cubic_links_kernel, (const void *)cubic_prepare_kernel},
+                           links_lds_bytes(CKPT_CUBIC_MAX_LAYERS));
 }
 
 }  // namespace
@@ -2127,7 +2116,7 @@ hipError_t launch_solve_cubic(const int64_t *d, int64_t batch, int n, Strides st
 
     hipLaunchKernelGGL(cubic_prologue_kernel, dim3((unsigned)batch), dim3(kWave), 0, stream, d, batch, n,
                        st.chain, st.pos, w);
-    if (links_lds_bytes(n) > 65536) {  // beyond the default limit for dynamic LDS
+    if (links_lds_bytes(n) > kDefaultLdsLimit) {
         const hipError_t e = raise_links_lds_limit();
         if (e != hipSuccess) return e;
     }

@@ -1076,7 +1076,6 @@ namespace {
 // One copy per GPU, at an address of its own on each; held until the process ends.
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
 
-constexpr int kMaxDevices = 64;
 std::atomic<void *> scratch_of_device[kMaxDevices];
 }  // namespace
 

@@ -166,6 +166,8 @@ __global__ __launch_bounds__(kWave) void quadratic_kernel(const int64_t *__restr
     }
 }
 
+std::atomic<bool> quadratic_lds_raised[kMaxDevices];
+
 }  // namespace
 
 size_t quadratic_lds_bytes(int n) { return ((size_t)n + 1) * 26 + 16; }
@@ -175,9 +177,9 @@ hipError_t launch_solve_quadratic(const int64_t *d, int64_t batch, int n, Stride
 {
     if (batch == 0) return hipSuccess;
     const size_t lds = quadratic_lds_bytes(n);
-    if (lds > 65536) {  // beyond the default limit for dynamic LDS
-        const hipError_t e = hipFuncSetAttribute((const void *)quadratic_kernel<4>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (lds > kDefaultLdsLimit) {
+        const hipError_t e = raise_lds_limit(quadratic_lds_raised, {(const void *)quadratic_kernel<4>},
+                                             quadratic_lds_bytes(CKPT_QUADRATIC_MAX_LAYERS));
         if (e != hipSuccess) return e;
     }
     // enough waves to fill the machine several times over; each walks its share of the batch

@@ -5,16 +5,19 @@
 #include <stdlib.h>
 #include <sys/mman.h>
 
+#include <map>
+
 namespace emu {
 
 dim3 thread, block, threads, blocks;
 unsigned char *dynamic_lds;
 uint64_t rendezvous_limit = ~0ull;
+std::function<void()> meanwhile;
 
 namespace {
 constexpr unsigned kMostLanes = 1024;
 constexpr size_t kStack = 128 << 10, kPage = 4096;
-constexpr size_t kLdsOfACu = 160 << 10;
+constexpr size_t kLdsOfACu = 160 << 10, kLdsLimit = 64 << 10;
 
 struct Lane {
     void *sp;
@@ -34,6 +37,7 @@ void *scheduler;
 const std::function<void()> *kernel;
 const char *kernel_name;
 uint64_t meetings;
+std::map<const void *, size_t> lds_limit;
 
 [[noreturn]] void stop(const char *why)
 {
@@ -110,12 +114,13 @@ void *device_memory(size_t bytes)
     return p + kPage + pages - body;
 }
 
-void launch(const char *name, dim3 grid, dim3 group, size_t lds, const std::function<void()> &f)
+void launch(const char *name, const void *entry, dim3 grid, dim3 group, size_t lds, const std::function<void()> &f)
 {
     kernel_name = name;
     kernel = &f;
     meetings = 0;
     if (group.x > kMostLanes || (uint64_t)grid.x * group.x > UINT32_MAX || lds > kLdsOfACu) stop("no such launch");
+    if (lds > kLdsLimit && (!lds_limit.count(entry) || lds > lds_limit[entry])) stop("more LDS than is allowed");
     if (!stacks)
         stacks = (char *)mmap(nullptr, kMostLanes * kStack, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0);
     blocks = grid;
@@ -150,3 +155,12 @@ void launch(const char *name, dim3 grid, dim3 group, size_t lds, const std::func
 }
 
 }  // namespace emu
+
+hipError_t hipFuncSetAttribute(const void *kernel, int, int bytes)
+{
+    emu::lds_limit[kernel] = (size_t)bytes;
+    std::function<void()> other;
+    std::swap(other, emu::meanwhile);  // (once)
+    if (other) other();
+    return hipSuccess;
+}

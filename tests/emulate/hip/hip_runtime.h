@@ -1,5 +1,5 @@
-// Stands in for HIP's header when csrc/cubic_search.hip is built for the CPU (tests/test_emulated_search.py): as much
-// of HIP as that file uses.  A lane is a fiber of its own, and every operation across lanes is a rendezvous of the
+// Stands in for HIP's header when sources under csrc/ are built for the CPU (tests/test_emulated_kernels.py): as much
+// of HIP as those use.  A lane is a fiber of its own, and every operation across lanes is a rendezvous of the
 // wave (see fibers.cpp): what the lanes of a wave or a workgroup do together has to be reached by all of them that
 // have not ended, or the run is stopped.
 #pragma once
@@ -11,6 +11,9 @@
 #include <algorithm>
 #include <functional>
 
+using std::max;
+using std::min;
+
 #define __global__
 #define __device__
 #define __host__
@@ -21,9 +24,15 @@
 
 typedef int hipError_t;
 typedef void *hipStream_t;
-enum { hipSuccess, hipErrorInvalidDevice, hipErrorInvalidConfiguration, hipFuncAttributeMaxDynamicSharedMemorySize };
+enum {
+    hipSuccess,
+    hipErrorInvalidDevice,
+    hipErrorInvalidConfiguration,
+    hipErrorInvalidValue,
+    hipFuncAttributeMaxDynamicSharedMemorySize
+};
+hipError_t hipFuncSetAttribute(const void *kernel, int, int bytes);
 inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
-inline hipError_t hipFuncSetAttribute(const void *, int, int) { return hipSuccess; }
 inline hipError_t hipGetLastError() { return hipSuccess; }
 struct dim3 {
     unsigned x, y, z;
@@ -35,8 +44,11 @@ constexpr int kLanes = 64;
 enum Kind { kNone, kBallot, kReadLane, kFirstLane, kDpp, kShfl, kMin, kSelect, kBarrier };
 extern dim3 thread, block, threads, blocks;
 extern unsigned char *dynamic_lds;
-// One launch: the grid's workgroups one after the other.  LDS ends at a page that cannot be touched.
-void launch(const char *name, dim3 grid, dim3 block, size_t lds, const std::function<void()> &kernel);
+// One launch: the grid's workgroups one after the other.  Dynamic LDS ends at a page that cannot be touched, and more
+// than 64 KB of it must have been allowed for the kernel (`entry`).
+void launch(const char *name, const void *entry, dim3 grid, dim3 block, size_t lds, const std::function<void()> &kernel);
+// Called after every hipFuncSetAttribute: what another thread does at that moment.
+extern std::function<void()> meanwhile;
 // Device memory of exactly this many bytes, between pages that cannot be touched, full of a pattern.
 void *device_memory(size_t bytes);
 // A launch whose waves meet more often than this is taken not to end.
@@ -55,6 +67,11 @@ inline uint64_t ballot(bool b)
     for (int l = 0; l < kLanes; ++l)
         if (((taking_part() >> l) & 1) && v[l]) m |= 1ull << l;
     return m;
+}
+inline int first_lane(int x)
+{
+    const uint64_t *v = meet((uint32_t)x, kFirstLane);
+    return (int)(uint32_t)v[__builtin_ctzll(taking_part())];
 }
 inline int read_lane(int x, int l) { return (int)(uint32_t)meet((uint32_t)x, kReadLane)[l & 63]; }
 inline int dpp(int old, int x, int control, int row_mask)
@@ -83,7 +100,7 @@ template <class T> T least(T *p, T v) { const T was = *p; *p = v < was ? v : was
 #define blockIdx (emu::block)
 #define blockDim (emu::threads)
 #define gridDim (emu::blocks)
-#define hipLaunchKernelGGL(k, grid, block, lds, stream, ...) emu::launch(#k, grid, block, lds, [&] { k(__VA_ARGS__); })
+#define hipLaunchKernelGGL(k, grid, block, lds, stream, ...) emu::launch(#k, (const void *)(k), grid, block, lds, [&] { k(__VA_ARGS__); })
 
 inline void __syncthreads() { (void)emu::meet(0, emu::kBarrier); }
 inline bool __any(int b) { return emu::ballot(b != 0) != 0; }
@@ -96,6 +113,9 @@ template <class T> T __shfl_up(T v, int d, int)
 }
 #define __builtin_amdgcn_ballot_w64(b) emu::ballot(b)
 #define __builtin_amdgcn_readlane(v, l) emu::read_lane(v, l)
+#define __builtin_amdgcn_readfirstlane(v) emu::first_lane(v)
+#define __builtin_nontemporal_load(p) (*(p))
+#define __builtin_nontemporal_store(v, p) ((void)(*(p) = (v)))
 #define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) emu::dpp(old, v, control, rows)
 #define __builtin_amdgcn_fence(...) ((void)0)
 #define __HIP_MEMORY_SCOPE_WORKGROUP 0
