@@ -273,6 +273,8 @@ __global__ __launch_bounds__(PARTS ? kBlock * kRaggedWaves : kBlock) void eval_p
                                     peak_stage + g.first, status_stage + g.first, c, batch);
 }
 
+std::atomic<bool> parts_lds_raised[kMaxDevices];
+
 }  // namespace
 
 hipError_t launch_eval_peak(const int64_t *d, const uint8_t *mask, int64_t batch, int n, Strides st,
@@ -281,9 +283,17 @@ hipError_t launch_eval_peak(const int64_t *d, const uint8_t *mask, int64_t batch
     if (batch == 0) return hipSuccess;
     const unsigned grid = (unsigned)((batch + kBlock - 1) / kBlock);
     const int waves = parts_of(grid, n);
-    auto parts = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kBlock), parts_lds_bytes(objective, waves), stream, d, mask,
-                           batch, n, st.chain, st.pos, peak_out, status_out);
+    auto parts = [&](auto kernel) -> hipError_t {
+        const size_t lds = parts_lds_bytes(objective, waves);
+        if (lds > kDefaultLdsLimit) {  // (16 waves with the dynamic objective)
+            const hipError_t e = raise_lds_limit(parts_lds_raised,
+                                                 {(const void *)eval_peak_parts_kernel<CKPT_OBJ_DYNAMIC>,
+                                                  (const void *)eval_peak_parts_kernel<CKPT_OBJ_BOTH>},
+                                                 parts_lds_bytes(CKPT_OBJ_BOTH, kPartWaves));
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kBlock), lds, stream, d, mask, batch, n, st.chain,
+                           st.pos, peak_out, status_out);
         return hipGetLastError();
     };
     auto walk = [&](auto kernel) {

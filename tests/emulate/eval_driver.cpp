@@ -75,7 +75,7 @@ int main()
         for (const int n : {1, 7, 32, 33, 512, 513, 600, 1024, 1025}) timeline(n == 33 ? 65 : 3, n, objective);
     }
     for (const int objective : {CKPT_OBJ_STATIC, CKPT_OBJ_DYNAMIC, CKPT_OBJ_BOTH}) {
-        for (const int n : {1, 16, 31, 32, 100}) peak(n == 32 ? 65 : 3, n, objective);
+        for (const int n : {1, 16, 31, 32, 127, 128, 129, 640}) peak(n == 32 ? 65 : 3, n, objective);  // 1 to 16 waves
     }
     printf(failures ? "eval_driver: %d failed\n" : "eval_driver ok\n", failures);
     return failures != 0;
