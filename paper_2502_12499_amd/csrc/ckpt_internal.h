@@ -8,6 +8,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <initializer_list>
 
@@ -224,19 +225,23 @@ struct RaggedGroupDev {
     int64_t stage_off;
     int64_t pitch;
     int32_t tiles_x;  // tiles across the chains: ceil(count / 64)
-    int32_t linear_first;  // the linear solver's first wave of the group: it numbers its waves on its own
+    int32_t linear_first;  // the linear solver's first wave of the group, where it gives some chains a wave each
 };
 
 // The sums over the groups laid out so far (all of them at the end); `bad` is set by the device's
 // count of the lengths when an offset is out of range.
 struct RaggedTotals {
-    int32_t n_groups, bad, max_layers, pad;
+    int32_t n_groups, bad, max_layers;
+    int32_t wave_longest;  // of the groups that ragged_wave_per_chain takes: the longest chains' length ...
     int64_t chains, waves, linear_waves, tiles, tiles2, staged;
+    int64_t wave_layers;   // ... the layers of all their chains ...
+    int64_t lane_waves;    // ... and the waves that they take with a lane per chain
 };
 
-// Groups whose chains the linear solver gives a wave each instead of a lane each: few chains (they would fill a
-// handful of waves) and long ones (whose lane-per-chain form takes 660 ns a position, four times what a wave per
-// chain takes; 65,536 chains with sixteen of 1,001 layers among them: 0.70 ms -> 0.30 ms).
+// Groups whose chains the linear solver gives a wave each instead of a lane each, if all such groups together are
+// small enough (ragged_waves_pay): few chains (they would fill a handful of waves) and long ones (whose lane-per-chain
+// form takes 660 ns a position, four times what a wave per chain takes; 65,536 chains with sixteen of 1,001 layers
+// among them: 0.70 ms -> 0.30 ms).
 __host__ __device__ inline bool ragged_wave_per_chain(int n, int64_t count)
 {
     return n > 256 && n <= 4095 && count <= 1024;
@@ -244,6 +249,17 @@ __host__ __device__ inline bool ragged_wave_per_chain(int n, int64_t count)
 __host__ __device__ inline int64_t ragged_linear_waves(int n, int64_t count)
 {
     return ragged_wave_per_chain(n, count) ? count : (count + 63) / 64;
+}
+
+// With a wave per chain these groups take 80 ps a layer once they fill the chip; with a lane per chain 660 ns a layer of
+// the longest, and in proportion more from about five waves to four SIMDs on.  Measured, lanes and waves: 1,000 chains of
+// 257 to 1,001 layers 597 and 338 us, 8,192 746 and 620, 12,288 790 and 793, 65,536 1,116 and 3,331; of 257 to 300 layers
+// 6,144 322 and 264, 8,192 309 and 304, 12,288 320 and 403; of 257 to 4,095, where nearly every length is a group of its
+// own, 4,096 2,482 and 1,667, 12,288 3,110 and 3,156, 16,384 6,513 and 3,822, 32,768 8,805 and 6,496.
+inline bool ragged_waves_pay(const RaggedTotals &t)
+{
+    constexpr int64_t kChains = 6144, kLaneWaves = 1280;
+    return t.wave_layers <= kChains * t.wave_longest * std::max(t.lane_waves, kLaneWaves) / kLaneWaves;
 }
 
 // Elements from one position to the next in a group's staging: rows start on 256 bytes for groups
@@ -274,6 +290,11 @@ __host__ __device__ inline RaggedGroupDev ragged_next_group(RaggedTotals &t, int
     t.chains += many;
     t.waves += (many + 63) / 64;
     t.linear_waves += ragged_linear_waves(n, many);
+    if (ragged_wave_per_chain(n, many)) {
+        t.wave_longest = n;
+        t.wave_layers += n * many;
+        t.lane_waves += (many + 63) / 64;
+    }
     t.tiles += (int64_t)g.tiles_x * ((n + 1 + 63) / 64);
     t.tiles2 += (int64_t)g.tiles_x * ((2 * n + 2 + 63) / 64);
     t.staged += ((int64_t)(n + 1) * g.pitch + 31) / 32 * 32;  // the next group starts on 256 bytes
@@ -326,10 +347,10 @@ hipError_t launch_eval_peak_ragged(const int64_t *d_stage, const uint8_t *mask_s
 hipError_t launch_eval_timeline_ragged(const int64_t *d_stage, const uint8_t *mask_stage,
                                        const RaggedGroupDev *groups, int n_groups, int64_t waves, int objective,
                                        int64_t *wide_stage, int32_t *status_stage, hipStream_t stream);
-// batch: chains in all groups; max_layers: the longest chain.  ws as for launch_solve_linear(batch, max_layers).
-hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, int n_groups,
-                                      int64_t waves, int64_t batch, int max_layers, uint8_t *mask_stage,
-                                      int64_t *peak_stage, int32_t *status_stage, void *ws, hipStream_t stream);
+// batch: chains in all groups.  ws as for launch_solve_linear(batch, t.max_layers).
+hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, const RaggedTotals &t,
+                                      int64_t batch, uint8_t *mask_stage, int64_t *peak_stage, int32_t *status_stage,
+                                      void *ws, hipStream_t stream);
 
 // which: a ckpt_call; offsets_host: batch + 1 element offsets in host memory
 size_t ragged_workspace_bytes(int which, const int64_t *offsets_host, int64_t batch);

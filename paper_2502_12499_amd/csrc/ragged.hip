@@ -117,12 +117,13 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
 {
     __shared__ int64_t wave_sum[kCountThreads / kWave][kSums];
     __shared__ unsigned long long used;  // bit k: some length of tile k occurs
-    __shared__ int longest;
+    __shared__ unsigned long long wave_layers, lane_waves;
+    __shared__ int longest, wave_longest;
     constexpr int kTiles = (CKPT_MAX_LAYERS + kCountThreads - 1) / kCountThreads;
     static_assert(kTiles <= 64, "one bit per tile");
     if (threadIdx.x == 0) {
-        longest = 0;
-        used = 0;
+        longest = wave_longest = 0;
+        used = wave_layers = lane_waves = 0;
     }
     __syncthreads();
     unsigned long long mine = 0;
@@ -138,6 +139,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
     }
     __syncthreads();
     RaggedTotals at = {};  // the totals before the tile
+    RaggedTotals long_ones = {};  // of the thread's groups: only their sums are wanted
     for (unsigned long long todo = used; todo != 0; todo &= todo - 1) {
         const int n = 1 + (__ffsll(todo) - 1) * kCountThreads + (int)threadIdx.x;
         const int64_t many = n <= max_layers ? hist[n] : 0;
@@ -167,7 +169,22 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         at.tiles += all[4];
         at.tiles2 += all[5];
         at.staged += all[6];
+        long_ones.wave_longest = one.wave_longest ? one.wave_longest : long_ones.wave_longest;  // (ascending)
+        long_ones.wave_layers += one.wave_layers;
+        long_ones.lane_waves += one.lane_waves;
     }
+#pragma unroll
+    for (int s = kWave / 2; s >= 1; s >>= 1) {
+        long_ones.wave_longest = max(long_ones.wave_longest, __shfl_xor(long_ones.wave_longest, s));
+        long_ones.wave_layers += __shfl_xor(long_ones.wave_layers, s);
+        long_ones.lane_waves += __shfl_xor(long_ones.lane_waves, s);
+    }
+    if (threadIdx.x % kWave == 0) {
+        atomicMax(&wave_longest, long_ones.wave_longest);
+        atomicAdd(&wave_layers, (unsigned long long)long_ones.wave_layers);
+        atomicAdd(&lane_waves, (unsigned long long)long_ones.lane_waves);
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
         totals->n_groups = at.n_groups;
         totals->max_layers = longest;
@@ -177,6 +194,9 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         totals->tiles = at.tiles;
         totals->tiles2 = at.tiles2;
         totals->staged = at.staged;
+        totals->wave_longest = wave_longest;
+        totals->wave_layers = (int64_t)wave_layers;
+        totals->lane_waves = (int64_t)lane_waves;
     }
 }
 
@@ -465,8 +485,7 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
     if (which == CKPT_CALL_EVAL_PEAK) {
         e = launch_eval_peak_ragged(sd, smask, groups, n_groups, p.t.waves, batch, objective, speak, sstatus, stream);
     } else if (which == CKPT_CALL_SOLVE_LINEAR) {
-        e = launch_solve_linear_ragged(sd, groups, n_groups, p.t.linear_waves, batch, p.t.max_layers, smask, speak, sstatus,
-                                       base + w.inner, stream);
+        e = launch_solve_linear_ragged(sd, groups, p.t, batch, smask, speak, sstatus, base + w.inner, stream);
     } else if (which == CKPT_CALL_EVAL_TIMELINE) {
         e = launch_eval_timeline_ragged(sd, smask, groups, n_groups, p.t.waves, objective, swide, sstatus, stream);
     } else {

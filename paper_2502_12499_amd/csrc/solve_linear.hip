@@ -997,8 +997,9 @@ __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const
 // Every group of a ragged call in one launch: a wave looks up the group its 64 chains belong to
 // and solves them where that group is staged, with the step log in registers if the group's
 // chains have up to kLogMaxLayers layers (a wave-uniform branch: long and short groups run side by
-// side on the chip), or one chain of the group as the wave kernel does (ragged_wave_per_chain).  The last groups,
-// the longest chains, start first.  Results go to the chains' places.
+// side on the chip), or, with PER_CHAIN, one chain of the group as the wave kernel does (ragged_wave_per_chain).
+// The last groups, the longest chains, start first.  Results go to the chains' places.
+template <bool PER_CHAIN>
 __global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t *__restrict__ d_stage,
                                                                    const RaggedGroupDev *__restrict__ groups,
                                                                    int n_groups, uint8_t *__restrict__ mask_stage,
@@ -1007,10 +1008,11 @@ __global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t
 {
     __shared__ __attribute__((aligned(4096))) uint32_t ring[kPlanes][kRing][kWave];
     const unsigned wave = gridDim.x - 1 - blockIdx.x;
-    const RaggedGroupDev g = groups[ragged_group_of_linear_wave(groups, n_groups, wave)];
+    const RaggedGroupDev g = groups[PER_CHAIN ? ragged_group_of_linear_wave(groups, n_groups, wave)
+                                              : ragged_group_of_wave(groups, n_groups, wave)];
     const unsigned waves = (unsigned)((g.count + kWave - 1) / kWave);
-    const unsigned block = wave - (unsigned)g.linear_first;
-    if (ragged_wave_per_chain(g.n, g.count)) {
+    const unsigned block = wave - (unsigned)(PER_CHAIN ? g.linear_first : g.wave_first);
+    if (PER_CHAIN && ragged_wave_per_chain(g.n, g.count)) {
         static_assert(sizeof(ring) >= 2 * (4095 + 1), "the wave's LDS for the longest of these chains");
         const int64_t at = g.stage_off + block, c = g.first + (int64_t)block;
         const bool done = wave_chain(d_stage + at, g.n, g.pitch, mask_stage + at, peak_stage + c, status_stage + c,
@@ -1155,14 +1157,17 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     return hipGetLastError();
 }
 
-hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, int n_groups,
-                                      int64_t waves, int64_t batch, int max_layers, uint8_t *mask_stage,
-                                      int64_t *peak_stage, int32_t *status_stage, void *ws, hipStream_t stream)
+hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, const RaggedTotals &t,
+                                      int64_t batch, uint8_t *mask_stage, int64_t *peak_stage, int32_t *status_stage,
+                                      void *ws, hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
+    const int n_groups = t.n_groups, max_layers = t.max_layers;
+    const bool per_chain = ragged_waves_pay(t);
     LinearWs w = carve_linear(ws, batch, max_layers);
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, stream, w);
-    hipLaunchKernelGGL(linear_ring_ragged_kernel, dim3((unsigned)waves), dim3(kWave), 0, stream, d_stage, groups,
+    hipLaunchKernelGGL(per_chain ? linear_ring_ragged_kernel<true> : linear_ring_ragged_kernel<false>,
+                       dim3((unsigned)(per_chain ? t.linear_waves : t.waves)), dim3(kWave), 0, stream, d_stage, groups,
                        n_groups, mask_stage, peak_stage, status_stage, w);
     launch_wide(d_stage, batch, max_layers, 1, 0, mask_stage, peak_stage, status_stage, w, groups, n_groups, stream);
     const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <initializer_list>
+#include <vector>
 
 #include "../../include/ckpt.h"
 
@@ -47,8 +48,8 @@ int ragged_run(int, const int64_t *, const uint8_t *, const int64_t *off, const 
     ++ragged_runs;
     // the groups ascend in length, follow each other without gaps (places, waves, tiles, staging)
     // and hold every chain of their length
-    int64_t seen = 0, waves = 0, tiles = 0, tiles2 = 0, staged = 0;
-    int last_n = 0;
+    int64_t seen = 0, waves = 0, tiles = 0, tiles2 = 0, staged = 0, linear = 0, layers = 0, lane_waves = 0;
+    int last_n = 0, longest = 0;
     size_t gi = 0;
     for (const RaggedGroupDev &g : plan.groups) {
         if (g.first != seen || g.count <= 0 || g.n <= last_n) return CKPT_ERR_DEVICE;
@@ -60,6 +61,12 @@ int ragged_run(int, const int64_t *, const uint8_t *, const int64_t *off, const 
         if (have != g.count) return CKPT_ERR_DEVICE;
         seen += g.count;
         waves += (g.count + 63) / 64;
+        if (g.linear_first != linear) return CKPT_ERR_DEVICE;
+        const bool one_each = g.n > 256 && g.n <= 4095 && g.count <= 1024;
+        linear += one_each ? g.count : (g.count + 63) / 64;
+        layers += one_each ? (int64_t)g.n * g.count : 0;
+        lane_waves += one_each ? (g.count + 63) / 64 : 0;
+        longest = one_each ? g.n : longest;
         tiles += (int64_t)g.tiles_x * ((g.n + 1 + 63) / 64);
         tiles2 += (int64_t)g.tiles_x * ((2 * g.n + 2 + 63) / 64);
         staged = g.stage_off + (int64_t)(g.n + 1) * g.pitch;
@@ -68,7 +75,8 @@ int ragged_run(int, const int64_t *, const uint8_t *, const int64_t *off, const 
     }
     if (!plan.groups.empty() &&
         (seen != batch || waves != plan.t.waves || tiles != plan.t.tiles || tiles2 != plan.t.tiles2 ||
-         staged > plan.t.staged || last_n != plan.t.max_layers || (int)gi != plan.t.n_groups))
+         linear != plan.t.linear_waves || layers != plan.t.wave_layers || lane_waves != plan.t.lane_waves ||
+         longest != plan.t.wave_longest || staged > plan.t.staged || last_n != plan.t.max_layers || (int)gi != plan.t.n_groups))
         return CKPT_ERR_DEVICE;
     if (plan.t.chains != batch || plan.t.n_groups < 1 || (int64_t)plan.t.n_groups > batch) return CKPT_ERR_DEVICE;
     if (w.total % 256 != 0 || w.inner > w.total || w.totals < w.perm + (size_t)batch * 4 ||
@@ -229,6 +237,20 @@ int main()
         CHECK(ckpt_ragged_workspace_bytes(CKPT_CALL_EVAL_TIMELINE, offs, many) > (size_t)many * 12);
         std::free(offs);
         CHECK(ckpt::launches == 10);
+    }
+    // the linear solver's choice between a wave and a lane for the long chains of a ragged call: by all of them together
+    {
+        struct { int chains, lo, hi; bool waves; } const calls[] = {
+            {16, 1001, 1001, true}, {1000, 257, 1001, true}, {8192, 257, 1001, true}, {16384, 257, 1001, false},
+            {65536, 257, 1001, false}, {200000, 257, 699, false}, {4096, 257, 300, true}, {16384, 257, 300, false},
+            {16384, 257, 4095, true}, {200000, 15, 24, true}};
+        for (const auto &call : calls) {
+            std::vector<int64_t> offs((size_t)call.chains + 1, 0);
+            for (int c = 0; c < call.chains; ++c) offs[(size_t)c + 1] = offs[(size_t)c] + call.lo + 1 + (int64_t)c * 7919 % (call.hi - call.lo + 1);
+            ckpt::RaggedPlan plan;
+            CHECK(ckpt::ragged_make_plan(offs.data(), call.chains, CKPT_MAX_LAYERS, plan) == CKPT_OK);
+            CHECK(ckpt::ragged_waves_pay(plan.t) == call.waves);
+        }
     }
     // the first bound of the cubic search: sizes of several kinds, and the same for every size in front and at the end
     {

@@ -137,3 +137,20 @@ def test_long_groups_of_a_ragged_batch():
         assert (status.cpu().numpy() == 0).all()
         assert np.array_equal(peak.cpu().numpy(), want_peak)
         assert np.array_equal(mask.cpu().numpy(), want_mask)
+
+
+@pytest.mark.parametrize("batch", [3000, 12288])
+def test_many_long_chains_of_a_ragged_batch(batch):
+    """Groups of 257 to 300 layers and some of 40: a wave to a chain, and (all of them together being too many) a lane."""
+    rng = np.random.default_rng(batch)
+    lengths = np.where(rng.random(batch) < 0.1, 40, rng.integers(257, 301, size=batch))
+    d, _, off = inputs.ragged_batch(8, lengths)
+    for c in range(0, batch, 5):
+        d[off[c]:off[c + 1]] += 1
+    want_peak, want_mask = oracle.ragged_solve_dynamic(d, off)
+    for off_dev in (None, torch.from_numpy(off).cuda()):
+        mask, peak, status = B.ckpt_ragged_solve_linear(torch.from_numpy(d).cuda(), off, offsets_dev=off_dev)
+        torch.cuda.synchronize()
+        assert (status.cpu().numpy() == 0).all()
+        assert np.array_equal(peak.cpu().numpy(), want_peak)
+        assert np.array_equal(mask.cpu().numpy(), want_mask)
