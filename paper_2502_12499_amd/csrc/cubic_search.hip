@@ -843,11 +843,11 @@ namespace {
 //   round x 2  `points` waves per chain evaluate a point each, cutting the open intervals evenly
 //   close x 2  (after each) takes the best cost and lists the intervals that stay open
 //   list       a thread per start: the budgets inside the open intervals, each value once (a table of the
-//              values seen keeps most repeated ones out)
+//              values seen keeps most repeated ones out); if they are many, a workgroup cuts the intervals further
 //   finish     a wave per listed budget, and one for the best point so far; each keeps the set of its best
 //   result     the best of the waves, its set spread to bytes
-// After two rounds of 1,024 points one to twenty budgets are left on every kind of chain tried, so `finish` takes
-// one pass; it takes whatever is left.  A call is bound by three passes in a row, one after another, each as long as
+// After two rounds of 1,024 points one to twenty budgets are left where sizes are of one order, so `finish` takes one
+// pass; it takes whatever is left.  A call is bound by three passes in a row, one after another, each as long as
 // its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves stops: a
 // small s would have a head at every cell.
 // Measured, with every budget evaluated in brackets: one chain of 4,096 aligned layers 312 us (1,650), of 1,001 of a
@@ -1100,10 +1100,10 @@ __device__ inline void point_of(const Open *open, int count, int points, int g, 
     s = o.lo + part * (t + 1) + rest * (t + 1) / many;
 }
 
-// A chain's point, evaluated: F_s(n), or less if it stopped (`exact` false then); RECORD: `head` as in wave_cost.
+// A chain's point, evaluated: F_s(n), or less if it stopped (`exact` false then); RECORD, `head`, F: as in wave_cost.
 template <typename U, bool RECORD>
 __device__ __forceinline__ uint64_t long_cost(const LongWs &w, const LongMeta *meta, const int64_t c, const int n,
-                                              const int64_t prev, const int64_t s, bool &exact, uint16_t *head)
+                                              const int64_t prev, const int64_t s, bool &exact, uint16_t *head, U *F)
 {
     const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
     exact = true;
@@ -1117,7 +1117,7 @@ __device__ __forceinline__ uint64_t long_cost(const LongWs &w, const LongMeta *m
         if (out) exact = false;
         return out;
     };
-    const U v = wave_cost<U, RECORD>(P, n, (U)s, (U *)search_lds, head, stop);
+    const U v = wave_cost<U, RECORD>(P, n, (U)s, F, head, stop);
     exact = exact && v != std::numeric_limits<U>::max();
     return (uint64_t)v;
 }
@@ -1134,8 +1134,8 @@ __global__ __launch_bounds__(kWave) void search_round_kernel(int n, int points, 
     Point p{prev, s, ~0ull, 0};
     if (s > prev) {
         bool exact;
-        p.c = meta->narrow ? long_cost<uint32_t, false>(w, meta, c, n, prev, s, exact, nullptr)
-                           : long_cost<uint64_t, false>(w, meta, c, n, prev, s, exact, nullptr);
+        p.c = meta->narrow ? long_cost<uint32_t, false>(w, meta, c, n, prev, s, exact, nullptr, (uint32_t *)search_lds)
+                           : long_cost<uint64_t, false>(w, meta, c, n, prev, s, exact, nullptr, (uint64_t *)search_lds);
         p.exact = exact;
         if (exact && lane == 0) atomicMin((unsigned long long *)&meta->ub, (unsigned long long)(p.c + (uint64_t)s));
     }
@@ -1261,63 +1261,299 @@ __global__ __launch_bounds__(kWave) void search_close_kernel(int points, int rou
 
 // ---- the budgets that are left ----
 
-constexpr int kListThreads = 256;
+// The budgets inside the open intervals are listed, each value once as far as a table of the values seen tells.  Two
+// rounds of points that cut the intervals evenly leave few of them where sizes are of one order; where one layer
+// outweighs the others 10^8 times, most budgets lie within a single cut (4,096 layers, one of 10^15 among others up to
+// 10^6: 935,000 of 8.4 million).  So when there are more than `most`, a workgroup cuts the intervals itself, at budgets
+// drawn evenly from those that are left, whatever their scale, and at the largest that is one layer; a wave evaluates
+// each, and lists again.  One such chain of 300, 1,001 and 4,096 layers: 105, 258 and 300 us where finishing the list as
+// it was took 1.7, 8.2 and 64 ms (every budget evaluated: 0.2, 1.5 and 92 ms).
+constexpr int kListMost = 1024;   // threads
+constexpr int kListWaves = kListMost / kWave;
+constexpr int kListPasses = 32;   // then all that are left are listed (two were the most on any kind of chain tried)
+constexpr int kListStarts = 4;    // starts whose bisections a thread runs side by side
+
+// Bytes of F in LDS, before the heads.
+__host__ __device__ inline size_t long_f_bytes(int n) { return ((size_t)n + 1 + kWave) * 8; }
+
+// A thread per start, and eight waves where the chip has room for them.
+__host__ inline int list_threads(int64_t batch, int n)
+{
+    const int starts = n < kListMost ? (n + kWave - 1) / kWave * kWave : kListMost;
+    return batch <= 512 && starts < 512 ? 512 : starts;
+}
+// Waves of it that evaluate points: as many as their F leave the chains of a CU room for (the lists themselves take 9 KB).
+__host__ inline int list_waves(int64_t batch, int n)
+{
+    const size_t room = (size_t)(160 << 10) / (size_t)((batch + 255) / 256), own = 10 << 10;
+    const int fit = room > own ? (int)((room - own) / long_f_bytes(n)) : 0, waves = list_threads(batch, n) / kWave;
+    return fit < 1 ? 1 : fit < waves ? fit : waves;
+}
+
+struct ListLds {
+    Open open[2][kOpenMax];
+    int64_t drawn[kListWaves], s[kListWaves];  // the budgets drawn, and in ascending order
+    uint64_t c[kListWaves];
+    int exact[kListWaves];
+    unsigned sum[kListWaves];                  // budgets counted by a wave's lanes
+    unsigned long long single;                 // the largest that is one layer
+    int count;
+};
+
+// The first x in [from, n) with P[x] - pa > bound, n if there is none.
+template <typename U>
+__device__ inline int first_end(const U *P, int from, int n, uint64_t pa, uint64_t bound)
+{
+    int lo = from, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if ((uint64_t)P[mid] - pa > bound) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
+// first_end from a + 1 on for kListStarts starts side by side, none from n - 1 on.
+template <typename U>
+__device__ __forceinline__ void first_ends(const U *P, const int n, const int (&a)[kListStarts],
+                                           const uint64_t (&pa)[kListStarts], const uint64_t bound, int (&x)[kListStarts])
+{
+    int hi[kListStarts];
+#pragma unroll
+    for (int j = 0; j < kListStarts; ++j) {
+        x[j] = a[j] < n - 1 ? a[j] + 1 : n;
+        hi[j] = n;
+    }
+    for (int step = n; step > 0; step >>= 1) {
+#pragma unroll
+        for (int j = 0; j < kListStarts; ++j) {
+            const int mid = (x[j] + hi[j]) >> 1;
+            const bool between = x[j] < hi[j], up = between && (uint64_t)P[mid] - pa[j] <= bound;
+            hi[j] = between && !up ? mid : hi[j];
+            x[j] = up ? mid + 1 : x[j];
+        }
+    }
+}
+
+// The budgets of start a inside the intervals (which ascend) go on the list until it holds `most`.
 template <typename U>
 __device__ __forceinline__ void list_start(const LongWs &w, LongMeta *meta, const Open *open, const int count,
-                                           const int64_t c, const int n, const int a, const uint64_t lowest,
-                                           const uint64_t highest)
+                                           const int most, const int64_t c, const int n, const int a)
 {
     const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
     const int slots = seen_slots(n);
     const uint64_t pa = P[a];
-    int lo = a + 1, hi = n;  // the first end with P[x] - P[a] > lowest
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if ((uint64_t)P[mid] - pa > lowest) hi = mid; else lo = mid + 1;
-    }
-    for (int x = lo; x < n; ++x) {
-        const uint64_t sv = (uint64_t)P[x] - pa;
-        if (sv > highest) break;
-        bool in = false;
-        for (int k = 0; k < count && !in; ++k) in = (int64_t)sv > open[k].lo && (int64_t)sv <= open[k].hi;
-        if (!in) continue;
-        // (sv > 0: it lies above an interval's lower end; an empty slot is 0)
-        unsigned slot = (unsigned)((sv * 0x9E3779B97F4A7C15ull) >> 54) % slots;
-        bool fresh = true;
-        for (int probe = 0; probe < 8; ++probe, slot = (slot + 1) % slots) {
-            const uint64_t was = atomicCAS((unsigned long long *)w.seen + c * slots + slot, 0ull,
-                                           (unsigned long long)sv);
-            if (was == sv) fresh = false;
-            if (was == sv || was == 0) break;
+    int x = a + 1;
+    for (int k = 0; k < count && x < n; ++k) {
+        const uint64_t lo = (uint64_t)open[k].lo, hi = (uint64_t)open[k].hi;
+        if ((uint64_t)P[x] - pa <= lo) x = first_end(P, x + 1, n, pa, lo);
+        for (; x < n; ++x) {
+            const uint64_t sv = (uint64_t)P[x] - pa;
+            if (sv > hi) break;
+            // (sv > 0: it lies above an interval's lower end; an empty slot is 0)
+            unsigned slot = (unsigned)((sv * 0x9E3779B97F4A7C15ull) >> 54) % slots;
+            bool fresh = true;
+            for (int probe = 0; probe < 8; ++probe, slot = (slot + 1) % slots) {
+                const uint64_t was = atomicCAS((unsigned long long *)w.seen + c * slots + slot, 0ull,
+                                               (unsigned long long)sv);
+                if (was == sv) fresh = false;
+                if (was == sv || was == 0) break;
+            }
+            if (!fresh) continue;
+            const int at = atomicAdd(&meta->listed, 1);
+            if (at >= most) return;
+            w.list[c * long_budgets(n) + at] = (uint32_t)a << 13 | (uint32_t)x;
         }
-        if (fresh) w.list[c * long_budgets(n) + atomicAdd(&meta->listed, 1)] = (uint32_t)a << 13 | (uint32_t)x;
     }
 }
 
-__global__ __launch_bounds__(kListThreads) void search_list_kernel(int n, LongWs w)
+__device__ inline unsigned mixed(unsigned a, unsigned b)
 {
-    __shared__ Open open[kOpenMax];
+    unsigned h = a * 0x9E3779B1u ^ b * 0x85EBCA77u;
+    h ^= h >> 15;
+    h *= 0x2C1B3C6Du;
+    return h ^ h >> 13;
+}
+
+// As many budgets as `points` drawn from those inside the intervals, the first of them the largest that is a single
+// layer: where that outweighs the others, it gives the cost that settles all smaller ones.
+template <typename U>
+__device__ __forceinline__ void draw_budgets(const LongWs &w, ListLds &l, const Open *open, const int count,
+                                                 const int64_t c, const int n, const int points, const unsigned pass)
+{
+    const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave, threads = blockDim.x;
+    // every thread keeps one of its own, each as likely as any other
+    unsigned mine = 0;   // (below 2^25 in all)
+    int at_a = 0, at_x = 0;
+    uint64_t single = 0;
+    if (tid == 0) l.single = 0;
+    __syncthreads();
+    for (int a0 = tid; a0 < n - 1; a0 += kListStarts * threads) {
+        int a[kListStarts];
+        uint64_t pa[kListStarts];
+#pragma unroll
+        for (int j = 0; j < kListStarts; ++j) {
+            a[j] = min(a0 + j * threads, n);
+            pa[j] = P[a[j]];
+        }
+        for (int k = 0; k < count; ++k) {
+            const uint64_t lo = (uint64_t)open[k].lo, hi = (uint64_t)open[k].hi;
+            int from[kListStarts], to[kListStarts];
+            first_ends(P, n, a, pa, lo, from);
+            first_ends(P, n, a, pa, hi, to);
+#pragma unroll
+            for (int j = 0; j < kListStarts; ++j) {
+                const unsigned here = (unsigned)(to[j] - from[j]);
+                if (here == 0) continue;
+                mine += here;
+                const uint64_t one = (uint64_t)P[a[j] + 1] - pa[j];
+                if (one > lo && one <= hi && one > single) single = one;
+                const unsigned r = mixed((unsigned)a[j] * 131u + (unsigned)k, pass);
+                if (r % mine < here) {
+                    at_a = a[j];
+                    at_x = from[j] + (int)(mixed(r, pass) % here);
+                }
+            }
+        }
+    }
+    unsigned incl = mine;
+#pragma unroll
+    for (int k = 1; k < kWave; k <<= 1) {
+        const unsigned o = __shfl_up(incl, k, kWave);
+        if (lane >= k) incl += o;
+    }
+    if (lane == kWave - 1) l.sum[wave] = incl;
+    single = ~wave_min_u64(~single);
+    if (lane == 0) atomicMax(&l.single, (unsigned long long)single);
+    if (tid < kListWaves) l.drawn[tid] = -1;
+    __syncthreads();
+    unsigned before = incl - mine, all = 0;
+    for (int k = 0; k < threads / kWave; ++k) {
+        before += k < wave ? l.sum[k] : 0;
+        all += l.sum[k];
+    }
+    // point k: the budget of the thread that holds number k * all / points and a bit
+    const bool has_single = l.single != 0 && (points > 1 || pass % 2 == 0);
+    const unsigned part = all / (unsigned)points;
+    for (int k = 0; k < points && mine != 0; ++k) {
+        const unsigned r = (unsigned)((uint64_t)all * (unsigned)k / (unsigned)points) + (part ? mixed(pass, (unsigned)k) % part : 0);
+        if (k == 0 && has_single) continue;
+        if (r >= before && r - before < mine) l.drawn[k] = (int64_t)((uint64_t)P[at_x] - (uint64_t)P[at_a]);
+    }
+    if (tid == 0 && has_single) l.drawn[0] = (int64_t)l.single;
+    __syncthreads();
+}
+
+// Cuts the intervals at up to `points` of the budgets that are left.  (By the whole workgroup.)
+template <typename U>
+__device__ __forceinline__ void cut_at_budgets(const LongWs &w, ListLds &l, LongMeta *meta, const Open *open, Open *out,
+                                               const int64_t c, const int n, const int points, const unsigned pass)
+{
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), count = l.count;
+    draw_budgets<U>(w, l, open, count, c, n, points, pass);
+    if (tid < points) {
+        const int64_t mine = l.drawn[tid];
+        int rank = 0;
+        for (int k = 0; k < points; ++k) rank += l.drawn[k] < mine || (l.drawn[k] == mine && k < tid);
+        l.s[rank] = mine;
+    }
+    __syncthreads();
+    if (wave < points) {
+        // (the same one twice, or none: left out)
+        const int64_t s = uniform_lane((int64_t)l.s[wave], 0), below = wave > 0 ? uniform_lane((int64_t)l.s[wave - 1], 0) : -1;
+        uint64_t v = ~0ull;
+        bool exact = false;
+        if (s > 0 && s != below) {
+            int64_t prev = below;
+            for (int k = 0; k < count; ++k)
+                if (open[k].lo < s && open[k].lo > prev) prev = open[k].lo;
+            prev = uniform_lane(prev, 0);
+            v = long_cost<U, false>(w, meta, c, n, prev, s, exact, nullptr, (U *)(search_lds + wave * long_f_bytes(n)));
+            if (exact && lane == 0) atomicMin((unsigned long long *)&meta->ub, (unsigned long long)(v + (uint64_t)s));
+        }
+        if (lane == 0) {
+            l.c[wave] = v;
+            l.exact[wave] = exact ? 1 : 0;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        uint64_t bc = meta->best_cost, bs = meta->best_s;
+        for (int k = 0; k < points; ++k) {
+            const uint64_t cost = l.c[k] + (uint64_t)l.s[k];
+            if (l.exact[k] && (cost < bc || (cost == bc && (uint64_t)l.s[k] < bs))) {
+                bc = cost;
+                bs = (uint64_t)l.s[k];
+            }
+        }
+        meta->best_cost = bc;
+        meta->best_s = bs;
+        const uint64_t known = shared_load(&meta->ub), ub = known < bc ? known : bc;
+        int kept = 0, k = 0;
+        auto keep = [&](const int64_t lo, const int64_t last, const uint64_t at_least) {
+            if (at_least > ub) return;
+            const int64_t hi = last < (int64_t)(ub - at_least) ? last : (int64_t)(ub - at_least);
+            if (hi <= lo) return;
+            if (kept < kOpenMax) {
+                out[kept++] = Open{lo, hi, at_least, 0, 0};
+            } else {  // (joined with the last)
+                Open &o = out[kOpenMax - 1];
+                o.hi = hi;
+                o.c = at_least < o.c ? at_least : o.c;
+            }
+        };
+        for (int i = 0; i < count; ++i) {
+            int64_t lo = open[i].lo;
+            for (; k < points && l.s[k] <= open[i].hi; ++k) {
+                if (l.s[k] <= lo || (k > 0 && l.s[k] == l.s[k - 1])) continue;
+                keep(lo, l.exact[k] ? l.s[k] - 1 : l.s[k], l.c[k]);
+                lo = l.s[k];
+            }
+            keep(lo, open[i].hi, open[i].c);
+        }
+        l.count = kept;
+        __hip_atomic_store(&meta->listed, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (int k = tid; k < seen_slots(n); k += (int)blockDim.x)
+        __hip_atomic_store(w.seen + c * seen_slots(n) + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+}
+
+// The list, and with CUT what has to be done about one that is too long.  LISTED: an earlier launch has made it.
+template <typename U, bool LISTED, bool CUT>
+__device__ __forceinline__ void list_budgets(const LongWs &w, ListLds &l, LongMeta *meta, const int64_t c, const int n,
+                                             const int points, const int most)
+{
+    for (unsigned pass = 0;; ++pass) {
+        const Open *open = l.open[pass & 1];
+        const bool last = pass == kListPasses;
+        if (!LISTED || pass > 0)
+            for (int a = (int)(blockIdx.x * blockDim.x + threadIdx.x); a < n - 1; a += (int)(gridDim.x * blockDim.x))
+                list_start<U>(w, meta, open, l.count, last ? INT32_MAX : most, c, n, a);
+        if (!CUT) return;
+        __syncthreads();
+        if (shared_load(&meta->listed) <= most || last) return;
+        cut_at_budgets<U>(w, l, meta, open, l.open[~pass & 1], c, n, points, pass);
+    }
+}
+
+// Up to kListMost layers one launch does both; longer chains are listed by several workgroups, and a launch of one
+// workgroup a chain follows, which has nothing to do as a rule (a workgroup alone lists 4,096 starts 7 us slower).
+template <bool LISTED, bool CUT>
+__global__ __launch_bounds__(kListMost) void search_list_kernel(int n, int points, int most, LongWs w)
+{
+    __shared__ ListLds l;
     const int64_t c = blockIdx.y;
     LongMeta *meta = w.meta + c;
     const int count = meta->left;
-    if (meta->status != CKPT_OK || count == 0) return;
-    for (int k = threadIdx.x; k < count; k += kListThreads) open[k] = w.open[(c * 3 + 2) * kOpenMax + k];
+    if (meta->status != CKPT_OK || count == 0 || (LISTED && meta->listed <= most)) return;
+    for (int k = threadIdx.x; k < count; k += (int)blockDim.x) l.open[0][k] = w.open[(c * 3 + 2) * kOpenMax + k];
+    if (threadIdx.x == 0) l.count = count;
     __syncthreads();
-    int64_t lowest = open[0].lo, highest = open[0].hi;
-    for (int k = 1; k < count; ++k) {
-        lowest = open[k].lo < lowest ? open[k].lo : lowest;
-        highest = open[k].hi > highest ? open[k].hi : highest;
-    }
-    const int a = (int)blockIdx.x * kListThreads + (int)threadIdx.x;
-    if (a >= n - 1) return;
-    if (meta->narrow)
-        list_start<uint32_t>(w, meta, open, count, c, n, a, (uint64_t)lowest, (uint64_t)highest);
-    else
-        list_start<uint64_t>(w, meta, open, count, c, n, a, (uint64_t)lowest, (uint64_t)highest);
+    if (meta->narrow) list_budgets<uint32_t, LISTED, CUT>(w, l, meta, c, n, points, most);
+    else list_budgets<uint64_t, LISTED, CUT>(w, l, meta, c, n, points, most);
 }
-
-// Bytes of F in LDS, before the heads.
-__host__ __device__ inline size_t long_f_bytes(int n) { return ((size_t)n + 1 + kWave) * 8; }
 
 // A wave per budget, its set recorded on the way (a pass of its own for the set of the best took
 // 143 us at 1,001 layers of a network and 85 at 4,096 aligned ones; recording makes a pass 7 to 20 % longer).  The last wave of
@@ -1343,8 +1579,10 @@ __global__ __launch_bounds__(kWave) void search_finish_kernel(int n, LongWs w)
             s = meta->narrow ? (uint64_t)(P32[x] - P32[a]) : P64[x] - P64[a];
         }
         bool exact;
-        const uint64_t v = meta->narrow ? long_cost<uint32_t, true>(w, meta, c, n, (int64_t)s - 1, (int64_t)s, exact, head)
-                                        : long_cost<uint64_t, true>(w, meta, c, n, (int64_t)s - 1, (int64_t)s, exact, head);
+        const int64_t at_s = (int64_t)s;
+        const uint64_t v =
+            meta->narrow ? long_cost<uint32_t, true>(w, meta, c, n, at_s - 1, at_s, exact, head, (uint32_t *)search_lds)
+                         : long_cost<uint64_t, true>(w, meta, c, n, at_s - 1, at_s, exact, head, (uint64_t *)search_lds);
         if (!exact || v + s > cost || (v + s == cost && s > at)) continue;
         uint64_t known = 0;
         if (lane == 0) known = atomicMin((unsigned long long *)&meta->ub, (unsigned long long)(v + s));
@@ -1374,7 +1612,8 @@ __global__ __launch_bounds__(kWave) void search_finish_kernel(int n, LongWs w)
 
 // ---- results ----
 
-__global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int waves, int64_t cstride, int64_t pstride,
+constexpr int kResultThreads = 256;
+__global__ __launch_bounds__(kResultThreads) void search_result_kernel(int n, int waves, int64_t cstride, int64_t pstride,
                                                                      uint8_t *__restrict__ mask_out,
                                                                      int64_t *__restrict__ peak_out,
                                                                      int64_t *__restrict__ budget_out,
@@ -1402,7 +1641,7 @@ __global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int 
     const int32_t status = m.status == CKPT_OK && best == ~0ull ? CKPT_ERR_DEVICE : m.status;
     if (tid == 0 && status_out) status_out[c] = status;
     if (status != CKPT_OK) {
-        for (int k = tid; k <= n; k += kListThreads) mp[(int64_t)k * pstride] = 0;
+        for (int k = tid; k <= n; k += kResultThreads) mp[(int64_t)k * pstride] = 0;
         if (tid == 0) {
             peak_out[c] = -1;
             if (budget_out) budget_out[c] = -1;
@@ -1410,7 +1649,7 @@ __global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int 
         return;
     }
     const uint64_t *set = w.set + (c * waves + by) * (n / kWave + 1);
-    for (int k = tid; k <= n; k += kListThreads)
+    for (int k = tid; k <= n; k += kResultThreads)
         mp[(int64_t)k * pstride] = (uint8_t)((set[k / kWave] >> (k % kWave)) & 1ull);
     if (tid == 0) {
         peak_out[c] = (int64_t)(best * m.unit);
@@ -1419,11 +1658,14 @@ __global__ __launch_bounds__(kListThreads) void search_result_kernel(int n, int 
 }
 
 std::atomic<bool> long_lds_raised[kMaxDevices];
-constexpr size_t kLongLds = ((size_t)CKPT_CUBIC_MAX_LAYERS + 1 + kWave) * 10;  // F and the heads
+constexpr size_t kLongLds = 150 << 10;  // the most that list_waves() takes (F and the heads of the longest chain: 81 KB)
 
 hipError_t raise_long_lds_limit()
 {
-    return raise_lds_limit(long_lds_raised, {(const void *)search_round_kernel, (const void *)search_finish_kernel}, kLongLds);
+    return raise_lds_limit(long_lds_raised,
+                           {(const void *)search_round_kernel, (const void *)search_list_kernel<false, true>,
+                            (const void *)search_list_kernel<true, true>, (const void *)search_finish_kernel},
+                           kLongLds);
 }
 
 }  // namespace
@@ -1440,14 +1682,16 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
 {
     if (batch == 0) return hipSuccess;
     if (batch > 65535) return hipErrorInvalidConfiguration;
-    const size_t f_lds = long_f_bytes(n), set_lds = ((size_t)n + 1 + kWave) * 10;
-    if (set_lds > kDefaultLdsLimit) {
+    const int at_once = list_waves(batch, n);
+    const size_t f_lds = long_f_bytes(n), set_lds = ((size_t)n + 1 + kWave) * 10, list_lds = at_once * f_lds;
+    if (set_lds > kDefaultLdsLimit || list_lds > kDefaultLdsLimit) {
         const hipError_t e = raise_long_lds_limit();
         if (e != hipSuccess) return e;
     }
     LongWs w;
     (void)carve_long(ws, batch, n, &w);
     const int points = long_points(batch, n), waves = finish_waves(batch, n);
+    const int most = 2 * waves < seen_slots(n) / 2 ? 2 * waves : seen_slots(n) / 2;
     const unsigned B = (unsigned)batch;
     hipLaunchKernelGGL(search_table_kernel, dim3(B), dim3(kTableThreads), ((size_t)n + 1) * 4, stream, d, n, st.chain,
                        st.pos, points, waves, w);
@@ -1455,10 +1699,16 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
         hipLaunchKernelGGL(search_round_kernel, dim3((unsigned)points, B), dim3(kWave), f_lds, stream, n, points, round, w);
         hipLaunchKernelGGL(search_close_kernel, dim3(B), dim3(kWave), 0, stream, points, round, w);
     }
-    hipLaunchKernelGGL(search_list_kernel, dim3((unsigned)((n + kListThreads - 1) / kListThreads), B), dim3(kListThreads),
-                       0, stream, n, w);
+    const dim3 cutters((unsigned)list_threads(batch, n));
+    if (n <= kListMost) {
+        hipLaunchKernelGGL((search_list_kernel<false, true>), dim3(1, B), cutters, list_lds, stream, n, at_once, most, w);
+    } else {
+        hipLaunchKernelGGL((search_list_kernel<false, false>), dim3((unsigned)((n + 255) / 256), B), dim3(256), 0, stream, n,
+                           at_once, most, w);
+        hipLaunchKernelGGL((search_list_kernel<true, true>), dim3(1, B), cutters, list_lds, stream, n, at_once, most, w);
+    }
     hipLaunchKernelGGL(search_finish_kernel, dim3((unsigned)waves, B), dim3(kWave), set_lds, stream, n, w);
-    hipLaunchKernelGGL(search_result_kernel, dim3(B), dim3(kListThreads), 0, stream, n, waves, st.chain, st.pos, mask_out,
+    hipLaunchKernelGGL(search_result_kernel, dim3(B), dim3(kResultThreads), 0, stream, n, waves, st.chain, st.pos, mask_out,
                        peak_out, budget_out, status_out, w);
     return hipGetLastError();
 }

@@ -100,7 +100,7 @@ template <class T> T least(T *p, T v) { const T was = *p; *p = v < was ? v : was
 #define blockIdx (emu::block)
 #define blockDim (emu::threads)
 #define gridDim (emu::blocks)
-#define hipLaunchKernelGGL(k, grid, block, lds, stream, ...) emu::launch(#k, (const void *)(k), grid, block, lds, [&] { k(__VA_ARGS__); })
+#define hipLaunchKernelGGL(k, grid, block, lds, stream, ...) emu::launch(#k, (const void *)(k), grid, block, lds, [&] { (k)(__VA_ARGS__); })
 
 inline void __syncthreads() { (void)emu::meet(0, emu::kBarrier); }
 inline bool __any(int b) { return emu::ballot(b != 0) != 0; }
@@ -121,10 +121,12 @@ template <class T> T __shfl_up(T v, int d, int)
 #define __HIP_MEMORY_SCOPE_WORKGROUP 0
 #define __HIP_MEMORY_SCOPE_AGENT 1
 #define __hip_atomic_load(p, ...) (*(p))
+#define __hip_atomic_store(p, v, ...) ((void)(*(p) = (v)))
 #define __hip_atomic_fetch_min(p, v, ...) emu::least(p, v)
 #define __hip_atomic_exchange(p, v, ...) emu::exchange(p, v)
 template <class T> T atomicAdd(T *p, int v) { return emu::exchange(p, (T)(*p + v)); }
 template <class T> T atomicMin(T *p, T v) { return emu::least(p, v); }
+template <class T> T atomicMax(T *p, T v) { return emu::exchange(p, *p < v ? v : *p); }
 template <class T> T atomicCAS(T *p, T a, T b) { const T was = *p; if (was == a) *p = b; return was; }
 inline int __ffsll(unsigned long long v) { return __builtin_ffsll((long long)v); }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }

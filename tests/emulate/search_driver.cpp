@@ -117,6 +117,12 @@ int main()
         if (n > 128) check("kinds of sizes", chains, kWavePerPoint);
     }
     check("large sizes in front", {with(uniform(257, 1, 1000000), 0, 1ll << 43), with(uniform(257, 1, 1000000), 0, top)}, kWavePerPoint);
+    // sizes of very different orders: more budgets are left after the rounds than are listed
+    for (const int n : {142, 300}) {
+        Sizes d = with(uniform(n, 1, 1000000), n / 3, 1000000000000000);
+        check("one large layer", {d}, kWavePerPoint);
+        check("two large layers", {with(d, n - 1, 1000000000012345)}, kWavePerPoint);
+    }
     printf(failures ? "search_driver: %d failed\n" : "search_driver ok\n", failures);
     return failures != 0;
 }

@@ -187,6 +187,40 @@ def test_sizes_at_the_ends_that_outweigh_the_rest(n):
         check(d[:, c:c + 1])
 
 
+@pytest.mark.parametrize("n", [129, 142, 200, 300, 640])
+def test_layers_that_outweigh_the_rest(n):
+    """Sizes of very different orders: two rounds of evenly placed points leave most budgets in one interval."""
+    rng = np.random.default_rng(n)
+    plain = rng.integers(1, 1000001, size=n + 1).astype(np.int64)
+    columns = []
+    for at, size in (((1,), 10**9), ((n // 3,), 10**14), ((n - 1,), 10**15), ((n // 2,), 10**18),
+                     ((n // 4, n // 2), 10**15), ((n // 5, n // 4, n // 3, n // 2), 10**16)):
+        x = plain.copy()
+        for k, place in enumerate(at):
+            x[place] = size + 12345 * k if len(at) == 2 else size // 1000**k
+        columns.append(x)
+    columns.append(1 << rng.integers(0, 50, size=n + 1))
+    columns.append(np.exp2(45 * rng.random(n + 1)).astype(np.int64) + 1)
+    columns.append(np.where(np.arange(n + 1) % 2 == 0, 1000003, 999999937))
+    d = np.stack(columns, axis=1).astype(np.int64)
+    print(f"cubic search, sizes of different orders: n = {n}", flush=True)
+    check(d)                                                                     # few waves to a chain
+    check(np.tile(d, (1, 34)) if n < 300 else d[:, ::-1])
+    for c in (1, 2, 3, 4, 5, 7):
+        check(d[:, c:c + 1])                                                     # many
+
+
+def test_a_chain_whose_budgets_several_workgroups_list():
+    rng = np.random.default_rng(1100)
+    plain = rng.integers(1, 1000001, size=1101).astype(np.int64)
+    heavy = plain.copy()
+    heavy[366] = 10**15
+    print("cubic search: 1,100 layers, one of 10^15", flush=True)
+    check(heavy[:, None])
+    heavy[800] = 10**15 + 12345
+    check(np.stack([plain, heavy], axis=1))
+
+
 @pytest.mark.parametrize("batch", [2, 33])
 def test_batches_of_long_chains(batch):
     d = inputs.uniform_aligned_chains(7, 270, batch, 256, 32768)
