@@ -735,16 +735,16 @@ __global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t 
     }
 }
 
-// The chains of a ragged batch that have n_lo .. n_hi layers, each where it lies in the flat array.
+// The chains of a ragged batch from number `first` on that have n_lo .. n_hi layers, each where it lies in the flat array.
 template <bool WIDE>
 __global__ __launch_bounds__(kWave) void cubic_search_ragged_kernel(const int64_t *__restrict__ d,
-                                                                    const int64_t *__restrict__ off, int n_lo, int n_hi,
-                                                                    uint8_t *__restrict__ mask_out,
+                                                                    const int64_t *__restrict__ off, int64_t first,
+                                                                    int n_lo, int n_hi, uint8_t *__restrict__ mask_out,
                                                                     int64_t *__restrict__ peak_out,
                                                                     int64_t *__restrict__ budget_out,
                                                                     int32_t *__restrict__ status_out, SearchWs w)
 {
-    const int64_t c = blockIdx.x, o = off[c], n = off[c + 1] - o - 1;
+    const int64_t c = first + blockIdx.x, o = off[c], n = off[c + 1] - o - 1;
     if (n < n_lo || n > n_hi) return;
     const bool done = search_one<true, WIDE>(d + o, 1, (int)n, mask_out + o, 1, peak_out + c,
                                              budget_out ? budget_out + c : nullptr,
@@ -784,6 +784,8 @@ hipError_t raise_search_lds_limit()
 // chains that need 64 bits follow in a second one; fewer chains do not fill the chip either way.
 constexpr int64_t kSearchSplitFrom = 1024;
 constexpr int kSearchWideBlocks = 1024;
+// (a launch has fewer than 2^32 threads)
+constexpr int64_t kMostWavesOfALaunch = 1 << 25;
 
 }  // namespace
 
@@ -818,7 +820,7 @@ hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_d
     if (batch == 0) return hipSuccess;
     const hipError_t e = raise_search_lds_limit();
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)batch), block(kWave);
+    const dim3 block(kWave);
     const SearchWs w{count, list};
     const bool wide = batch < kSearchSplitFrom;
     if (!wide) hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
@@ -827,12 +829,12 @@ hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_d
         const int n = longest[k], below = k > 0 ? search_class_limit(k - 1) + 1 : 1;
         if (n == 0) continue;
         all = all > n ? all : n;
-        if (wide)
-            hipLaunchKernelGGL(cubic_search_ragged_kernel<true>, grid, block, search_lds_bytes(n, 8), stream, d,
-                               offsets_dev, below, n, mask_out, peak_out, budget_out, status_out, w);
-        else
-            hipLaunchKernelGGL(cubic_search_ragged_kernel<false>, grid, block, search_lds_bytes(n, 4), stream, d,
-                               offsets_dev, below, n, mask_out, peak_out, budget_out, status_out, w);
+        for (int64_t first = 0; first < batch; first += kMostWavesOfALaunch) {
+            const dim3 grid((unsigned)std::min(batch - first, kMostWavesOfALaunch));
+            hipLaunchKernelGGL(wide ? cubic_search_ragged_kernel<true> : cubic_search_ragged_kernel<false>, grid, block,
+                               search_lds_bytes(n, wide ? 8 : 4), stream, d, offsets_dev, first, below, n, mask_out, peak_out,
+                               budget_out, status_out, w);
+        }
     }
     if (!wide)
         hipLaunchKernelGGL(cubic_search_ragged_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(all, 8),

@@ -47,6 +47,8 @@ extern unsigned char *dynamic_lds;
 // One launch: the grid's workgroups one after the other.  Dynamic LDS ends at a page that cannot be touched, and more
 // than 64 KB of it must have been allowed for the kernel (`entry`).
 void launch(const char *name, const void *entry, dim3 grid, dim3 block, size_t lds, const std::function<void()> &kernel);
+// If set, launches are only checked and handed to this.
+extern std::function<void(const char *name, dim3 grid)> instead_of_running;
 // Called after every hipFuncSetAttribute: what another thread does at that moment.
 extern std::function<void()> meanwhile;
 // Device memory of exactly this many bytes, between pages that cannot be touched, full of a pattern.

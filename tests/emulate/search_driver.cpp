@@ -123,6 +123,15 @@ int main()
         check("one large layer", {d}, kWavePerPoint);
         check("two large layers", {with(d, n - 1, 1000000000012345)}, kWavePerPoint);
     }
+    // the largest ragged batches: every chain once for each class of lengths, in launches that there can be
+    for (const int64_t batch : {(int64_t)1000, (int64_t)1 << 25, ((int64_t)1 << 26) + 1, (int64_t)INT32_MAX}) {
+        const int longest[kSearchClasses] = {20, 0, 100, 256};
+        int64_t chains = 0;
+        emu::instead_of_running = [&](const char *name, dim3 grid) { chains += strstr(name, "ragged_kernel") ? grid.x : 0; };
+        launch_cubic_search_ragged(nullptr, nullptr, batch, longest, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+        emu::instead_of_running = nullptr;
+        failures += chains != 3 * batch;
+    }
     printf(failures ? "search_driver: %d failed\n" : "search_driver ok\n", failures);
     return failures != 0;
 }
