@@ -19,6 +19,10 @@ constexpr int64_t kRaggedPartsMax = 2048;
 // From here on the inputs cannot be in the memory-side cache (256 MiB) from the call that wrote them, and loads past the
 // caches are 1 % faster (2.4 GB: 471 us against 476); below, they lose what is there (235 MB: 53 us against 40).
 constexpr int64_t kBypassBytes = 1ll << 30;
+// In a ragged call they are faster where the waves hold few chains each (the walk of 3,000 chains of 2 to 4,095 layers,
+// 1.4 a wave, 1,408 us past the caches, 1,483 through them; of 30,000, 7 a wave, 2,055 and 2,117) and slower where they
+// are full (524,288 of 152 and 257 layers: the call 1,008 us past, 985 through).
+constexpr int64_t kRaggedBypassChains = 16;
 
 // The evaluation of chain c of a batch laid out by (cstride, pstride).  OBJ = CKPT_OBJ_BOTH keeps
 // the running values of both objectives and writes the dynamic peak `second` values after the
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(kBlock *kPartWaves) void eval_peak_parts_kernel(
 // Every group of a ragged call in one launch: a workgroup looks up the group its 64 chains belong to
 // and evaluates them where that group is staged; results go to the chains' places (with both
 // objectives the dynamic peaks `batch` values, the number of chains of all groups, further on).
-template <int OBJ, bool PARTS>
+template <int OBJ, bool PARTS, bool BYPASS = false>
 __global__ __launch_bounds__(PARTS ? kBlock * kRaggedWaves : kBlock) void eval_peak_ragged_kernel(
     const int64_t *__restrict__ d_stage, const uint8_t *__restrict__ mask_stage,
     const RaggedGroupDev *__restrict__ groups, int n_groups, int64_t batch, int64_t *__restrict__ peak_stage,
@@ -269,8 +273,8 @@ __global__ __launch_bounds__(PARTS ? kBlock * kRaggedWaves : kBlock) void eval_p
         eval_peak_parts<OBJ>(d_stage + g.stage_off, mask_stage + g.stage_off, g.count, g.n, 1, g.pitch,
                              peak_stage + g.first, status_stage + g.first, c, batch);
     else
-        eval_peak_chain<OBJ, false>(d_stage + g.stage_off, mask_stage + g.stage_off, g.count, g.n, 1, g.pitch,
-                                    peak_stage + g.first, status_stage + g.first, c, batch);
+        eval_peak_chain<OBJ, BYPASS>(d_stage + g.stage_off, mask_stage + g.stage_off, g.count, g.n, 1, g.pitch,
+                                     peak_stage + g.first, status_stage + g.first, c, batch);
 }
 
 std::atomic<bool> parts_lds_raised[kMaxDevices];
@@ -315,9 +319,11 @@ hipError_t launch_eval_peak(const int64_t *d, const uint8_t *mask, int64_t batch
 }
 
 hipError_t launch_eval_peak_ragged(const int64_t *d_stage, const uint8_t *mask_stage, const RaggedGroupDev *groups,
-                                   int n_groups, int64_t waves, int64_t batch, int objective, int64_t *peak_stage,
+                                   const RaggedTotals &t, int64_t batch, int objective, int64_t *peak_stage,
                                    int32_t *status_stage, hipStream_t stream)
 {
+    const int n_groups = t.n_groups;
+    const int64_t waves = t.waves;
     if (waves == 0) return hipSuccess;
     static_assert(kBlock == kWave, "a workgroup takes one of the groups' waves");
     const bool parts = waves <= kRaggedPartsMax;
@@ -331,6 +337,10 @@ hipError_t launch_eval_peak_ragged(const int64_t *d_stage, const uint8_t *mask_s
         return objective == CKPT_OBJ_STATIC    ? go(eval_peak_ragged_kernel<CKPT_OBJ_STATIC, true>)
                : objective == CKPT_OBJ_DYNAMIC ? go(eval_peak_ragged_kernel<CKPT_OBJ_DYNAMIC, true>)
                                                : go(eval_peak_ragged_kernel<CKPT_OBJ_BOTH, true>);
+    if (batch < kRaggedBypassChains * waves)
+        return objective == CKPT_OBJ_STATIC    ? go(eval_peak_ragged_kernel<CKPT_OBJ_STATIC, false, true>)
+               : objective == CKPT_OBJ_DYNAMIC ? go(eval_peak_ragged_kernel<CKPT_OBJ_DYNAMIC, false, true>)
+                                               : go(eval_peak_ragged_kernel<CKPT_OBJ_BOTH, false, true>);
     return objective == CKPT_OBJ_STATIC    ? go(eval_peak_ragged_kernel<CKPT_OBJ_STATIC, false>)
            : objective == CKPT_OBJ_DYNAMIC ? go(eval_peak_ragged_kernel<CKPT_OBJ_DYNAMIC, false>)
                                            : go(eval_peak_ragged_kernel<CKPT_OBJ_BOTH, false>);

@@ -483,7 +483,7 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
                            off, perm, groups, tile_first2, n_groups, 1, smask);
     hipError_t e = hipSuccess;
     if (which == CKPT_CALL_EVAL_PEAK) {
-        e = launch_eval_peak_ragged(sd, smask, groups, n_groups, p.t.waves, batch, objective, speak, sstatus, stream);
+        e = launch_eval_peak_ragged(sd, smask, groups, p.t, batch, objective, speak, sstatus, stream);
     } else if (which == CKPT_CALL_SOLVE_LINEAR) {
         e = launch_solve_linear_ragged(sd, groups, p.t, batch, smask, speak, sstatus, base + w.inner, stream);
     } else if (which == CKPT_CALL_EVAL_TIMELINE) {

@@ -122,6 +122,15 @@ def test_peaks_on_both_sides_of_the_rule_for_small_calls(batch):
         assert np.array_equal(np_(peak), oracle.ragged_peak(d, m, off, obj)), f"objective {obj}"
 
 
+def test_peaks_of_more_lengths_than_the_rule_for_small_calls():
+    """2,100 groups of one chain or two: beyond the parts, and waves that hold few chains."""
+    lengths = np.concatenate([np.arange(1, 2101), np.arange(1, 2101, 7)])
+    np.random.default_rng(4).shuffle(lengths)
+    d, m, off = inputs.ragged_batch(14, lengths)
+    say("ragged peaks: 2,100 lengths")
+    check_eval(d, m, off)
+
+
 def test_chain_with_a_bad_size_is_reported_alone():
     lengths = [15, 24, 15, 3]
     d, m, off = inputs.ragged_batch(15, lengths)
