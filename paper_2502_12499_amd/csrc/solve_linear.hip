@@ -69,12 +69,12 @@ constexpr int kRing = 16;        // slots per lane in each ring
 constexpr int kChunk = 8;        // rows in flight per lane
 constexpr int kListBlocks = 1024;
 
-// Whether T(i) + d_i + max(d), which bounds M(i) and every U(i,j), is beyond INT64_MAX, T(i) itself not being so.  (The
-// three may wrap together: T + d_i alone is below 2^64, with a largest size near INT64_MAX the sum of all is not.)
+// Whether T(i), or T(i) + d_i + max(d), which bounds M(i) and every U(i,j), is beyond INT64_MAX, T(i+1) and the sizes not
+// being so.  (All three together may wrap around 2^64; T + d_i alone does not, and then shows in its top bit.)
 __device__ inline bool value_overflows(uint64_t T, int64_t di, int64_t dmax)
 {
-    const uint64_t room = (uint64_t)INT64_MAX - T;
-    return (uint64_t)di > room || (uint64_t)dmax > room - (uint64_t)di;
+    const uint64_t two = T + (uint64_t)di, all = two + (uint64_t)dmax;
+    return (int64_t)(T | two | all) < 0;
 }
 
 constexpr int kLdsStackMaxN = 2047;
@@ -623,8 +623,7 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
             dmax = di > dmax ? di : dmax;
             T += (uint64_t)dnext;
             dnext = di;
-            out |= T > (uint64_t)INT64_MAX;
-            if (!out) out |= value_overflows(T, di, dmax);
+            out |= value_overflows(T, di, dmax);
             if (out) return;
             const int64_t Ti = (int64_t)T;
             Rp = di > Rp ? di : Rp;
