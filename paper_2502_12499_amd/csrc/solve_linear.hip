@@ -1055,7 +1055,14 @@ __global__ __launch_bounds__(kWave) void linear_wave_kernel(const int64_t *__res
 // the times grow with the number of chains here and stay there (unaligned sizes: 37 against 152 us at 64 layers).
 __host__ inline int64_t wave_max_batch(int n) { return n <= kLogMaxLayers ? 4096 : 6144; }
 constexpr int kWaveMaxLayers = 16383;    // 32 KB of LDS
-constexpr int kOwnListMaxLayers = 511;   // 15 KB of LDS for the stacks, kept free for a case that hardly happens
+constexpr int kOwnListMaxLayers = 511;   // 15 KB of LDS for the stacks, kept free for a case that hardly happens ...
+// ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes): in two turns 4,096
+// chains of 511 layers took 286 us, and take 201 with the list in a launch of its own; 2,600 198 and 158.
+inline bool own_list(int64_t batch, int n)
+{
+    const int64_t per_cu = (160 << 10) / (int64_t)align_up(lds_stack_bytes(n), 1280);
+    return n <= kOwnListMaxLayers && batch <= 256 * per_cu;
+}
 
 }  // namespace
 
@@ -1129,7 +1136,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     LinearWs w = carve_linear(ws, batch, n);
     const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
     if (batch <= wave_max_batch(n) && n <= kWaveMaxLayers) {
-        if (n <= kOwnListMaxLayers) {
+        if (own_list(batch, n)) {
             hipLaunchKernelGGL(linear_wave_kernel<true>, dim3((unsigned)batch), dim3(kWave), lds_stack_bytes(n), stream, d,
                                n, st.chain, st.pos, mask_out, peak_out, status_out, w);
             return hipGetLastError();

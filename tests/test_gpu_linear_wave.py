@@ -57,6 +57,14 @@ def test_long_chains(n):
     check(live_entries(n))
 
 
+@pytest.mark.parametrize("batch", [2560, 2561])
+def test_a_list_of_their_own_where_all_waves_fit_the_chip(batch):
+    d = inputs.uniform_aligned_chains(4, 511, batch, 256, 32768)
+    d[:, 7:9] = live_entries(511)                                                # more than 64 live entries: for the list
+    d[:, batch - 1] = live_entries(511)[:, 0]
+    check(d)
+
+
 @pytest.mark.parametrize("batch", [4096, 4097])
 def test_batches_on_both_sides_of_the_rule(batch):
     d = inputs.uniform_aligned_chains(3, 40, batch, 256, 32768)
