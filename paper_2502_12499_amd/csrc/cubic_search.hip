@@ -668,7 +668,8 @@ __device__ __forceinline__ bool search_one(const int64_t *__restrict__ dp, const
         bound = bound > ends ? bound : ends;
         const uint64_t span = all < bound - ends ? all : bound - ends;
         const uint64_t largest = mx >> shift;
-        const uint64_t heavy = largest > all / 4 && largest <= span ? largest : 0;  // (or one at the ends: any cut will do)
+        // (it may be one at the ends: any cut will do)
+        const uint64_t heavy = largest > all / 4 && largest <= span ? largest : 0;
         const bool narrow = bound < (1ull << 31) - 1 && span + largest < (1ull << 31) &&
                             (kLookahead - 1) * largest < (1ull << 31);
         if (narrow ? !NARROW : !WIDE) return false;
@@ -735,7 +736,8 @@ __global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t 
     }
 }
 
-// The chains of a ragged batch from number `first` on that have n_lo .. n_hi layers, each where it lies in the flat array.
+// The chains of a ragged batch from number `first` on that have n_lo .. n_hi layers, each where it lies in the flat
+// array.
 template <bool WIDE>
 __global__ __launch_bounds__(kWave) void cubic_search_ragged_kernel(const int64_t *__restrict__ d,
                                                                     const int64_t *__restrict__ off, int64_t first,
@@ -832,8 +834,8 @@ hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_d
         for (int64_t first = 0; first < batch; first += kMostWavesOfALaunch) {
             const dim3 grid((unsigned)std::min(batch - first, kMostWavesOfALaunch));
             hipLaunchKernelGGL(wide ? cubic_search_ragged_kernel<true> : cubic_search_ragged_kernel<false>, grid, block,
-                               search_lds_bytes(n, wide ? 8 : 4), stream, d, offsets_dev, first, below, n, mask_out, peak_out,
-                               budget_out, status_out, w);
+                               search_lds_bytes(n, wide ? 8 : 4), stream, d, offsets_dev, first, below, n, mask_out,
+                               peak_out, budget_out, status_out, w);
         }
     }
     if (!wide)
@@ -1281,7 +1283,7 @@ __global__ __launch_bounds__(kWave) void search_close_kernel(int points, int rou
 // it was took 1.7, 8.2 and 64 ms (every budget evaluated: 0.2, 1.5 and 92 ms).
 constexpr int kListMost = 1024;   // threads
 constexpr int kListWaves = kListMost / kWave;
-constexpr int kListPasses = 32;   // then all that are left are listed (two were the most on any kind of chain tried)
+constexpr int kListPasses = 32;   // then all that are left are listed (two were the most on any chain tried)
 constexpr int kListStarts = 4;    // starts whose bisections a thread runs side by side
 
 // Bytes of F in LDS, before the heads.
@@ -1447,7 +1449,8 @@ __device__ __forceinline__ void draw_budgets(const LongWs &w, ListLds &l, const 
     const bool has_single = l.single != 0 && (points > 1 || pass % 2 == 0);
     const unsigned part = all / (unsigned)points;
     for (int k = 0; k < points && mine != 0; ++k) {
-        const unsigned r = (unsigned)((uint64_t)all * (unsigned)k / (unsigned)points) + (part ? mixed(pass, (unsigned)k) % part : 0);
+        const unsigned r = (unsigned)((uint64_t)all * (unsigned)k / (unsigned)points) +
+                           (part ? mixed(pass, (unsigned)k) % part : 0);
         if (k == 0 && has_single) continue;
         if (r >= before && r - before < mine) l.drawn[k] = (int64_t)((uint64_t)P[at_x] - (uint64_t)P[at_a]);
     }
@@ -1472,7 +1475,8 @@ __device__ __forceinline__ void cut_at_budgets(const LongWs &w, ListLds &l, Long
     __syncthreads();
     if (wave < points) {
         // (the same one twice, or none: left out)
-        const int64_t s = uniform_lane((int64_t)l.s[wave], 0), below = wave > 0 ? uniform_lane((int64_t)l.s[wave - 1], 0) : -1;
+        const int64_t s = uniform_lane((int64_t)l.s[wave], 0);
+        const int64_t below = wave > 0 ? uniform_lane((int64_t)l.s[wave - 1], 0) : -1;
         uint64_t v = ~0ull;
         bool exact = false;
         if (s > 0 && s != below) {
@@ -1714,8 +1718,8 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
     if (n <= kListMost) {
         hipLaunchKernelGGL((search_list_kernel<false, true>), dim3(1, B), cutters, list_lds, stream, n, at_once, most, w);
     } else {
-        hipLaunchKernelGGL((search_list_kernel<false, false>), dim3((unsigned)((n + 255) / 256), B), dim3(256), 0, stream, n,
-                           at_once, most, w);
+        hipLaunchKernelGGL((search_list_kernel<false, false>), dim3((unsigned)((n + 255) / 256), B), dim3(256), 0, stream,
+                           n, at_once, most, w);
         hipLaunchKernelGGL((search_list_kernel<true, true>), dim3(1, B), cutters, list_lds, stream, n, at_once, most, w);
     }
     hipLaunchKernelGGL(search_finish_kernel, dim3((unsigned)waves, B), dim3(kWave), set_lds, stream, n, w);
