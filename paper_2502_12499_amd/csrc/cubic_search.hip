@@ -401,16 +401,19 @@ __device__ inline uint64_t select_lanes(uint64_t off, uint64_t on, uint64_t mask
            select_lanes((uint32_t)off, (uint32_t)on, mask);
 }
 
-// F_s(n) by a whole wave, head by head.  While the head h stays in the window, F(j) = d_j + F(h) and h is the
-// smallest minimal predecessor of j, for all those j at once; when it leaves (cell e), the new head is the
-// smallest index with minimal F in the window of e: what enters later is larger than the minimum, and what lies
-// before it is larger or gone.  The lanes hold three neighbouring slices of 64 positions in registers and slide
-// along the chain: Z, the positions before, A, where the next cells are, and B, whose prefix sums are
-// under way; a window that reaches back beyond Z is finished from the values parked in F.
-// What bounds it is the chain of dependent instructions of a head (about 50, half of them scalar, eight to nine
-// cycles each); a form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips.
-// P: prefix sums, P[n] below 2^31 or 2^63; F (and head): room for n + 1 + kWave values; RECORD: head[j], the
-// predecessor of j, is written for j = 1..n.  stop(F(h)) is asked once per slice; when it says so the pass ends with
+// F_s(n) by a whole wave, head by head.  While the head h stays in the window, F(j) = d_j + F(h) and h is a
+// minimal predecessor of j, for all those j at once; when it leaves (cell e), the new head is an
+// index with minimal F in the window of e: what enters later is larger than the minimum, and what lies
+// before it is larger or gone.  Of several such indices the last one is taken, which stays longest: networks repeat
+// their layers, and a chain of 1,001 of theirs has 64 heads in its slowest pass so, 575 if the first one is taken.
+// (The canonical set wants the first one: see first_pred.)  The lanes hold three neighbouring slices of 64 positions
+// in registers and slide along the chain: Z, the positions before, A, where the next cells are, and B, whose prefix
+// sums are under way; a window that reaches back beyond Z is finished from two older slices and from the values
+// parked in F (whose sums come from memory: 64 layers a segment are usual in a chain of 4,096).
+// What bounds it is the chain of dependent instructions of a head (about 45, half of them scalar, eight to nine
+// cycles each; a loop of its own for the heads of a slice takes three jumps a head out of it, 7 % at 4,096 layers); a form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips.
+// P: prefix sums, P[n] below 2^31 or 2^63; F (and head): room for n + 1 + kWave values; RECORD: head[j], a minimal
+// predecessor of j, is written for j = 1..n, F(j) for j < n, and *ties says whether any was one of several.  stop(F(h)) is asked once per slice; when it says so the pass ends with
 // F(h), which F_s(n) is not below.  The pass ends whatever the sums are: a new head keeps the cell it was chosen for,
 // seen or not (on sums that ascend it always sees it; a test for an empty window took 5 % of a call), and a slice past
 // the last cell ends the pass with the largest value of the type.
@@ -418,8 +421,10 @@ struct NeverStop {
     template <typename U>
     __device__ bool operator()(U) const { return false; }
 };
+constexpr int kOlder = 2;
 template <typename U, bool RECORD, typename H, class Stop = NeverStop>
-__device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F, H *head, Stop stop = Stop())
+__device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F, H *head, Stop stop = Stop(),
+                                       bool *ties = nullptr)
 {
     constexpr U kMax = std::numeric_limits<U>::max();
     const int lane = threadIdx.x % kWave;
@@ -430,74 +435,126 @@ __device__ __forceinline__ U wave_cost(const U *P, const int n, const U s, U *F,
     // per position: P + s (a window of sums ending in x begins where this reaches x), the size, P before, F
     U SZ = 0, FZ = kMax, PA = at(lane), QA = before(lane), PB = at(kWave + lane), QB = before(kWave + lane);
     U SA = PA + s, DA = PA - QA;
+    U SY[kOlder] = {}, FY[kOlder] = {};    // the slices before Z
     U FA = PA;                             // (F(0) = P[0] in lane 0)
     int HA = 0;
-    int h = 0;
+    int h = 0, most = 1;                   // most: of equal values among which a head was chosen
     uint64_t from = ~1ull, test = ~1ull;   // the lanes of the head's cells, and of those that may end it
     U fh = uniform_lane_u(PA, 0), Sh = fh + s;
     for (;;) {
-        // as if h stayed for all of its cells (a later head overwrites them)
-        FA = select_lanes(FA, DA + fh, from);
-        if (RECORD) HA = (int)select_lanes((uint32_t)HA, (uint32_t)h, from);
-        const uint64_t out = __builtin_amdgcn_ballot_w64(QA > Sh) & test;
-        if (out == 0) {
-            // h outlasts A: slide
-            if (stop(fh)) return fh;
-            F[base + lane] = FA;
-            if (RECORD) head[base + lane] = (H)HA;
-            base += kWave;
-            if (__builtin_expect(base > n + 1, 0)) return kMax;
-            from = test = ~0ull;
-            SZ = SA; FZ = FA;
-            PA = PB; QA = QB;
-            SA = PA + s; DA = PA - QA;
-            PB = at(base + kWave + lane);
-            QB = before(base + kWave + lane);
-            continue;
+        uint64_t out;
+        for (;;) {
+            // as if h stayed for all of its cells (a later head overwrites them)
+            FA = select_lanes(FA, DA + fh, from);
+            if (RECORD) HA = (int)select_lanes((uint32_t)HA, (uint32_t)h, from);
+            out = __builtin_amdgcn_ballot_w64(QA > Sh) & test;
+            if (out == 0) break;
+            const int e = __builtin_ctzll((unsigned long long)out);  // the first cell that does not see h
+            if (__builtin_expect(base + e > n, 0)) break;
+            // The window of e: P[i] + s >= P[e - 1], i < e; h and what lies before it are out by themselves.  (Before
+            // the first slide Z holds no positions: its values are the largest there are.)
+            const U Pe = uniform_lane_u(QA, e);
+            from = ~0ull << e;
+            test = from << 1;
+            const uint64_t wa = __builtin_amdgcn_ballot_w64(SA >= Pe) & ~from;
+            const uint64_t wz = __builtin_amdgcn_ballot_w64(SZ >= Pe);
+            const U va = select_lanes(kMax, FA, wa), vz = select_lanes(kMax, FZ, wz);
+            if constexpr (sizeof(U) == 4) fh = wave_min_u32(va < vz ? va : vz); else fh = wave_min_u64(va < vz ? va : vz);
+            const uint64_t ea = __builtin_amdgcn_ballot_w64(FA == fh) & wa;
+            const uint64_t ez = __builtin_amdgcn_ballot_w64(FZ == fh) & wz;
+            // (on sums that do not ascend both may be 0: any lane will do)
+            const bool in_a = ea != 0;
+            const int last = 63 - __builtin_clzll((unsigned long long)((in_a ? ea : ez) | 1ull));
+            const U pa = uniform_lane_u(SA, last), pz = uniform_lane_u(SZ, last);
+            if (RECORD) {
+                h = (in_a ? base : base - kWave) + last;
+                const int equal = (int)__popcll((unsigned long long)ea) + (int)__popcll((unsigned long long)ez);
+                most = equal > most ? equal : most;
+            }
+            Sh = in_a ? pa : pz;
+            if (__builtin_expect((wz & 1ull) != 0, 0)) {
+                // The whole of Z lies in the window: the slices before it, the last two from registers, then the parked
+                // values, if there are any (other lanes stored them: the fence keeps the compiler from moving the loads
+                // up; it costs no instruction).
+                // 64 positions, lane by lane downwards from `top` or upwards to it: true if all of them are in
+                auto join = [&](const U si, const U fi, const int top, const bool downwards) -> bool {
+                    const uint64_t in = __builtin_amdgcn_ballot_w64(si >= Pe);
+                    const U v = select_lanes(kMax, fi, in);
+                    U m;
+                    if constexpr (sizeof(U) == 4) m = wave_min_u32(v); else m = wave_min_u64(v);
+                    const uint64_t equal = __builtin_amdgcn_ballot_w64(fi == m) & in;
+                    if (in != 0 && m < fh) {
+                        fh = m;
+                        // (some lane holds the minimum, if a value of the type is left for it)
+                        const int at_lane = downwards ? __builtin_ctzll((unsigned long long)(equal | 1ull << 63))
+                                                      : 63 - __builtin_clzll((unsigned long long)(equal | 1ull));
+                        h = downwards ? top - at_lane : top - kWave + 1 + at_lane;
+                        Sh = uniform_lane_u(si, at_lane);
+                        if (RECORD) most = (equal & (equal - 1)) != 0 ? 2 : most;
+                    } else if (RECORD && in != 0 && m == fh) {
+                        most = 2;
+                    }
+                    return in == ~0ull;
+                };
+                int top = base - kWave - 1;        // (63 or more, or -1)
+                bool on = top >= 0;
+#pragma unroll
+                for (int k = 0; k < kOlder; ++k, top -= kWave)
+                    if (on) on = join(SY[k], FY[k], top, false) && top >= kWave;
+                if (on) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    for (; top >= 0; top -= kWave)
+                        if (!join(P[top - lane] + s, F[top - lane], top, true)) break;
+                }
+            }
         }
-        const int e = __ffsll((unsigned long long)out) - 1;  // the first cell that does not see h
-        if (__builtin_expect(base + e > n, 0)) {
-            if (RECORD && base + lane <= n) head[base + lane] = (H)HA;
+        if (out != 0) {
+            // cell n sees h
+            if (RECORD) {
+                F[base + lane] = FA;               // (base <= n + 1; what lies past n is not looked at)
+                if (base + lane <= n) head[base + lane] = (H)HA;
+                if (ties) *ties = most > 1;
+            }
             // (no cell in A yet and cell n the last of the slice before: its value is in Z)
             return n >= base ? uniform_lane_u(FA, n - base) : uniform_lane_u(FZ, kWave - 1);
         }
-        // The window of e: P[i] + s >= P[e - 1], i < e; h and what lies before it are out by themselves.  (Before the
-        // first slide Z holds no positions: its values are the largest there are.)
-        const U Pe = uniform_lane_u(QA, e);
-        from = ~0ull << e;
-        test = from << 1;
-        const uint64_t wa = __builtin_amdgcn_ballot_w64(SA >= Pe) & ~from;
-        const uint64_t wz = __builtin_amdgcn_ballot_w64(SZ >= Pe);
-        const U va = select_lanes(kMax, FA, wa), vz = select_lanes(kMax, FZ, wz);
-        if constexpr (sizeof(U) == 4) fh = wave_min_u32(va < vz ? va : vz); else fh = wave_min_u64(va < vz ? va : vz);
-        const uint64_t ea = __builtin_amdgcn_ballot_w64(FA == fh) & wa;
-        const uint64_t ez = __builtin_amdgcn_ballot_w64(FZ == fh) & wz;
-        const int sa = __ffsll((unsigned long long)ea) - 1, sz = __ffsll((unsigned long long)ez) - 1;
-        const bool in_z = ez != 0;
-        const U pa = uniform_lane_u(SA, sa & 63), pz = uniform_lane_u(SZ, sz & 63);
-        if (RECORD) h = in_z ? base - kWave + sz : base + sa;
-        Sh = in_z ? pz : pa;
-        if (__builtin_expect((wz & 1ull) != 0, 0)) {
-            // the whole of Z lies in the window: the parked values before it, if there are any (other lanes stored
-            // them: the fence keeps the compiler from moving the loads up; it costs no instruction)
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            for (int top = base - kWave - 1; top >= 0; top -= kWave) {
-                const int i = top - lane;          // (top is 63 or more)
-                const U si = P[i] + s, fi = F[i];
-                const uint64_t in = __builtin_amdgcn_ballot_w64(si >= Pe);
-                const U v = select_lanes(kMax, fi, in);
-                U m;
-                if constexpr (sizeof(U) == 4) m = wave_min_u32(v); else m = wave_min_u64(v);
-                if (in != 0 && m <= fh) {
-                    fh = m;
-                    const int far = 63 - __clzll((unsigned long long)(__builtin_amdgcn_ballot_w64(fi == m) & in));
-                    h = top - far;
-                    Sh = uniform_lane_u(si, far);
-                }
-                if (in != ~0ull) break;
-            }
+        // h outlasts A: slide
+        if (stop(fh)) return fh;
+        F[base + lane] = FA;
+        if (RECORD) head[base + lane] = (H)HA;
+        base += kWave;
+        if (__builtin_expect(base > n + 1, 0)) return kMax;
+        from = test = ~0ull;
+#pragma unroll
+        for (int k = kOlder - 1; k > 0; --k) {
+            SY[k] = SY[k - 1]; FY[k] = FY[k - 1];
         }
+        SY[0] = SZ; FY[0] = FZ;
+        SZ = SA; FZ = FA;
+        PA = PB; QA = QB;
+        SA = PA + s; DA = PA - QA;
+        PB = at(base + kWave + lane);
+        QB = before(base + kWave + lane);
     }
+}
+
+// The first minimal predecessor of j, given one of them, from the sums and F as wave_cost leaves it: the canonical set
+// takes that one.  The positions before h that hold F(h) and lie in the window of j, 64 at a time.
+template <typename U>
+__device__ __forceinline__ int first_pred(const U *P, const U *F, const U s, const int j, const int h)
+{
+    const int lane = threadIdx.x % kWave;
+    const U v = F[h], Pj = P[j - 1];
+    int first = h;
+    for (int top = h - 1; top >= 0; top -= kWave) {
+        const int i = top - lane, at = i > 0 ? i : 0;
+        const U si = P[at] + s, fi = F[at];
+        const uint64_t in = __builtin_amdgcn_ballot_w64(i >= 0 && si >= Pj);
+        const uint64_t equal = __builtin_amdgcn_ballot_w64(fi == v) & in;
+        if (equal != 0) first = top - (63 - __clzll((unsigned long long)equal));
+        if (in != ~0ull) break;
+    }
+    return first;
 }
 
 template <typename U>
@@ -543,14 +600,17 @@ __device__ __forceinline__ void solve_short(const uint64_t (&sum)[kSearchPer], c
     }
     __syncthreads();
     uint64_t *const F = full + n + 1;
-    uint8_t *const head = (uint8_t *)(F + n + kWave);
+    uint8_t *const head = (uint8_t *)(F + n + 1 + kWave);
     static_assert(kSearchMaxLayers <= 256, "a head's position is a byte");
-    (void)wave_cost<uint64_t, true>(full, n, (uint64_t)bs, F, head);
+    bool ties = false;
+    (void)wave_cost<uint64_t, true>(full, n, (uint64_t)bs, F, head, NeverStop(), &ties);
     __syncthreads();
     bits = 0;
-    for (int j = n;; j = head[j]) {  // (downwards: on sums that ascend a head lies below its cell)
+    for (int j = n;;) {  // (downwards: on sums that ascend a head lies below its cell)
         if ((j & (kWave - 1)) == lane) bits |= 1u << (j / kWave);
         if (j == 0) break;
+        const int h = __builtin_amdgcn_readfirstlane(head[j]);
+        j = ties ? first_pred(full, F, (uint64_t)bs, j, h) : h;
     }
     cost = (int64_t)((uint64_t)bc << shift);
     budget = (int64_t)((uint64_t)bs << shift);
@@ -859,12 +919,13 @@ namespace {
 //              values seen keeps most repeated ones out); if they are many, a workgroup cuts the intervals further
 //   finish     a wave per listed budget, and one for the best point so far; each keeps the set of its best
 //   result     the best of the waves, its set spread to bytes
-// After two rounds of 1,024 points one to twenty budgets are left where sizes are of one order, so `finish` takes one
-// pass; it takes whatever is left.  A call is bound by three passes in a row, one after another, each as long as
-// its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves stops: a
+// After a round of 1,024 points a few hundred budgets are left of up to 2,000 layers of one order, and after two one to
+// twenty, so `finish` takes one pass; it takes whatever is left.  A call is bound by two or three passes in a row, each
+// as long as its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves stops: a
 // small s would have a head at every cell.
-// Measured, with every budget evaluated in brackets: one chain of 4,096 aligned layers 312 us (1,650), of 1,001 of a
-// network 467 (1,200 to 1,490); two of 3,115 aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484
+// Measured, with every budget evaluated in brackets: one chain of 4,096 aligned layers 290 us (1,650), of 1,001 of a
+// network 97 (1,200 to 1,490; 480 while the first of equal predecessors was taken and there were always two rounds), of
+// 152 of a network 48 (121 to 137; 90 then); two of 3,115 aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484
 // (118,000); 1,000 of 300 600 (3,710), unrounded 685 (34,000).
 constexpr int kOpenMax = 128;       // open intervals kept (more are joined)
 constexpr int kMostPoints = 1024;   // of a round, per chain
@@ -878,6 +939,7 @@ struct LongMeta {
     uint64_t unit;       // the sizes were divided by this
     uint64_t ub;         // the best cost known (a bound, then costs); lowered while a round runs
     uint64_t ends;       // d_0 + d_n
+    uint64_t all;        // the sizes between them
     uint64_t best_cost;  // of the evaluated points (~0: none)
     uint64_t best_s;
     int32_t open[2];     // intervals before round 0 / 1 ...
@@ -1084,6 +1146,7 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
     ub = ub < total ? ub : total;
     m.ub = ub;
     m.ends = ends;
+    m.all = all;
     m.best_cost = total <= ub ? total : ~0ull;  // s = 0: every layer a checkpoint
     m.best_s = 0;
     const uint64_t span = all < ub - ends ? all : ub - ends;
@@ -1116,7 +1179,8 @@ __device__ inline void point_of(const Open *open, int count, int points, int g, 
 // A chain's point, evaluated: F_s(n), or less if it stopped (`exact` false then); RECORD, `head`, F: as in wave_cost.
 template <typename U, bool RECORD>
 __device__ __forceinline__ uint64_t long_cost(const LongWs &w, const LongMeta *meta, const int64_t c, const int n,
-                                              const int64_t prev, const int64_t s, bool &exact, uint16_t *head, U *F)
+                                              const int64_t prev, const int64_t s, bool &exact, uint16_t *head, U *F,
+                                              bool *ties = nullptr)
 {
     const U *P = (const U *)((const uint64_t *)w.P + c * (n + 1));
     exact = true;
@@ -1130,7 +1194,7 @@ __device__ __forceinline__ uint64_t long_cost(const LongWs &w, const LongMeta *m
         if (out) exact = false;
         return out;
     };
-    const U v = wave_cost<U, RECORD>(P, n, (U)s, F, head, stop);
+    const U v = wave_cost<U, RECORD>(P, n, (U)s, F, head, stop, ties);
     exact = exact && v != std::numeric_limits<U>::max();
     return (uint64_t)v;
 }
@@ -1158,7 +1222,7 @@ __global__ __launch_bounds__(kWave) void search_round_kernel(int n, int points, 
 // The end of a round, one wave per chain: the best of the points, and the intervals that stay open under the best
 // cost.  (A launch of its own: as the work of the round's last wave it took a device-wide fence in every wave, 36 ns
 // of the whole chip each, 2.2 of 2.3 ms for 1,000 chains of 300 layers.)
-__global__ __launch_bounds__(kWave) void search_close_kernel(int points, int round, LongWs w)
+__global__ __launch_bounds__(kWave) void search_close_kernel(int n, int points, int most, int round, LongWs w)
 {
     const int64_t c = blockIdx.x;
     LongMeta *meta = w.meta + c;
@@ -1208,7 +1272,14 @@ __global__ __launch_bounds__(kWave) void search_close_kernel(int points, int rou
         if (lane >= k) incl += o;
     }
     const int count = __builtin_amdgcn_readlane(incl, kWave - 1);
-    Open *out = w.open + (c * 3 + round + 1) * kOpenMax;
+    float whole = (float)width;
+#pragma unroll
+    for (int k = kWave / 2; k >= 1; k >>= 1) whole += __shfl_xor(whole, k, kWave);
+    // About n budgets lie in a width of one mean layer (counted on chains of 152 to 4,096 layers of every kind: within
+    // 30 %, repeated values among them).  If as many as the finish has waves for are left, the second round is left out:
+    // 1,024 points leave 70 to 350 of a chain of 1,001 layers.
+    const bool few = round == 0 && count < kOpenMax && whole * (float)n * (float)n <= (float)most * (float)meta->all;
+    Open *out = w.open + (c * 3 + (few ? 2 : round + 1)) * kOpenMax;
     int slot = incl - many;
     int64_t tail_lo = INT64_MAX, tail_hi = -1;
     uint64_t tail_c = ~0ull;
@@ -1238,13 +1309,7 @@ __global__ __launch_bounds__(kWave) void search_close_kernel(int points, int rou
     }
     __syncthreads();
     // points for the next round: one each, the others by width
-    if (round == 0 && kept > 0) {
-        const float whole = [&] {
-            float v = (float)width;
-#pragma unroll
-            for (int k = kWave / 2; k >= 1; k >>= 1) v += __shfl_xor(v, k, kWave);
-            return v;
-        }();
+    if (round == 0 && !few && kept > 0) {
         int given = 0;
         const int spare = points > kept ? points - kept : 0;
         for (int k0 = 0; k0 < kept; k0 += kWave) {
@@ -1268,7 +1333,8 @@ __global__ __launch_bounds__(kWave) void search_close_kernel(int points, int rou
         meta->best_cost = bc;
         meta->best_s = bs;
         meta->ub = ub;
-        if (round == 0) meta->open[1] = kept; else meta->left = kept;
+        if (round == 0) meta->open[1] = few ? 0 : kept;
+        if (round == 1 || few) meta->left = kept;
     }
 }
 
@@ -1593,11 +1659,12 @@ __global__ __launch_bounds__(kWave) void search_finish_kernel(int n, LongWs w)
             const uint32_t *P32 = (const uint32_t *)P64;
             s = meta->narrow ? (uint64_t)(P32[x] - P32[a]) : P64[x] - P64[a];
         }
-        bool exact;
+        bool exact, ties = false;
         const int64_t at_s = (int64_t)s;
         const uint64_t v =
-            meta->narrow ? long_cost<uint32_t, true>(w, meta, c, n, at_s - 1, at_s, exact, head, (uint32_t *)search_lds)
-                         : long_cost<uint64_t, true>(w, meta, c, n, at_s - 1, at_s, exact, head, (uint64_t *)search_lds);
+            meta->narrow
+                ? long_cost<uint32_t, true>(w, meta, c, n, at_s - 1, at_s, exact, head, (uint32_t *)search_lds, &ties)
+                : long_cost<uint64_t, true>(w, meta, c, n, at_s - 1, at_s, exact, head, (uint64_t *)search_lds, &ties);
         if (!exact || v + s > cost || (v + s == cost && s > at)) continue;
         uint64_t known = 0;
         if (lane == 0) known = atomicMin((unsigned long long *)&meta->ub, (unsigned long long)(v + s));
@@ -1613,7 +1680,14 @@ __global__ __launch_bounds__(kWave) void search_finish_kernel(int n, LongWs w)
             uint64_t bits = 0;
             while (cur >= b) {
                 bits |= 1ull << (cur - b);
+                const int j = cur;
                 cur = cur == 0 ? -1 : __builtin_amdgcn_readlane(pred, cur - b);
+                if (ties && cur > 0) {
+                    const uint64_t *P64 = (const uint64_t *)w.P + c * (n + 1);
+                    cur = meta->narrow
+                              ? first_pred((const uint32_t *)P64, (const uint32_t *)search_lds, (uint32_t)s, j, cur)
+                              : first_pred(P64, (const uint64_t *)search_lds, s, j, cur);
+                }
             }
             if (lane == 0) set[word] = bits;
         }
@@ -1712,7 +1786,7 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
                        st.pos, points, waves, w);
     for (int round = 0; round < 2; ++round) {
         hipLaunchKernelGGL(search_round_kernel, dim3((unsigned)points, B), dim3(kWave), f_lds, stream, n, points, round, w);
-        hipLaunchKernelGGL(search_close_kernel, dim3(B), dim3(kWave), 0, stream, points, round, w);
+        hipLaunchKernelGGL(search_close_kernel, dim3(B), dim3(kWave), 0, stream, n, points, most, round, w);
     }
     const dim3 cutters((unsigned)list_threads(batch, n));
     if (n <= kListMost) {

@@ -107,7 +107,7 @@ int main()
     }
     emu::rendezvous_limit = ~0ull;
     const int64_t top = INT64_MAX;
-    for (const int n : {1, 2, 8, 9, 64, 65, 130}) {
+    for (const int n : {1, 2, 8, 9, 63, 64, 65, 127, 130}) {
         std::vector<Sizes> chains = {uniform(n, 1, 1000000), uniform(n, 1, 3), uniform(n, 1, top / (2 * n + 4)), with(uniform(n, 1, 9), n / 2, 0)};
         for (const int k : {0, n}) {
             chains.push_back(with(uniform(n, 100, 100), k, 1ll << 40));
@@ -115,6 +115,16 @@ int main()
         }
         check("kinds of sizes", chains, kLanePerPoint);
         if (n > 128) check("kinds of sizes", chains, kWavePerPoint);
+    }
+    // repeated layers: a predecessor is one of many equal ones, next to each other and far apart
+    for (const int n : {130, 257, 300}) {
+        Sizes blocks = uniform(n, 5, 5), late = blocks;
+        for (int k = 0; k <= n; ++k) {
+            blocks[(size_t)k] = k % 3 == 2 ? 16 : 4;
+            late[(size_t)k] = k % 97 == 40 ? 1 : 1000;
+        }
+        check("repeated layers", {uniform(n, 5, 5), blocks, late, with(blocks, n / 2, 900)}, kWavePerPoint);
+        if (n <= 256) check("repeated layers", {uniform(n, 5, 5), blocks, late, with(blocks, n / 2, 900)}, kLanePerPoint);
     }
     check("large sizes in front", {with(uniform(257, 1, 1000000), 0, 1ll << 43), with(uniform(257, 1, 1000000), 0, top)}, kWavePerPoint);
     // sizes of very different orders: more budgets are left after the rounds than are listed

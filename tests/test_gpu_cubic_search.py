@@ -252,3 +252,15 @@ def test_both_forms_of_the_search(n):
 @pytest.mark.parametrize("batch", [512, 513])
 def test_both_forms_around_the_largest_batch(batch):
     check(inputs.uniform_aligned_chains(5, 150, batch, 1, 4))
+
+
+@pytest.mark.parametrize("n", [130, 256, 257, 320, 1001])
+def test_repeated_layers(n):
+    """Equal values among which the passes take the last predecessor and the canonical set the first: next to each other,
+    a slice apart, and farther back than the slices in registers."""
+    k = np.arange(n + 1)
+    chains = [np.full(n + 1, 5), np.where(k % 3 == 2, 16, 4), np.where(k % 97 == 40, 1, 1000), np.where(k % 150 == 20, 7, 100 + k % 5),
+              1 + k % 2]
+    print(f"repeated layers: n = {n}", flush=True)
+    check(np.stack(chains, axis=1).astype(np.int64))
+    check((np.stack(chains[1:3], axis=1).astype(np.int64)) * ((1 << 40) + 1))     # the same in 64 bits
