@@ -55,12 +55,10 @@
 //        the workspace.  Correct for any input, and the only writer of error
 //        statuses.
 #include "ckpt_internal.h"
+#include "linear_wave.h"
 
 #include <atomic>
 #include <type_traits>
-
-// v_writelane_b32 (the compiler has an intrinsic for it, but no builtin)
-extern "C" __device__ int ckpt_write_lane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 namespace ckpt {
 namespace {
@@ -78,6 +76,7 @@ __device__ inline bool value_overflows(uint64_t T, int64_t di, int64_t dmax)
 }
 
 constexpr int kLdsStackMaxN = 2047;
+constexpr int kWaveMaxLayers = 16383;  // of the wave kernel: 34 KB of LDS
 
 struct LinearWs {
     int32_t *count;   // [2] chains deferred by the ring kernel, chains deferred again by the wide kernel
@@ -851,79 +850,6 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
 // wave kernel: one wave per chain
 // ---------------------------------------------------------------------------
 
-__device__ inline uint32_t get_lane(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
-__device__ inline uint64_t get_lane(uint64_t v, int lane)
-{
-    return ((uint64_t)get_lane((uint32_t)(v >> 32), lane) << 32) | get_lane((uint32_t)v, lane);
-}
-__device__ inline uint32_t put_lane(uint32_t v, uint32_t x, int lane)
-{
-    return (uint32_t)ckpt_write_lane((int)x, lane, (int)v);
-}
-__device__ inline uint64_t put_lane(uint64_t v, uint64_t x, int lane)
-{
-    return ((uint64_t)put_lane((uint32_t)(v >> 32), (uint32_t)(x >> 32), lane) << 32) |
-           put_lane((uint32_t)v, (uint32_t)x, lane);
-}
-
-// The recurrence of one chain with the live entries of Q in the lanes of a wave: slot p of the stack in
-// lane p % 64, with M(j), A(j), T(j), R(i, j) and j.  Every live entry raises its own R with d_i, so nothing is
-// folded when the crossover moves, and the two loops of the algorithm are a compare each: the entries that
-// satisfy U(i,j) >= M(j) are the ones from pt on towards the head, those that M(i) dominates the ones from the
-// head down, and a bit count of the lanes says how far either pointer moves.  Sizes come from `load` (scaled);
-// the chosen step of every position goes to nxt.  Returns false if more than 64 entries are live.
-template <typename U, class Load>
-__device__ __forceinline__ bool wave_steps(const Load load, const int n, uint16_t *nxt, U &result)
-{
-    const int lane = threadIdx.x % kWave;
-    U dprev = get_lane(load(n), 0);
-    U M = dprev, A = dprev, Tj = 0, R = 0, T = 0, Mi = dprev;  // (Q = {n} in lane 0)
-    uint32_t J = (uint32_t)n;
-    uint64_t live = 1;
-    int pt = 0, hd = 0;
-    int most = 0;  // live entries, less one: looked at once per 64 steps (an overfull stack only spoils values)
-    U rows = load(n - 1 - lane);
-    for (int ihi = n - 1; ihi >= 0; ihi -= kWave) {
-        const U ahead = load(ihi - kWave - lane);  // (positions below 0 repeat position 0 and are not used)
-        const int many = ihi + 1 < kWave ? ihi + 1 : kWave;
-        uint32_t steps = 0;
-        for (int k = 0; k < many; ++k) {
-            const U di = get_lane(rows, k);
-            T += dprev;
-            dprev = di;
-            R = R > di ? R : di;
-            const U X = R + T;
-            const uint64_t sat = __builtin_amdgcn_ballot_w64(X >= A) & live;  // the entry at pt always is
-            pt += (int)__popcll((unsigned long long)sat) - 1;
-            const int at = pt & (kWave - 1), cand = (pt + 1) & (kWave - 1);
-            live = (live & ~sat) | (1ull << at);
-            const U u = X - Tj, v = u > M ? u : M;                            // max(M(j), U(i, j))
-            const U vp = get_lane(v, at), vc = get_lane(v, cand);
-            const bool take = pt != hd && vc <= vp;                           // ties go to the lower index
-            Mi = di + (take ? vc : vp);
-            steps = put_lane(steps, get_lane(J, take ? cand : at), k);
-            const uint64_t drop = __builtin_amdgcn_ballot_w64(M >= Mi) & live;
-            hd += 1 - (int)__popcll((unsigned long long)drop);
-            most = hd - pt > most ? hd - pt : most;
-            const int top = hd & (kWave - 1);
-            live = (live & ~drop) | (1ull << top);
-            M = put_lane(M, Mi, top);
-            A = put_lane(A, Mi + T, top);
-            Tj = put_lane(Tj, T, top);
-            R = put_lane(R, (U)0, top);
-            J = put_lane(J, (uint32_t)(ihi - k), top);
-        }
-        if (most >= kWave) return false;
-        if (lane < many) nxt[ihi - lane] = (uint16_t)steps;
-        rows = ahead;
-    }
-    result = Mi;
-    return true;
-}
-
-// Bytes of LDS for the steps of a chain.
-__host__ __device__ inline size_t wave_lds_bytes(int n) { return ((size_t)n + 1) * 2; }
-
 // One chain, its results included; false (with nothing written) if it is left to the list kernel.
 __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const int n, const int64_t pstride,
                                            uint8_t *__restrict__ mp, int64_t *__restrict__ peak_out,
@@ -931,44 +857,52 @@ __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const
 {
     const int lane = threadIdx.x % kWave;
     // the chain once over: validity, the trailing zeros its sizes share, their sum and largest
-    uint64_t bits = 0, sum = 0, high = 0, mx = 0;
+    int64_t bits = 0, sum = 0, mx = 0;
     bool bad = false;
-    for (int k0 = 0; k0 <= n; k0 += 4 * kWave) {
-        int64_t x[4];
+    const auto pass = [&](auto in_flight) {
+        constexpr int kRows = decltype(in_flight)::value;
+        for (int k0 = 0; k0 <= n; k0 += kRows * kWave) {
+            int64_t x[kRows];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = dp[(int64_t)min(k0 + u * kWave + lane, n) * pstride];
+            for (int u = 0; u < kRows; ++u) x[u] = dp[(int64_t)min(k0 + u * kWave + lane, n) * pstride];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool in = k0 + u * kWave + lane <= n;
-            bad |= x[u] <= 0;
-            bits |= (uint64_t)x[u];
-            sum += in ? (uint64_t)x[u] : 0;
-            high += in ? (uint64_t)x[u] >> 32 : 0;
-            mx = (uint64_t)x[u] > mx ? (uint64_t)x[u] : mx;
+            for (int u = 0; u < kRows; ++u) {
+                bad |= x[u] <= 0;
+                bits |= x[u];
+                sum = (int64_t)((uint64_t)sum + (k0 + u * kWave + lane <= n ? (uint64_t)x[u] : 0));
+                mx = larger(mx, x[u]);
+            }
         }
+    };
+    if (n < 4 * kWave) pass(std::integral_constant<int, 4>());
+    else pass(std::integral_constant<int, 16>());
+    bits = lane_value(bits_up_to(bits), kWave - 1);
+    sum = lane_value(sum_up_to(sum), kWave - 1);
+    mx = lane_value(max_up_to(mx), kWave - 1);
+    int32_t status = __any(bad) ? CKPT_ERR_SIZE : CKPT_OK;
+    static_assert(kWaveMaxLayers + 2 <= 1 << 15, "sizes below 2^48 do not overflow");
+    if (status == CKPT_OK && (bits >> 48) != 0) {
+        int64_t high = 0;
+        for (int k = lane; k <= n; k += kWave) high += dp[(int64_t)k * pstride] >> 32;
+        high = lane_value(sum_up_to(high), kWave - 1);
+        if (chain_overflows((uint64_t)sum, (uint64_t)high, (uint64_t)mx)) status = CKPT_ERR_OVERFLOW;
     }
-#pragma unroll
-    for (int m = kWave / 2; m >= 1; m >>= 1) {
-        bits |= (uint64_t)__shfl_xor((long long)bits, m, kWave);
-        sum += (uint64_t)__shfl_xor((long long)sum, m, kWave);
-        high += (uint64_t)__shfl_xor((long long)high, m, kWave);
-    }
-    mx = ~wave_min_u64(~mx);
-    const int32_t status = __any(bad) ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
-    uint16_t *const nxt = (uint16_t *)lds;
+    uint16_t *const nxt = (uint16_t *)(lds + kQueueBytes);
     int64_t peak = -1;
     if (status == CKPT_OK) {
         const int sh = uniform_bits(__ffsll((unsigned long long)bits) - 1);
         const auto at = [&](int k) -> uint64_t { return (uint64_t)dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
         bool done;
-        if (((sum + mx) >> sh) < (1ull << 30)) {
-            uint32_t m0;
-            done = wave_steps<uint32_t>([&](int k) { return (uint32_t)at(k); }, n, nxt, m0);
-            peak = (int64_t)((uint64_t)m0 << sh);
+        const uint64_t most = (uint64_t)(sum + mx) >> sh;
+        if (most < (uint64_t)kBeyond<int32_t>) {
+            int32_t m0;
+            done = wave_steps<int32_t>([&](int k) { return (int32_t)at(k); }, n, lds, nxt, m0);
+            peak = (int64_t)m0 << sh;
         } else {
-            uint64_t m0;
-            done = wave_steps<uint64_t>(at, n, nxt, m0);
-            peak = (int64_t)(m0 << sh);
+            int64_t m0;
+            done = most < (uint64_t)kBeyond<int64_t> &&
+                   wave_steps<int64_t>([&](int k) { return (int64_t)at(k); }, n, lds, nxt, m0);
+            peak = done ? m0 << sh : -1;
         }
         if (!done) return false;
     }
@@ -977,14 +911,16 @@ __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const
     __syncthreads();
     const int none = n + 2 * kWave;
     int cur = status == CKPT_OK ? 0 : none;
+    int steps = nxt[min(lane, n - 1)];
     for (int b = 0; b <= n; b += kWave) {
-        const int steps = status == CKPT_OK ? nxt[min(b + lane, n - 1)] : 0;
+        const int ahead = nxt[min(b + kWave + lane, n - 1)];
         uint64_t set = 0;
         while (cur < b + kWave) {
             set |= 1ull << (cur - b);
             cur = cur == n ? none : __builtin_amdgcn_readlane(steps, cur - b);
         }
         if (b + lane <= n) mp[(int64_t)(b + lane) * pstride] = (uint8_t)((set >> lane) & 1ull);
+        steps = ahead;
     }
     if (lane == 0) {
         *peak_out = peak;
@@ -1012,7 +948,7 @@ __global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t
     const unsigned waves = (unsigned)((g.count + kWave - 1) / kWave);
     const unsigned block = wave - (unsigned)(PER_CHAIN ? g.linear_first : g.wave_first);
     if (PER_CHAIN && ragged_wave_per_chain(g.n, g.count)) {
-        static_assert(sizeof(ring) >= 2 * (4095 + 1), "the wave's LDS for the longest of these chains");
+        static_assert(sizeof(ring) >= kQueueBytes + 2 * (4095 + 1), "the wave's LDS for the longest of these chains");
         const int64_t at = g.stage_off + block, c = g.first + (int64_t)block;
         const bool done = wave_chain(d_stage + at, g.n, g.pitch, mask_stage + at, peak_stage + c, status_stage + c,
                                      (unsigned char *)ring);
@@ -1025,10 +961,9 @@ __global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t
                                 peak_stage + g.first, status_stage + g.first, w, block, waves, g.first, ring);
 }
 
-// Few chains: a wave each.  A lane-per-chain wave alone on its SIMD takes 330 ns a position (660 ns beyond 256
-// layers); here the step is a chain of about 35 instructions, half of them scalar, and takes 150 ns (32 bits):
-// one chain of 152 layers 57 us -> 27 us, 997 chains of 1,001 layers 672 us -> 158 us.  What bounds it is that chain:
-// a position needs the one before it.
+// Few chains: a wave each.  A lane-per-chain wave alone on its SIMD takes 640 ns a position, this 40 (32 bits): one chain
+// of 152 layers 11 us (23 with a ballot per pointer move of Algorithm 6 and 150 ns a position), 997 of 1,001 layers 59 us
+// (157).
 // OWN_LIST: a chain of more than 64 live entries is done by list_chain in the same LDS at once; else it is
 // marked in w.list and left to linear_list_kernel.
 template <bool OWN_LIST>
@@ -1050,17 +985,17 @@ __global__ __launch_bounds__(kWave) void linear_wave_kernel(const int64_t *__res
     }
 }
 
-// A wave per chain up to this many chains: beyond, the lanes of the ring kernel do more per instruction.  4,096 chains
-// of aligned sizes: 30 us against 46 us at 64 layers, 110 against 158 us at 256, 403 against 660 us at 1,001;
-// the times grow with the number of chains here and stay there (unaligned sizes: 37 against 152 us at 64 layers).
-__host__ inline int64_t wave_max_batch(int n) { return n <= kLogMaxLayers ? 4096 : 6144; }
-constexpr int kWaveMaxLayers = 16383;    // 32 KB of LDS
+// A wave per chain up to this many chains: beyond, the lanes of the ring kernel do more per instruction.  16,384 chains of
+// aligned sizes: 35 us against 48 us at 64 layers, 81 against 100 at 152, 126 against 160 at 256, 618 against 667 at
+// 1,001, where 20,000 take 773; unaligned ones 76 against 125 us at 64 layers, 1,162 against 1,650 at 1,001.
+constexpr int64_t kWaveMaxBatch = 16384;
 constexpr int kOwnListMaxLayers = 511;   // 15 KB of LDS for the stacks, kept free for a case that hardly happens ...
+__host__ inline size_t own_list_lds_bytes(int n) { return std::max(lds_stack_bytes(n), wave_lds_bytes(n)); }
 // ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes): in two turns 4,096
 // chains of 511 layers took 286 us, and take 201 with the list in a launch of its own; 2,600 198 and 158.
 inline bool own_list(int64_t batch, int n)
 {
-    const int64_t per_cu = (160 << 10) / (int64_t)align_up(lds_stack_bytes(n), 1280);
+    const int64_t per_cu = (160 << 10) / (int64_t)align_up(own_list_lds_bytes(n), 1280);
     return n <= kOwnListMaxLayers && batch <= 256 * per_cu;
 }
 
@@ -1135,9 +1070,9 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     if (batch == 0) return hipSuccess;
     LinearWs w = carve_linear(ws, batch, n);
     const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
-    if (batch <= wave_max_batch(n) && n <= kWaveMaxLayers) {
+    if (batch <= kWaveMaxBatch && n <= kWaveMaxLayers) {
         if (own_list(batch, n)) {
-            hipLaunchKernelGGL(linear_wave_kernel<true>, dim3((unsigned)batch), dim3(kWave), lds_stack_bytes(n), stream, d,
+            hipLaunchKernelGGL(linear_wave_kernel<true>, dim3((unsigned)batch), dim3(kWave), own_list_lds_bytes(n), stream, d,
                                n, st.chain, st.pos, mask_out, peak_out, status_out, w);
             return hipGetLastError();
         }

@@ -51,6 +51,22 @@ def test_lengths_and_kinds_of_sizes(n):
         check(live_entries(n))
 
 
+@pytest.mark.parametrize("n", [7, 8, 9, 31, 32, 33, 56, 57, 72, 73, 96, 97, 160, 161])
+def test_ends_of_blocks_and_limits_of_the_values(n):
+    rng = np.random.default_rng(n)
+    check(inputs.uniform_aligned_chains(n, n, 3, 256, 32768))
+    check(inputs.log_uniform_chains(n, n, 3))
+    for most in (1 << 30, 1 << 62, (1 << 63) - 1):  # of sum(d) + max(d): 32 bits, 64 bits, what only the list takes
+        for at in (0, n // 2, n):
+            d = np.stack([rng.integers(1, max(2, most // (4 * n)), size=n + 1) for _ in range(3)], axis=1).astype(np.int64)
+            d[(at + 1) % (n + 1)] |= 1
+            for c in range(3):  # the size at `at` takes sum(d) + max(d) about to `most`, and not beyond INT64_MAX
+                rest = int(d[:, c].sum()) - int(d[at, c])
+                d[at, c] = (most - 1 + c - rest) // 2 if most < (1 << 63) - 1 else (most - c - rest) // 2
+                assert rest + 2 * int(d[at, c]) <= (1 << 63) - 1
+            check(d)
+
+
 @pytest.mark.parametrize("n", [2047, 2048, 3000])
 def test_long_chains(n):
     check(inputs.uniform_aligned_chains(n, n, 2, 256, 32768))
@@ -65,7 +81,7 @@ def test_a_list_of_their_own_where_all_waves_fit_the_chip(batch):
     check(d)
 
 
-@pytest.mark.parametrize("batch", [4096, 4097])
+@pytest.mark.parametrize("batch", [4096, 4097, 16384, 16385])
 def test_batches_on_both_sides_of_the_rule(batch):
     d = inputs.uniform_aligned_chains(3, 40, batch, 256, 32768)
     d[:, ::9] += 1
