@@ -202,7 +202,7 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
 // themselves.  A launch per class of lengths (its LDS is that of the longest chain in it); longest[k]: the
 // longest chain of class k, 0 if it has none.  count: one value, list: `batch` values of scratch.
 constexpr int kSearchClasses = 4;
-inline int search_class_limit(int k) { return 32 << k; }
+__host__ __device__ inline int search_class_limit(int k) { return 32 << k; }
 static_assert((32 << (kSearchClasses - 1)) == kSearchMaxLayers, "the last class ends where the search does");
 hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch, const int *longest,
                                       uint8_t *mask_out, int64_t *peak_out, int64_t *budget_out, int32_t *status_out,

@@ -675,7 +675,7 @@ template <bool NARROW, bool WIDE>
 __device__ __forceinline__ bool search_one(const int64_t *__restrict__ dp, const int64_t pstride, const int n,
                                            uint8_t *__restrict__ mp, const int64_t mstride,
                                            int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
-                                           int32_t *__restrict__ status_out)
+                                           int32_t *__restrict__ status_out, const unsigned lds)
 {
     const int lane = threadIdx.x;
     uint64_t sum[kSearchPer];  // the sizes, then P[q * 64 + lane]
@@ -732,7 +732,7 @@ __device__ __forceinline__ bool search_one(const int64_t *__restrict__ dp, const
         const uint64_t heavy = largest > all / 4 && largest <= span ? largest : 0;
         const bool narrow = bound < (1ull << 31) - 1 && span + largest < (1ull << 31) &&
                             (kLookahead - 1) * largest < (1ull << 31);
-        if (narrow ? !NARROW : !WIDE) return false;
+        if (narrow ? !NARROW : !WIDE || search_lds_bytes(n, 8) > lds) return false;
         if (NARROW && narrow)
             solve_short<uint32_t>(sum, n, shift, total, bound, span, (float)all, heavy, cost, budget, on);
         else if (WIDE)
@@ -775,7 +775,7 @@ __global__ __launch_bounds__(kWave) void cubic_search_kernel(const int64_t *__re
     const int64_t c = xcd_blocked(blockIdx.x, gridDim.x);
     const bool done = search_one<true, WIDE>(d + c * cstride, pstride, n, mask_out + c * cstride, pstride,
                                              peak_out + c, budget_out ? budget_out + c : nullptr,
-                                             status_out ? status_out + c : nullptr);
+                                             status_out ? status_out + c : nullptr, ~0u);
     if (!WIDE && !done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
 }
 
@@ -791,27 +791,30 @@ __global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t 
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
         const int64_t c = w.list[item];
         (void)search_one<false, true>(d + c * cstride, pstride, n, mask_out + c * cstride, pstride, peak_out + c,
-                                      budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr);
+                                      budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr, ~0u);
         __syncthreads();
     }
 }
 
-// The chains of a ragged batch from number `first` on that have n_lo .. n_hi layers, each where it lies in the flat
-// array.
-template <bool WIDE>
+// `chains` chains of a ragged batch from number `first` on, each where it lies in the flat array, class after class, a grid
+// of `chains` workgroups for each (`classes`: four bits a class, the first in the lowest).  lds: the launch's; chains that
+// need 64 bits and more of it go on the list.
 __global__ __launch_bounds__(kWave) void cubic_search_ragged_kernel(const int64_t *__restrict__ d,
                                                                     const int64_t *__restrict__ off, int64_t first,
-                                                                    int n_lo, int n_hi, uint8_t *__restrict__ mask_out,
+                                                                    unsigned chains, unsigned classes, unsigned lds,
+                                                                    uint8_t *__restrict__ mask_out,
                                                                     int64_t *__restrict__ peak_out,
                                                                     int64_t *__restrict__ budget_out,
                                                                     int32_t *__restrict__ status_out, SearchWs w)
 {
-    const int64_t c = first + blockIdx.x, o = off[c], n = off[c + 1] - o - 1;
-    if (n < n_lo || n > n_hi) return;
-    const bool done = search_one<true, WIDE>(d + o, 1, (int)n, mask_out + o, 1, peak_out + c,
+    const unsigned down = blockIdx.x / chains;
+    const int k = (int)(classes >> (4 * down)) & 15;
+    const int64_t c = first + (blockIdx.x - down * chains), o = off[c], n = off[c + 1] - o - 1;
+    if (n > search_class_limit(k) || (k > 0 && n <= search_class_limit(k - 1))) return;
+    const bool done = search_one<true, true>(d + o, 1, (int)n, mask_out + o, 1, peak_out + c,
                                              budget_out ? budget_out + c : nullptr,
-                                             status_out ? status_out + c : nullptr);
-    if (!WIDE && !done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
+                                             status_out ? status_out + c : nullptr, lds);
+    if (!done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
 }
 
 __global__ __launch_bounds__(kWave) void cubic_search_ragged_wide_kernel(const int64_t *__restrict__ d,
@@ -825,7 +828,7 @@ __global__ __launch_bounds__(kWave) void cubic_search_ragged_wide_kernel(const i
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
         const int64_t c = w.list[item], o = off[c], n = off[c + 1] - o - 1;
         (void)search_one<false, true>(d + o, 1, (int)n, mask_out + o, 1, peak_out + c,
-                                      budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr);
+                                      budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr, ~0u);
         __syncthreads();
     }
 }
@@ -837,8 +840,8 @@ hipError_t raise_search_lds_limit()
 {
     return raise_lds_limit(search_lds_raised,
                            {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
-                            (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel<true>,
-                            (const void *)cubic_search_ragged_kernel<false>, (const void *)cubic_search_ragged_wide_kernel},
+                            (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel,
+                            (const void *)cubic_search_ragged_wide_kernel},
                            search_lds_bytes(kSearchMaxLayers, 8));
 }
 
@@ -848,6 +851,16 @@ constexpr int64_t kSearchSplitFrom = 1024;
 constexpr int kSearchWideBlocks = 1024;
 // (a launch has fewer than 2^32 threads)
 constexpr int64_t kMostWavesOfALaunch = 1 << 25;
+// Waves of this much LDS that the chip holds (LDS is handed out in units of 1,280 bytes).
+inline int64_t at_once(size_t lds) { return 256 * ((160 << 10) / (int64_t)align_up(lds, 1280)); }
+// A ragged batch goes in one launch up to this many turns of it, with the longest chain's LDS for all: the classes one
+// after the other each wait for their slowest wave.  1,000 chains of 2 to 152 layers 114 us (four launches 247), 4,096 194
+// (335), 8,192 373 (387), 16,384 668 (567); of 2 to 256 layers 4,096 427 (519), 8,192 785 (798), 16,384 1,546 (1,309).
+constexpr int64_t kOneLaunchTurns = 8;
+// ... with LDS for 64 bits up to this many turns of that: a second launch for the chains that need them costs as much as
+// a second turn, and more than 192 layers of unrounded sizes mostly need them.  512 chains of 2 to 256 unrounded layers
+// 283 us with two turns, 548 in 32 bits with a second launch; of 15, 24 and 152 layers 219 and 155.
+inline int64_t wide_turns(int longest) { return longest > 192 ? 2 : 1; }
 
 }  // namespace
 
@@ -884,18 +897,29 @@ hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_d
     if (e != hipSuccess) return e;
     const dim3 block(kWave);
     const SearchWs w{count, list};
-    const bool wide = batch < kSearchSplitFrom;
+    int top = kSearchClasses - 1;
+    while (longest[top] == 0) --top;
+    const int all = longest[top];
+    const bool one_launch = batch <= kOneLaunchTurns * at_once(search_lds_bytes(all, 4));
+    // all of the arithmetic in the first launch (the longest chains' LDS says whether the rest needs a second one)
+    const bool wide = one_launch ? batch <= wide_turns(all) * at_once(search_lds_bytes(all, 8)) : batch < kSearchSplitFrom;
+    const auto lds = [&](int n) { return (unsigned)search_lds_bytes(n, wide ? 8 : 4); };
     if (!wide) hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
-    int all = 0;
-    for (int k = kSearchClasses - 1; k >= 0; --k) {  // the longest chains first
-        const int n = longest[k], below = k > 0 ? search_class_limit(k - 1) + 1 : 1;
-        if (n == 0) continue;
-        all = all > n ? all : n;
-        for (int64_t first = 0; first < batch; first += kMostWavesOfALaunch) {
-            const dim3 grid((unsigned)std::min(batch - first, kMostWavesOfALaunch));
-            hipLaunchKernelGGL(wide ? cubic_search_ragged_kernel<true> : cubic_search_ragged_kernel<false>, grid, block,
-                               search_lds_bytes(n, wide ? 8 : 4), stream, d, offsets_dev, first, below, n, mask_out,
-                               peak_out, budget_out, status_out, w);
+    if (one_launch) {
+        unsigned classes = 0, many = 0;
+        for (int k = top; k >= 0; --k)  // the longest chains first
+            if (longest[k] != 0) classes |= (unsigned)k << (4 * many++);
+        hipLaunchKernelGGL(cubic_search_ragged_kernel, dim3((unsigned)batch * many), block, lds(all), stream, d, offsets_dev,
+                           (int64_t)0, (unsigned)batch, classes, lds(all), mask_out, peak_out, budget_out, status_out, w);
+    } else {
+        for (int k = top; k >= 0; --k) {
+            const int n = longest[k];
+            if (n == 0) continue;
+            for (int64_t first = 0; first < batch; first += kMostWavesOfALaunch) {
+                const unsigned chains = (unsigned)std::min(batch - first, kMostWavesOfALaunch);
+                hipLaunchKernelGGL(cubic_search_ragged_kernel, dim3(chains), block, lds(n), stream, d, offsets_dev, first,
+                                   chains, (unsigned)k, lds(n), mask_out, peak_out, budget_out, status_out, w);
+            }
         }
     }
     if (!wide)

@@ -257,3 +257,20 @@ def test_host_checks_and_the_empty_batch():
     assert lib.ckpt_ragged_workspace_bytes(B.CALL_SOLVE_LINEAR, None, 3) == 0
     assert lib.ckpt_ragged_workspace_bytes(9, off.ctypes.data, 2) == 0
     assert lib.ckpt_ragged_workspace_bytes(B.CALL_SOLVE_CUBIC, off.ctypes.data, 2) > 0
+
+
+@pytest.mark.parametrize("batch, longest", [(256, 256), (257, 256), (512, 256), (513, 256), (4096, 256), (4097, 256),
+                                            (256, 152), (257, 152), (6145, 152), (300, 32), (300, 33)])
+def test_cubic_classes_in_one_launch_and_in_several(batch, longest):
+    """Batches on both sides of the rules for one launch and for 64 bits in it; a class of lengths that has no chain, and
+    chains in each of the others that need 64 bits."""
+    say(f"ragged cubic: {batch} chains of up to {longest} layers")
+    rng = np.random.default_rng(batch)
+    lengths = rng.integers(1, 9, size=batch)
+    ends = [n for n in (32, 33, 64, 129, longest) if n <= longest]
+    where = rng.permutation(batch)[:4 * len(ends)]
+    lengths[where] = np.repeat(ends, 4)
+    d, _, off = inputs.ragged_batch(17, [int(n) for n in lengths])
+    for c in where[::2]:
+        d[off[c]:off[c + 1]] = rng.integers(1, (1 << 62) // (lengths[c] + 2), size=lengths[c] + 1)
+    check_cubic(d, off)
