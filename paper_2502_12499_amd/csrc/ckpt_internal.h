@@ -68,6 +68,15 @@ __device__ inline unsigned xcd_paired_block(unsigned b, unsigned grid)
     return (b / (2 * kXcds)) * (2 * kXcds) + (b % kXcds) * 2 + (b / kXcds) % 2;
 }
 
+// Workgroups go to the eight XCDs in turn, and each XCD has its own L2; a wave of one chain (four)
+// reads 8 (32) of the 128 bytes of a line of a position-major batch.  Within every 512 workgroups the 64 that one XCD receives take
+// neighbouring ones.  A bijection on [0, grid).
+__device__ inline unsigned xcd_blocked(unsigned b, unsigned grid)
+{
+    if (b >= grid / 512 * 512) return b;
+    return b / 512 * 512 + (b % 8) * 64 + (b / 8) % 64;
+}
+
 // ---- wave reductions on the data-parallel-primitive path (no LDS traffic) --------------------------
 
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
@@ -351,6 +360,12 @@ hipError_t launch_eval_timeline_ragged(const int64_t *d_stage, const uint8_t *ma
 hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, const RaggedTotals &t,
                                       int64_t batch, uint8_t *mask_stage, int64_t *peak_stage, int32_t *status_stage,
                                       void *ws, hipStream_t stream);
+// The same for few enough chains, where they lie in the flat arrays; perm: the chains in order of their lengths, n_most: the
+// longest one's; ws as above, its first two 32-bit words 0.
+bool linear_takes_flat(int64_t batch, int n);
+hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
+                                    uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws,
+                                    hipStream_t stream);
 
 // which: a ckpt_call; offsets_host: batch + 1 element offsets in host memory
 size_t ragged_workspace_bytes(int which, const int64_t *offsets_host, int64_t batch);

@@ -747,15 +747,6 @@ __device__ __forceinline__ bool search_one(const int64_t *__restrict__ dp, const
     return true;
 }
 
-// Workgroups go to the eight XCDs in turn, and each XCD has its own L2; a wave reads 8 of the 128 bytes of
-// a line of a position-major batch.  Within every 512 workgroups the 64 that one XCD receives take
-// neighbouring chains.  A bijection on [0, grid).
-__device__ inline unsigned xcd_blocked(unsigned b, unsigned grid)
-{
-    if (b >= grid / 512 * 512) return b;
-    return b / 512 * 512 + (b % 8) * 64 + (b / 8) % 64;
-}
-
 // Chains whose launch has no LDS for 64-bit arithmetic and that need it.
 struct SearchWs {
     int32_t *count;  // [1] (first 256 bytes)

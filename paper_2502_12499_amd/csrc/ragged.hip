@@ -259,10 +259,12 @@ __global__ __launch_bounds__(kPermThreads) void ragged_perm_kernel(const int64_t
     if (valid) perm[groups[g].first + place] = (int32_t)c;
 }
 
-__global__ void ragged_clear_kernel(int32_t *cursor, int n_groups)
+// (counts: two more words, or null)
+__global__ void ragged_clear_kernel(int32_t *cursor, int n_groups, int32_t *counts)
 {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g < n_groups) cursor[g] = 0;
+    if (counts && g < 2) counts[g] = 0;
 }
 
 // Flat -> position-major, every group in one launch.  A workgroup takes one tile of 64 chains x 64
@@ -408,7 +410,7 @@ int ragged_plan_on_device(const int64_t *offsets_dev, int64_t batch, int max_lay
     // the totals and the counts lie behind each other: one fill clears both
     const int64_t words = (int64_t)((w.hist - w.totals) / 4) + max_layers + 1;
     hipLaunchKernelGGL(ragged_clear_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream,
-                       (int32_t *)totals, (int)words);
+                       (int32_t *)totals, (int)words, (int32_t *)nullptr);
     hipLaunchKernelGGL(ragged_count_kernel, dim3((unsigned)((batch + kCountThreads - 1) / kCountThreads)),
                        dim3(kCountThreads), 0, stream, offsets_dev, batch, max_layers, hist, totals);
     hipLaunchKernelGGL(ragged_layout_kernel, dim3(1), dim3(kCountThreads), 0, stream, hist, max_layers,
@@ -471,10 +473,17 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
             return CKPT_ERR_DEVICE;
         if (hipStreamSynchronize(stream) != hipSuccess) return CKPT_ERR_DEVICE;
     }
+    const bool flat = which == CKPT_CALL_SOLVE_LINEAR && linear_takes_flat(batch, p.t.max_layers);
     hipLaunchKernelGGL(ragged_clear_kernel, dim3((unsigned)((n_groups + 255) / 256)), dim3(256), 0, stream, cursor,
-                       n_groups);
+                       n_groups, flat ? (int32_t *)(base + w.inner) : nullptr);
     hipLaunchKernelGGL(ragged_perm_kernel, dim3((unsigned)((batch + kPermThreads - 1) / kPermThreads)),
                        dim3(kPermThreads), 0, stream, off, batch, groups, n_groups, cursor, perm);
+    if (flat) {
+        // few chains: a row of lanes or a wave reads a chain where it lies, nothing is staged or put back
+        const hipError_t e = launch_solve_linear_flat(d, off, perm, batch, p.t.max_layers, mask_out, peak_out, status_out,
+                                                      base + w.inner, stream);
+        return e == hipSuccess ? CKPT_OK : CKPT_ERR_DEVICE;
+    }
     // every group's chains into the position-major staging
     hipLaunchKernelGGL(ragged_gather_kernel<int64_t>, dim3((unsigned)p.t.tiles), dim3(kTileThreads), 0, stream, d, off, perm,
                        groups, tile_first2, n_groups, 1, sd);

@@ -55,6 +55,7 @@
 //        the workspace.  Correct for any input, and the only writer of error
 //        statuses.
 #include "ckpt_internal.h"
+#include "linear_rows.h"
 #include "linear_wave.h"
 
 #include <atomic>
@@ -811,8 +812,9 @@ __device__ void list_chain(const int64_t *__restrict__ dp, const int n, const in
     }
 }
 
-// n_all: the chains' length, or in a ragged call (`groups`) the longest one, for which the stacks
-// are laid out; a listed number is then a chain's place among all chains, as in the wide kernel.
+// n_all: the chains' length, or in a ragged call (`groups` or `off`) the longest one, for which the stacks
+// are laid out; a listed number is then a chain's place among all chains, as in the wide kernel, or with `off` the chain
+// itself, where it lies in the flat arrays (with strides of 0 and 1).
 // flagged: 0, or the number of chains of a batch in which the wave kernel marked those left (w.list[c] != 0).
 template <bool LDS_STACKS>
 __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__restrict__ d, int n_all,
@@ -821,7 +823,7 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
                                                             int64_t *__restrict__ peak_out,
                                                             int32_t *__restrict__ status_out, LinearWs w,
                                                             const RaggedGroupDev *__restrict__ groups, int n_groups,
-                                                            int flagged)
+                                                            const int64_t *__restrict__ off, int flagged)
 {
     if (threadIdx.x != 0) return;
     const int count = flagged ? flagged : w.count[1];
@@ -841,6 +843,10 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
             pstride = g.pitch;
             dp = d + g.stage_off + (c - g.first);
             mp = mask_out + g.stage_off + (c - g.first);
+        } else if (off) {
+            n = (int)(off[c + 1] - off[c] - 1);
+            dp = d + off[c];
+            mp = mask_out + off[c];
         }
         list_chain<Pos>(dp, n, pstride, mp, peak_out + c, status_out ? status_out + c : nullptr, base, n_all);
     }
@@ -985,12 +991,139 @@ __global__ __launch_bounds__(kWave) void linear_wave_kernel(const int64_t *__res
     }
 }
 
-// A wave per chain up to this many chains: beyond, the lanes of the ring kernel do more per instruction.  16,384 chains of
-// aligned sizes: 35 us against 48 us at 64 layers, 81 against 100 at 152, 126 against 160 at 256, 618 against 667 at
-// 1,001, where 20,000 take 773; unaligned ones 76 against 125 us at 64 layers, 1,162 against 1,650 at 1,001.
+// The four chains of a wave, a row of lanes each (what is passed is a lane's own chain's); false in the rows whose chain is
+// left to wave_chain (nothing of it is written).  n_most: at least the longest one's length; lds: rows_lds_bytes(n_most).
+__device__ __forceinline__ bool rows_chains(const int64_t *__restrict__ dp, const bool is_chain, const int n,
+                                            const int n_most, const int64_t pstride, uint8_t *__restrict__ mp, int64_t *__restrict__ peak_out,
+                                            int32_t *__restrict__ status_out, unsigned char *lds)
+{
+    const int lane = threadIdx.x % kWave, l = lane % kRow;
+    // the chain once over: validity, the trailing zeros its sizes share, their sum and largest
+    constexpr int kLoads = 4;
+    int64_t bits = 0, sum = 0, mx = 0;
+    for (int k0 = 0; __builtin_amdgcn_ballot_w64(k0 <= n) != 0; k0 += kLoads * kRow) {
+        int64_t x[kLoads];
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) x[u] = dp[(int64_t)min(k0 + u * kRow + l, n) * pstride];
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            bits |= x[u] > 0 ? x[u] : INT64_MIN;
+            sum += k0 + u * kRow + l <= n ? x[u] & (((int64_t)1 << 48) - 1) : 0;
+            mx = larger(mx, x[u]);
+        }
+    }
+    bits = row_value<kRow - 1>(row_up_to(bits, (int64_t)0, [](int64_t a, int64_t b) { return a | b; }));
+    sum = row_value<kRow - 1>(row_up_to(sum, (int64_t)0, [](int64_t a, int64_t b) { return a + b; }));
+    mx = row_value<kRow - 1>(row_up_to(mx, (int64_t)0, [](int64_t a, int64_t b) { return larger(a, b); }));
+    static_assert(kWaveMaxLayers + 2 <= 1 << 15, "sums of sizes below 2^48 stay below 2^63");
+    const int sh = __ffsll((unsigned long long)bits) - 1;
+    const int64_t most = bits >> 48 == 0 ? (sum + mx) >> sh : INT64_MAX;  // (a size that is not positive sets the top bit)
+    const bool fits = most < kRowBeyond<double>;
+    const auto at = [&](int k) -> int64_t { return dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
+    uint16_t *const nxt = (uint16_t *)(lds + kRowsQueueBytes) + (size_t)(lane / kRow) * (n_most + 1);
+    int64_t peak = -1;
+    if (__builtin_amdgcn_ballot_w64(fits) != 0) {
+        if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<int32_t>) != 0)
+            peak = (int64_t)rows_steps<double>([&](int k) { return (double)at(k); }, n, lds, nxt);
+        else
+            peak = rows_steps<int32_t>([&](int k) { return (int32_t)at(k); }, n, lds, nxt);
+    }
+    const bool done = fits && peak >= 0;
+    // the set: from one checkpoint to the next, each step marked where it lies
+    static_assert(kWaveMaxLayers < 0x8000, "the mark is a step's top bit");
+    __syncthreads();
+    for (int cur = done ? 0 : n; __builtin_amdgcn_ballot_w64(cur < n) != 0;) {
+        const int step = nxt[cur];
+        if (cur < n) {
+            if (l == 0) nxt[cur] = (uint16_t)(step | 0x8000);
+            cur = step;
+        }
+    }
+    __syncthreads();
+    if (done && is_chain) {
+        for (int k = l; k <= n; k += kRow) mp[(int64_t)k * pstride] = k == n ? 1 : (uint8_t)(nxt[k] >> 15);
+        if (l == 0) {
+            *peak_out = peak << sh;
+            if (status_out) *status_out = CKPT_OK;
+        }
+    }
+    return done;
+}
+
+// Batches between: four chains a wave, what does not fit a row by the whole wave afterwards.
+template <bool OWN_LIST>
+__global__ __launch_bounds__(kWave, 4) void linear_rows_kernel(const int64_t *__restrict__ d, int64_t batch, int n,
+                                                            int64_t cstride, int64_t pstride,
+                                                            uint8_t *__restrict__ mask_out,
+                                                            int64_t *__restrict__ peak_out,
+                                                            int32_t *__restrict__ status_out, LinearWs w)
+{
+    const int lane = threadIdx.x % kWave, row = lane / kRow;
+    const int64_t c0 = (int64_t)xcd_blocked(blockIdx.x, gridDim.x) * kRowsOfWave;
+    const bool is_chain = c0 + row < batch;
+    const int64_t c = is_chain ? c0 + row : batch - 1;
+    const bool done = rows_chains(d + c * cstride, is_chain, n, n, pstride, mask_out + c * cstride, peak_out + c,
+                                  status_out ? status_out + c : nullptr, lin_lds);
+    if (!OWN_LIST && is_chain && lane % kRow == 0) w.list[c] = 0;
+    for (uint64_t left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0); left != 0; left &= left - 1) {
+        const int64_t one = c0 + __builtin_ctzll((unsigned long long)left) / kRow;
+        const int64_t *dp = d + one * cstride;
+        uint8_t *mp = mask_out + one * cstride;
+        int32_t *st = status_out ? status_out + one : nullptr;
+        __syncthreads();
+        const bool by_wave = wave_chain(dp, n, pstride, mp, peak_out + one, st, lin_lds);
+        if (by_wave || lane != 0) continue;
+        if (OWN_LIST) list_chain<uint16_t>(dp, n, pstride, mp, peak_out + one, st, (char *)lin_lds, n);
+        else w.list[one] = 1;
+    }
+}
+
+// The chains of a ragged batch where they lie in the flat arrays, four to a wave or one, in the order of `perm`, which
+// ascends in their lengths; the longest start first.  What is left goes on the second list.
+template <bool ROWS>
+__global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__restrict__ d, const int64_t *__restrict__ off,
+                                                               const int32_t *__restrict__ perm, int64_t batch, int n_most,
+                                                               uint8_t *__restrict__ mask_out,
+                                                               int64_t *__restrict__ peak_out,
+                                                               int32_t *__restrict__ status_out, LinearWs w)
+{
+    const int lane = threadIdx.x % kWave;
+    const int64_t p0 = (int64_t)(gridDim.x - 1 - blockIdx.x) * (ROWS ? kRowsOfWave : 1);
+    uint64_t left = 1;
+    if (ROWS) {
+        const bool is_chain = p0 + lane / kRow < batch;
+        const int64_t c = perm[is_chain ? p0 + lane / kRow : batch - 1], o = off[c];
+        const bool done = rows_chains(d + o, is_chain, (int)(off[c + 1] - o - 1), n_most, 1, mask_out + o, peak_out + c,
+                                      status_out ? status_out + c : nullptr, lin_lds);
+        left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0);
+    }
+    for (; left != 0; left &= left - 1) {
+        const int64_t c = perm[p0 + __builtin_ctzll((unsigned long long)left) / kRow], o = off[c];
+        __syncthreads();
+        const bool done = wave_chain(d + o, (int)(off[c + 1] - o - 1), 1, mask_out + o, peak_out + c,
+                                     status_out ? status_out + c : nullptr, lin_lds);
+        if (!done && lane == 0) w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)c;
+    }
+}
+
+// A wave per chain up to 1,024 chains, one for each SIMD of the chip; four chains to a wave up to 65,536, and the ring
+// kernel's lanes beyond.  Waves and rows, us: 1,001 layers, 1,024 chains 62 and 79, 2,048 chains 100 and 82, unrounded ones
+// 131 and 115, 204 and 121.  Rows and lanes at 65,536 chains: 64 layers 49 and 51 (unrounded, which the lanes try in 32
+// bits first, 72 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at 131,072
+// aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD four waves, or one up to 16,384 chains:
+// 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than those.
+constexpr int64_t kWaveBatch = 1024, kRowsFewBatch = 16384, kRowsBatch = 65536;
+constexpr int kRowsFewMaxLayers = 4095, kRowsMaxLayers = 1279;
+inline bool rows_fit(int64_t batch, int n)
+{
+    return batch > kWaveBatch && (batch <= kRowsFewBatch ? n <= kRowsFewMaxLayers : batch <= kRowsBatch && n <= kRowsMaxLayers);
+}
+// A wave per chain where those do not fit.
 constexpr int64_t kWaveMaxBatch = 16384;
+constexpr int kRowsOwnListMaxLayers = 320;  // LDS for the list's stacks, 16 waves a CU (at 511 layers 134 us for 16,384 chains, 104 without)
 constexpr int kOwnListMaxLayers = 511;   // 15 KB of LDS for the stacks, kept free for a case that hardly happens ...
 __host__ inline size_t own_list_lds_bytes(int n) { return std::max(lds_stack_bytes(n), wave_lds_bytes(n)); }
+__host__ inline size_t rows_all_lds_bytes(int n, bool own) { return std::max(rows_lds_bytes(n), own ? own_list_lds_bytes(n) : wave_lds_bytes(n)); }
 // ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes): in two turns 4,096
 // chains of 511 layers took 286 us, and take 201 with the list in a launch of its own; 2,600 198 and 158.
 inline bool own_list(int64_t batch, int n)
@@ -1043,15 +1176,14 @@ hipError_t launch_solve_linear_noalloc(const int64_t *d, int64_t batch, int n, S
 
 namespace {
 void launch_list(const int64_t *d, int n, Strides st, uint8_t *mask_out, int64_t *peak_out, int32_t *status_out,
-                 const LinearWs &w, unsigned grid, int flagged, hipStream_t stream)
+                 const LinearWs &w, int64_t batch, const RaggedGroupDev *groups, int n_groups, const int64_t *off,
+                 int flagged, hipStream_t stream)
 {
-    if (n <= kLdsStackMaxN)
-        hipLaunchKernelGGL(linear_list_kernel<true>, dim3(grid), dim3(kWave), lds_stack_bytes(n), stream, d, n,
-                           st.chain, st.pos, mask_out, peak_out, status_out, w, (const RaggedGroupDev *)nullptr, 0,
-                           flagged);
-    else
-        hipLaunchKernelGGL(linear_list_kernel<false>, dim3(grid), dim3(kWave), 0, stream, d, n, st.chain, st.pos,
-                           mask_out, peak_out, status_out, w, (const RaggedGroupDev *)nullptr, 0, flagged);
+    const unsigned grid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
+    const bool in_lds = n <= kLdsStackMaxN;
+    hipLaunchKernelGGL(in_lds ? linear_list_kernel<true> : linear_list_kernel<false>, dim3(grid), dim3(kWave),
+                       in_lds ? lds_stack_bytes(n) : 0, stream, d, n, st.chain, st.pos, mask_out, peak_out, status_out, w,
+                       groups, n_groups, off, flagged);
 }
 void launch_wide(const int64_t *d, int64_t batch, int n, int64_t cstride, int64_t pstride, uint8_t *mask_out,
                  int64_t *peak_out, int32_t *status_out, const LinearWs &w, const RaggedGroupDev *groups, int n_groups,
@@ -1069,7 +1201,15 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
 {
     if (batch == 0) return hipSuccess;
     LinearWs w = carve_linear(ws, batch, n);
-    const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
+    if (rows_fit(batch, n)) {
+        const bool own = n <= kRowsOwnListMaxLayers;
+        const unsigned rgrid = (unsigned)((batch + kRowsOfWave - 1) / kRowsOfWave);
+        hipLaunchKernelGGL(own ? linear_rows_kernel<true> : linear_rows_kernel<false>, dim3(rgrid), dim3(kWave),
+                           rows_all_lds_bytes(n, own), stream, d, batch, n, st.chain, st.pos, mask_out, peak_out,
+                           status_out, w);
+        if (!own) launch_list(d, n, st, mask_out, peak_out, status_out, w, batch, nullptr, 0, nullptr, (int)batch, stream);
+        return hipGetLastError();
+    }
     if (batch <= kWaveMaxBatch && n <= kWaveMaxLayers) {
         if (own_list(batch, n)) {
             hipLaunchKernelGGL(linear_wave_kernel<true>, dim3((unsigned)batch), dim3(kWave), own_list_lds_bytes(n), stream, d,
@@ -1078,7 +1218,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
         }
         hipLaunchKernelGGL(linear_wave_kernel<false>, dim3((unsigned)batch), dim3(kWave), wave_lds_bytes(n), stream, d, n,
                            st.chain, st.pos, mask_out, peak_out, status_out, w);
-        launch_list(d, n, st, mask_out, peak_out, status_out, w, lgrid, (int)batch, stream);
+        launch_list(d, n, st, mask_out, peak_out, status_out, w, batch, nullptr, 0, nullptr, (int)batch, stream);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((batch + kWave - 1) / kWave);
@@ -1094,7 +1234,25 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
         hipLaunchKernelGGL(linear_defer_all_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, stream,
                            batch, w);
     launch_wide(d, batch, n, st.chain, st.pos, mask_out, peak_out, status_out, w, nullptr, 0, stream);
-    launch_list(d, n, st, mask_out, peak_out, status_out, w, lgrid, 0, stream);
+    launch_list(d, n, st, mask_out, peak_out, status_out, w, batch, nullptr, 0, nullptr, 0, stream);
+    return hipGetLastError();
+}
+
+bool linear_takes_flat(int64_t batch, int n)
+{
+    return rows_fit(batch, n) || (batch <= kWaveMaxBatch && n <= kWaveMaxLayers);
+}
+
+hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
+                                    uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws, hipStream_t stream)
+{
+    LinearWs w = carve_linear(ws, batch, n_most);
+    const bool rows = rows_fit(batch, n_most);
+    hipLaunchKernelGGL(rows ? linear_flat_kernel<true> : linear_flat_kernel<false>,
+                       dim3((unsigned)(rows ? (batch + kRowsOfWave - 1) / kRowsOfWave : batch)), dim3(kWave),
+                       rows ? rows_all_lds_bytes(n_most, false) : wave_lds_bytes(n_most), stream, d, off, perm, batch, n_most,
+                       mask_out, peak_out, status_out, w);
+    launch_list(d, n_most, Strides{0, 1}, mask_out, peak_out, status_out, w, batch, nullptr, 0, off, 0, stream);
     return hipGetLastError();
 }
 
@@ -1111,13 +1269,8 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
                        dim3((unsigned)(per_chain ? t.linear_waves : t.waves)), dim3(kWave), 0, stream, d_stage, groups,
                        n_groups, mask_stage, peak_stage, status_stage, w);
     launch_wide(d_stage, batch, max_layers, 1, 0, mask_stage, peak_stage, status_stage, w, groups, n_groups, stream);
-    const unsigned lgrid = (unsigned)(batch < kListBlocks ? batch : kListBlocks);
-    if (max_layers <= kLdsStackMaxN)
-        hipLaunchKernelGGL(linear_list_kernel<true>, dim3(lgrid), dim3(kWave), lds_stack_bytes(max_layers), stream,
-                           d_stage, max_layers, 1, 0, mask_stage, peak_stage, status_stage, w, groups, n_groups, 0);
-    else
-        hipLaunchKernelGGL(linear_list_kernel<false>, dim3(lgrid), dim3(kWave), 0, stream, d_stage, max_layers, 1, 0,
-                           mask_stage, peak_stage, status_stage, w, groups, n_groups, 0);
+    launch_list(d_stage, max_layers, Strides{1, 0}, mask_stage, peak_stage, status_stage, w, batch, groups, n_groups, nullptr, 0,
+                stream);
     return hipGetLastError();
 }
 
