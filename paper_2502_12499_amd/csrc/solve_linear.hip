@@ -1079,7 +1079,10 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_kernel(const int64_t *__
 }
 
 // The chains of a ragged batch where they lie in the flat arrays, four to a wave or one, in the order of `perm`, which
-// ascends in their lengths; the longest start first.  What is left goes on the second list.
+// ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the kLongest longest
+// get a wave each all the same: a row takes 72 ns a position, a wave 40, and a few deep chains are what a call waits for
+// (65,536 chains of 15 to 257 layers, sixteen of 1,001 among them: 148 us, 139).
+constexpr int kLongest = 64;
 template <bool ROWS>
 __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__restrict__ d, const int64_t *__restrict__ off,
                                                                const int32_t *__restrict__ perm, int64_t batch, int n_most,
@@ -1088,11 +1091,13 @@ __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__
                                                                int32_t *__restrict__ status_out, LinearWs w)
 {
     const int lane = threadIdx.x % kWave;
-    const int64_t p0 = (int64_t)(gridDim.x - 1 - blockIdx.x) * (ROWS ? kRowsOfWave : 1);
+    const bool alone = !ROWS || blockIdx.x < kLongest;
+    const int64_t p0 = alone ? batch - 1 - blockIdx.x : (int64_t)(gridDim.x - 1 - blockIdx.x) * kRowsOfWave;
     uint64_t left = 1;
-    if (ROWS) {
-        const bool is_chain = p0 + lane / kRow < batch;
-        const int64_t c = perm[is_chain ? p0 + lane / kRow : batch - 1], o = off[c];
+    if (!alone) {
+        const int64_t many = batch - kLongest;
+        const bool is_chain = p0 + lane / kRow < many;
+        const int64_t c = perm[is_chain ? p0 + lane / kRow : many - 1], o = off[c];
         const bool done = rows_chains(d + o, is_chain, (int)(off[c + 1] - o - 1), n_most, 1, mask_out + o, peak_out + c,
                                       status_out ? status_out + c : nullptr, lin_lds);
         left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0);
@@ -1112,6 +1117,7 @@ __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__
 // bits first, 72 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at 131,072
 // aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD four waves, or one up to 16,384 chains:
 // 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than those.
+static_assert(kLongest <= 1024, "fewer than the chains of a batch that takes rows");
 constexpr int64_t kWaveBatch = 1024, kRowsFewBatch = 16384, kRowsBatch = 65536;
 constexpr int kRowsFewMaxLayers = 4095, kRowsMaxLayers = 1279;
 inline bool rows_fit(int64_t batch, int n)
@@ -1121,10 +1127,10 @@ inline bool rows_fit(int64_t batch, int n)
 // A wave per chain where those do not fit.
 constexpr int64_t kWaveMaxBatch = 16384;
 constexpr int kRowsOwnListMaxLayers = 320;  // LDS for the list's stacks, 16 waves a CU (at 511 layers 134 us for 16,384 chains, 104 without)
-constexpr int kOwnListMaxLayers = 511;   // 15 KB of LDS for the stacks, kept free for a case that hardly happens ...
+constexpr int kOwnListMaxLayers = 2047;  // 60 KB of LDS for the stacks, kept free for a case that hardly happens ...
 __host__ inline size_t own_list_lds_bytes(int n) { return std::max(lds_stack_bytes(n), wave_lds_bytes(n)); }
 __host__ inline size_t rows_all_lds_bytes(int n, bool own) { return std::max(rows_lds_bytes(n), own ? own_list_lds_bytes(n) : wave_lds_bytes(n)); }
-// ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes): in two turns 4,096
+// ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes; 997 chains of 1,001 layers 59 us, 58 so): in two turns 4,096
 // chains of 511 layers took 286 us, and take 201 with the list in a launch of its own; 2,600 198 and 158.
 inline bool own_list(int64_t batch, int n)
 {
@@ -1248,8 +1254,8 @@ hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const 
 {
     LinearWs w = carve_linear(ws, batch, n_most);
     const bool rows = rows_fit(batch, n_most);
-    hipLaunchKernelGGL(rows ? linear_flat_kernel<true> : linear_flat_kernel<false>,
-                       dim3((unsigned)(rows ? (batch + kRowsOfWave - 1) / kRowsOfWave : batch)), dim3(kWave),
+    const int64_t waves = rows ? kLongest + (batch - kLongest + kRowsOfWave - 1) / kRowsOfWave : batch;
+    hipLaunchKernelGGL(rows ? linear_flat_kernel<true> : linear_flat_kernel<false>, dim3((unsigned)waves), dim3(kWave),
                        rows ? rows_all_lds_bytes(n_most, false) : wave_lds_bytes(n_most), stream, d, off, perm, batch, n_most,
                        mask_out, peak_out, status_out, w);
     launch_list(d, n_most, Strides{0, 1}, mask_out, peak_out, status_out, w, batch, nullptr, 0, off, 0, stream);
