@@ -41,7 +41,7 @@ extern __shared__ __align__(16) unsigned char search_lds[];
 // LDS space leaves (20 KB a wave at 64 layers in 32 bits): 310 cycles a cell of 64 points alone, 390 with two
 // waves.  The loads a cell depends on are issued a cell ahead (the predecessor j-1 always lies in the window
 // and is joined from its register), those that the window's start depends on two.
-// 65,536 chains of 64 layers of unrounded sizes: 1.40 ms, where evaluating all 2,017 budgets of each with
+// 65,536 chains of 64 layers of unrounded sizes: 1.28 ms, where evaluating all 2,017 budgets of each with
 // a queue per lane took 31.2 ms; one chain of 152 layers 88 us (129 us).
 //
 // Arithmetic.  UB, the cost of a feasible set, bounds the optimum, so a value of F above UB may
@@ -93,8 +93,10 @@ __device__ inline void lds_min(U *p, U v)
     (void)__hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// F_s(n) for the lane's s, 0 <= s <= UB; in 32 bits values above 2^31 are cut to that.
-template <typename U>
+// F_s(n) for the lane's s, 0 <= s <= UB; in 32 bits values above 2^31 are cut to that.  FLAT: the prefix sums are those in
+// full, so that they are compared with x - s as they are, not by their differences from x (three instructions less a cell:
+// 65,536 unrounded chains of 64 layers 1.37 ms, 1.31 with this).
+template <bool FLAT, typename U>
 __device__ __forceinline__ U lane_cost(const SearchLds<U> &m, const int n, const U s)
 {
     typedef std::make_signed_t<U> I;
@@ -111,16 +113,16 @@ __device__ __forceinline__ U lane_cost(const SearchLds<U> &m, const int n, const
     // until x itself: the differences beyond are negative)
     auto advance = [&](int l, const U x) -> int {
         const I w = (I)s;
-        l += (int)((I)(x - p0) > w) + (int)((I)(x - p1) > w) + (int)((I)(x - p2) > w);
-        bool far = (I)(x - p3) > w;
+        const U edge = x > s ? x - s : 0;
+        const auto out = [&](const U p) { return FLAT ? p < edge : (I)(x - p) > w; };
+        l += (int)out(p0) + (int)out(p1) + (int)out(p2);
+        bool far = out(p3);
         l += (int)far;
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {
             do {
                 const U q0 = P[l], q1 = P[l + 1], q2 = P[l + 2], q3 = P[l + 3];
-                l += far ? (int)((I)(x - q0) > w) + (int)((I)(x - q1) > w) + (int)((I)(x - q2) > w) +
-                               (int)((I)(x - q3) > w)
-                         : 0;
-                far = far && (I)(x - q3) > w;
+                l += far ? (int)out(q0) + (int)out(q1) + (int)out(q2) + (int)out(q3) : 0;
+                far = far && out(q3);
             } while (__builtin_amdgcn_ballot_w64(far) != 0);
         }
         return l;
@@ -229,6 +231,7 @@ __device__ __forceinline__ void search_chain(const SearchLds<U> &m, const int n,
     // s = 0 makes every layer a checkpoint: `total`, optimal only if no set costs less
     best_cost = total <= bound ? (U)total : std::numeric_limits<U>::max();
     best_s = 0;
+    const bool flat = total <= std::numeric_limits<U>::max();
     U ub = bound;   // the best cost known
     // the first points cut (0, span] evenly
     I prev = (I)(span >> 6) * lane + (I)(((span & 63) * (U)lane) >> 6);
@@ -247,7 +250,7 @@ __device__ __forceinline__ void search_chain(const SearchLds<U> &m, const int n,
     enum { kCut, kListed, kEveryBudget } step = kCut;
     int a = 0, x0 = 1;  // kEveryBudget: the start and the first end to come
     for (;;) {
-        const U c = lane_cost<U>(m, n, (U)s);
+        const U c = sizeof(U) == 8 || flat ? lane_cost<true>(m, n, (U)s) : lane_cost<false>(m, n, (U)s);
         {
             // (a point that is no budget may cost more than the optimum's type holds: it wraps nowhere
             // below 2^63 or 2^32, and what is above the bound is no candidate)
@@ -591,26 +594,33 @@ __device__ __forceinline__ void solve_short(const uint64_t (&sum)[kSearchPer], c
     U bc, bs;
     search_chain<U>(m, n, total, (U)bound, (U)span, ends, steps, all, (U)heavy, bc, bs);
     // The canonical set for the budget bs: the heads of one pass over the prefix sums in full (in the room of L1
-    // again), then the walk back from n.
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kSearchPer; ++q) {
-        const int k = q * kWave + lane;
-        if (k <= n) full[k] = sum[q] >> shift;
-    }
-    __syncthreads();
-    uint64_t *const F = full + n + 1;
-    uint8_t *const head = (uint8_t *)(F + n + 1 + kWave);
-    static_assert(kSearchMaxLayers <= 256, "a head's position is a byte");
-    bool ties = false;
-    (void)wave_cost<uint64_t, true>(full, n, (uint64_t)bs, F, head, NeverStop(), &ties);
+    // again; in 32 bits where they are), then the walk back from n.
     __syncthreads();
     bits = 0;
-    for (int j = n;;) {  // (downwards: on sums that ascend a head lies below its cell)
-        if ((j & (kWave - 1)) == lane) bits |= 1u << (j / kWave);
-        if (j == 0) break;
-        const int h = __builtin_amdgcn_readfirstlane(head[j]);
-        j = ties ? first_pred(full, F, (uint64_t)bs, j, h) : h;
+    static_assert(kSearchMaxLayers <= 256, "a head's position is a byte");
+    const auto walk = [&](const auto *P, auto *F) {
+        typedef std::remove_pointer_t<decltype(F)> V;
+        uint8_t *const head = (uint8_t *)(F + n + 1 + kWave);
+        bool ties = false;
+        (void)wave_cost<V, true>(P, n, (V)bs, F, head, NeverStop(), &ties);
+        __syncthreads();
+        for (int j = n;;) {  // (downwards: on sums that ascend a head lies below its cell)
+            if ((j & (kWave - 1)) == lane) bits |= 1u << (j / kWave);
+            if (j == 0) break;
+            const int h = __builtin_amdgcn_readfirstlane(head[j]);
+            j = ties ? first_pred(P, F, (V)bs, j, h) : h;
+        }
+    };
+    if (sizeof(U) == 4 && total < (1ull << 31)) {
+        walk((const uint32_t *)m.P, (uint32_t *)m.L1);
+    } else {
+#pragma unroll
+        for (int q = 0; q < kSearchPer; ++q) {
+            const int k = q * kWave + lane;
+            if (k <= n) full[k] = sum[q] >> shift;
+        }
+        __syncthreads();
+        walk(full, full + n + 1);
     }
     cost = (int64_t)((uint64_t)bc << shift);
     budget = (int64_t)((uint64_t)bs << shift);
