@@ -1078,6 +1078,51 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_kernel(const int64_t *__
     }
 }
 
+// The chains that the ring kernel left, four to a wave, or a wave each if they are few (a handful that outgrew the ring
+// would wait for a row's pace and then for the wave's: 65,537 chains of 2,047 aligned layers 1.68 ms so).  With `groups` a
+// listed number is a chain's place among all chains.  What does not fit a row is done by the whole wave, what that cannot
+// do goes on the second list.
+constexpr unsigned kRowsListBlocks = 4096;  // four waves a SIMD
+constexpr int kListedAlone = 1024;
+__global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_t *__restrict__ d, int n_all,
+                                                                    int64_t cstride, int64_t pstride_all,
+                                                                    uint8_t *__restrict__ mask_out,
+                                                                    int64_t *__restrict__ peak_out,
+                                                                    int32_t *__restrict__ status_out, LinearWs w,
+                                                                    const RaggedGroupDev *__restrict__ groups, int n_groups)
+{
+    const int lane = threadIdx.x % kWave, count = w.count[0];
+    // (c the same in the lanes that are to have the chain)
+    struct Chain { int64_t at, pstride; int n; };
+    const auto chain = [&](int64_t c) -> Chain {
+        if (!groups) return {c * cstride, pstride_all, n_all};
+        const RaggedGroupDev g = groups[ragged_group_of_place(groups, n_groups, c)];
+        return {g.stage_off + (c - g.first), g.pitch, g.n};
+    };
+    const bool alone = count <= kListedAlone;
+    const int per = alone ? 1 : kRowsOfWave;
+    for (int64_t first = (int64_t)xcd_blocked(blockIdx.x, gridDim.x) * per; first < count; first += (int64_t)gridDim.x * per) {
+        uint64_t left = 1;
+        if (!alone) {
+            const bool is_chain = first + lane / kRow < count;
+            const int64_t c = w.list[is_chain ? first + lane / kRow : count - 1];
+            const Chain its = chain(c);
+            const bool done = rows_chains(d + its.at, is_chain, its.n, n_all, its.pstride, mask_out + its.at, peak_out + c,
+                                          status_out ? status_out + c : nullptr, lin_lds);
+            left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0);
+        }
+        for (; left != 0; left &= left - 1) {
+            const int64_t one = w.list[first + __builtin_ctzll((unsigned long long)left) / kRow];
+            const Chain at = chain(one);
+            __syncthreads();
+            const bool by_wave = wave_chain(d + at.at, at.n, at.pstride, mask_out + at.at, peak_out + one,
+                                            status_out ? status_out + one : nullptr, lin_lds);
+            if (!by_wave && lane == 0) w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)one;
+        }
+        __syncthreads();
+    }
+}
+
 // The chains of a ragged batch where they lie in the flat arrays, four to a wave or one, in the order of `perm`, which
 // ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the kLongest longest
 // get a wave each all the same: a row takes 72 ns a position, a wave 40, and a few deep chains are what a call waits for
@@ -1123,6 +1168,13 @@ constexpr int kRowsFewMaxLayers = 4095, kRowsMaxLayers = 1279;
 inline bool rows_fit(int64_t batch, int n)
 {
     return batch > kWaveBatch && (batch <= kRowsFewBatch ? n <= kRowsFewMaxLayers : batch <= kRowsBatch && n <= kRowsMaxLayers);
+}
+// Rows also take what the ring kernel leaves of larger batches (unrounded sizes: all of it), where that kernel's form in 64
+// bits, a lane per chain, is slower: 131,072 unrounded chains of 64 layers 202 us (267), 262,144 of 1,001 5.6 ms (8.8), but
+// of 12 layers 142 us (130) and of 3,000 28.8 ms (27.5).
+inline bool rows_list_pays(int64_t batch, int n)
+{
+    return n > kRow && n <= kRowsFewMaxLayers && (n <= 2047 || batch <= 131072);
 }
 // A wave per chain where those do not fit.
 constexpr int64_t kWaveMaxBatch = 16384;
@@ -1195,6 +1247,12 @@ void launch_wide(const int64_t *d, int64_t batch, int n, int64_t cstride, int64_
                  int64_t *peak_out, int32_t *status_out, const LinearWs &w, const RaggedGroupDev *groups, int n_groups,
                  hipStream_t stream)
 {
+    if (rows_list_pays(batch, n)) {
+        const unsigned blocks = (unsigned)std::min<int64_t>((batch + kRowsOfWave - 1) / kRowsOfWave, kRowsListBlocks);
+        hipLaunchKernelGGL(linear_rows_list_kernel, dim3(blocks), dim3(kWave), rows_all_lds_bytes(n, false), stream, d, n,
+                           cstride, pstride, mask_out, peak_out, status_out, w, groups, n_groups);
+        return;
+    }
     const int64_t need = (batch + kWave - 1) / kWave;
     const dim3 grid((unsigned)(need < kWideBlocks ? need : kWideBlocks));
     hipLaunchKernelGGL(linear_wide_kernel, grid, dim3(kWave), 0, stream, d, n, cstride, pstride, mask_out, peak_out,
