@@ -31,7 +31,9 @@ __global__ __launch_bounds__(kCountThreads) void ragged_count_kernel(const int64
                                                                      RaggedTotals *__restrict__ totals)
 {
     __shared__ uint32_t near_count[kCountLds];
+    __shared__ int longest;
     for (int b = threadIdx.x; b < kCountLds; b += kCountThreads) near_count[b] = 0;
+    if (threadIdx.x == 0) longest = 0;
     __syncthreads();
     const int64_t c = (int64_t)blockIdx.x * kCountThreads + threadIdx.x;
     const int lane = threadIdx.x % kWave;
@@ -56,14 +58,16 @@ __global__ __launch_bounds__(kCountThreads) void ragged_count_kernel(const int64
         if (lane == leader) {
             const uint32_t many = (uint32_t)__popcll((unsigned long long)same);
             if (nl < (uint32_t)kCountLds) atomicAdd(near_count + nl, many); else atomicAdd(hist + nl, many);
+            atomicMax(&longest, (int)nl);
         }
         todo &= ~same;
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < kCountLds && b <= max_layers; b += kCountThreads) {
+    for (int b = threadIdx.x; b < kCountLds && b <= longest; b += kCountThreads) {
         const uint32_t many = near_count[b];
         if (many) atomicAdd(hist + b, many);
     }
+    if (threadIdx.x == 0 && longest > 0) atomicMax(&totals->max_layers, longest);
 }
 
 // Exclusive prefix sums of N values per thread over the workgroup (kCountThreads threads), and their totals.
@@ -106,11 +110,11 @@ __device__ inline void block_exclusive_sums(int64_t (&v)[kSums], int64_t (&total
 }
 
 // One workgroup: the lengths in tiles of kCountThreads, a length per thread.  Most of the 65,535 possible lengths do
-// not occur, so the tiles that hold none are found first (every thread reads its length of every tile, all
-// loads in flight) and passed over; in a tile that holds some, every thread adds up what its group
+// not occur, so the tiles that hold none are found first (every thread reads its length of every tile up to the longest
+// that was counted, the loads in flight together; 13 us with 1,001 layers at most, 18 through all 64 tiles) and passed over; in a tile that holds some, every thread adds up what its group
 // contributes to the totals and, knowing the totals before it, writes the group's descriptor.  (A
 // thread per stretch of 64 lengths, each walked twice, took 65 us; this takes 16.)
-__global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint32_t *__restrict__ hist, int max_layers,
+__global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint32_t *__restrict__ hist,
                                                                       RaggedGroupDev *__restrict__ groups,
                                                                       int64_t *__restrict__ tile_first2,
                                                                       RaggedTotals *__restrict__ totals)
@@ -118,25 +122,23 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
     __shared__ int64_t wave_sum[kCountThreads / kWave][kSums];
     __shared__ unsigned long long used;  // bit k: some length of tile k occurs
     __shared__ unsigned long long wave_layers, lane_waves;
-    __shared__ int longest, wave_longest;
+    __shared__ int wave_longest;
+    const int max_layers = totals->max_layers;
     constexpr int kTiles = (CKPT_MAX_LAYERS + kCountThreads - 1) / kCountThreads;
     static_assert(kTiles <= 64, "one bit per tile");
     if (threadIdx.x == 0) {
-        longest = wave_longest = 0;
+        wave_longest = 0;
         used = wave_layers = lane_waves = 0;
     }
     __syncthreads();
     unsigned long long mine = 0;
 #pragma unroll 16
-    for (int k = 0; k < kTiles; ++k) {  // (a load behind a branch would wait for the one before it)
+    for (int k = 0; k < (max_layers + kCountThreads - 1) / kCountThreads; ++k) {  // (a load behind a branch would wait for the one before it)
         const int n = 1 + k * kCountThreads + (int)threadIdx.x;
         const bool some = hist[n <= max_layers ? n : max_layers] != 0 && n <= max_layers;
         mine |= some ? 1ull << k : 0;
     }
-    if (mine) {
-        atomicOr(&used, mine);
-        atomicMax(&longest, 1 + (63 - __clzll(mine)) * kCountThreads + (int)threadIdx.x);
-    }
+    if (mine) atomicOr(&used, mine);
     __syncthreads();
     RaggedTotals at = {};  // the totals before the tile
     RaggedTotals long_ones = {};  // of the thread's groups: only their sums are wanted
@@ -187,7 +189,6 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
     __syncthreads();
     if (threadIdx.x == 0) {
         totals->n_groups = at.n_groups;
-        totals->max_layers = longest;
         totals->chains = at.chains;
         totals->waves = at.waves;
         totals->linear_waves = at.linear_waves;
@@ -413,7 +414,7 @@ int ragged_plan_on_device(const int64_t *offsets_dev, int64_t batch, int max_lay
                        (int32_t *)totals, (int)words, (int32_t *)nullptr);
     hipLaunchKernelGGL(ragged_count_kernel, dim3((unsigned)((batch + kCountThreads - 1) / kCountThreads)),
                        dim3(kCountThreads), 0, stream, offsets_dev, batch, max_layers, hist, totals);
-    hipLaunchKernelGGL(ragged_layout_kernel, dim3(1), dim3(kCountThreads), 0, stream, hist, max_layers,
+    hipLaunchKernelGGL(ragged_layout_kernel, dim3(1), dim3(kCountThreads), 0, stream, hist,
                        (RaggedGroupDev *)(base + w.groups), (int64_t *)(base + w.tiles2), totals);
     if (hipGetLastError() != hipSuccess) return CKPT_ERR_DEVICE;
     // the call's one wait: the launches that follow are sized by the totals
