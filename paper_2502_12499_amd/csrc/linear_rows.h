@@ -9,7 +9,7 @@
 // queue outgrows its row, or a size is not positive, the chain is left to the form of a wave per chain.
 //
 // What bounds it is issue again, and alone on a SIMD the wait states around DPP operands: 72 ns a position (32 bits; 105 in
-// doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 66 us, where a lane per chain took 137
+// doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 61 us (66 with a move for each half of a double), where a lane per chain took 137
 // (a try in 32 bits, then 64-bit integers with a queue in LDS, 1.8 us a position).
 #pragma once
 #include <type_traits>
@@ -18,27 +18,28 @@
 #include "ckpt_internal.h"
 #include "linear_wave.h"
 
+// v_mov_b64_dpp (the builtin takes a double, but not where its control depends on a template's argument)
+extern "C" __device__ double ckpt_update_dpp(double old, double value, int control, int rows, int banks, bool bound)
+    __asm("llvm.amdgcn.update.dpp.f64");
+
 namespace ckpt {
 namespace {
 
 constexpr int kRow = 16;             // lanes of a chain, positions of a block
 constexpr int kRowsOfWave = kWave / kRow;
 
-template <int CTRL, class S>
-__device__ inline S row_dpp(S v)  // (every lane has a source)
+// The value of lane LANE of the row, in all its lanes (8 bytes: one instruction too, as a double).
+template <int LANE, class S>
+__device__ inline S row_value(S v)
 {
+    constexpr int kRowNewBcast = 0x150;
     if constexpr (sizeof(S) == 4) {
-        return __builtin_bit_cast(S, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+        return __builtin_bit_cast(S, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kRowNewBcast + LANE, 0xf, 0xf, true));
     } else {
-        const uint64_t u = __builtin_bit_cast(uint64_t, v);
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-        return __builtin_bit_cast(S, ((uint64_t)hi << 32) | lo);
+        const double x = __builtin_bit_cast(double, v);
+        return __builtin_bit_cast(S, ckpt_update_dpp(x, x, kRowNewBcast + LANE, 0xf, 0xf, true));
     }
 }
-// The value of lane LANE of the row, in all its lanes.
-template <int LANE, class S>
-__device__ inline S row_value(S v) { return row_dpp<0x150 + LANE>(v); }
 // The value of the lane CTRL names, `none` in lanes without one.
 template <int CTRL, class S>
 __device__ inline S row_or(S none, S v)
