@@ -247,10 +247,9 @@ struct RaggedTotals {
     int64_t lane_waves;    // ... and the waves that they take with a lane per chain
 };
 
-// Groups whose chains the linear solver gives a wave each instead of a lane each, if all such groups together are
-// small enough (ragged_waves_pay): few chains (they would fill a handful of waves) and long ones (whose lane-per-chain
-// form takes 660 ns a position, four times what a wave per chain takes; 65,536 chains with sixteen of 1,001 layers
-// among them: 0.70 ms -> 0.30 ms).
+// Groups of a large ragged batch (linear_takes_flat takes the others) whose chains the linear solver gives a wave each
+// instead of a lane each, if all such groups together are small enough (ragged_waves_pay): few chains (they would fill a
+// handful of waves) and long ones (whose lane-per-chain form takes 660 ns a position, a wave per chain 40).
 __host__ __device__ inline bool ragged_wave_per_chain(int n, int64_t count)
 {
     return n > 256 && n <= 4095 && count <= 1024;
@@ -260,11 +259,10 @@ __host__ __device__ inline int64_t ragged_linear_waves(int n, int64_t count)
     return ragged_wave_per_chain(n, count) ? count : (count + 63) / 64;
 }
 
-// With a wave per chain these groups take 80 ps a layer once they fill the chip; with a lane per chain 660 ns a layer of
-// the longest, and in proportion more from about five waves to four SIMDs on.  Measured, lanes and waves: 1,000 chains of
-// 257 to 1,001 layers 597 and 338 us, 8,192 746 and 620, 12,288 790 and 793, 65,536 1,116 and 3,331; of 257 to 300 layers
-// 6,144 322 and 264, 8,192 309 and 304, 12,288 320 and 403; of 257 to 4,095, where nearly every length is a group of its
-// own, 4,096 2,482 and 1,667, 12,288 3,110 and 3,156, 16,384 6,513 and 3,822, 32,768 8,805 and 6,496.
+// With a wave per chain these groups take 40 ps a layer once they fill the chip (110 in 64 bits); with a lane per chain
+// 660 ns a layer of the longest, and in proportion more from about five waves to four SIMDs on (unrounded ones, whose
+// 64 bits are taken by rows, 100 ps a layer).  A line at 16,384 chains instead: 66,000 chains of up to 1,001 layers 883 ->
+// 708 us, unrounded ones 675 -> 1,029, and of up to 600 layers 131,072 unrounded ones 828 -> 1,249.
 inline bool ragged_waves_pay(const RaggedTotals &t)
 {
     constexpr int64_t kChains = 6144, kLaneWaves = 1280;

@@ -45,11 +45,11 @@
 //        A lane defers its chain when a ring fills, the values outgrow 30 bits,
 //        a step exceeds 255 positions, or a size is not positive: it appends
 //        the chain to a list in the workspace.
-//   wide kernel     one lane per chain on that list: the same algorithm in
-//        64-bit arithmetic with plain loops (sizes that are not multiples of a
-//        large power of two end up here).  Chains it cannot take either (ring
-//        full, step beyond 255, sizes not positive, sums beyond 64 bits) go on
-//        a second list.
+//   rows and waves  few chains, and what the ring kernel leaves of many: four chains to a wave (linear_rows.h) or one
+//        (linear_wave.h), in 32-bit integers, doubles or 64-bit integers.  Chains they cannot take either (more than 64
+//        entries live, sums beyond 62 bits) go on a second list.
+//   wide kernel     one lane per chain on the first list, where rows do not pay (up to 16 layers, more than 2,047): the
+//        ring kernel's algorithm in 64-bit arithmetic with plain loops.  What it cannot take goes on the second list.
 //   list kernel     one wave per chain of the second list (lane 0 works),
 //        64-bit values, stacks of full capacity n+1 in LDS (n <= 2047) or in
 //        the workspace.  Correct for any input, and the only writer of error
@@ -1302,16 +1302,24 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     return hipGetLastError();
 }
 
+namespace {
+// Of a ragged batch the lanes need a staging and wait for the longest chains of every wave, so rows pay longer: 131,072 and
+// 262,144 chains of up to 24 layers 110 and 141 us (125 and 143), of up to 1,001 562 and 1,028 (1,141 and 1,616),
+// unrounded 661 and 1,228 (1,042 and 1,962), 65,536 of up to 4,000 0.97 ms (2.4).  At 262,144 short ones the two meet.
+constexpr int64_t kFlatBatch = 262144;
+bool flat_rows(int64_t batch, int n) { return batch > kWaveBatch && batch <= kFlatBatch && n <= kRowsFewMaxLayers; }
+}  // namespace
+
 bool linear_takes_flat(int64_t batch, int n)
 {
-    return rows_fit(batch, n) || (batch <= kWaveMaxBatch && n <= kWaveMaxLayers);
+    return flat_rows(batch, n) || (batch <= kWaveMaxBatch && n <= kWaveMaxLayers);
 }
 
 hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
                                     uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws, hipStream_t stream)
 {
     LinearWs w = carve_linear(ws, batch, n_most);
-    const bool rows = rows_fit(batch, n_most);
+    const bool rows = flat_rows(batch, n_most);
     const int64_t waves = rows ? kLongest + (batch - kLongest + kRowsOfWave - 1) / kRowsOfWave : batch;
     hipLaunchKernelGGL(rows ? linear_flat_kernel<true> : linear_flat_kernel<false>, dim3((unsigned)waves), dim3(kWave),
                        rows ? rows_all_lds_bytes(n_most, false) : wave_lds_bytes(n_most), stream, d, off, perm, batch, n_most,

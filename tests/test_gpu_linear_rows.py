@@ -115,11 +115,13 @@ def test_bad_chains_are_reported_alone():
     assert not mask[~good].any()
 
 
-@pytest.mark.parametrize("batch, longest", [(5, 700), (1024, 90), (1025, 90), (4000, 300), (16385, 30), (65537, 12)])
+@pytest.mark.parametrize("batch, longest", [(5, 700), (1024, 90), (1025, 90), (4000, 300), (16385, 30), (65537, 12),
+                                            (16400, 4095), (16400, 4096), (262144, 5), (262145, 5)])
 def test_ragged_chains_where_they_lie(batch, longest):
     print(f"ragged linear: {batch} chains of up to {longest} layers", flush=True)
     rng = np.random.default_rng(batch)
-    lengths = [int(n) for n in np.minimum(np.exp(rng.uniform(0, np.log(longest + 1), size=batch)), longest)]
+    lengths = [int(n) for n in np.minimum(np.exp(rng.uniform(0, np.log(min(longest, 700) + 1), size=batch)), longest)]
+    lengths[batch // 3] = longest
     d, _, off = inputs.ragged_batch(19, lengths)
     for c in range(0, batch, 7):  # unrounded, more than doubles hold, many live entries
         n, part = lengths[c], slice(off[c], off[c + 1])
