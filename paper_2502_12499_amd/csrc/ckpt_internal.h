@@ -69,8 +69,8 @@ __device__ inline unsigned xcd_paired_block(unsigned b, unsigned grid)
 }
 
 // Workgroups go to the eight XCDs in turn, and each XCD has its own L2; a wave of one chain (four)
-// reads 8 (32) of the 128 bytes of a line of a position-major batch.  Within every 512 workgroups the 64 that one XCD receives take
-// neighbouring ones.  A bijection on [0, grid).
+// reads 8 (32) of the 128 bytes of a line of a position-major batch.  Within every 512 workgroups the 64 that one XCD
+// receives take neighbouring ones.  A bijection on [0, grid).
 __device__ inline unsigned xcd_blocked(unsigned b, unsigned grid)
 {
     if (b >= grid / 512 * 512) return b;
@@ -261,8 +261,8 @@ __host__ __device__ inline int64_t ragged_linear_waves(int n, int64_t count)
 
 // With a wave per chain these groups take 40 ps a layer once they fill the chip (110 in 64 bits); with a lane per chain
 // 660 ns a layer of the longest, and in proportion more from about five waves to four SIMDs on (unrounded ones, whose
-// 64 bits are taken by rows, 100 ps a layer).  A line at 16,384 chains instead: 66,000 chains of up to 1,001 layers 883 ->
-// 708 us, unrounded ones 675 -> 1,029, and of up to 600 layers 131,072 unrounded ones 828 -> 1,249.
+// 64 bits are taken by rows, 100 ps a layer).  A line at 16,384 chains instead: 66,000 chains of up to 1,001 layers
+// 883 -> 708 us, unrounded ones 675 -> 1,029, and of up to 600 layers 131,072 unrounded ones 828 -> 1,249.
 inline bool ragged_waves_pay(const RaggedTotals &t)
 {
     constexpr int64_t kChains = 6144, kLaneWaves = 1280;
@@ -358,8 +358,8 @@ hipError_t launch_eval_timeline_ragged(const int64_t *d_stage, const uint8_t *ma
 hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, const RaggedTotals &t,
                                       int64_t batch, uint8_t *mask_stage, int64_t *peak_stage, int32_t *status_stage,
                                       void *ws, hipStream_t stream);
-// The same for few enough chains, where they lie in the flat arrays; perm: the chains in order of their lengths, n_most: the
-// longest one's; ws as above, its first two 32-bit words 0.
+// The same for few enough chains, where they lie in the flat arrays; perm: the chains in order of their lengths,
+// n_most: the longest one's; ws as above, its first two 32-bit words 0.
 bool linear_takes_flat(int64_t batch, int n);
 hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
                                     uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws,

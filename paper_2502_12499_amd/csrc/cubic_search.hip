@@ -93,9 +93,9 @@ __device__ inline void lds_min(U *p, U v)
     (void)__hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// F_s(n) for the lane's s, 0 <= s <= UB; in 32 bits values above 2^31 are cut to that.  FLAT: the prefix sums are those in
-// full, so that they are compared with x - s as they are, not by their differences from x (three instructions less a cell:
-// 65,536 unrounded chains of 64 layers 1.37 ms, 1.31 with this).
+// F_s(n) for the lane's s, 0 <= s <= UB; in 32 bits values above 2^31 are cut to that.  FLAT: the prefix sums are
+// those in full, so that they are compared with x - s as they are, not by their differences from x (three instructions
+// less a cell: 65,536 unrounded chains of 64 layers 1.37 ms, 1.31 with this).
 template <bool FLAT, typename U>
 __device__ __forceinline__ U lane_cost(const SearchLds<U> &m, const int n, const U s)
 {
@@ -217,9 +217,10 @@ __device__ inline void wave_best(uint64_t &a, uint64_t &b)
 
 constexpr int kSearchPer = kSearchMaxLayers / kWave + 1;  // positions per lane
 
-// The least s + c_s and the smallest s that attains it.  `total`: the sum of all sizes; `bound`: the cost of a feasible set; `span`: no s
-// beyond it can be optimal; `ends[q]`: the first x > r with P[x] - P[r] > span, r = q * 64 + lane (n if there is none
-// below n); `all`: the sum of the interior layers; `heavy`: a layer that outweighs the others, within the span, or 0.
+// The least s + c_s and the smallest s that attains it.  `total`: the sum of all sizes; `bound`: the cost of a
+// feasible set; `span`: no s beyond it can be optimal; `ends[q]`: the first x > r with P[x] - P[r] > span, r = q * 64
+// + lane (n if there is none below n); `all`: the sum of the interior layers; `heavy`: a layer that outweighs the
+// others, within the span, or 0.
 template <typename U>
 __device__ __forceinline__ void search_chain(const SearchLds<U> &m, const int n, const uint64_t total, const U bound, const U span,
                                              const int (&ends)[kSearchPer], const int steps, const float all,
@@ -414,12 +415,13 @@ __device__ inline uint64_t select_lanes(uint64_t off, uint64_t on, uint64_t mask
 // sums are under way; a window that reaches back beyond Z is finished from two older slices and from the values
 // parked in F (whose sums come from memory: 64 layers a segment are usual in a chain of 4,096).
 // What bounds it is the chain of dependent instructions of a head (about 45, half of them scalar, eight to nine
-// cycles each; a loop of its own for the heads of a slice takes three jumps a head out of it, 7 % at 4,096 layers); a form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips.
-// P: prefix sums, P[n] below 2^31 or 2^63; F (and head): room for n + 1 + kWave values; RECORD: head[j], a minimal
-// predecessor of j, is written for j = 1..n, F(j) for j < n, and *ties says whether any was one of several.  stop(F(h)) is asked once per slice; when it says so the pass ends with
-// F(h), which F_s(n) is not below.  The pass ends whatever the sums are: a new head keeps the cell it was chosen for,
-// seen or not (on sums that ascend it always sees it; a test for an empty window took 5 % of a call), and a slice past
-// the last cell ends the pass with the largest value of the type.
+// cycles each; a loop of its own for the heads of a slice takes three jumps a head out of it, 7 % at 4,096 layers); a
+// form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips. P: prefix sums, P[n]
+// below 2^31 or 2^63; F (and head): room for n + 1 + kWave values; RECORD: head[j], a minimal predecessor of j, is
+// written for j = 1..n, F(j) for j < n, and *ties says whether any was one of several.  stop(F(h)) is asked once per
+// slice; when it says so the pass ends with F(h), which F_s(n) is not below.  The pass ends whatever the sums are: a
+// new head keeps the cell it was chosen for, seen or not (on sums that ascend it always sees it; a test for an empty
+// window took 5 % of a call), and a slice past the last cell ends the pass with the largest value of the type.
 struct NeverStop {
     template <typename U>
     __device__ bool operator()(U) const { return false; }
@@ -797,9 +799,9 @@ __global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t 
     }
 }
 
-// `chains` chains of a ragged batch from number `first` on, each where it lies in the flat array, class after class, a grid
-// of `chains` workgroups for each (`classes`: four bits a class, the first in the lowest).  lds: the launch's; chains that
-// need 64 bits and more of it go on the list.
+// `chains` chains of a ragged batch from number `first` on, each where it lies in the flat array, class after class, a
+// grid of `chains` workgroups for each (`classes`: four bits a class, the first in the lowest).  lds: the launch's;
+// chains that need 64 bits and more of it go on the list.
 __global__ __launch_bounds__(kWave) void cubic_search_ragged_kernel(const int64_t *__restrict__ d,
                                                                     const int64_t *__restrict__ off, int64_t first,
                                                                     unsigned chains, unsigned classes, unsigned lds,
@@ -855,8 +857,9 @@ constexpr int64_t kMostWavesOfALaunch = 1 << 25;
 // Waves of this much LDS that the chip holds (LDS is handed out in units of 1,280 bytes).
 inline int64_t at_once(size_t lds) { return 256 * ((160 << 10) / (int64_t)align_up(lds, 1280)); }
 // A ragged batch goes in one launch up to this many turns of it, with the longest chain's LDS for all: the classes one
-// after the other each wait for their slowest wave.  1,000 chains of 2 to 152 layers 114 us (four launches 247), 4,096 194
-// (335), 8,192 373 (387), 16,384 668 (567); of 2 to 256 layers 4,096 427 (519), 8,192 785 (798), 16,384 1,546 (1,309).
+// after the other each wait for their slowest wave.  1,000 chains of 2 to 152 layers 114 us (four launches 247), 4,096
+// 194 (335), 8,192 373 (387), 16,384 668 (567); of 2 to 256 layers 4,096 427 (519), 8,192 785 (798), 16,384 1,546
+// (1,309).
 constexpr int64_t kOneLaunchTurns = 8;
 // ... with LDS for 64 bits up to this many turns of that: a second launch for the chains that need them costs as much as
 // a second turn, and more than 192 layers of unrounded sizes mostly need them.  512 chains of 2 to 256 unrounded layers
@@ -946,12 +949,12 @@ namespace {
 //   result     the best of the waves, its set spread to bytes
 // After a round of 1,024 points a few hundred budgets are left of up to 2,000 layers of one order, and after two one to
 // twenty, so `finish` takes one pass; it takes whatever is left.  A call is bound by two or three passes in a row, each
-// as long as its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves stops: a
-// small s would have a head at every cell.
-// Measured, with every budget evaluated in brackets: one chain of 4,096 aligned layers 290 us (1,650), of 1,001 of a
-// network 97 (1,200 to 1,490; 480 while the first of equal predecessors was taken and there were always two rounds), of
-// 152 of a network 48 (121 to 137; 90 then); two of 3,115 aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484
-// (118,000); 1,000 of 300 600 (3,710), unrounded 685 (34,000).
+// as long as its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves
+// stops: a small s would have a head at every cell. Measured, with every budget evaluated in brackets: one chain of
+// 4,096 aligned layers 290 us (1,650), of 1,001 of a network 97 (1,200 to 1,490; 480 while the first of equal
+// predecessors was taken and there were always two rounds), of 152 of a network 48 (121 to 137; 90 then); two of 3,115
+// aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484 (118,000); 1,000 of 300 600 (3,710), unrounded
+// 685 (34,000).
 constexpr int kOpenMax = 128;       // open intervals kept (more are joined)
 constexpr int kMostPoints = 1024;   // of a round, per chain
 constexpr int kTableThreads = 1024;
@@ -1386,7 +1389,8 @@ __host__ inline int list_threads(int64_t batch, int n)
     const int starts = n < kListMost ? (n + kWave - 1) / kWave * kWave : kListMost;
     return batch <= 512 && starts < 512 ? 512 : starts;
 }
-// Waves of it that evaluate points: as many as their F leave the chains of a CU room for (the lists themselves take 9 KB).
+// Waves of it that evaluate points: as many as their F leave the chains of a CU room for (the lists themselves take 9
+// KB).
 __host__ inline int list_waves(int64_t batch, int n)
 {
     const size_t room = (size_t)(160 << 10) / (size_t)((batch + 255) / 256), own = 10 << 10;
@@ -1662,8 +1666,8 @@ __global__ __launch_bounds__(kListMost) void search_list_kernel(int n, int point
 }
 
 // A wave per budget, its set recorded on the way (a pass of its own for the set of the best took
-// 143 us at 1,001 layers of a network and 85 at 4,096 aligned ones; recording makes a pass 7 to 20 % longer).  The last wave of
-// a chain takes the best point of the rounds besides: its set is not known yet.
+// 143 us at 1,001 layers of a network and 85 at 4,096 aligned ones; recording makes a pass 7 to 20 % longer).  The
+// last wave of a chain takes the best point of the rounds besides: its set is not known yet.
 __global__ __launch_bounds__(kWave) void search_finish_kernel(int n, LongWs w)
 {
     const int64_t c = blockIdx.y;

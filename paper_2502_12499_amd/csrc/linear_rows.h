@@ -8,9 +8,10 @@
 // an int64 maximum is three): where the sizes, divided by their common power of two, need more than that, where a
 // queue outgrows its row, or a size is not positive, the chain is left to the form of a wave per chain.
 //
-// What bounds it is issue again, and alone on a SIMD the wait states around DPP operands: 72 ns a position (32 bits; 105 in
-// doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 61 us (66 with a move for each half of a double), where a lane per chain took 137
-// (a try in 32 bits, then 64-bit integers with a queue in LDS, 1.8 us a position).
+// What bounds it is issue again, and alone on a SIMD the wait states around DPP operands: 72 ns a position (32 bits;
+// 105 in doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 61 us (66 with a move for
+// each half of a double), where a lane per chain took 137 (a try in 32 bits, then 64-bit integers with a queue in LDS,
+// 1.8 us a position).
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -100,9 +101,9 @@ template <class S> constexpr int64_t kRowBeyond = sizeof(S) == 4 ? (int64_t)1 <<
 constexpr int kRowsQueueBytes = 2048;
 __host__ __device__ inline size_t rows_lds_bytes(int n) { return kRowsQueueBytes + (size_t)kRowsOfWave * ((size_t)n + 1) * 2; }
 
-// Sizes come from `load` (scaled; of the lane's own chain, of n layers), the chosen steps go to the row's nxt.  Returns M(0),
-// or a negative value if the row's queue was too short.  Rows of several lengths start together, each with its last
-// block; one that has come to its first position runs along on sizes that no lane takes.
+// Sizes come from `load` (scaled; of the lane's own chain, of n layers), the chosen steps go to the row's nxt.
+// Returns M(0), or a negative value if the row's queue was too short.  Rows of several lengths start together, each
+// with its last block; one that has come to its first position runs along on sizes that no lane takes.
 template <class S, class Load>
 __device__ __forceinline__ S rows_steps(const Load load, const int n, unsigned char *lds, uint16_t *nxt)
 {

@@ -44,7 +44,10 @@ __device__ inline int64_t with_lane(int64_t v, int64_t x, int lane)
 }
 
 template <int CTRL, int ROWS>
-__device__ inline int32_t dpp_value(int32_t old, int32_t v) { return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false); }
+__device__ inline int32_t dpp_value(int32_t old, int32_t v)
+{
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
 template <int CTRL, int ROWS>
 __device__ inline int64_t dpp_value(int64_t old, int64_t v)
 {

@@ -111,9 +111,10 @@ __device__ inline void block_exclusive_sums(int64_t (&v)[kSums], int64_t (&total
 
 // One workgroup: the lengths in tiles of kCountThreads, a length per thread.  Most of the 65,535 possible lengths do
 // not occur, so the tiles that hold none are found first (every thread reads its length of every tile up to the longest
-// that was counted, the loads in flight together; 13 us with 1,001 layers at most, 18 through all 64 tiles) and passed over; in a tile that holds some, every thread adds up what its group
-// contributes to the totals and, knowing the totals before it, writes the group's descriptor.  (A
-// thread per stretch of 64 lengths, each walked twice, took 65 us; this takes 16.)
+// that was counted, the loads in flight together; 13 us with 1,001 layers at most, 18 through all 64 tiles) and passed
+// over; in a tile that holds some, every thread adds up what its group contributes to the totals and, knowing the
+// totals before it, writes the group's descriptor.  (A thread per stretch of 64 lengths, each walked twice, took 65
+// us; this takes 16.)
 __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint32_t *__restrict__ hist,
                                                                       RaggedGroupDev *__restrict__ groups,
                                                                       int64_t *__restrict__ tile_first2,

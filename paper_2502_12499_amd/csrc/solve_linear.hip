@@ -991,8 +991,9 @@ __global__ __launch_bounds__(kWave) void linear_wave_kernel(const int64_t *__res
     }
 }
 
-// The four chains of a wave, a row of lanes each (what is passed is a lane's own chain's); false in the rows whose chain is
-// left to wave_chain (nothing of it is written).  n_most: at least the longest one's length; lds: rows_lds_bytes(n_most).
+// The four chains of a wave, a row of lanes each (what is passed is a lane's own chain's); false in the rows whose
+// chain is left to wave_chain (nothing of it is written).  n_most: at least the longest one's length; lds:
+// rows_lds_bytes(n_most).
 __device__ __forceinline__ bool rows_chains(const int64_t *__restrict__ dp, const bool is_chain, const int n,
                                             const int n_most, const int64_t pstride, uint8_t *__restrict__ mp, int64_t *__restrict__ peak_out,
                                             int32_t *__restrict__ status_out, unsigned char *lds)
@@ -1079,9 +1080,9 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_kernel(const int64_t *__
 }
 
 // The chains that the ring kernel left, four to a wave, or a wave each if they are few (a handful that outgrew the ring
-// would wait for a row's pace and then for the wave's: 65,537 chains of 2,047 aligned layers 1.68 ms so).  With `groups` a
-// listed number is a chain's place among all chains.  What does not fit a row is done by the whole wave, what that cannot
-// do goes on the second list.
+// would wait for a row's pace and then for the wave's: 65,537 chains of 2,047 aligned layers 1.68 ms so).  With
+// `groups` a listed number is a chain's place among all chains.  What does not fit a row is done by the whole wave,
+// what that cannot do goes on the second list.
 constexpr unsigned kRowsListBlocks = 4096;  // four waves a SIMD
 constexpr int kListedAlone = 1024;
 __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_t *__restrict__ d, int n_all,
@@ -1124,9 +1125,9 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
 }
 
 // The chains of a ragged batch where they lie in the flat arrays, four to a wave or one, in the order of `perm`, which
-// ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the kLongest longest
-// get a wave each all the same: a row takes 72 ns a position, a wave 40, and a few deep chains are what a call waits for
-// (65,536 chains of 15 to 257 layers, sixteen of 1,001 among them: 148 us, 139).
+// ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the kLongest
+// longest get a wave each all the same: a row takes 72 ns a position, a wave 40, and a few deep chains are what a call
+// waits for (65,536 chains of 15 to 257 layers, sixteen of 1,001 among them: 148 us, 139).
 constexpr int kLongest = 64;
 template <bool ROWS>
 __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__restrict__ d, const int64_t *__restrict__ off,
@@ -1157,11 +1158,11 @@ __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__
 }
 
 // A wave per chain up to 1,024 chains, one for each SIMD of the chip; four chains to a wave up to 65,536, and the ring
-// kernel's lanes beyond.  Waves and rows, us: 1,001 layers, 1,024 chains 62 and 79, 2,048 chains 100 and 82, unrounded ones
-// 131 and 115, 204 and 121.  Rows and lanes at 65,536 chains: 64 layers 49 and 51 (unrounded, which the lanes try in 32
-// bits first, 72 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at 131,072
-// aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD four waves, or one up to 16,384 chains:
-// 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than those.
+// kernel's lanes beyond.  Waves and rows, us: 1,001 layers, 1,024 chains 62 and 79, 2,048 chains 100 and 82, unrounded
+// ones 131 and 115, 204 and 121.  Rows and lanes at 65,536 chains: 64 layers 49 and 51 (unrounded, which the lanes try
+// in 32 bits first, 72 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at
+// 131,072 aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD four waves, or one up to
+// 16,384 chains: 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than those.
 static_assert(kLongest <= 1024, "fewer than the chains of a batch that takes rows");
 constexpr int64_t kWaveBatch = 1024, kRowsFewBatch = 16384, kRowsBatch = 65536;
 constexpr int kRowsFewMaxLayers = 4095, kRowsMaxLayers = 1279;
@@ -1169,21 +1170,26 @@ inline bool rows_fit(int64_t batch, int n)
 {
     return batch > kWaveBatch && (batch <= kRowsFewBatch ? n <= kRowsFewMaxLayers : batch <= kRowsBatch && n <= kRowsMaxLayers);
 }
-// Rows also take what the ring kernel leaves of larger batches (unrounded sizes: all of it), where that kernel's form in 64
-// bits, a lane per chain, is slower: 131,072 unrounded chains of 64 layers 202 us (267), 262,144 of 1,001 5.6 ms (8.8), but
-// of 12 layers 142 us (130) and of 3,000 28.8 ms (27.5).
+// Rows also take what the ring kernel leaves of larger batches (unrounded sizes: all of it), where that kernel's form
+// in 64 bits, a lane per chain, is slower: 131,072 unrounded chains of 64 layers 202 us (267), 262,144 of 1,001 5.6 ms
+// (8.8), but of 12 layers 142 us (130) and of 3,000 28.8 ms (27.5).
 inline bool rows_list_pays(int64_t batch, int n)
 {
     return n > kRow && n <= kRowsFewMaxLayers && (n <= 2047 || batch <= 131072);
 }
 // A wave per chain where those do not fit.
 constexpr int64_t kWaveMaxBatch = 16384;
-constexpr int kRowsOwnListMaxLayers = 320;  // LDS for the list's stacks, 16 waves a CU (at 511 layers 134 us for 16,384 chains, 104 without)
+// LDS for the list's stacks that leaves a CU 16 waves (at 511 layers 134 us for 16,384 chains, 104 without).
+constexpr int kRowsOwnListMaxLayers = 320;
 constexpr int kOwnListMaxLayers = 2047;  // 60 KB of LDS for the stacks, kept free for a case that hardly happens ...
 __host__ inline size_t own_list_lds_bytes(int n) { return std::max(lds_stack_bytes(n), wave_lds_bytes(n)); }
-__host__ inline size_t rows_all_lds_bytes(int n, bool own) { return std::max(rows_lds_bytes(n), own ? own_list_lds_bytes(n) : wave_lds_bytes(n)); }
-// ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes; 997 chains of 1,001 layers 59 us, 58 so): in two turns 4,096
-// chains of 511 layers took 286 us, and take 201 with the list in a launch of its own; 2,600 198 and 158.
+__host__ inline size_t rows_all_lds_bytes(int n, bool own)
+{
+    return std::max(rows_lds_bytes(n), own ? own_list_lds_bytes(n) : wave_lds_bytes(n));
+}
+// ... and only where all the waves fit the chip with it (LDS is handed out in units of 1,280 bytes; 997 chains of
+// 1,001 layers 59 us, 58 so): in two turns 4,096 chains of 511 layers took 286 us, and take 201 with the list in a
+// launch of its own; 2,600 198 and 158.
 inline bool own_list(int64_t batch, int n)
 {
     const int64_t per_cu = (160 << 10) / (int64_t)align_up(own_list_lds_bytes(n), 1280);
@@ -1303,9 +1309,10 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
 }
 
 namespace {
-// Of a ragged batch the lanes need a staging and wait for the longest chains of every wave, so rows pay longer: 131,072 and
-// 262,144 chains of up to 24 layers 110 and 141 us (125 and 143), of up to 1,001 562 and 1,028 (1,141 and 1,616),
-// unrounded 661 and 1,228 (1,042 and 1,962), 65,536 of up to 4,000 0.97 ms (2.4).  At 262,144 short ones the two meet.
+// Of a ragged batch the lanes need a staging and wait for the longest chains of every wave, so rows pay longer:
+// 131,072 and 262,144 chains of up to 24 layers 110 and 141 us (125 and 143), of up to 1,001 562 and 1,028 (1,141 and
+// 1,616), unrounded 661 and 1,228 (1,042 and 1,962), 65,536 of up to 4,000 0.97 ms (2.4).  At 262,144 short ones the
+// two meet.
 constexpr int64_t kFlatBatch = 262144;
 bool flat_rows(int64_t batch, int n) { return batch > kWaveBatch && batch <= kFlatBatch && n <= kRowsFewMaxLayers; }
 }  // namespace
