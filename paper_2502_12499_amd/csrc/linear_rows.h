@@ -70,23 +70,6 @@ __device__ inline S row_from(S v, const S none, const Op op)
     return op(v, row_or<kDppRowShl8>(none, v));
 }
 
-// (one instruction; the compiler quiets NaNs first, or compares and selects.  The results are not DPP operands: the
-// compiler does not count the wait states those need after an assembly statement.)
-__device__ inline int32_t top_of(int32_t a, int32_t b) { return a > b ? a : b; }
-__device__ inline int32_t least_of(int32_t a, int32_t b) { return a < b ? a : b; }
-__device__ inline double top_of(double a, double b)
-{
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ inline double least_of(double a, double b)
-{
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 template <int FROM, int TO, class F>
 __device__ __forceinline__ void unrolled(const F f)  // f(FROM), .., f(TO - 1)
 {

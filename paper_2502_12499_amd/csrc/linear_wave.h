@@ -56,8 +56,39 @@ __device__ inline int64_t dpp_value(int64_t old, int64_t v)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ inline double lane_value(double v, int lane)
+{
+    return __builtin_bit_cast(double, lane_value(__builtin_bit_cast(int64_t, v), lane));
+}
+__device__ inline double with_lane(double v, double x, int lane)
+{
+    return __builtin_bit_cast(double, with_lane(__builtin_bit_cast(int64_t, v), __builtin_bit_cast(int64_t, x), lane));
+}
+template <int CTRL, int ROWS>
+__device__ inline double dpp_value(double old, double v)
+{
+    return __builtin_bit_cast(double, dpp_value<CTRL, ROWS>(__builtin_bit_cast(int64_t, old), __builtin_bit_cast(int64_t, v)));
+}
+
 template <class S> __device__ inline S larger(S a, S b) { return a > b ? a : b; }
 template <class S> __device__ inline S smaller(S a, S b) { return a < b ? a : b; }
+// (one instruction; the compiler quiets NaNs first, or compares and selects.  The results are not DPP operands: the
+// compiler does not count the wait states those need after an assembly statement.)
+template <class S> __device__ inline S top_of(S a, S b) { return a > b ? a : b; }
+template <class S> __device__ inline S least_of(S a, S b) { return a < b ? a : b; }
+__device__ inline double top_of(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ inline double least_of(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 
 // Sums and maxima over the lanes up to this one.  (A lane without a source gets the operation's neutral value, which lets
 // the compiler make one instruction of a step.)
@@ -75,7 +106,7 @@ __device__ inline S sum_up_to(S v)
 template <class S>
 __device__ inline S max_up_to(S v)
 {
-    constexpr S kNone = std::numeric_limits<S>::min();
+    constexpr S kNone = std::numeric_limits<S>::lowest();
     v = larger(v, dpp_value<kDppRowShr1, 0xf>(kNone, v));
     v = larger(v, dpp_value<kDppRowShr2, 0xf>(kNone, v));
     v = larger(v, dpp_value<kDppRowShr4, 0xf>(kNone, v));
@@ -101,7 +132,7 @@ constexpr int kDppRowShl1 = 0x101, kDppRowShl2 = 0x102, kDppRowShl4 = 0x104, kDp
 template <class S>
 __device__ inline S max_above(S v, const S none)
 {
-    constexpr S kNone = std::numeric_limits<S>::min();
+    constexpr S kNone = std::numeric_limits<S>::lowest();
     const int row = threadIdx.x % kWave / 16;
     v = larger(v, dpp_value<kDppRowShl1, 0xf>(kNone, v));
     v = larger(v, dpp_value<kDppRowShl2, 0xf>(kNone, v));
@@ -116,6 +147,7 @@ __device__ inline S max_above(S v, const S none)
 template <class S> constexpr int kBlockOf = sizeof(S) == 4 ? 64 : 32;
 // Values the recurrence may reach: (sum(d) + max(d)) >> shift stays below.
 template <class S> constexpr S kBeyond = (S)1 << (8 * sizeof(S) - 2);
+template <> constexpr double kBeyond<double> = (double)((int64_t)1 << 52);  // (integers, exact to 2^53)
 
 constexpr int kQueueBytes = 2048;
 // Bytes of LDS: the queue while it is put together, the steps of a chain.
@@ -142,7 +174,7 @@ __device__ __forceinline__ bool wave_steps(const Load load, const int n, unsigne
     qM = lane == 0 ? qM : kTop;
     S rows = load(n - 1 - lane);
     for (int hi = n - 1;; hi -= kBlock) {
-        const int many = smaller(hi + 1, kBlock);
+        const int many = hi + 1 < kBlock ? hi + 1 : kBlock;
         const S d = lane < many ? rows : 0;
         rows = load(hi - kBlock - lane);  // (positions below 0 repeat position 0 and are not used)
         const S sums = sum_up_to(d), front = max_up_to(d);
@@ -165,10 +197,10 @@ __device__ __forceinline__ bool wave_steps(const Load load, const int n, unsigne
             S u;
 #pragma unroll
             for (int p = 0; p < kEntries; ++p) {
-                u = larger(front, G[p]) + T + minus[p];
-                const S v = larger(u, M[p]);
+                u = top_of(front, G[p]) + T + minus[p];
+                const S v = top_of(u, M[p]);
                 back = v < B ? hi - j[p] : back;  // ties go to the lower index
-                B = smaller(v, B);
+                B = least_of(v, B);
             }
             if (__builtin_amdgcn_ballot_w64(u < B) == 0) break;
         }
@@ -190,7 +222,7 @@ __device__ __forceinline__ bool wave_steps(const Load load, const int n, unsigne
 #pragma unroll
                 for (int k = kGroup - 1; k >= 0; --k) {
                     table[g * kGroup + k] = R + T + minus[k];
-                    R = with_lane(larger(R, dm[k]), dm[k], g * kGroup + k);
+                    R = with_lane(top_of(R, dm[k]), dm[k], g * kGroup + k);
                 }
             }
         }
@@ -202,9 +234,9 @@ __device__ __forceinline__ bool wave_steps(const Load load, const int n, unsigne
             if (g * kGroup < many) {
 #pragma unroll
                 for (int m = g * kGroup; m < g * kGroup + kGroup; ++m) {
-                    const S v = larger(table[m], lane_value(B + weight, m));
+                    const S v = top_of(table[m], lane_value((S)(B + weight), m));
                     back = v <= B ? m : back;
-                    B = smaller(v, B);
+                    B = least_of(v, B);
                 }
             }
         }
