@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kWave) void linear_ring_kernel(const int64_t *__res
 struct alignas(32) WideEntry {
     int64_t M;   // M(j)
     int64_t G;   // max of d over [j, j'), j' the next entry towards the far end
-    int64_t A;   // M(j) + T(j)
+    uint64_t A;  // M(j) + T(j), both of up to 63 bits
     int32_t J;   // j
     int32_t pad;
 };
@@ -610,11 +610,12 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
         int64_t dmax = x, dnext = x, Mi = x;
         uint64_t T = 0;
         int hd = 0, pt = 0;
-        at(0) = WideEntry{x, 0, x, n, 0};
+        at(0) = WideEntry{x, 0, (uint64_t)x, n, 0};
         int64_t Tpt = 0, Rp = 0;
         int Jpt = n;
         bool has_c = false;
-        int64_t Mc = 0, Ac = 0, Rc = 0;
+        int64_t Mc = 0, Rc = 0;
+        uint64_t Ac = 0;
         int Jc = 0;
         int64_t Mh = x, Gh = 0, M1 = 0, G1 = 0;  // M and G of the entry at hd and of the one before it
 
@@ -629,9 +630,9 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
             Rp = di > Rp ? di : Rp;
             Rc = di > Rc ? di : Rc;
             // the crossover moves towards the head while the candidate satisfies U(i,j) >= M(j)
-            while (has_c && Ti + Rc >= Ac) {
+            while (has_c && (uint64_t)(Ti + Rc) >= Ac) {
                 ++pt;
-                Tpt = Ac - Mc;
+                Tpt = (int64_t)(Ac - (uint64_t)Mc);
                 Jpt = Jc;
                 Rp = Rc;
                 has_c = pt != hd;
@@ -664,14 +665,14 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
             }
             ++hd;
             out |= hd - pt >= kRing;
-            at(hd) = WideEntry{Mi, Gacc, Mi + Ti, i, 0};
+            at(hd) = WideEntry{Mi, Gacc, (uint64_t)Mi + T, i, 0};
             M1 = Mh;
             G1 = Gh;
             Mh = Mi;
             Gh = Gacc;
             if (hd == pt + 1) {
                 has_c = true;
-                Mc = Mi; Ac = Mi + Ti; Jc = i; Rc = 0;
+                Mc = Mi; Ac = (uint64_t)Mi + T; Jc = i; Rc = 0;
             }
         };
         for (int i0 = n - 1; i0 >= 0; i0 -= kWideRows) {

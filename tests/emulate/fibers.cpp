@@ -40,12 +40,6 @@ const char *kernel_name;
 uint64_t meetings;
 std::map<const void *, size_t> lds_limit;
 
-[[noreturn]] void stop(const char *why)
-{
-    printf("%s: %s\n", kernel_name, why);
-    exit(1);
-}
-
 extern "C" void emu_switch(void **save, void *to);
 asm(".text\n.globl emu_switch\nemu_switch:\n"
     "push %rbp\npush %rbx\npush %r12\npush %r13\npush %r14\npush %r15\n"
@@ -91,6 +85,12 @@ bool run_wave(unsigned w, unsigned count)
     }
 }
 }  // namespace
+
+void stop(const char *why)
+{
+    printf("%s: %s\n", kernel_name, why);
+    exit(1);
+}
 
 const uint64_t *meet(uint64_t value, Kind kind)
 {

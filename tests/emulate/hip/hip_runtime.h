@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <functional>
 
 using std::max;
@@ -27,6 +28,7 @@ typedef void *hipStream_t;
 enum {
     hipSuccess,
     hipErrorInvalidDevice,
+    hipErrorInvalidSymbol,
     hipErrorInvalidConfiguration,
     hipErrorInvalidValue,
     hipFuncAttributeMaxDynamicSharedMemorySize
@@ -34,6 +36,8 @@ enum {
 hipError_t hipFuncSetAttribute(const void *kernel, int, int bytes);
 inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 inline hipError_t hipGetLastError() { return hipSuccess; }
+#define HIP_SYMBOL(x) ((void *)&(x))
+inline hipError_t hipGetSymbolAddress(void **p, const void *symbol) { *p = (void *)symbol; return hipSuccess; }
 struct dim3 {
     unsigned x, y, z;
     dim3(unsigned a = 1, unsigned b = 1, unsigned c = 1) : x(a), y(b), z(c) {}
@@ -51,6 +55,7 @@ void launch(const char *name, const void *entry, dim3 grid, dim3 block, size_t l
 extern std::function<void(const char *name, dim3 grid)> instead_of_running;
 // Called after every hipFuncSetAttribute: what another thread does at that moment.
 extern std::function<void()> meanwhile;
+[[noreturn]] void stop(const char *why);
 // Device memory of exactly this many bytes, between pages that cannot be touched, full of a pattern.
 void *device_memory(size_t bytes);
 // A launch whose waves meet more often than this is taken not to end.
@@ -82,9 +87,18 @@ inline int dpp(int old, int x, int control, int row_mask)
     const int row = lane() / 16;
     int from = -1;
     if (control > 0x110 && control < 0x120) from = lane() - (control - 0x110) >= row * 16 ? lane() - (control - 0x110) : -1;
+    if (control > 0x100 && control < 0x110) from = lane() + (control - 0x100) < row * 16 + 16 ? lane() + (control - 0x100) : -1;
+    if (control >= 0x150 && control < 0x160) from = row * 16 + (control - 0x150);
     if (control == 0x142) from = row * 16 - 1;
     if (control == 0x143) from = row > 1 ? 31 : -1;
     return from < 0 || !((row_mask >> row) & 1) ? old : (int)(uint32_t)v[from];
+}
+inline double dpp(double old, double x, int control, int row_mask)
+{
+    uint64_t r = 0;
+    for (int k = 0; k < 64; k += 32)
+        r |= (uint64_t)(uint32_t)dpp((int)(uint32_t)(bits(old) >> k), (int)(uint32_t)(bits(x) >> k), control, row_mask) << k;
+    return value<double>(r);
 }
 inline uint32_t min_u32(uint32_t x)
 {
@@ -93,6 +107,13 @@ inline uint32_t min_u32(uint32_t x)
     for (int l = 0; l < kLanes; ++l)
         if ((taking_part() >> l) & 1) m = std::min(m, (uint32_t)v[l]);
     return m;
+}
+// The bytes of a (4..7) and b (0..3) that the bytes of sel name.
+inline uint32_t permuted(uint32_t a, uint32_t b, uint32_t sel)
+{
+    uint32_t r = 0;
+    for (int k = 0; k < 32; k += 8) r |= (uint32_t)(uint8_t)((((uint64_t)a << 32) | b) >> (8 * ((sel >> k) & 7))) << k;
+    return r;
 }
 template <class T> T exchange(T *p, T v) { const T was = *p; *p = v; return was; }
 template <class T> T least(T *p, T v) { const T was = *p; *p = v < was ? v : was; return was; }
@@ -105,6 +126,7 @@ template <class T> T least(T *p, T v) { const T was = *p; *p = v < was ? v : was
 #define hipLaunchKernelGGL(k, grid, block, lds, stream, ...) emu::launch(#k, (const void *)(k), grid, block, lds, [&] { (k)(__VA_ARGS__); })
 
 inline void __syncthreads() { (void)emu::meet(0, emu::kBarrier); }
+inline void __threadfence_block() {}
 inline bool __any(int b) { return emu::ballot(b != 0) != 0; }
 template <class T> T __shfl(T v, int l, int) { return emu::value<T>(emu::meet(emu::bits(v), emu::kShfl)[l & 63]); }
 template <class T> T __shfl_xor(T v, int m, int) { return emu::value<T>(emu::meet(emu::bits(v), emu::kShfl)[emu::lane() ^ m]); }
@@ -119,6 +141,10 @@ template <class T> T __shfl_up(T v, int d, int)
 #define __builtin_nontemporal_load(p) (*(p))
 #define __builtin_nontemporal_store(v, p) ((void)(*(p) = (v)))
 #define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) emu::dpp(old, v, control, rows)
+#define __builtin_amdgcn_mov_dpp(v, control, rows, banks, bound) emu::dpp(0, v, control, rows)
+#define __builtin_amdgcn_sched_barrier(...) ((void)0)
+#define __builtin_amdgcn_alignbit(hi, lo, shift) ((uint32_t)((((uint64_t)(hi) << 32) | (uint32_t)(lo)) >> ((shift) & 31)))
+#define __builtin_amdgcn_perm(a, b, sel) emu::permuted(a, b, sel)
 #define __builtin_amdgcn_fence(...) ((void)0)
 #define __HIP_MEMORY_SCOPE_WORKGROUP 0
 #define __HIP_MEMORY_SCOPE_AGENT 1
@@ -131,6 +157,9 @@ template <class T> T atomicMin(T *p, T v) { return emu::least(p, v); }
 template <class T> T atomicMax(T *p, T v) { return emu::exchange(p, *p < v ? v : *p); }
 template <class T> T atomicCAS(T *p, T a, T b) { const T was = *p; if (was == a) *p = b; return was; }
 inline int __ffsll(unsigned long long v) { return __builtin_ffsll((long long)v); }
+inline int __ffs(int v) { return __builtin_ffs(v); }
+inline int __popc(unsigned v) { return __builtin_popcount(v); }
+inline int __clz(int v) { return v ? __builtin_clz((unsigned)v) : 32; }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 inline int __clzll(unsigned long long v) { return v ? __builtin_clzll(v) : 64; }
 inline uint32_t __float_as_uint(float f) { return (uint32_t)emu::bits(f); }

@@ -102,3 +102,21 @@ def test_cubic_calls_in_flight_on_two_streams():
             mask, peak, budget = got[k][0], got[k][1], got[k][2]
             assert int(peak.cpu()[0]) == v and int(budget.cpu()[0]) == s
             assert np.array_equal(mask.cpu().numpy()[:, 0], mk)
+
+
+@pytest.mark.parametrize("n", [3, 7, 12, 16])
+def test_sums_between_2_62_and_2_63_a_lane_per_chain(n):
+    """M(j) + T(j), which the lanes in 64 bits compare with U(i,j) + T(j), is beyond 2^63 there."""
+    say(f"linear: 65,600 chains of {n} layers with sums beyond 2^62")
+    rng = np.random.default_rng(n)
+    d = rng.integers((1 << 62) // (n + 2), ((1 << 63) - 1) // (n + 2), size=(n + 1, 65600)).astype(np.int64)
+    d[:, 1::2] = rng.integers(1, (1 << 59) // (n + 2), size=(n + 1, 32800))
+    for c in range(1, 65600, 2):  # one large size among small ones
+        at = (0, n // 2, n)[c % 3]
+        d[at, c] = 0
+        d[at, c] = ((1 << 63) - 1 - int(d[:, c].sum())) // 2
+    mask, peak, status = B.ckpt_solve_linear(torch.from_numpy(d).to(DEV))
+    want_peak, want_mask = oracle.batch_solve_dynamic(inputs.chain_major(d))
+    assert not status.any().item()
+    assert np.array_equal(peak.cpu().numpy(), want_peak)
+    assert np.array_equal(mask.cpu().numpy().T, want_mask)
