@@ -232,7 +232,8 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
                 // fewer common trailing zeros: rescale everything held so far
                 const int tz = __ffs(low) - 1;
                 const int k = sh - tz;
-                const bool fits = k < 30 && ((Ti + dnext + dmax) >> (30 - k)) == 0;
+                // (and every size held so far, which a G may be, still below 2^24)
+                const bool fits = k < 24 && ((Ti + dnext + dmax) >> (30 - k)) == 0 && (dmax >> (24 - k)) == 0;
                 defer |= !fits;
                 const int kk = fits ? k : 0;
                 auto scale_gj = [kk](uint32_t gj) -> uint32_t { return ((gj & ~255u) << kk) | (gj & 255u); };

@@ -179,6 +179,19 @@ std::vector<Sizes> kinds(int n)
 int main()
 {
     for (const int n : {1, 2, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 100, 130, 257, 330}) check("kinds of sizes", kinds(n), kEqualLengths);
+    // ever fewer trailing zeros towards the front, with sizes up to the lanes' limit of 2^24 before and after each of them
+    for (const int n : {9, 12, 17, 24}) {
+        std::vector<Sizes> chains;
+        for (int c = 0; c < 400; ++c) {
+            Sizes d = uniform(n, 1, 1 << 22);
+            for (int k = 0; k <= n; ++k) {
+                if (rng() % 4 == 0) d[(size_t)k] = between(1 << 22, (1 << 24) + (1 << 23));
+                d[(size_t)k] = std::max<int64_t>(1, d[(size_t)k] >> (k / 3)) << (k / 3);
+            }
+            chains.push_back(d);
+        }
+        check("fewer trailing zeros", chains, {kLanes});
+    }
     for (const int longest : {5, 40, 200}) {
         std::vector<Sizes> chains;
         while (chains.size() < 90)

@@ -120,3 +120,22 @@ def test_sums_between_2_62_and_2_63_a_lane_per_chain(n):
     assert not status.any().item()
     assert np.array_equal(peak.cpu().numpy(), want_peak)
     assert np.array_equal(mask.cpu().numpy().T, want_mask)
+
+
+@pytest.mark.parametrize("n", [9, 12, 24, 300])
+def test_ever_fewer_trailing_zeros(n):
+    """Sizes about the 2^24 that a lane holds, whose common power of two falls along the chain: the sizes a lane has
+    shifted to fewer trailing zeros have to stay below 2^24 too."""
+    say(f"linear: 65,600 chains of {n} layers with ever fewer trailing zeros")
+    rng = np.random.default_rng(n)
+    d = rng.integers(1, 1 << 22 if n < 50 else 1 << 20, size=(n + 1, 65600)).astype(np.int64)
+    large = rng.random(d.shape) < min(0.25, 4 / n)
+    d[large] = rng.integers(1 << 22, (1 << 24) + (1 << 23), size=int(large.sum()))
+    zeros = np.minimum(np.arange(n + 1) // max(3, n // 6), 8)[:, None]
+    d = np.maximum(1, d >> zeros) << zeros
+    pick = np.arange(65600) if n < 50 else np.arange(0, 65600, 41)  # (the oracle takes its time with the long ones)
+    mask, peak, status = B.ckpt_solve_linear(torch.from_numpy(d).to(DEV))
+    want_peak, want_mask = oracle.batch_solve_dynamic(inputs.chain_major(np.ascontiguousarray(d[:, pick])))
+    assert not status.any().item()
+    assert np.array_equal(peak.cpu().numpy()[pick], want_peak)
+    assert np.array_equal(mask.cpu().numpy().T[pick], want_mask)
