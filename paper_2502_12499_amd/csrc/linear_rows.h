@@ -80,7 +80,7 @@ __device__ __forceinline__ void unrolled(const F f)  // f(FROM), .., f(TO - 1)
 }
 
 // (sum(d) + max(d)) >> shift of a chain stays below.
-template <class S> constexpr int64_t kRowBeyond = sizeof(S) == 4 ? (int64_t)1 << 30 : (int64_t)1 << 52;
+template <class S> constexpr uint64_t kRowBeyond = (uint64_t)kBeyond<S>;
 constexpr int kRowsQueueBytes = 2048;
 __host__ __device__ inline size_t rows_lds_bytes(int n) { return kRowsQueueBytes + (size_t)kRowsOfWave * ((size_t)n + 1) * 2; }
 

@@ -56,6 +56,14 @@ __device__ inline int64_t dpp_value(int64_t old, int64_t v)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ inline uint64_t lane_value(uint64_t v, int lane) { return (uint64_t)lane_value((int64_t)v, lane); }
+__device__ inline uint64_t with_lane(uint64_t v, uint64_t x, int lane) { return (uint64_t)with_lane((int64_t)v, (int64_t)x, lane); }
+template <int CTRL, int ROWS>
+__device__ inline uint64_t dpp_value(uint64_t old, uint64_t v)
+{
+    return (uint64_t)dpp_value<CTRL, ROWS>((int64_t)old, (int64_t)v);
+}
+
 __device__ inline double lane_value(double v, int lane)
 {
     return __builtin_bit_cast(double, lane_value(__builtin_bit_cast(int64_t, v), lane));
@@ -146,8 +154,13 @@ __device__ inline S max_above(S v, const S none)
 // Positions of a block: a register (pair) of the table for each.
 template <class S> constexpr int kBlockOf = sizeof(S) == 4 ? 64 : 32;
 // Values the recurrence may reach: (sum(d) + max(d)) >> shift stays below.
-template <class S> constexpr S kBeyond = (S)1 << (8 * sizeof(S) - 2);
+template <class S> constexpr S kBeyond = (S)1 << 30;
 template <> constexpr double kBeyond<double> = (double)((int64_t)1 << 52);  // (integers, exact to 2^53)
+template <> constexpr uint64_t kBeyond<uint64_t> = (uint64_t)1 << 63;       // (twice as much fits: every checked chain)
+
+// Turns the order around: the smallest of values is what the largest of these is turned back.
+template <class S> __device__ inline S turned(S v) { return ~v; }
+__device__ inline double turned(double v) { return -v; }
 
 constexpr int kQueueBytes = 2048;
 // Bytes of LDS: the queue while it is put together, the steps of a chain.
@@ -249,7 +262,7 @@ __device__ __forceinline__ bool wave_steps(const Load load, const int n, unsigne
 
         // The queue seen from the next block: this block's entries, then those of the old ones whose M is smaller.
         const S below = max_above(d, (S)0);                             // max(d_lowest..d_{j-1})
-        const S next = -max_above(lane < kBlock ? -M : -kTop, -kTop);   // the smallest M of the positions below
+        const S next = turned(max_above(turned(lane < kBlock ? M : kTop), turned(kTop)));  // the smallest M of the positions below
         const S Tlow = lane_value(T, kBlock - 1);
         uint64_t fresh = __builtin_amdgcn_ballot_w64(lane < kBlock && M < next);
         const uint64_t fresh_sat = __builtin_amdgcn_ballot_w64(below + (Tlow - T) >= M) & fresh;

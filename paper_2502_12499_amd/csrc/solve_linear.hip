@@ -47,7 +47,7 @@
 //        the chain to a list in the workspace.
 //   rows and waves  few chains, and what the ring kernel leaves of many: four chains to a wave (linear_rows.h) or one
 //        (linear_wave.h), in 32-bit integers, doubles or 64-bit integers.  Chains they cannot take either (more than 64
-//        entries live, sums beyond 62 bits) go on a second list.
+//        entries live) go on a second list.
 //   wide kernel     one lane per chain on the first list, where rows do not pay (up to 16 layers, more than 2,047): the
 //        ring kernel's algorithm in 64-bit arithmetic with plain loops.  What it cannot take goes on the second list.
 //   list kernel     one wave per chain of the second list (lane 0 works),
@@ -914,10 +914,9 @@ __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const
             done = wave_steps<double>([&](int k) { return (double)at(k); }, n, lds, nxt, m0);
             peak = done ? (int64_t)m0 << sh : -1;
         } else {
-            int64_t m0;
-            done = most < (uint64_t)kBeyond<int64_t> &&
-                   wave_steps<int64_t>([&](int k) { return (int64_t)at(k); }, n, lds, nxt, m0);
-            peak = done ? m0 << sh : -1;
+            uint64_t m0;
+            done = wave_steps<uint64_t>([&](int k) { return at(k); }, n, lds, nxt, m0);
+            peak = done ? (int64_t)(m0 << sh) : -1;
         }
         if (!done) return false;
     }

@@ -178,3 +178,33 @@ def test_many_long_chains_of_a_ragged_batch(batch):
         assert (status.cpu().numpy() == 0).all()
         assert np.array_equal(peak.cpu().numpy(), want_peak)
         assert np.array_equal(mask.cpu().numpy(), want_mask)
+
+
+def shortest_us(call, tries=7, calls=8):
+    """The shortest mean time of `calls` calls in a row."""
+    call()
+    best = float("inf")
+    for _ in range(tries):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(calls):
+            call()
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, begin.elapsed_time(end) / calls * 1e3)
+    return best
+
+
+# sum(d) + max(d) up to 2^61, which signed 64-bit values of the recurrence have room for, and beyond 2^62
+@pytest.mark.parametrize("least, most", [(0, 61), (62, 63)])
+@pytest.mark.parametrize("batch, n", [(1, 152), (1000, 64)])
+def test_what_64_bits_cost(batch, n, least, most):
+    """Chains that need 64 bits go with the others' kernels, in wider arithmetic, and not one after the other to a lane:
+    nine times as long then, up to two in 64 bits."""
+    rng = np.random.default_rng(n)
+    aligned = torch.from_numpy(inputs.uniform_aligned_chains(1, n, batch, 256, 32768)).cuda()
+    lo = (1 << least) // (n + 2) + 1
+    wide = torch.from_numpy(rng.integers(lo, ((1 << most) - 1) // (n + 2), size=(n + 1, batch)).astype(np.int64) | 1).cuda()
+    a, w = (shortest_us(lambda: B.ckpt_solve_linear(d)) for d in (aligned, wide))
+    print(f"{batch} chains of {n} layers: aligned {a:.1f} us, in 64 bits {w:.1f} us", flush=True)
+    assert w < 4 * a
