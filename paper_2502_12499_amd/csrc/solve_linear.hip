@@ -1009,7 +1009,8 @@ __device__ __forceinline__ bool rows_chains(const int64_t *__restrict__ dp, cons
     const int lane = threadIdx.x % kWave, l = lane % kRow;
     // the chain once over: validity, the trailing zeros its sizes share, their sum and largest
     constexpr int kLoads = 4;
-    int64_t bits = 0, sum = 0, mx = 0;
+    int64_t bits = 0, mx = 0;
+    uint64_t sum = 0;
     for (int k0 = 0; __builtin_amdgcn_ballot_w64(k0 <= n) != 0; k0 += kLoads * kRow) {
         int64_t x[kLoads];
 #pragma unroll
@@ -1017,23 +1018,33 @@ __device__ __forceinline__ bool rows_chains(const int64_t *__restrict__ dp, cons
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
             bits |= x[u] > 0 ? x[u] : INT64_MIN;
-            sum += k0 + u * kRow + l <= n ? x[u] & (((int64_t)1 << 48) - 1) : 0;
+            sum += k0 + u * kRow + l <= n ? (uint64_t)x[u] : 0;
             mx = larger(mx, x[u]);
         }
     }
     bits = row_value<kRow - 1>(row_up_to(bits, (int64_t)0, [](int64_t a, int64_t b) { return a | b; }));
-    sum = row_value<kRow - 1>(row_up_to(sum, (int64_t)0, [](int64_t a, int64_t b) { return a + b; }));
+    const auto add = [](uint64_t a, uint64_t b) { return a + b; };
+    sum = row_value<kRow - 1>(row_up_to(sum, (uint64_t)0, add));
     mx = row_value<kRow - 1>(row_up_to(mx, (int64_t)0, [](int64_t a, int64_t b) { return larger(a, b); }));
     static_assert(kWaveMaxLayers + 2 <= 1 << 15, "sums of sizes below 2^48 stay below 2^63");
+    bool fits = bits > 0;  // (a size that is not positive sets the top bit)
+    if (__builtin_amdgcn_ballot_w64(bits >> 48 != 0) != 0) {
+        uint64_t high = 0;
+        for (int k0 = 0; __builtin_amdgcn_ballot_w64(k0 <= n) != 0; k0 += kRow)
+            high += k0 + l <= n ? (uint64_t)dp[(int64_t)(k0 + l) * pstride] >> 32 : 0;
+        high = row_value<kRow - 1>(row_up_to(high, (uint64_t)0, add));
+        fits = fits && !chain_overflows(sum, high, (uint64_t)mx);
+    }
     const int sh = __ffsll((unsigned long long)bits) - 1;
-    const int64_t most = bits >> 48 == 0 ? (sum + mx) >> sh : INT64_MAX;  // (a size that is not positive sets the top bit)
-    const bool fits = most < kRowBeyond<double>;
-    const auto at = [&](int k) -> int64_t { return dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
+    const uint64_t most = (sum + (uint64_t)mx) >> sh;
+    const auto at = [&](int k) -> uint64_t { return (uint64_t)dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
     uint16_t *const nxt = (uint16_t *)(lds + kRowsQueueBytes) + (size_t)(lane / kRow) * (n_most + 1);
     int64_t peak = -1;
     if (__builtin_amdgcn_ballot_w64(fits) != 0) {
-        if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<int32_t>) != 0)
-            peak = (int64_t)rows_steps<double>([&](int k) { return (double)at(k); }, n, lds, nxt);
+        if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<double>) != 0)
+            peak = (int64_t)rows_steps<uint64_t>([&](int k) { return at(k); }, n, lds, nxt);
+        else if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<int32_t>) != 0)
+            peak = (int64_t)rows_steps<double>([&](int k) { return (double)(int64_t)at(k); }, n, lds, nxt);
         else
             peak = rows_steps<int32_t>([&](int k) { return (int32_t)at(k); }, n, lds, nxt);
     }

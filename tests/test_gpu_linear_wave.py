@@ -197,10 +197,10 @@ def shortest_us(call, tries=7, calls=8):
 
 # sum(d) + max(d) up to 2^61, which signed 64-bit values of the recurrence have room for, and beyond 2^62
 @pytest.mark.parametrize("least, most", [(0, 61), (62, 63)])
-@pytest.mark.parametrize("batch, n", [(1, 152), (1000, 64)])
+@pytest.mark.parametrize("batch, n", [(1, 152), (1000, 64), (2048, 64), (16384, 64), (65536, 12), (65536, 64), (65537, 64)])
 def test_what_64_bits_cost(batch, n, least, most):
-    """Chains that need 64 bits go with the others' kernels, in wider arithmetic, and not one after the other to a lane:
-    nine times as long then, up to two in 64 bits."""
+    """Chains that need 64 bits go with the others' kernels, in wider arithmetic, and not one after the other to a lane or
+    a wave: four to twenty times as long then, up to 2.4 times so."""
     rng = np.random.default_rng(n)
     aligned = torch.from_numpy(inputs.uniform_aligned_chains(1, n, batch, 256, 32768)).cuda()
     lo = (1 << least) // (n + 2) + 1
