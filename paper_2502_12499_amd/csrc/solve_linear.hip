@@ -44,12 +44,13 @@
 //        the chain's mask_out slot i.  A final forward sweep turns them into the mask.
 //        A lane defers its chain when a ring fills, the values outgrow 30 bits,
 //        a step exceeds 255 positions, or a size is not positive: it appends
-//        the chain to a list in the workspace.
+//        the chain to a list in the workspace, those with sizes of 2^44 and more from the list's end.
 //   rows and waves  few chains, and what the ring kernel leaves of many: four chains to a wave (linear_rows.h) or one
 //        (linear_wave.h), in 32-bit integers, doubles or 64-bit integers.  Chains they cannot take either (more than 64
 //        entries live) go on a second list.
-//   wide kernel     one lane per chain on the first list, where rows do not pay (up to 16 layers, more than 2,047): the
-//        ring kernel's algorithm in 64-bit arithmetic with plain loops.  What it cannot take goes on the second list.
+//   wide kernel     one lane per chain on the first list, where rows do not pay: short and long chains (rows_list_pays),
+//        and up to 64 layers those that are many (Deferred): the ring kernel's algorithm in 64-bit arithmetic with plain
+//        loops.  What it cannot take goes on the second list, or is done by the wave.
 //   list kernel     one wave per chain of the second list (lane 0 works),
 //        64-bit values, stacks of full capacity n+1 in LDS (n <= 2047) or in
 //        the workspace.  Correct for any input, and the only writer of error
@@ -80,11 +81,12 @@ constexpr int kLdsStackMaxN = 2047;
 constexpr int kWaveMaxLayers = 16383;  // of the wave kernel: 34 KB of LDS
 
 struct LinearWs {
-    int32_t *count;   // [2] chains deferred by the ring kernel, chains deferred again by the wide kernel
-                      // (first 256 bytes)
-    int32_t *list;    // [batch] the former
-    int32_t *list2;   // [batch] the latter
+    int32_t *count;   // [3] chains deferred by the ring kernel, chains deferred again by the kernels after it, and those
+                      // of the former that have a size of 2^44 or more (first 256 bytes)
+    int32_t *list;    // [batch] the first; the last from the end backwards
+    int32_t *list2;   // [batch] the second
     char *scratch;    // kListBlocks * stack_bytes(n)
+    int32_t *list_end;
 };
 
 // Full-capacity state of one chain: qM, qT, recD (int64), qJ, recK, nxt (int32), padded to 256 bytes.
@@ -98,12 +100,34 @@ __host__ LinearWs carve_linear(void *ws, int64_t batch, int n)
     LinearWs w;
     w.count = (int32_t *)p; p += 256;
     w.list = (int32_t *)p;  p += align_up((size_t)batch * 4);
+    w.list_end = w.list + batch;
     w.list2 = (int32_t *)p; p += align_up((size_t)batch * 4);
     w.scratch = p;
     return w;
 }
 
-__global__ void linear_reset_kernel(LinearWs w) { w.count[0] = 0; w.count[1] = 0; }
+__global__ void linear_reset_kernel(LinearWs w) { w.count[0] = w.count[1] = w.count[2] = 0; }
+
+// The chains that the ring kernel deferred, and the part of them that lanes take and not rows: up to kLanesLayers layers
+// the chains with large sizes, which need 64 bits, up to kLanesFewLayers the others, where there are enough of them.
+// Lanes take 1.8 us a position whatever their number, up to 80,000; rows take time in proportion and start better.  Rows
+// and lanes, us: 65,537 chains in 64 bits, 17 layers 70 and 50, 24 71 and 63, 32 74 and 79; 131,072 of 32 137 and 122, of
+// 48 183 and 171; 1,048,576 of 48 1,357 and 1,310; in doubles 65,537 of 17 60 and 49, of 24 64 and 62, 131,072 of 24 115
+// and 114; but one chain in fifty in 64 bits, 65,537 of 24 layers 41 and 65.
+constexpr int kLanesFewLayers = 23, kLanesLayers = kWave, kLanesPerLayer = 1984;
+struct Deferred {
+    int few, all;       // the first `few` numbers are those without large sizes
+    int first, end;     // lanes take these
+    const int32_t *list, *list_end;
+    __device__ Deferred(const LinearWs &w, int n) : few(w.count[0]), all(few + w.count[2]), list(w.list), list_end(w.list_end)
+    {
+        const bool these = n <= kLanesFewLayers && few >= kLanesPerLayer * n,
+                   large = n <= kLanesLayers && all - few >= kLanesPerLayer * n;
+        first = these ? 0 : few;
+        end = large ? all : few;
+    }
+    __device__ int32_t operator[](int item) const { return item < few ? list[item] : list_end[few - 1 - item]; }
+};
 
 // Puts every chain on the first deferred list (layouts the ring kernel does not address).
 __global__ void linear_defer_all_kernel(int64_t batch, LinearWs w)
@@ -263,6 +287,7 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
         defer |= (Jfull - (uint32_t)ilow) > 248u;
     };
 
+    uint32_t large = 0;            // the sizes' upper halves together
     u32x32 logA = {}, logB = {};   // LOG_REGS: the steps of chunk k as bytes of logA[k] (u = 0..3) and logB[k] (u = 4..7)
     uint32_t acc0 = 0, acc1 = 0;   // ... of the chunk under way
     // One step of the recurrence for position i = ihi - u, whose size x is already in a register.
@@ -464,6 +489,7 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
             all |= x;
             zero |= x == 0;
         }
+        large |= (uint32_t)(all >> 32);
         if (!defer) chunk_check(all, zero, max(ihi - kChunk + 1, 0));
         if (!defer) {
 #pragma unroll
@@ -483,8 +509,10 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
 
     if (!live) return;
     if (defer) {
-        const int slot = atomicAdd(w.count, 1);
-        w.list[slot] = (int32_t)(c + list_base);
+        if (large >> 12)
+            w.list_end[-1 - atomicAdd(w.count + 2, 1)] = (int32_t)(c + list_base);
+        else
+            w.list[atomicAdd(w.count, 1)] = (int32_t)(c + list_base);
         return;
     }
     peak_out[c] = (int64_t)((uint64_t)Mi << sh);
@@ -548,6 +576,97 @@ __global__ __launch_bounds__(kWave) void linear_ring_kernel(const int64_t *__res
 }
 
 // ---------------------------------------------------------------------------
+// one chain by one wave
+// ---------------------------------------------------------------------------
+
+__device__ inline int uniform_bits(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// DOUBLES: for values below 2^52 (997 unrounded chains of 1,001 layers 106 us, 124 in 64-bit integers); not where it only
+// takes what rows leave, for it costs those registers.
+// One chain, its results included; false (with nothing written) if it is left to the list kernel.
+template <bool DOUBLES = false>
+__device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const int n, const int64_t pstride,
+                                           uint8_t *__restrict__ mp, int64_t *__restrict__ peak_out,
+                                           int32_t *__restrict__ status_out, unsigned char *lds)
+{
+    const int lane = threadIdx.x % kWave;
+    // the chain once over: validity, the trailing zeros its sizes share, their sum and largest
+    int64_t bits = 0, sum = 0, mx = 0;
+    bool bad = false;
+    const auto pass = [&](auto in_flight) {
+        constexpr int kRows = decltype(in_flight)::value;
+        for (int k0 = 0; k0 <= n; k0 += kRows * kWave) {
+            int64_t x[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) x[u] = dp[(int64_t)min(k0 + u * kWave + lane, n) * pstride];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                bad |= x[u] <= 0;
+                bits |= x[u];
+                sum = (int64_t)((uint64_t)sum + (k0 + u * kWave + lane <= n ? (uint64_t)x[u] : 0));
+                mx = larger(mx, x[u]);
+            }
+        }
+    };
+    if (n < 4 * kWave) pass(std::integral_constant<int, 4>());
+    else pass(std::integral_constant<int, 16>());
+    bits = lane_value(bits_up_to(bits), kWave - 1);
+    sum = lane_value(sum_up_to(sum), kWave - 1);
+    mx = lane_value(max_up_to(mx), kWave - 1);
+    int32_t status = __any(bad) ? CKPT_ERR_SIZE : CKPT_OK;
+    static_assert(kWaveMaxLayers + 2 <= 1 << 15, "sizes below 2^48 do not overflow");
+    if (status == CKPT_OK && (bits >> 48) != 0) {
+        int64_t high = 0;
+        for (int k = lane; k <= n; k += kWave) high += dp[(int64_t)k * pstride] >> 32;
+        high = lane_value(sum_up_to(high), kWave - 1);
+        if (chain_overflows((uint64_t)sum, (uint64_t)high, (uint64_t)mx)) status = CKPT_ERR_OVERFLOW;
+    }
+    uint16_t *const nxt = (uint16_t *)(lds + kQueueBytes);
+    int64_t peak = -1;
+    if (status == CKPT_OK) {
+        const int sh = uniform_bits(__ffsll((unsigned long long)bits) - 1);
+        const auto at = [&](int k) -> uint64_t { return (uint64_t)dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
+        bool done;
+        const uint64_t most = (uint64_t)(sum + mx) >> sh;
+        if (most < (uint64_t)kBeyond<int32_t>) {
+            int32_t m0;
+            done = wave_steps<int32_t>([&](int k) { return (int32_t)at(k); }, n, lds, nxt, m0);
+            peak = (int64_t)m0 << sh;
+        } else if (DOUBLES && most < (uint64_t)kBeyond<double>) {
+            double m0;
+            done = wave_steps<double>([&](int k) { return (double)at(k); }, n, lds, nxt, m0);
+            peak = done ? (int64_t)m0 << sh : -1;
+        } else {
+            uint64_t m0;
+            done = wave_steps<uint64_t>([&](int k) { return at(k); }, n, lds, nxt, m0);
+            peak = done ? (int64_t)(m0 << sh) : -1;
+        }
+        if (!done) return false;
+    }
+    // The set: 64 positions at a time, their steps in the lanes, and from one checkpoint to the next by reading a lane
+    // (an LDS read per checkpoint costs three times as much).
+    __syncthreads();
+    const int none = n + 2 * kWave;
+    int cur = status == CKPT_OK ? 0 : none;
+    int steps = nxt[min(lane, n - 1)];
+    for (int b = 0; b <= n; b += kWave) {
+        const int ahead = nxt[min(b + kWave + lane, n - 1)];
+        uint64_t set = 0;
+        while (cur < b + kWave) {
+            set |= 1ull << (cur - b);
+            cur = cur == n ? none : __builtin_amdgcn_readlane(steps, cur - b);
+        }
+        if (b + lane <= n) mp[(int64_t)(b + lane) * pstride] = (uint8_t)((set >> lane) & 1ull);
+        steps = ahead;
+    }
+    if (lane == 0) {
+        *peak_out = peak;
+        if (status_out) *status_out = status;
+    }
+    return true;
+}
+
+// ---------------------------------------------------------------------------
 // wide kernel: one lane per chain deferred by the ring kernel, 64-bit values
 // ---------------------------------------------------------------------------
 
@@ -574,6 +693,9 @@ constexpr int kWideRows = 8;  // rows read together
 // 262,144 chains.)
 // With `groups` (a ragged call) a listed number is a chain's place among all chains: its group
 // gives the length, where the chain is staged and where its results go, per lane.
+// PART: the deferred chains that rows leave to lanes (of at most kLanesLayers layers), and what is left of those by the
+// whole wave, chain by chain; else all that are deferred.
+template <bool PART>
 __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__restrict__ d, int n_all,
                                                             int64_t cstride, int64_t pstride_all,
                                                             uint8_t *__restrict__ mask_out,
@@ -583,10 +705,11 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
 {
     __shared__ WideEntry ring[kRing][kWave];
     const int lane = threadIdx.x;
-    const int count = w.count[0];
-    for (int item0 = blockIdx.x * kWave; item0 < count; item0 += gridDim.x * kWave) {
+    const Deferred deferred(w, n_all);
+    const int count = PART ? deferred.end : deferred.all;
+    for (int item0 = (PART ? deferred.first : 0) + blockIdx.x * kWave; item0 < count; item0 += gridDim.x * kWave) {
         const bool live = item0 + lane < count;
-        const int64_t c = w.list[live ? item0 + lane : count - 1];  // the number results are filed under
+        const int64_t c = deferred[live ? item0 + lane : count - 1];  // the number results are filed under
         int n = n_all;
         int64_t pstride = pstride_all;
         const int64_t *dp = d + c * cstride;
@@ -690,9 +813,22 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
 #pragma unroll
             for (int u = 0; u < kWideRows; ++u) rows[u] = ahead[u];
         }
+        if (PART) {
+            for (uint64_t left = __builtin_amdgcn_ballot_w64(live && out); left != 0; left &= left - 1) {
+                const int of = __builtin_ctzll((unsigned long long)left);
+                const int64_t one = __shfl(c, of, kWave);
+                const int its_n = __shfl(n, of, kWave);
+                const int64_t its_stride = __shfl(pstride, of, kWave), at_d = __shfl((int64_t)(dp - d), of, kWave);
+                static_assert(sizeof(ring) >= kQueueBytes + 2 * (kLanesLayers + 1), "the wave's LDS, none of it in use now");
+                __syncthreads();
+                (void)wave_chain(d + at_d, its_n, its_stride, mask_out + at_d, peak_out + one,
+                                 status_out ? status_out + one : nullptr, (unsigned char *)ring);
+            }
+            __syncthreads();
+        }
         if (!live) continue;
         if (out) {
-            w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)c;
+            if (!PART) w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)c;
             continue;
         }
         peak_out[c] = Mi;
@@ -720,8 +856,6 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
 // ---------------------------------------------------------------------------
 
 extern __shared__ __align__(16) unsigned char lin_lds[];
-
-__device__ inline int uniform_bits(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // One chain by one lane: the recurrence with stacks of full capacity.  `base`: room for the stacks and the steps
 // of a chain of n_room layers.
@@ -858,91 +992,6 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
 // wave kernel: one wave per chain
 // ---------------------------------------------------------------------------
 
-// DOUBLES: for values below 2^52 (997 unrounded chains of 1,001 layers 106 us, 124 in 64-bit integers); not where it only
-// takes what rows leave, for it costs those registers.
-// One chain, its results included; false (with nothing written) if it is left to the list kernel.
-template <bool DOUBLES = false>
-__device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const int n, const int64_t pstride,
-                                           uint8_t *__restrict__ mp, int64_t *__restrict__ peak_out,
-                                           int32_t *__restrict__ status_out, unsigned char *lds)
-{
-    const int lane = threadIdx.x % kWave;
-    // the chain once over: validity, the trailing zeros its sizes share, their sum and largest
-    int64_t bits = 0, sum = 0, mx = 0;
-    bool bad = false;
-    const auto pass = [&](auto in_flight) {
-        constexpr int kRows = decltype(in_flight)::value;
-        for (int k0 = 0; k0 <= n; k0 += kRows * kWave) {
-            int64_t x[kRows];
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) x[u] = dp[(int64_t)min(k0 + u * kWave + lane, n) * pstride];
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) {
-                bad |= x[u] <= 0;
-                bits |= x[u];
-                sum = (int64_t)((uint64_t)sum + (k0 + u * kWave + lane <= n ? (uint64_t)x[u] : 0));
-                mx = larger(mx, x[u]);
-            }
-        }
-    };
-    if (n < 4 * kWave) pass(std::integral_constant<int, 4>());
-    else pass(std::integral_constant<int, 16>());
-    bits = lane_value(bits_up_to(bits), kWave - 1);
-    sum = lane_value(sum_up_to(sum), kWave - 1);
-    mx = lane_value(max_up_to(mx), kWave - 1);
-    int32_t status = __any(bad) ? CKPT_ERR_SIZE : CKPT_OK;
-    static_assert(kWaveMaxLayers + 2 <= 1 << 15, "sizes below 2^48 do not overflow");
-    if (status == CKPT_OK && (bits >> 48) != 0) {
-        int64_t high = 0;
-        for (int k = lane; k <= n; k += kWave) high += dp[(int64_t)k * pstride] >> 32;
-        high = lane_value(sum_up_to(high), kWave - 1);
-        if (chain_overflows((uint64_t)sum, (uint64_t)high, (uint64_t)mx)) status = CKPT_ERR_OVERFLOW;
-    }
-    uint16_t *const nxt = (uint16_t *)(lds + kQueueBytes);
-    int64_t peak = -1;
-    if (status == CKPT_OK) {
-        const int sh = uniform_bits(__ffsll((unsigned long long)bits) - 1);
-        const auto at = [&](int k) -> uint64_t { return (uint64_t)dp[(int64_t)(k > 0 ? k : 0) * pstride] >> sh; };
-        bool done;
-        const uint64_t most = (uint64_t)(sum + mx) >> sh;
-        if (most < (uint64_t)kBeyond<int32_t>) {
-            int32_t m0;
-            done = wave_steps<int32_t>([&](int k) { return (int32_t)at(k); }, n, lds, nxt, m0);
-            peak = (int64_t)m0 << sh;
-        } else if (DOUBLES && most < (uint64_t)kBeyond<double>) {
-            double m0;
-            done = wave_steps<double>([&](int k) { return (double)at(k); }, n, lds, nxt, m0);
-            peak = done ? (int64_t)m0 << sh : -1;
-        } else {
-            uint64_t m0;
-            done = wave_steps<uint64_t>([&](int k) { return at(k); }, n, lds, nxt, m0);
-            peak = done ? (int64_t)(m0 << sh) : -1;
-        }
-        if (!done) return false;
-    }
-    // The set: 64 positions at a time, their steps in the lanes, and from one checkpoint to the next by reading a lane
-    // (an LDS read per checkpoint costs three times as much).
-    __syncthreads();
-    const int none = n + 2 * kWave;
-    int cur = status == CKPT_OK ? 0 : none;
-    int steps = nxt[min(lane, n - 1)];
-    for (int b = 0; b <= n; b += kWave) {
-        const int ahead = nxt[min(b + kWave + lane, n - 1)];
-        uint64_t set = 0;
-        while (cur < b + kWave) {
-            set |= 1ull << (cur - b);
-            cur = cur == n ? none : __builtin_amdgcn_readlane(steps, cur - b);
-        }
-        if (b + lane <= n) mp[(int64_t)(b + lane) * pstride] = (uint8_t)((set >> lane) & 1ull);
-        steps = ahead;
-    }
-    if (lane == 0) {
-        *peak_out = peak;
-        if (status_out) *status_out = status;
-    }
-    return true;
-}
-
 // Every group of a ragged call in one launch: a wave looks up the group its 64 chains belong to
 // and solves them where that group is staged, with the step log in registers if the group's
 // chains have up to kLogMaxLayers layers (a wave-uniform branch: long and short groups run side by
@@ -1028,7 +1077,7 @@ __device__ __forceinline__ bool rows_chains(const int64_t *__restrict__ dp, cons
     mx = row_value<kRow - 1>(row_up_to(mx, (int64_t)0, [](int64_t a, int64_t b) { return larger(a, b); }));
     static_assert(kWaveMaxLayers + 2 <= 1 << 15, "sums of sizes below 2^48 stay below 2^63");
     bool fits = bits > 0;  // (a size that is not positive sets the top bit)
-    if (__builtin_amdgcn_ballot_w64(bits >> 48 != 0) != 0) {
+    if (__builtin_amdgcn_ballot_w64(bits >> 48 > 0) != 0) {
         uint64_t high = 0;
         for (int k0 = 0; __builtin_amdgcn_ballot_w64(k0 <= n) != 0; k0 += kRow)
             high += k0 + l <= n ? (uint64_t)dp[(int64_t)(k0 + l) * pstride] >> 32 : 0;
@@ -1111,7 +1160,10 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
                                                                     int32_t *__restrict__ status_out, LinearWs w,
                                                                     const RaggedGroupDev *__restrict__ groups, int n_groups)
 {
-    const int lane = threadIdx.x % kWave, count = w.count[0];
+    const int lane = threadIdx.x % kWave;
+    const Deferred deferred(w, n_all);
+    const int lanes_take = deferred.end - deferred.first, count = deferred.all - lanes_take;
+    const auto listed = [&](int64_t item) -> int64_t { return deferred[(int)(item < deferred.first ? item : item + lanes_take)]; };
     // (c the same in the lanes that are to have the chain)
     struct Chain { int64_t at, pstride; int n; };
     const auto chain = [&](int64_t c) -> Chain {
@@ -1125,14 +1177,14 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
         uint64_t left = 1;
         if (!alone) {
             const bool is_chain = first + lane / kRow < count;
-            const int64_t c = w.list[is_chain ? first + lane / kRow : count - 1];
+            const int64_t c = listed(is_chain ? first + lane / kRow : count - 1);
             const Chain its = chain(c);
             const bool done = rows_chains(d + its.at, is_chain, its.n, n_all, its.pstride, mask_out + its.at, peak_out + c,
                                           status_out ? status_out + c : nullptr, lin_lds);
             left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0);
         }
         for (; left != 0; left &= left - 1) {
-            const int64_t one = w.list[first + __builtin_ctzll((unsigned long long)left) / kRow];
+            const int64_t one = listed(first + __builtin_ctzll((unsigned long long)left) / kRow);
             const Chain at = chain(one);
             __syncthreads();
             const bool by_wave = wave_chain(d + at.at, at.n, at.pstride, mask_out + at.at, peak_out + one,
@@ -1268,20 +1320,23 @@ void launch_list(const int64_t *d, int n, Strides st, uint8_t *mask_out, int64_t
                        in_lds ? lds_stack_bytes(n) : 0, stream, d, n, st.chain, st.pos, mask_out, peak_out, status_out, w,
                        groups, n_groups, off, flagged);
 }
-void launch_wide(const int64_t *d, int64_t batch, int n, int64_t cstride, int64_t pstride, uint8_t *mask_out,
-                 int64_t *peak_out, int32_t *status_out, const LinearWs &w, const RaggedGroupDev *groups, int n_groups,
-                 hipStream_t stream)
+// What the ring kernel deferred.
+void launch_deferred(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out, int64_t *peak_out,
+                     int32_t *status_out, const LinearWs &w, const RaggedGroupDev *groups, int n_groups, hipStream_t stream)
 {
-    if (rows_list_pays(batch, n)) {
+    const bool rows = rows_list_pays(batch, n), part = rows && n <= kLanesLayers;
+    if (rows) {
         const unsigned blocks = (unsigned)std::min<int64_t>((batch + kRowsOfWave - 1) / kRowsOfWave, kRowsListBlocks);
         hipLaunchKernelGGL(linear_rows_list_kernel, dim3(blocks), dim3(kWave), rows_all_lds_bytes(n, false), stream, d, n,
-                           cstride, pstride, mask_out, peak_out, status_out, w, groups, n_groups);
-        return;
+                           st.chain, st.pos, mask_out, peak_out, status_out, w, groups, n_groups);
     }
-    const int64_t need = (batch + kWave - 1) / kWave;
-    const dim3 grid((unsigned)(need < kWideBlocks ? need : kWideBlocks));
-    hipLaunchKernelGGL(linear_wide_kernel, grid, dim3(kWave), 0, stream, d, n, cstride, pstride, mask_out, peak_out,
-                       status_out, w, groups, n_groups);
+    if (!rows || part) {
+        const unsigned blocks = (unsigned)std::min<int64_t>((batch + kWave - 1) / kWave, kWideBlocks);
+        hipLaunchKernelGGL(part ? linear_wide_kernel<true> : linear_wide_kernel<false>, dim3(blocks), dim3(kWave), 0, stream, d,
+                           n, st.chain, st.pos, mask_out, peak_out, status_out, w, groups, n_groups);
+    }
+    // (of so few layers the end of a block never has more than 64 entries live: rows put nothing on the second list either)
+    if (!part) launch_list(d, n, st, mask_out, peak_out, status_out, w, batch, groups, n_groups, nullptr, 0, stream);
 }
 }  // namespace
 
@@ -1322,8 +1377,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     else
         hipLaunchKernelGGL(linear_defer_all_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, stream,
                            batch, w);
-    launch_wide(d, batch, n, st.chain, st.pos, mask_out, peak_out, status_out, w, nullptr, 0, stream);
-    launch_list(d, n, st, mask_out, peak_out, status_out, w, batch, nullptr, 0, nullptr, 0, stream);
+    launch_deferred(d, batch, n, st, mask_out, peak_out, status_out, w, nullptr, 0, stream);
     return hipGetLastError();
 }
 
@@ -1366,9 +1420,7 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
     hipLaunchKernelGGL(per_chain ? linear_ring_ragged_kernel<true> : linear_ring_ragged_kernel<false>,
                        dim3((unsigned)(per_chain ? t.linear_waves : t.waves)), dim3(kWave), 0, stream, d_stage, groups,
                        n_groups, mask_stage, peak_stage, status_stage, w);
-    launch_wide(d_stage, batch, max_layers, 1, 0, mask_stage, peak_stage, status_stage, w, groups, n_groups, stream);
-    launch_list(d_stage, max_layers, Strides{1, 0}, mask_stage, peak_stage, status_stage, w, batch, groups, n_groups, nullptr, 0,
-                stream);
+    launch_deferred(d_stage, batch, max_layers, Strides{1, 0}, mask_stage, peak_stage, status_stage, w, groups, n_groups, stream);
     return hipGetLastError();
 }
 

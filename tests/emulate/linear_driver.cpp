@@ -45,9 +45,9 @@ Sizes up_to(int n, int k, int64_t most)
     return with(d, k, (most - rest) / 2);
 }
 
-enum Form { kLanes, kWideLanes, kWaves, kRows, kListedRows, kFlatWaves, kFlatRows };
+enum Form { kLanes, kWideLanes, kWaves, kRows, kListedRows, kRowsAndLanes, kFlatWaves, kFlatRows };
 const char *const kNames[] = {"a lane per chain", "a lane per chain in 64 bits", "a wave per chain", "a row per chain",
-                              "a row per listed chain", "a wave per chain of a ragged batch", "a row per chain of a ragged batch"};
+                              "a row per listed chain", "a row or a lane per listed chain", "a wave per chain of a ragged batch", "a row per chain of a ragged batch"};
 
 void launch_form(Form form, const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n, Strides st,
                  uint8_t *mask, int64_t *peak, int32_t *status)
@@ -60,18 +60,22 @@ void launch_form(Form form, const int64_t *d, const int64_t *off, const int32_t 
     case kLanes:
     case kWideLanes:
     case kListedRows:
-        if (form == kLanes)
+    case kRowsAndLanes:
+        if (form == kLanes || form == kRowsAndLanes)
             hipLaunchKernelGGL(n <= kLogMaxLayers ? linear_ring_kernel<true> : linear_ring_kernel<false>, dim3(lanes),
                                dim3(kWave), 0, nullptr, d, batch, n, st.chain, st.pos, mask, peak, status, w);
         else
             hipLaunchKernelGGL(linear_defer_all_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, nullptr, batch, w);
-        if (form == kListedRows)
+        if (form == kListedRows || form == kRowsAndLanes)
             hipLaunchKernelGGL(linear_rows_list_kernel, dim3(rows), dim3(kWave), rows_all_lds_bytes(n, false), nullptr, d, n,
                                st.chain, st.pos, mask, peak, status, w, (const RaggedGroupDev *)nullptr, 0);
-        else
-            hipLaunchKernelGGL(linear_wide_kernel, dim3(lanes), dim3(kWave), 0, nullptr, d, n, st.chain, st.pos, mask, peak,
+        if (form == kRowsAndLanes)
+            hipLaunchKernelGGL(linear_wide_kernel<true>, dim3(lanes), dim3(kWave), 0, nullptr, d, n, st.chain, st.pos, mask, peak,
                                status, w, (const RaggedGroupDev *)nullptr, 0);
-        launch_list(d, n, st, mask, peak, status, w, batch, nullptr, 0, nullptr, 0, nullptr);
+        else if (form != kListedRows)
+            hipLaunchKernelGGL(linear_wide_kernel<false>, dim3(lanes), dim3(kWave), 0, nullptr, d, n, st.chain, st.pos, mask, peak,
+                               status, w, (const RaggedGroupDev *)nullptr, 0);
+        if (form != kRowsAndLanes) launch_list(d, n, st, mask, peak, status, w, batch, nullptr, 0, nullptr, 0, nullptr);
         break;
     case kWaves:
         launch_solve_linear(d, batch, n, st, mask, peak, status, ws, nullptr);  // (as few as these get a wave each)
@@ -192,6 +196,15 @@ int main()
         }
         check("fewer trailing zeros", chains, {kLanes});
     }
+    // what the lanes defer, on both sides of the numbers from which on the lanes of the next kernel take it
+    for (const int few : {2 * kLanesPerLayer - 1, 2 * kLanesPerLayer})
+        for (const int large : {2 * kLanesPerLayer - 1, 2 * kLanesPerLayer}) {
+            std::vector<Sizes> chains;
+            for (int c = 0; c < few; ++c) chains.push_back(with(uniform(2, 1ll << 31, 1ll << 34), 1, c % 500 ? (1ll << 32) + 1 : -c));
+            for (int c = 0; c < large; ++c) chains.push_back(with(uniform(2, 1ll << 60, INT64_MAX / 5), 0, c % 500 ? (1ll << 59) + 1 : INT64_MAX));
+            std::shuffle(chains.begin(), chains.end(), rng);
+            check("deferred chains", chains, {kRowsAndLanes});
+        }
     for (const int longest : {5, 40, 200}) {
         std::vector<Sizes> chains;
         while (chains.size() < 90)

@@ -70,6 +70,26 @@ def test_what_the_lanes_of_a_larger_batch_leave(n, unrounded):
     assert np.array_equal(mask.cpu().numpy().reshape(want_mask.shape), want_mask)
 
 
+@pytest.mark.parametrize("n, large", [(16, 60000), (17, 33727), (17, 33728), (24, 47615), (24, 47616), (33, 65600), (64, 900)])
+def test_large_sizes_that_the_lanes_of_a_larger_batch_leave(n, large):
+    """Those of 65,600 chains that need 64 bits, on both sides of the number from which on lanes take them and not rows, a
+    bad one in fifty among them."""
+    print(f"linear: 65,600 chains of {n} layers, {large} with large sizes", flush=True)
+    rng = np.random.default_rng(n)
+    d = inputs.uniform_aligned_chains(8, n, 65600, 256, 32768)
+    at = rng.permutation(65600)[:large]
+    d[:, at] = rng.integers(1 << 44, (1 << 62) // (n + 2), size=(n + 1, large)) | 1
+    want_peak, want_mask = oracle.batch_solve_dynamic(inputs.chain_major(d))
+    want_status = np.zeros(65600, dtype=np.int32)
+    for k, c in enumerate(at[::50]):
+        d[k % (n + 1), c] = 0 if k % 2 else (1 << 63) - 1
+        want_status[c], want_peak[c], want_mask[c] = 3 if k % 2 else 4, -1, 0
+    mask, peak, status = B.ckpt_solve_linear(torch.from_numpy(d).cuda())
+    assert np.array_equal(status.cpu().numpy(), want_status)
+    assert np.array_equal(peak.cpu().numpy(), want_peak)
+    assert np.array_equal(mask.cpu().numpy().T, want_mask)
+
+
 def test_sums_at_the_ends_of_the_value_ranges():
     n, batch = 40, 1028
     rng = np.random.default_rng(5)

@@ -197,7 +197,8 @@ def shortest_us(call, tries=7, calls=8):
 
 # sum(d) + max(d) up to 2^61, which signed 64-bit values of the recurrence have room for, and beyond 2^62
 @pytest.mark.parametrize("least, most", [(0, 61), (62, 63)])
-@pytest.mark.parametrize("batch, n", [(1, 152), (1000, 64), (2048, 64), (16384, 64), (65536, 12), (65536, 64), (65537, 64)])
+@pytest.mark.parametrize("batch, n", [(1, 152), (1000, 64), (2048, 64), (16384, 64), (65536, 12), (65536, 64), (65537, 64),
+                                      (131072, 17)])
 def test_what_64_bits_cost(batch, n, least, most):
     """Chains that need 64 bits go with the others' kernels, in wider arithmetic, and not one after the other to a lane or
     a wave: four to twenty times as long then, up to 2.4 times so."""
