@@ -1250,7 +1250,7 @@ __global__ __launch_bounds__(kWave) void search_round_kernel(int n, int points, 
 // The end of a round, one wave per chain: the best of the points, and the intervals that stay open under the best
 // cost.  (A launch of its own: as the work of the round's last wave it took a device-wide fence in every wave, 36 ns
 // of the whole chip each, 2.2 of 2.3 ms for 1,000 chains of 300 layers.)
-__global__ __launch_bounds__(kWave) void search_close_kernel(int n, int points, int most, int round, LongWs w)
+__global__ __launch_bounds__(kWave) void search_close_kernel(int n, int points, int few_budgets, int round, LongWs w)
 {
     const int64_t c = blockIdx.x;
     LongMeta *meta = w.meta + c;
@@ -1304,9 +1304,9 @@ __global__ __launch_bounds__(kWave) void search_close_kernel(int n, int points, 
 #pragma unroll
     for (int k = kWave / 2; k >= 1; k >>= 1) whole += __shfl_xor(whole, k, kWave);
     // About n budgets lie in a width of one mean layer (counted on chains of 152 to 4,096 layers of every kind: within
-    // 30 %, repeated values among them).  If as many as the finish has waves for are left, the second round is left out:
-    // 1,024 points leave 70 to 350 of a chain of 1,001 layers.
-    const bool few = round == 0 && count < kOpenMax && whole * (float)n * (float)n <= (float)most * (float)meta->all;
+    // 30 %, repeated values among them).  If few are left, the second round is left out: 1,024 points leave 70 to 350 of a
+    // chain of 1,001 layers.
+    const bool few = round == 0 && count < kOpenMax && whole * (float)n * (float)n <= (float)few_budgets * (float)meta->all;
     Open *out = w.open + (c * 3 + (few ? 2 : round + 1)) * kOpenMax;
     int slot = incl - many;
     int64_t tail_lo = INT64_MAX, tail_hi = -1;
@@ -1810,12 +1810,17 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
     (void)carve_long(ws, batch, n, &w);
     const int points = long_points(batch, n), waves = finish_waves(batch, n);
     const int most = 2 * waves < seen_slots(n) / 2 ? 2 * waves : seen_slots(n) / 2;
+    // Budgets that a second round does not pay for: one for each wave of the finish; half as many where the chains fill the
+    // chip, for the round's points take a wave each too, and the finish records sets.  At one and at two budgets a wave
+    // instead, 16 unrounded chains of 152 layers 104 and 140 us (87), of 256 105 and 120 (104), 100 of 129 116 and 184 (116);
+    // at half, 4 chains of 256 layers of a network 98 (81), one of 256 aligned ones 71 (61).
+    const int few_budgets = batch < 8 ? waves : waves / 2;
     const unsigned B = (unsigned)batch;
     hipLaunchKernelGGL(search_table_kernel, dim3(B), dim3(kTableThreads), ((size_t)n + 1) * 4, stream, d, n, st.chain,
                        st.pos, points, waves, w);
     for (int round = 0; round < 2; ++round) {
         hipLaunchKernelGGL(search_round_kernel, dim3((unsigned)points, B), dim3(kWave), f_lds, stream, n, points, round, w);
-        hipLaunchKernelGGL(search_close_kernel, dim3(B), dim3(kWave), 0, stream, n, points, most, round, w);
+        hipLaunchKernelGGL(search_close_kernel, dim3(B), dim3(kWave), 0, stream, n, points, few_budgets, round, w);
     }
     const dim3 cutters((unsigned)list_threads(batch, n));
     if (n <= kListMost) {

@@ -9,6 +9,7 @@ import oracle
 from paper_2502_12499_amd import binding as B
 from paper_2502_12499_amd import inputs
 from test_gpu_cubic_search import one_large_size
+from timing import shortest_us
 
 pytestmark = pytest.mark.gpu
 
@@ -178,21 +179,6 @@ def test_many_long_chains_of_a_ragged_batch(batch):
         assert (status.cpu().numpy() == 0).all()
         assert np.array_equal(peak.cpu().numpy(), want_peak)
         assert np.array_equal(mask.cpu().numpy(), want_mask)
-
-
-def shortest_us(call, tries=7, calls=8):
-    """The shortest mean time of `calls` calls in a row."""
-    call()
-    best = float("inf")
-    for _ in range(tries):
-        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        begin.record()
-        for _ in range(calls):
-            call()
-        end.record()
-        torch.cuda.synchronize()
-        best = min(best, begin.elapsed_time(end) / calls * 1e3)
-    return best
 
 
 # sum(d) + max(d) up to 2^61, which signed 64-bit values of the recurrence have room for, and beyond 2^62
