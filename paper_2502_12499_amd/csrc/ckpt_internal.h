@@ -208,14 +208,20 @@ hipError_t launch_cubic_search_long(const int64_t *d, int64_t batch, int n, Stri
                                     int64_t *peak_out, int64_t *budget_out, int32_t *status_out, void *ws,
                                     hipStream_t stream);
 // The same for a ragged batch whose chains all have up to kSearchMaxLayers layers, on the flat arrays
-// themselves.  A launch per class of lengths (its LDS is that of the longest chain in it); longest[k]: the
-// longest chain of class k, 0 if it has none.  count: one value, list: `batch` values of scratch.
+// themselves, in one launch with the LDS of the longest chain or in one per class of lengths.  count: one value,
+// list: `batch` values of scratch.
 constexpr int kSearchClasses = 4;
 __host__ __device__ inline int search_class_limit(int k) { return 32 << k; }
 static_assert((32 << (kSearchClasses - 1)) == kSearchMaxLayers, "the last class ends where the search does");
-hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch, const int *longest,
-                                      uint8_t *mask_out, int64_t *peak_out, int64_t *budget_out, int32_t *status_out,
-                                      int32_t *count, int32_t *list, hipStream_t stream);
+// About what a chain of n layers takes a wave, us (aligned ones; 24 layers 13, 64 32, 152 102, 256 234).
+inline float search_us(int n) { return 6.0f + 0.25f * (float)n + 0.0025f * (float)n * (float)n; }
+struct SearchClass {
+    int longest = 0;      // 0: no chain
+    float us = 0.0f;      // search_us of all its chains
+};
+hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch,
+                                      const SearchClass (&classes)[kSearchClasses], uint8_t *mask_out, int64_t *peak_out,
+                                      int64_t *budget_out, int32_t *status_out, int32_t *count, int32_t *list, hipStream_t stream);
 // entries per chain of the two trace arrays: one per lane of the chain's waves of 64 budgets
 int64_t cubic_trace_len(int n);
 

@@ -859,12 +859,22 @@ inline int64_t at_once(size_t lds) { return 256 * ((160 << 10) / (int64_t)align_
 // A ragged batch goes in one launch up to this many turns of it, with the longest chain's LDS for all: the classes one
 // after the other each wait for their slowest wave.  1,000 chains of 2 to 152 layers 114 us (four launches 247), 4,096
 // 194 (335), 8,192 373 (387), 16,384 668 (567); of 2 to 256 layers 4,096 427 (519), 8,192 785 (798), 16,384 1,546
-// (1,309).
+// (1,309).  But a launch lasts as long as its slowest wave, and as all its chains together take the waves that the chip
+// holds with its LDS; where that says more than the launches of the classes would take (8 us more for each), the short
+// chains are too many for the long ones' LDS: 16,383 chains of 24 layers and one of 64 149 us (127 in two launches), 5,900
+// of 64 and 100 of 152 310 us (259).
 constexpr int64_t kOneLaunchTurns = 8;
-// ... with LDS for 64 bits up to this many turns of that: a second launch for the chains that need them costs as much as
-// a second turn, and more than 192 layers of unrounded sizes mostly need them.  512 chains of 2 to 256 unrounded layers
-// 283 us with two turns, 548 in 32 bits with a second launch; of 15, 24 and 152 layers 219 and 155.
-inline int64_t wide_turns(int longest) { return longest > 192 ? 2 : 1; }
+inline float launch_us(int longest, float us, int width) { return std::max(search_us(longest), us / (float)at_once(search_lds_bytes(longest, width))); }
+// ... with LDS for 64 bits up to one turn of that, for a second launch for the chains that need them costs as much as a
+// second turn: 512 chains of 15, 24 and 152 unrounded layers 219 us with two turns, 155 in 32 bits with a second launch.
+// More than 192 layers of unrounded sizes mostly need them, and a chain of those in the second launch is what the call
+// waits for: there up to twice the longest chain's time, 1,000 chains of 2 to 256 unrounded layers 400 us (627), 1,007 of
+// 24 and 16 of 256 339 (663); aligned ones 239 (244) and 209 (211).  700 of 224 to 256 layers are beyond: 573 (377) aligned.
+inline bool wide_first(int64_t batch, int longest, float us)
+{
+    const int64_t turn = at_once(search_lds_bytes(longest, 8));
+    return longest > 192 ? batch < kSearchSplitFrom && us <= 2.0f * search_us(longest) * (float)turn : batch <= turn;
+}
 
 }  // namespace
 
@@ -892,9 +902,9 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
     return hipGetLastError();
 }
 
-hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch, const int *longest,
-                                      uint8_t *mask_out, int64_t *peak_out, int64_t *budget_out, int32_t *status_out,
-                                      int32_t *count, int32_t *list, hipStream_t stream)
+hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_dev, int64_t batch,
+                                      const SearchClass (&class_of)[kSearchClasses], uint8_t *mask_out, int64_t *peak_out,
+                                      int64_t *budget_out, int32_t *status_out, int32_t *count, int32_t *list, hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
     const hipError_t e = raise_search_lds_limit();
@@ -902,22 +912,28 @@ hipError_t launch_cubic_search_ragged(const int64_t *d, const int64_t *offsets_d
     const dim3 block(kWave);
     const SearchWs w{count, list};
     int top = kSearchClasses - 1;
-    while (longest[top] == 0) --top;
-    const int all = longest[top];
-    const bool one_launch = batch <= kOneLaunchTurns * at_once(search_lds_bytes(all, 4));
+    while (class_of[top].longest == 0) --top;
+    const int all = class_of[top].longest;
+    float us = 0.0f, several = 0.0f;
+    for (const SearchClass &k : class_of)
+        if (k.longest != 0) {
+            us += k.us;
+            several += launch_us(k.longest, k.us, 4) + 8.0f;
+        }
+    const bool one_launch = batch <= kOneLaunchTurns * at_once(search_lds_bytes(all, 4)) && launch_us(all, us, 4) <= 1.1f * several;
     // all of the arithmetic in the first launch (the longest chains' LDS says whether the rest needs a second one)
-    const bool wide = one_launch ? batch <= wide_turns(all) * at_once(search_lds_bytes(all, 8)) : batch < kSearchSplitFrom;
+    const bool wide = one_launch ? wide_first(batch, all, us) : batch < kSearchSplitFrom;
     const auto lds = [&](int n) { return (unsigned)search_lds_bytes(n, wide ? 8 : 4); };
     if (!wide) hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
     if (one_launch) {
         unsigned classes = 0, many = 0;
         for (int k = top; k >= 0; --k)  // the longest chains first
-            if (longest[k] != 0) classes |= (unsigned)k << (4 * many++);
+            if (class_of[k].longest != 0) classes |= (unsigned)k << (4 * many++);
         hipLaunchKernelGGL(cubic_search_ragged_kernel, dim3((unsigned)batch * many), block, lds(all), stream, d, offsets_dev,
                            (int64_t)0, (unsigned)batch, classes, lds(all), mask_out, peak_out, budget_out, status_out, w);
     } else {
         for (int k = top; k >= 0; --k) {
-            const int n = longest[k];
+            const int n = class_of[k].longest;
             if (n == 0) continue;
             for (int64_t first = 0; first < batch; first += kMostWavesOfALaunch) {
                 const unsigned chains = (unsigned)std::min(batch - first, kMostWavesOfALaunch);

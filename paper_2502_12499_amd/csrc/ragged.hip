@@ -452,13 +452,14 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
                 hipStreamSynchronize(stream) != hipSuccess)  // the caller's offsets may end with the call
                 return CKPT_ERR_DEVICE;
         }
-        int longest[kSearchClasses] = {};
+        SearchClass classes[kSearchClasses];
         for (const RaggedGroupDev &g : p.groups) {
             int k = 0;
             while (g.n > search_class_limit(k)) ++k;
-            longest[k] = g.n;  // (the groups ascend in n)
+            classes[k].longest = g.n;  // (the groups ascend in n)
+            classes[k].us += (float)g.count * search_us(g.n);
         }
-        const hipError_t e = launch_cubic_search_ragged(d, off, batch, longest, mask_out, peak_out, budget_out,
+        const hipError_t e = launch_cubic_search_ragged(d, off, batch, classes, mask_out, peak_out, budget_out,
                                                         status_out, (int32_t *)(base + w.totals), perm, stream);
         return e == hipSuccess ? CKPT_OK : CKPT_ERR_DEVICE;
     }

@@ -133,15 +133,40 @@ int main()
         check("one large layer", {d}, kWavePerPoint);
         check("two large layers", {with(d, n - 1, 1000000000012345)}, kWavePerPoint);
     }
-    // the largest ragged batches: every chain once for each class of lengths, in launches that there can be
-    for (const int64_t batch : {(int64_t)1000, (int64_t)1 << 25, ((int64_t)1 << 26) + 1, (int64_t)INT32_MAX}) {
-        const int longest[kSearchClasses] = {20, 0, 100, 256};
-        int64_t chains = 0;
-        emu::instead_of_running = [&](const char *name, dim3 grid) { chains += strstr(name, "ragged_kernel") ? grid.x : 0; };
-        launch_cubic_search_ragged(nullptr, nullptr, batch, longest, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    // ragged batches, by lengths and numbers of chains: the launches they go in (the last of them may be that for the chains
+    // that need 64 bits)
+    const auto launches_of = [](int64_t batch, std::vector<std::pair<int, int64_t>> lengths, int64_t &waves, bool &second) {
+        SearchClass classes[kSearchClasses];
+        for (const auto &[n, many] : lengths) {
+            int k = 0;
+            while (n > search_class_limit(k)) ++k;
+            classes[k].longest = n;
+            classes[k].us += (float)many * search_us(n);
+        }
+        int launches = 0;
+        waves = 0;
+        second = false;
+        emu::instead_of_running = [&](const char *name, dim3 grid) {
+            second |= strstr(name, "ragged_wide_kernel") != nullptr;
+            if (strstr(name, "ragged_kernel")) ++launches, waves += grid.x;
+        };
+        launch_cubic_search_ragged(nullptr, nullptr, batch, classes, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
         emu::instead_of_running = nullptr;
-        failures += chains != 3 * batch;
+        return launches;
+    };
+    int64_t waves;
+    bool second;
+    // the largest: every chain once for each class of lengths, in launches that there can be
+    for (const int64_t batch : {(int64_t)1000, (int64_t)1 << 25, ((int64_t)1 << 26) + 1, (int64_t)INT32_MAX}) {
+        launches_of(batch, {{20, batch - 2}, {100, 1}, {256, 1}}, waves, second);
+        failures += waves != 3 * batch;
     }
+    // a few long chains among short ones: not with LDS for the long ones where the short ones wait for it, and with LDS for
+    // 64 bits where a second launch would cost more
+    failures += launches_of(16384, {{24, 16383}, {64, 1}}, waves, second) != 2;
+    failures += launches_of(4096, {{24, 4095}, {64, 1}}, waves, second) != 1;
+    failures += launches_of(1023, {{24, 1007}, {256, 16}}, waves, second) != 1 || second;
+    failures += launches_of(700, {{240, 700}}, waves, second) != 1 || !second;
     printf(failures ? "search_driver: %d failed\n" : "search_driver ok\n", failures);
     return failures != 0;
 }

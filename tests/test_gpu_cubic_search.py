@@ -277,3 +277,20 @@ def test_what_the_budgets_of_several_chains_cost():
             many = shortest_us(lambda: B.ckpt_solve_cubic(d))
             print(f"{n} unrounded layers: one chain {one:.1f} us, 16 {many:.1f} us", flush=True)
             assert many < 1.75 * one
+
+
+def test_what_a_few_long_chains_of_a_ragged_batch_cost():
+    """Sixteen long chains that need 64 bits among a thousand short ones cost what they cost alone, not twice that."""
+    rng = np.random.default_rng(2)
+    lengths = np.full(1023, 24)
+    lengths[rng.permutation(1023)[:16]] = 256
+
+    def us(lengths):
+        off = np.zeros(len(lengths) + 1, dtype=np.int64)
+        np.cumsum(lengths + 1, out=off[1:])
+        d = torch.from_numpy(np.floor(2 ** rng.uniform(16, 28, size=off[-1])).astype(np.int64)).cuda()
+        return shortest_us(lambda: B.ckpt_ragged_solve_cubic(d, off))
+
+    together, alone = us(lengths), us(lengths[lengths == 256])
+    print(f"16 unrounded chains of 256 layers {alone:.1f} us, with 1,007 of 24 {together:.1f} us", flush=True)
+    assert together < 1.5 * alone
