@@ -365,7 +365,7 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
                                       int64_t batch, uint8_t *mask_stage, int64_t *peak_stage, int32_t *status_stage,
                                       void *ws, hipStream_t stream);
 // The same for few enough chains, where they lie in the flat arrays; perm: the chains in order of their lengths,
-// n_most: the longest one's; ws as above, its first two 32-bit words 0.
+// n_most: the longest one's; ws as above, its first three 32-bit words 0.
 bool linear_takes_flat(int64_t batch, int n);
 hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
                                     uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws,

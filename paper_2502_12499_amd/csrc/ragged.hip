@@ -261,12 +261,12 @@ __global__ __launch_bounds__(kPermThreads) void ragged_perm_kernel(const int64_t
     if (valid) perm[groups[g].first + place] = (int32_t)c;
 }
 
-// (counts: two more words, or null)
+// (counts: three more words, or null)
 __global__ void ragged_clear_kernel(int32_t *cursor, int n_groups, int32_t *counts)
 {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g < n_groups) cursor[g] = 0;
-    if (counts && g < 2) counts[g] = 0;
+    if (counts && g < 3) counts[g] = 0;
 }
 
 // Flat -> position-major, every group in one launch.  A workgroup takes one tile of 64 chains x 64

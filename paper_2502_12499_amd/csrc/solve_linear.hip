@@ -44,7 +44,8 @@
 //        the chain's mask_out slot i.  A final forward sweep turns them into the mask.
 //        A lane defers its chain when a ring fills, the values outgrow 30 bits,
 //        a step exceeds 255 positions, or a size is not positive: it appends
-//        the chain to a list in the workspace, those with sizes of 2^44 and more from the list's end.
+//        the chain to a list in the workspace, those with sizes of 2^44 and more from the list's end if lanes and
+//        rows are to share it.
 //   rows and waves  few chains, and what the ring kernel leaves of many: four chains to a wave (linear_rows.h) or one
 //        (linear_wave.h), in 32-bit integers, doubles or 64-bit integers.  Chains they cannot take either (more than 64
 //        entries live) go on a second list.
@@ -81,12 +82,14 @@ constexpr int kLdsStackMaxN = 2047;
 constexpr int kWaveMaxLayers = 16383;  // of the wave kernel: 34 KB of LDS
 
 struct LinearWs {
-    int32_t *count;   // [3] chains deferred by the ring kernel, chains deferred again by the kernels after it, and those
-                      // of the former that have a size of 2^44 or more (first 256 bytes)
+    int32_t *count;   // [3] chains deferred by the ring kernel, without and with a size of 2^44 or more (one 64-bit word to a
+                      // wave that has both), and chains deferred again by the kernels after it (first 256 bytes)
     int32_t *list;    // [batch] the first; the last from the end backwards
     int32_t *list2;   // [batch] the second
     char *scratch;    // kListBlocks * stack_bytes(n)
     int32_t *list_end;
+    bool apart;       // the ring kernel files chains with large sizes from the list's end (where it matters: an atomic for
+                      // each end in every wave cost 1,048,576 chains of 4 layers 452 us, 269 without, 64-bit ones 283)
 };
 
 // Full-capacity state of one chain: qM, qT, recD (int64), qJ, recK, nxt (int32), padded to 256 bytes.
@@ -101,6 +104,7 @@ __host__ LinearWs carve_linear(void *ws, int64_t batch, int n)
     w.count = (int32_t *)p; p += 256;
     w.list = (int32_t *)p;  p += align_up((size_t)batch * 4);
     w.list_end = w.list + batch;
+    w.apart = false;
     w.list2 = (int32_t *)p; p += align_up((size_t)batch * 4);
     w.scratch = p;
     return w;
@@ -119,7 +123,7 @@ struct Deferred {
     int few, all;       // the first `few` numbers are those without large sizes
     int first, end;     // lanes take these
     const int32_t *list, *list_end;
-    __device__ Deferred(const LinearWs &w, int n) : few(w.count[0]), all(few + w.count[2]), list(w.list), list_end(w.list_end)
+    __device__ Deferred(const LinearWs &w, int n) : few(w.count[0]), all(few + w.count[1]), list(w.list), list_end(w.list_end)
     {
         const bool these = n <= kLanesFewLayers && few >= kLanesPerLayer * n,
                    large = n <= kLanesLayers && all - few >= kLanesPerLayer * n;
@@ -507,14 +511,25 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
         for (int u = 0; u < kChunk; ++u) rows[u] = ahead[u];
     }
 
-    if (!live) return;
-    if (defer) {
-        if (large >> 12)
-            w.list_end[-1 - atomicAdd(w.count + 2, 1)] = (int32_t)(c + list_base);
-        else
-            w.list[atomicAdd(w.count, 1)] = (int32_t)(c + list_base);
-        return;
+    const bool file = live && defer, is_large = w.apart && large >> 12 != 0;
+    const uint64_t filed = __builtin_amdgcn_ballot_w64(file);
+    if (filed != 0) {
+        const uint64_t large_ones = __builtin_amdgcn_ballot_w64(file && is_large), others = filed & ~large_ones;
+        const int first = __builtin_ctzll((unsigned long long)filed);
+        const int many_large = (int)__popcll((unsigned long long)large_ones), many = (int)__popcll((unsigned long long)others);
+        unsigned long long at = 0;
+        if (lane == first) {
+            if (many_large == 0) at = (uint32_t)atomicAdd(w.count, many);
+            else if (many == 0) at = (unsigned long long)atomicAdd(w.count + 1, many_large) << 32;
+            else at = atomicAdd((unsigned long long *)w.count, (unsigned long long)many_large << 32 | (unsigned long long)many);
+        }
+        const int at_other = __builtin_amdgcn_readlane((int)(uint32_t)at, first);
+        const int at_large = __builtin_amdgcn_readlane((int)(uint32_t)(at >> 32), first);
+        const uint64_t before = (1ull << lane) - 1;
+        if (file && is_large) w.list_end[-1 - at_large - (int)__popcll((unsigned long long)(large_ones & before))] = (int32_t)(c + list_base);
+        if (file && !is_large) w.list[at_other + (int)__popcll((unsigned long long)(others & before))] = (int32_t)(c + list_base);
     }
+    if (!live || defer) return;
     peak_out[c] = (int64_t)((uint64_t)Mi << sh);
     if (status_out) status_out[c] = CKPT_OK;
     if constexpr (LOG_REGS) {
@@ -828,7 +843,7 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
         }
         if (!live) continue;
         if (out) {
-            if (!PART) w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)c;
+            if (!PART) w.list2[atomicAdd(w.count + 2, 1)] = (int32_t)c;
             continue;
         }
         peak_out[c] = Mi;
@@ -962,7 +977,7 @@ __global__ __launch_bounds__(kWave) void linear_list_kernel(const int64_t *__res
                                                             const int64_t *__restrict__ off, int flagged)
 {
     if (threadIdx.x != 0) return;
-    const int count = flagged ? flagged : w.count[1];
+    const int count = flagged ? flagged : w.count[2];
     typedef std::conditional_t<LDS_STACKS, uint16_t, int32_t> Pos;
     static_assert(kLdsStackMaxN < 65536, "positions in LDS");
     char *const base = LDS_STACKS ? (char *)lin_lds : w.scratch + (size_t)blockIdx.x * stack_bytes(n_all);
@@ -1189,7 +1204,7 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
             __syncthreads();
             const bool by_wave = wave_chain(d + at.at, at.n, at.pstride, mask_out + at.at, peak_out + one,
                                             status_out ? status_out + one : nullptr, lin_lds);
-            if (!by_wave && lane == 0) w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)one;
+            if (!by_wave && lane == 0) w.list2[atomicAdd(w.count + 2, 1)] = (int32_t)one;
         }
         __syncthreads();
     }
@@ -1224,7 +1239,7 @@ __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__
         __syncthreads();
         const bool done = wave_chain<!ROWS>(d + o, (int)(off[c + 1] - o - 1), 1, mask_out + o, peak_out + c,
                                             status_out ? status_out + c : nullptr, lin_lds);
-        if (!done && lane == 0) w.list2[atomicAdd(w.count + 1, 1)] = (int32_t)c;
+        if (!done && lane == 0) w.list2[atomicAdd(w.count + 2, 1)] = (int32_t)c;
     }
 }
 
@@ -1320,11 +1335,13 @@ void launch_list(const int64_t *d, int n, Strides st, uint8_t *mask_out, int64_t
                        in_lds ? lds_stack_bytes(n) : 0, stream, d, n, st.chain, st.pos, mask_out, peak_out, status_out, w,
                        groups, n_groups, off, flagged);
 }
+// Rows and lanes share what the ring kernel deferred.
+bool lanes_share(int64_t batch, int n) { return rows_list_pays(batch, n) && n <= kLanesLayers; }
 // What the ring kernel deferred.
 void launch_deferred(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out, int64_t *peak_out,
                      int32_t *status_out, const LinearWs &w, const RaggedGroupDev *groups, int n_groups, hipStream_t stream)
 {
-    const bool rows = rows_list_pays(batch, n), part = rows && n <= kLanesLayers;
+    const bool rows = rows_list_pays(batch, n), part = w.apart;
     if (rows) {
         const unsigned blocks = (unsigned)std::min<int64_t>((batch + kRowsOfWave - 1) / kRowsOfWave, kRowsListBlocks);
         hipLaunchKernelGGL(linear_rows_list_kernel, dim3(blocks), dim3(kWave), rows_all_lds_bytes(n, false), stream, d, n,
@@ -1366,6 +1383,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((batch + kWave - 1) / kWave);
+    w.apart = lanes_share(batch, n);
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, stream, w);
     if (st.chain <= kRingMaxChainStride)
         if (n <= kLogMaxLayers)
@@ -1416,6 +1434,7 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
     const int n_groups = t.n_groups, max_layers = t.max_layers;
     const bool per_chain = ragged_waves_pay(t);
     LinearWs w = carve_linear(ws, batch, max_layers);
+    w.apart = lanes_share(batch, max_layers);
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, stream, w);
     hipLaunchKernelGGL(per_chain ? linear_ring_ragged_kernel<true> : linear_ring_ragged_kernel<false>,
                        dim3((unsigned)(per_chain ? t.linear_waves : t.waves)), dim3(kWave), 0, stream, d_stage, groups,

@@ -152,7 +152,7 @@ template <class T> T __shfl_up(T v, int d, int)
 #define __hip_atomic_store(p, v, ...) ((void)(*(p) = (v)))
 #define __hip_atomic_fetch_min(p, v, ...) emu::least(p, v)
 #define __hip_atomic_exchange(p, v, ...) emu::exchange(p, v)
-template <class T> T atomicAdd(T *p, int v) { return emu::exchange(p, (T)(*p + v)); }
+template <class T, class V> T atomicAdd(T *p, V v) { return emu::exchange(p, (T)(*p + v)); }
 template <class T> T atomicMin(T *p, T v) { return emu::least(p, v); }
 template <class T> T atomicMax(T *p, T v) { return emu::exchange(p, *p < v ? v : *p); }
 template <class T> T atomicCAS(T *p, T a, T b) { const T was = *p; if (was == a) *p = b; return was; }

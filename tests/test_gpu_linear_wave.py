@@ -195,3 +195,14 @@ def test_what_64_bits_cost(batch, n, least, most):
     a, w = (shortest_us(lambda: B.ckpt_solve_linear(d)) for d in (aligned, wide))
     print(f"{batch} chains of {n} layers: aligned {a:.1f} us, in 64 bits {w:.1f} us", flush=True)
     assert w < 4 * a
+
+
+def test_what_two_kinds_of_deferred_chains_cost():
+    """Chains that lanes defer from both ends of their list, as sizes about 2^44 make them, cost what chains of one end do:
+    1.7 times that with an atomic for each end in every wave, 1.0 with one."""
+    lo = torch.randint(1 << 40, 1 << 43, (5, 1048576), device="cuda") * 2 + 1
+    mixed = lo.clone()
+    mixed[2, ::2] += 1 << 45
+    one, two = (shortest_us(lambda: B.ckpt_solve_linear(d)) for d in (lo, mixed))
+    print(f"1,048,576 chains of 4 layers: {one:.1f} us, from both ends {two:.1f} us", flush=True)
+    assert two < 1.3 * one
