@@ -248,10 +248,20 @@ struct RaggedGroupDev {
 struct RaggedTotals {
     int32_t n_groups, bad, max_layers;
     int32_t wave_longest;  // of the groups that ragged_wave_per_chain takes: the longest chains' length ...
+    int32_t deep_chains;   // those of more than kDeepLayers layers
+    int32_t rows_longest;  // the longest chain but for the kLongest longest
     int64_t chains, waves, linear_waves, tiles, tiles2, staged;
     int64_t wave_layers;   // ... the layers of all their chains ...
     int64_t lane_waves;    // ... and the waves that they take with a lane per chain
+    int64_t layers, deep_layers;  // of all chains, of the deep ones
 };
+
+// A row of lanes' chain has its steps in the wave's LDS, and up to kDeepLayers layers that leaves a SIMD four waves.
+// Longer chains among many get a wave each, as the kLongest longest always do.
+constexpr int kDeepLayers = 1023, kLongest = 64;
+// They are few enough for that: a wave takes 40 to 110 ps a layer of the whole chip, rows 9 to 15, and 18 to 26 where
+// their LDS leaves a SIMD one wave.
+inline bool deep_ones_alone(const RaggedTotals &t) { return 8 * t.deep_layers <= t.layers; }
 
 // Groups of a large ragged batch (linear_takes_flat takes the others) whose chains the linear solver gives a wave each
 // instead of a lane each, if all such groups together are small enough (ragged_waves_pay): few chains (they would fill a
@@ -303,6 +313,11 @@ __host__ __device__ inline RaggedGroupDev ragged_next_group(RaggedTotals &t, int
     t.chains += many;
     t.waves += (many + 63) / 64;
     t.linear_waves += ragged_linear_waves(n, many);
+    t.layers += n * many;
+    if (n > kDeepLayers) {
+        t.deep_chains += (int32_t)many;
+        t.deep_layers += n * many;
+    }
     if (ragged_wave_per_chain(n, many)) {
         t.wave_longest = n;
         t.wave_layers += n * many;
@@ -364,11 +379,11 @@ hipError_t launch_eval_timeline_ragged(const int64_t *d_stage, const uint8_t *ma
 hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupDev *groups, const RaggedTotals &t,
                                       int64_t batch, uint8_t *mask_stage, int64_t *peak_stage, int32_t *status_stage,
                                       void *ws, hipStream_t stream);
-// The same for few enough chains, where they lie in the flat arrays; perm: the chains in order of their lengths,
-// n_most: the longest one's; ws as above, its first three 32-bit words 0.
+// The same for few enough chains, where they lie in the flat arrays; perm: the chains in order of their lengths;
+// ws as above, its first three 32-bit words 0.
 bool linear_takes_flat(int64_t batch, int n);
-hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
-                                    uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws,
+hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch,
+                                    const RaggedTotals &t, uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws,
                                     hipStream_t stream);
 
 // which: a ckpt_call; offsets_host: batch + 1 element offsets in host memory

@@ -116,20 +116,20 @@ __device__ inline void block_exclusive_sums(int64_t (&v)[kSums], int64_t (&total
 // totals before it, writes the group's descriptor.  (A thread per stretch of 64 lengths, each walked twice, took 65
 // us; this takes 16.)
 __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint32_t *__restrict__ hist,
-                                                                      RaggedGroupDev *__restrict__ groups,
+                                                                      int64_t batch, RaggedGroupDev *__restrict__ groups,
                                                                       int64_t *__restrict__ tile_first2,
                                                                       RaggedTotals *__restrict__ totals)
 {
     __shared__ int64_t wave_sum[kCountThreads / kWave][kSums];
     __shared__ unsigned long long used;  // bit k: some length of tile k occurs
-    __shared__ unsigned long long wave_layers, lane_waves;
-    __shared__ int wave_longest;
+    __shared__ unsigned long long wave_layers, lane_waves, layers, deep_layers;
+    __shared__ int wave_longest, deep_chains;
     const int max_layers = totals->max_layers;
     constexpr int kTiles = (CKPT_MAX_LAYERS + kCountThreads - 1) / kCountThreads;
     static_assert(kTiles <= 64, "one bit per tile");
     if (threadIdx.x == 0) {
-        wave_longest = 0;
-        used = wave_layers = lane_waves = 0;
+        wave_longest = deep_chains = 0;
+        used = wave_layers = lane_waves = layers = deep_layers = 0;
     }
     __syncthreads();
     unsigned long long mine = 0;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
     if (mine) atomicOr(&used, mine);
     __syncthreads();
     RaggedTotals at = {};  // the totals before the tile
-    RaggedTotals long_ones = {};  // of the thread's groups: only their sums are wanted
+    RaggedTotals own = {};  // of the thread's groups: only their sums are wanted
     for (unsigned long long todo = used; todo != 0; todo &= todo - 1) {
         const int n = 1 + (__ffsll(todo) - 1) * kCountThreads + (int)threadIdx.x;
         const int64_t many = n <= max_layers ? hist[n] : 0;
@@ -164,6 +164,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
             const int slot = t.n_groups;
             groups[slot] = ragged_next_group(t, n, many, &first2);
             tile_first2[slot] = first2;
+            if (groups[slot].first < batch - kLongest && batch - kLongest <= t.chains) totals->rows_longest = n;
         }
         at.n_groups += (int32_t)all[0];
         at.chains += all[1];
@@ -172,20 +173,29 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         at.tiles += all[4];
         at.tiles2 += all[5];
         at.staged += all[6];
-        long_ones.wave_longest = one.wave_longest ? one.wave_longest : long_ones.wave_longest;  // (ascending)
-        long_ones.wave_layers += one.wave_layers;
-        long_ones.lane_waves += one.lane_waves;
+        own.wave_longest = one.wave_longest ? one.wave_longest : own.wave_longest;  // (ascending)
+        own.wave_layers += one.wave_layers;
+        own.lane_waves += one.lane_waves;
+        own.deep_chains += one.deep_chains;
+        own.deep_layers += one.deep_layers;
+        own.layers += one.layers;
     }
 #pragma unroll
     for (int s = kWave / 2; s >= 1; s >>= 1) {
-        long_ones.wave_longest = max(long_ones.wave_longest, __shfl_xor(long_ones.wave_longest, s));
-        long_ones.wave_layers += __shfl_xor(long_ones.wave_layers, s);
-        long_ones.lane_waves += __shfl_xor(long_ones.lane_waves, s);
+        own.wave_longest = max(own.wave_longest, __shfl_xor(own.wave_longest, s));
+        own.wave_layers += __shfl_xor(own.wave_layers, s);
+        own.lane_waves += __shfl_xor(own.lane_waves, s);
+        own.deep_chains += __shfl_xor(own.deep_chains, s);
+        own.deep_layers += __shfl_xor(own.deep_layers, s);
+        own.layers += __shfl_xor(own.layers, s);
     }
     if (threadIdx.x % kWave == 0) {
-        atomicMax(&wave_longest, long_ones.wave_longest);
-        atomicAdd(&wave_layers, (unsigned long long)long_ones.wave_layers);
-        atomicAdd(&lane_waves, (unsigned long long)long_ones.lane_waves);
+        atomicMax(&wave_longest, own.wave_longest);
+        atomicAdd(&wave_layers, (unsigned long long)own.wave_layers);
+        atomicAdd(&lane_waves, (unsigned long long)own.lane_waves);
+        atomicAdd(&deep_chains, own.deep_chains);
+        atomicAdd(&deep_layers, (unsigned long long)own.deep_layers);
+        atomicAdd(&layers, (unsigned long long)own.layers);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -199,6 +209,9 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         totals->wave_longest = wave_longest;
         totals->wave_layers = (int64_t)wave_layers;
         totals->lane_waves = (int64_t)lane_waves;
+        totals->deep_chains = deep_chains;
+        totals->deep_layers = (int64_t)deep_layers;
+        totals->layers = (int64_t)layers;
     }
 }
 
@@ -415,7 +428,7 @@ int ragged_plan_on_device(const int64_t *offsets_dev, int64_t batch, int max_lay
                        (int32_t *)totals, (int)words, (int32_t *)nullptr);
     hipLaunchKernelGGL(ragged_count_kernel, dim3((unsigned)((batch + kCountThreads - 1) / kCountThreads)),
                        dim3(kCountThreads), 0, stream, offsets_dev, batch, max_layers, hist, totals);
-    hipLaunchKernelGGL(ragged_layout_kernel, dim3(1), dim3(kCountThreads), 0, stream, hist,
+    hipLaunchKernelGGL(ragged_layout_kernel, dim3(1), dim3(kCountThreads), 0, stream, hist, batch,
                        (RaggedGroupDev *)(base + w.groups), (int64_t *)(base + w.tiles2), totals);
     if (hipGetLastError() != hipSuccess) return CKPT_ERR_DEVICE;
     // the call's one wait: the launches that follow are sized by the totals
@@ -483,7 +496,7 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
                        dim3(kPermThreads), 0, stream, off, batch, groups, n_groups, cursor, perm);
     if (flat) {
         // few chains: a row of lanes or a wave reads a chain where it lies, nothing is staged or put back
-        const hipError_t e = launch_solve_linear_flat(d, off, perm, batch, p.t.max_layers, mask_out, peak_out, status_out,
+        const hipError_t e = launch_solve_linear_flat(d, off, perm, batch, p.t, mask_out, peak_out, status_out,
                                                       base + w.inner, stream);
         return e == hipSuccess ? CKPT_OK : CKPT_ERR_DEVICE;
     }

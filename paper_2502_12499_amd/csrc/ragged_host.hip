@@ -33,6 +33,7 @@ int ragged_make_plan(const int64_t *off, int64_t batch, int max_layers, RaggedPl
         int64_t first2;
         p.groups.push_back(ragged_next_group(p.t, n, many, &first2));
         p.tile_first2.push_back(first2);
+        if (p.groups.back().first < batch - kLongest) p.t.rows_longest = n;
     }
     return ragged_check_totals(p.t, batch);
 }

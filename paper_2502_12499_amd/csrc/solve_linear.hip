@@ -1164,15 +1164,15 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_kernel(const int64_t *__
 
 // The chains that the ring kernel left, four to a wave, or a wave each if they are few (a handful that outgrew the ring
 // would wait for a row's pace and then for the wave's: 65,537 chains of 2,047 aligned layers 1.68 ms so).  With
-// `groups` a listed number is a chain's place among all chains.  What does not fit a row is done by the whole wave,
-// what that cannot do goes on the second list.
+// `groups` a listed number is a chain's place among all chains.  What does not fit a row, more than n_rows layers among it,
+// is done by the whole wave, what that cannot do goes on the second list.
 constexpr unsigned kRowsListBlocks = 4096;  // four waves a SIMD
 constexpr int kListedAlone = 1024;
 __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_t *__restrict__ d, int n_all,
                                                                     int64_t cstride, int64_t pstride_all,
                                                                     uint8_t *__restrict__ mask_out,
                                                                     int64_t *__restrict__ peak_out,
-                                                                    int32_t *__restrict__ status_out, LinearWs w,
+                                                                    int32_t *__restrict__ status_out, LinearWs w, int n_rows,
                                                                     const RaggedGroupDev *__restrict__ groups, int n_groups)
 {
     const int lane = threadIdx.x % kWave;
@@ -1194,9 +1194,10 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
             const bool is_chain = first + lane / kRow < count;
             const int64_t c = listed(is_chain ? first + lane / kRow : count - 1);
             const Chain its = chain(c);
-            const bool done = rows_chains(d + its.at, is_chain, its.n, n_all, its.pstride, mask_out + its.at, peak_out + c,
-                                          status_out ? status_out + c : nullptr, lin_lds);
-            left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0);
+            const bool is_row = is_chain && its.n <= n_rows;
+            const bool done = rows_chains(d + its.at, is_row, min(its.n, n_rows), n_rows, its.pstride, mask_out + its.at,
+                                          peak_out + c, status_out ? status_out + c : nullptr, lin_lds);
+            left = __builtin_amdgcn_ballot_w64(is_chain && !(is_row && done) && lane % kRow == 0);
         }
         for (; left != 0; left &= left - 1) {
             const int64_t one = listed(first + __builtin_ctzll((unsigned long long)left) / kRow);
@@ -1211,26 +1212,28 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
 }
 
 // The chains of a ragged batch where they lie in the flat arrays, four to a wave or one, in the order of `perm`, which
-// ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the kLongest
+// ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the `longest`
 // longest get a wave each all the same: a row takes 72 ns a position, a wave 40, and a few deep chains are what a call
-// waits for (65,536 chains of 15 to 257 layers, sixteen of 1,001 among them: 148 us, 139).
-constexpr int kLongest = 64;
+// waits for (65,536 chains of 15 to 257 layers, sixteen of 1,001 among them: 148 us, 139); and the rows' LDS is that of
+// the n_rows layers the others have at most (262,143 chains of 257 layers and one of 4,095: 1,614 us with LDS for that
+// one in every row).
 template <bool ROWS>
 __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__restrict__ d, const int64_t *__restrict__ off,
-                                                               const int32_t *__restrict__ perm, int64_t batch, int n_most,
+                                                               const int32_t *__restrict__ perm, int64_t batch, int longest,
+                                                               int n_rows,
                                                                uint8_t *__restrict__ mask_out,
                                                                int64_t *__restrict__ peak_out,
                                                                int32_t *__restrict__ status_out, LinearWs w)
 {
     const int lane = threadIdx.x % kWave;
-    const bool alone = !ROWS || blockIdx.x < kLongest;
+    const bool alone = !ROWS || blockIdx.x < (unsigned)longest;
     const int64_t p0 = alone ? batch - 1 - blockIdx.x : (int64_t)(gridDim.x - 1 - blockIdx.x) * kRowsOfWave;
     uint64_t left = 1;
     if (!alone) {
-        const int64_t many = batch - kLongest;
+        const int64_t many = batch - longest;
         const bool is_chain = p0 + lane / kRow < many;
         const int64_t c = perm[is_chain ? p0 + lane / kRow : many - 1], o = off[c];
-        const bool done = rows_chains(d + o, is_chain, (int)(off[c + 1] - o - 1), n_most, 1, mask_out + o, peak_out + c,
+        const bool done = rows_chains(d + o, is_chain, (int)(off[c + 1] - o - 1), n_rows, 1, mask_out + o, peak_out + c,
                                       status_out ? status_out + c : nullptr, lin_lds);
         left = __builtin_amdgcn_ballot_w64(is_chain && !done && lane % kRow == 0);
     }
@@ -1339,13 +1342,15 @@ void launch_list(const int64_t *d, int n, Strides st, uint8_t *mask_out, int64_t
 bool lanes_share(int64_t batch, int n) { return rows_list_pays(batch, n) && n <= kLanesLayers; }
 // What the ring kernel deferred.
 void launch_deferred(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out, int64_t *peak_out,
-                     int32_t *status_out, const LinearWs &w, const RaggedGroupDev *groups, int n_groups, hipStream_t stream)
+                     int32_t *status_out, const LinearWs &w, int n_rows, const RaggedGroupDev *groups, int n_groups,
+                     hipStream_t stream)
 {
     const bool rows = rows_list_pays(batch, n), part = w.apart;
     if (rows) {
         const unsigned blocks = (unsigned)std::min<int64_t>((batch + kRowsOfWave - 1) / kRowsOfWave, kRowsListBlocks);
-        hipLaunchKernelGGL(linear_rows_list_kernel, dim3(blocks), dim3(kWave), rows_all_lds_bytes(n, false), stream, d, n,
-                           st.chain, st.pos, mask_out, peak_out, status_out, w, groups, n_groups);
+        hipLaunchKernelGGL(linear_rows_list_kernel, dim3(blocks), dim3(kWave),
+                           std::max(wave_lds_bytes(n), rows_lds_bytes(n_rows)), stream, d, n, st.chain, st.pos, mask_out,
+                           peak_out, status_out, w, n_rows, groups, n_groups);
     }
     if (!rows || part) {
         const unsigned blocks = (unsigned)std::min<int64_t>((batch + kWave - 1) / kWave, kWideBlocks);
@@ -1395,7 +1400,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     else
         hipLaunchKernelGGL(linear_defer_all_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, stream,
                            batch, w);
-    launch_deferred(d, batch, n, st, mask_out, peak_out, status_out, w, nullptr, 0, stream);
+    launch_deferred(d, batch, n, st, mask_out, peak_out, status_out, w, n, nullptr, 0, stream);
     return hipGetLastError();
 }
 
@@ -1413,16 +1418,18 @@ bool linear_takes_flat(int64_t batch, int n)
     return flat_rows(batch, n) || (batch <= kWaveMaxBatch && n <= kWaveMaxLayers);
 }
 
-hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n_most,
-                                    uint8_t *mask_out, int64_t *peak_out, int32_t *status_out, void *ws, hipStream_t stream)
+hipError_t launch_solve_linear_flat(const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch,
+                                    const RaggedTotals &t, uint8_t *mask_out, int64_t *peak_out, int32_t *status_out,
+                                    void *ws, hipStream_t stream)
 {
-    LinearWs w = carve_linear(ws, batch, n_most);
-    const bool rows = flat_rows(batch, n_most);
-    const int64_t waves = rows ? kLongest + (batch - kLongest + kRowsOfWave - 1) / kRowsOfWave : batch;
-    hipLaunchKernelGGL(rows ? linear_flat_kernel<true> : linear_flat_kernel<false>, dim3((unsigned)waves), dim3(kWave),
-                       rows ? rows_all_lds_bytes(n_most, false) : wave_lds_bytes(n_most), stream, d, off, perm, batch, n_most,
-                       mask_out, peak_out, status_out, w);
-    launch_list(d, n_most, Strides{0, 1}, mask_out, peak_out, status_out, w, batch, nullptr, 0, off, 0, stream);
+    LinearWs w = carve_linear(ws, batch, t.max_layers);
+    const bool rows = flat_rows(batch, t.max_layers), deep = t.deep_chains > kLongest && deep_ones_alone(t);
+    const int longest = deep ? t.deep_chains : kLongest, n_rows = deep ? std::min(t.rows_longest, kDeepLayers) : t.rows_longest;
+    const int64_t waves = rows ? longest + (batch - longest + kRowsOfWave - 1) / kRowsOfWave : batch;
+    const size_t lds = std::max(wave_lds_bytes(t.max_layers), rows ? rows_all_lds_bytes(n_rows, false) : 0);
+    hipLaunchKernelGGL(rows ? linear_flat_kernel<true> : linear_flat_kernel<false>, dim3((unsigned)waves), dim3(kWave), lds,
+                       stream, d, off, perm, batch, longest, n_rows, mask_out, peak_out, status_out, w);
+    launch_list(d, t.max_layers, Strides{0, 1}, mask_out, peak_out, status_out, w, batch, nullptr, 0, off, 0, stream);
     return hipGetLastError();
 }
 
@@ -1439,7 +1446,8 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
     hipLaunchKernelGGL(per_chain ? linear_ring_ragged_kernel<true> : linear_ring_ragged_kernel<false>,
                        dim3((unsigned)(per_chain ? t.linear_waves : t.waves)), dim3(kWave), 0, stream, d_stage, groups,
                        n_groups, mask_stage, peak_stage, status_stage, w);
-    launch_deferred(d_stage, batch, max_layers, Strides{1, 0}, mask_stage, peak_stage, status_stage, w, groups, n_groups, stream);
+    launch_deferred(d_stage, batch, max_layers, Strides{1, 0}, mask_stage, peak_stage, status_stage, w,
+                    deep_ones_alone(t) ? std::min(max_layers, kDeepLayers) : max_layers, groups, n_groups, stream);
     return hipGetLastError();
 }
 

@@ -45,9 +45,10 @@ Sizes up_to(int n, int k, int64_t most)
     return with(d, k, (most - rest) / 2);
 }
 
-enum Form { kLanes, kWideLanes, kWaves, kRows, kListedRows, kRowsAndLanes, kFlatWaves, kFlatRows };
+enum Form { kLanes, kWideLanes, kWaves, kRows, kListedRows, kRowsAndLanes, kFlatWaves, kFlatRows, kFlatFewRows, kStaged };
 const char *const kNames[] = {"a lane per chain", "a lane per chain in 64 bits", "a wave per chain", "a row per chain",
-                              "a row per listed chain", "a row or a lane per listed chain", "a wave per chain of a ragged batch", "a row per chain of a ragged batch"};
+                              "a row per listed chain", "a row or a lane per listed chain", "a wave per chain of a ragged batch", "a row per chain of a ragged batch",
+                              "a wave per long chain of a ragged batch", "a staged ragged batch"};
 
 void launch_form(Form form, const int64_t *d, const int64_t *off, const int32_t *perm, int64_t batch, int n, Strides st,
                  uint8_t *mask, int64_t *peak, int32_t *status)
@@ -69,7 +70,7 @@ void launch_form(Form form, const int64_t *d, const int64_t *off, const int32_t 
             hipLaunchKernelGGL(linear_defer_all_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, nullptr, batch, w);
         if (form == kListedRows || form == kRowsAndLanes)
             hipLaunchKernelGGL(linear_rows_list_kernel, dim3(rows), dim3(kWave), rows_all_lds_bytes(n, false), nullptr, d, n,
-                               st.chain, st.pos, mask, peak, status, w, (const RaggedGroupDev *)nullptr, 0);
+                               st.chain, st.pos, mask, peak, status, w, n, (const RaggedGroupDev *)nullptr, 0);
         if (form == kRowsAndLanes)
             hipLaunchKernelGGL(linear_wide_kernel<true>, dim3(lanes), dim3(kWave), 0, nullptr, d, n, st.chain, st.pos, mask, peak,
                                status, w, (const RaggedGroupDev *)nullptr, 0);
@@ -88,14 +89,50 @@ void launch_form(Form form, const int64_t *d, const int64_t *off, const int32_t 
         if (!own) launch_list(d, n, st, mask, peak, status, w, batch, nullptr, 0, nullptr, (int)batch, nullptr);
         break;
     }
-    case kFlatWaves:
-        launch_solve_linear_flat(d, off, perm, batch, n, mask, peak, status, ws, nullptr);
+    case kFlatWaves: {
+        RaggedTotals t = {};
+        t.max_layers = n;
+        launch_solve_linear_flat(d, off, perm, batch, t, mask, peak, status, ws, nullptr);
         break;
+    }
     case kFlatRows:
-        hipLaunchKernelGGL(linear_flat_kernel<true>, dim3(kLongest + (unsigned)((batch - kLongest + kRowsOfWave - 1) / kRowsOfWave)),
-                           dim3(kWave), rows_all_lds_bytes(n, false), nullptr, d, off, perm, batch, n, mask, peak, status, w);
+    case kFlatFewRows: {  // (as many by a wave each as are longer than the others' rows; more than those that always are)
+        int longest = kLongest;
+        if (form == kFlatFewRows) longest += ((int)batch - longest) / 2;
+        const int32_t last = perm[batch - longest - 1];
+        const int n_rows = (int)(off[last + 1] - off[last] - 1);
+        hipLaunchKernelGGL(linear_flat_kernel<true>, dim3(longest + (unsigned)((batch - longest + kRowsOfWave - 1) / kRowsOfWave)),
+                           dim3(kWave), std::max(rows_all_lds_bytes(n_rows, false), wave_lds_bytes(n)), nullptr, d, off, perm,
+                           batch, longest, n_rows, mask, peak, status, w);
         launch_list(d, n, Strides{0, 1}, mask, peak, status, w, batch, nullptr, 0, off, 0, nullptr);
         break;
+    }
+    case kStaged: {
+        RaggedTotals t = {};
+        RaggedGroupDev *const groups = (RaggedGroupDev *)emu::device_memory((size_t)n * sizeof(RaggedGroupDev));
+        const auto length = [&](int64_t p) { return (int)(off[perm[p] + 1] - off[perm[p]] - 1); };
+        for (int64_t p = 0, q; p < batch; p = q) {
+            for (q = p; q < batch && length(q) == length(p); ++q) {}
+            int64_t tile;
+            const int k = t.n_groups;
+            groups[k] = ragged_next_group(t, length(p), q - p, &tile);
+        }
+        const auto place = [&](const RaggedGroupDev &g, int64_t p, int k) { return (size_t)(g.stage_off + k * g.pitch + (p - g.first)); };
+        int64_t *const staged = (int64_t *)emu::device_memory((size_t)t.staged * 8), *const peaks = (int64_t *)emu::device_memory((size_t)batch * 8);
+        uint8_t *const masks = (uint8_t *)emu::device_memory((size_t)t.staged);
+        int32_t *const codes = (int32_t *)emu::device_memory((size_t)batch * 4);
+        for (int g = 0; g < t.n_groups; ++g)
+            for (int64_t p = groups[g].first; p < groups[g].first + groups[g].count; ++p)
+                for (int k = 0; k <= groups[g].n; ++k) staged[place(groups[g], p, k)] = d[off[perm[p]] + k];
+        launch_solve_linear_ragged(staged, groups, t, batch, masks, peaks, codes, ws, nullptr);
+        for (int g = 0; g < t.n_groups; ++g)
+            for (int64_t p = groups[g].first; p < groups[g].first + groups[g].count; ++p) {
+                for (int k = 0; k <= groups[g].n; ++k) mask[off[perm[p]] + k] = masks[place(groups[g], p, k)];
+                peak[perm[p]] = peaks[p];
+                status[perm[p]] = codes[p];
+            }
+        break;
+    }
     }
 }
 
@@ -210,7 +247,21 @@ int main()
         std::vector<Sizes> chains;
         while (chains.size() < 90)
             for (const Sizes &d : kinds((int)between(1, longest))) chains.push_back(d);
-        check("ragged", chains, {kFlatWaves, kFlatRows});
+        check("ragged", chains, {kFlatWaves, kFlatRows, kFlatFewRows, kStaged});
+    }
+    // many short chains and a few deep ones: what the lanes leave of them goes to rows with LDS for the short ones, more
+    // than so many that each gets a wave
+    for (const int longest : {40, kDeepLayers + 20}) {
+        std::vector<Sizes> chains;
+        for (int c = 0; c < kListedAlone + 100; ++c) {
+            const int n = (int)between(17, 24);
+            chains.push_back(c % 300 == 0 ? with(uniform(n, 1, 9), n / 2, c % 600 ? -1 : INT64_MAX)
+                                          : uniform(n, 1ll << 31, c % 3 ? 1ll << 40 : INT64_MAX / 32));
+        }
+        for (int c = 0; c < 2; ++c) chains.push_back(uniform(longest - c, 1ll << 31, 1ll << (c ? 34 : 50)));
+        for (const int n : {130, 257, 300}) chains.push_back(live_entries(std::min(n, longest)));
+        std::shuffle(chains.begin(), chains.end(), rng);
+        check("ragged, deep chains", chains, {kStaged, kFlatRows});
     }
     printf(failures ? "linear_driver: %d failed\n" : "linear_driver ok\n", failures);
     return failures != 0;

@@ -7,6 +7,7 @@ import torch
 import oracle
 from paper_2502_12499_amd import binding as B
 from paper_2502_12499_amd import inputs
+from timing import shortest_us
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -274,3 +275,36 @@ def test_cubic_classes_in_one_launch_and_in_several(batch, longest):
     for c in where[::2]:
         d[off[c]:off[c + 1]] = rng.integers(1, (1 << 62) // (lengths[c] + 2), size=lengths[c] + 1)
     check_cubic(d, off)
+
+
+@pytest.mark.parametrize("batch, deep", [(1100, 5), (1100, 64), (1100, 65), (4000, 70), (20000, 300), (20000, 3000)])
+def test_deep_chains_of_a_batch_that_is_taken_where_it_lies(batch, deep):
+    """A few chains longer than the rows' LDS has room for: the 64 longest get a wave each, more of them if they are few
+    among the others' layers."""
+    rng = np.random.default_rng(batch + deep)
+    lengths = rng.integers(120, 140, size=batch)
+    lengths[rng.permutation(batch)[:deep]] = rng.choice([1023, 1024, 1025, 1100] + [2000] * (deep < 100), size=deep)
+    d, _, off = inputs.ragged_batch(24, lengths)
+    for c in range(0, batch, 5):
+        d[off[c]:off[c + 1]] += 1
+    say(f"ragged linear: {batch} chains, {deep} deep ones")
+    check_linear(d, off)
+
+
+def test_what_one_deep_chain_of_a_ragged_batch_costs():
+    """One chain of 4,095 layers among many of 257 costs what it costs alone, and not its LDS in every wave."""
+    rng = np.random.default_rng(3)
+    lengths = np.full(131072, 257)
+    lengths[rng.integers(131072)] = 4095
+
+    def us(lengths):
+        off = np.zeros(len(lengths) + 1, dtype=np.int64)
+        np.cumsum(lengths + 1, out=off[1:])
+        d = torch.randint(256, 32769, (int(off[-1]),), device=DEV) * 4096
+        ws = torch.empty(B.load().ckpt_ragged_workspace_bytes(B.CALL_SOLVE_LINEAR, off.ctypes.data, len(lengths)),
+                         dtype=torch.uint8, device=DEV)
+        return shortest_us(lambda: B.ckpt_ragged_solve_linear(d, off, workspace=ws, offsets_dev=to_dev(off)))
+
+    together, short, alone = us(lengths), us(lengths[lengths == 257]), us(lengths[lengths > 257])
+    say(f"131,071 chains of 257 layers {short:.1f} us, one of 4,095 {alone:.1f} us, together {together:.1f} us")
+    assert together < 1.15 * (short + alone)
