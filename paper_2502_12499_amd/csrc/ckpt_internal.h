@@ -250,6 +250,7 @@ struct RaggedTotals {
     int32_t wave_longest;  // of the groups that ragged_wave_per_chain takes: the longest chains' length ...
     int32_t deep_chains;   // those of more than kDeepLayers layers
     int32_t rows_longest;  // the longest chain but for the kLongest longest
+    int32_t lane_longest;  // ... and of the groups that ragged_wave_per_chain does not take
     int64_t chains, waves, linear_waves, tiles, tiles2, staged;
     int64_t wave_layers;   // ... the layers of all their chains ...
     int64_t lane_waves;    // ... and the waves that they take with a lane per chain
@@ -322,6 +323,8 @@ __host__ __device__ inline RaggedGroupDev ragged_next_group(RaggedTotals &t, int
         t.wave_longest = n;
         t.wave_layers += n * many;
         t.lane_waves += (many + 63) / 64;
+    } else {
+        t.lane_longest = n;
     }
     t.tiles += (int64_t)g.tiles_x * ((n + 1 + 63) / 64);
     t.tiles2 += (int64_t)g.tiles_x * ((2 * n + 2 + 63) / 64);

@@ -123,12 +123,12 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
     __shared__ int64_t wave_sum[kCountThreads / kWave][kSums];
     __shared__ unsigned long long used;  // bit k: some length of tile k occurs
     __shared__ unsigned long long wave_layers, lane_waves, layers, deep_layers;
-    __shared__ int wave_longest, deep_chains;
+    __shared__ int wave_longest, lane_longest, deep_chains;
     const int max_layers = totals->max_layers;
     constexpr int kTiles = (CKPT_MAX_LAYERS + kCountThreads - 1) / kCountThreads;
     static_assert(kTiles <= 64, "one bit per tile");
     if (threadIdx.x == 0) {
-        wave_longest = deep_chains = 0;
+        wave_longest = lane_longest = deep_chains = 0;
         used = wave_layers = lane_waves = layers = deep_layers = 0;
     }
     __syncthreads();
@@ -174,6 +174,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         at.tiles2 += all[5];
         at.staged += all[6];
         own.wave_longest = one.wave_longest ? one.wave_longest : own.wave_longest;  // (ascending)
+        own.lane_longest = one.lane_longest ? one.lane_longest : own.lane_longest;
         own.wave_layers += one.wave_layers;
         own.lane_waves += one.lane_waves;
         own.deep_chains += one.deep_chains;
@@ -183,6 +184,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
 #pragma unroll
     for (int s = kWave / 2; s >= 1; s >>= 1) {
         own.wave_longest = max(own.wave_longest, __shfl_xor(own.wave_longest, s));
+        own.lane_longest = max(own.lane_longest, __shfl_xor(own.lane_longest, s));
         own.wave_layers += __shfl_xor(own.wave_layers, s);
         own.lane_waves += __shfl_xor(own.lane_waves, s);
         own.deep_chains += __shfl_xor(own.deep_chains, s);
@@ -191,6 +193,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
     }
     if (threadIdx.x % kWave == 0) {
         atomicMax(&wave_longest, own.wave_longest);
+        atomicMax(&lane_longest, own.lane_longest);
         atomicAdd(&wave_layers, (unsigned long long)own.wave_layers);
         atomicAdd(&lane_waves, (unsigned long long)own.lane_waves);
         atomicAdd(&deep_chains, own.deep_chains);
@@ -207,6 +210,7 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         totals->tiles2 = at.tiles2;
         totals->staged = at.staged;
         totals->wave_longest = wave_longest;
+        totals->lane_longest = lane_longest;
         totals->wave_layers = (int64_t)wave_layers;
         totals->lane_waves = (int64_t)lane_waves;
         totals->deep_chains = deep_chains;

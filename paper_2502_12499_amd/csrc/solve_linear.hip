@@ -90,6 +90,7 @@ struct LinearWs {
     int32_t *list_end;
     bool apart;       // the ring kernel files chains with large sizes from the list's end (where it matters: an atomic for
                       // each end in every wave cost 1,048,576 chains of 4 layers 452 us, 269 without, 64-bit ones 283)
+    int lanes_few, lanes_large;  // so many of either kind, and lanes take them
 };
 
 // Full-capacity state of one chain: qM, qT, recD (int64), qJ, recK, nxt (int32), padded to 256 bytes.
@@ -105,6 +106,7 @@ __host__ LinearWs carve_linear(void *ws, int64_t batch, int n)
     w.list = (int32_t *)p;  p += align_up((size_t)batch * 4);
     w.list_end = w.list + batch;
     w.apart = false;
+    w.lanes_few = w.lanes_large = INT32_MAX;
     w.list2 = (int32_t *)p; p += align_up((size_t)batch * 4);
     w.scratch = p;
     return w;
@@ -112,21 +114,14 @@ __host__ LinearWs carve_linear(void *ws, int64_t batch, int n)
 
 __global__ void linear_reset_kernel(LinearWs w) { w.count[0] = w.count[1] = w.count[2] = 0; }
 
-// The chains that the ring kernel deferred, and the part of them that lanes take and not rows: up to kLanesLayers layers
-// the chains with large sizes, which need 64 bits, up to kLanesFewLayers the others, where there are enough of them.
-// Lanes take 1.8 us a position whatever their number, up to 80,000; rows take time in proportion and start better.  Rows
-// and lanes, us: 65,537 chains in 64 bits, 17 layers 70 and 50, 24 71 and 63, 32 74 and 79; 131,072 of 32 137 and 122, of
-// 48 183 and 171; 1,048,576 of 48 1,357 and 1,310; in doubles 65,537 of 17 60 and 49, of 24 64 and 62, 131,072 of 24 115
-// and 114; but one chain in fifty in 64 bits, 65,537 of 24 layers 41 and 65.
-constexpr int kLanesFewLayers = 23, kLanesLayers = kWave, kLanesPerLayer = 1984;
+// The chains that the ring kernel deferred, and the part of them that lanes take and not rows (the limits: lanes_share).
 struct Deferred {
     int few, all;       // the first `few` numbers are those without large sizes
     int first, end;     // lanes take these
     const int32_t *list, *list_end;
-    __device__ Deferred(const LinearWs &w, int n) : few(w.count[0]), all(few + w.count[1]), list(w.list), list_end(w.list_end)
+    __device__ explicit Deferred(const LinearWs &w) : few(w.count[0]), all(few + w.count[1]), list(w.list), list_end(w.list_end)
     {
-        const bool these = n <= kLanesFewLayers && few >= kLanesPerLayer * n,
-                   large = n <= kLanesLayers && all - few >= kLanesPerLayer * n;
+        const bool these = few >= w.lanes_few, large = all - few >= w.lanes_large;
         first = these ? 0 : few;
         end = large ? all : few;
     }
@@ -708,6 +703,7 @@ constexpr int kWideRows = 8;  // rows read together
 // 262,144 chains.)
 // With `groups` (a ragged call) a listed number is a chain's place among all chains: its group
 // gives the length, where the chain is staged and where its results go, per lane.
+constexpr int kLanesLayers = kWave;
 // PART: the deferred chains that rows leave to lanes (of at most kLanesLayers layers), and what is left of those by the
 // whole wave, chain by chain; else all that are deferred.
 template <bool PART>
@@ -720,7 +716,7 @@ __global__ __launch_bounds__(kWave) void linear_wide_kernel(const int64_t *__res
 {
     __shared__ WideEntry ring[kRing][kWave];
     const int lane = threadIdx.x;
-    const Deferred deferred(w, n_all);
+    const Deferred deferred(w);
     const int count = PART ? deferred.end : deferred.all;
     for (int item0 = (PART ? deferred.first : 0) + blockIdx.x * kWave; item0 < count; item0 += gridDim.x * kWave) {
         const bool live = item0 + lane < count;
@@ -1030,7 +1026,7 @@ __global__ __launch_bounds__(kWave) void linear_ring_ragged_kernel(const int64_t
         const int64_t at = g.stage_off + block, c = g.first + (int64_t)block;
         const bool done = wave_chain(d_stage + at, g.n, g.pitch, mask_stage + at, peak_stage + c, status_stage + c,
                                      (unsigned char *)ring);
-        if (!done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
+        if (!done && threadIdx.x == 0) w.list2[atomicAdd(w.count + 2, 1)] = (int32_t)c;
     } else if (g.n <= kLogMaxLayers)
         linear_ring_wave<true>(d_stage + g.stage_off, g.count, g.n, 1, g.pitch, mask_stage + g.stage_off,
                                peak_stage + g.first, status_stage + g.first, w, block, waves, g.first, ring);
@@ -1176,7 +1172,7 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
                                                                     const RaggedGroupDev *__restrict__ groups, int n_groups)
 {
     const int lane = threadIdx.x % kWave;
-    const Deferred deferred(w, n_all);
+    const Deferred deferred(w);
     const int lanes_take = deferred.end - deferred.first, count = deferred.all - lanes_take;
     const auto listed = [&](int64_t item) -> int64_t { return deferred[(int)(item < deferred.first ? item : item + lanes_take)]; };
     // (c the same in the lanes that are to have the chain)
@@ -1215,8 +1211,8 @@ __global__ __launch_bounds__(kWave, 4) void linear_rows_list_kernel(const int64_
 // ascends in their lengths; the longest start first.  What is left goes on the second list.  With rows, the `longest`
 // longest get a wave each all the same: a row takes 72 ns a position, a wave 40, and a few deep chains are what a call
 // waits for (65,536 chains of 15 to 257 layers, sixteen of 1,001 among them: 148 us, 139); and the rows' LDS is that of
-// the n_rows layers the others have at most (262,143 chains of 257 layers and one of 4,095: 1,614 us with LDS for that
-// one in every row).
+// the n_rows layers the others have at most (262,143 chains of 257 layers and one of 4,095: 683 us, 1,614 with LDS for
+// that one in every row).
 template <bool ROWS>
 __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__restrict__ d, const int64_t *__restrict__ off,
                                                                const int32_t *__restrict__ perm, int64_t batch, int longest,
@@ -1338,12 +1334,26 @@ void launch_list(const int64_t *d, int n, Strides st, uint8_t *mask_out, int64_t
                        in_lds ? lds_stack_bytes(n) : 0, stream, d, n, st.chain, st.pos, mask_out, peak_out, status_out, w,
                        groups, n_groups, off, flagged);
 }
-// Rows and lanes share what the ring kernel deferred.
-bool lanes_share(int64_t batch, int n) { return rows_list_pays(batch, n) && n <= kLanesLayers; }
-// What the ring kernel deferred.
+// Lanes take part of what the ring kernel deferred, of chains of `mean` layers and of `longest` at most: up to kLanesLayers
+// layers those with large sizes, which need 64 bits, up to kLanesFewLayers the others, where there are enough of them.
+// Lanes take 1.8 us a position whatever their number, up to 80,000; rows take time in proportion and start better.  Rows
+// and lanes, us: 65,537 chains in 64 bits, 17 layers 70 and 50, 24 71 and 63, 32 74 and 79; 131,072 of 32 137 and 122, of
+// 48 183 and 171; 1,048,576 of 48 1,357 and 1,310; in doubles 65,537 of 17 60 and 49, of 24 64 and 62, 131,072 of 24 115
+// and 114; but one chain in fifty in 64 bits, 65,537 of 24 layers 41 and 65.  In a ragged batch a row takes 16 positions for
+// any fewer, and lanes the longest's time: unrounded chains of 2 to 24 layers, 500,000 427 and 379; of 2 to 40, 262,145
+// 303 and 329, 1,500,000 1,311 and 1,151; of 2 to 64, 262,145 346 and 465, 700,000 748 and 794, 1,500,000 1,556 and 1,457.
+constexpr int kLanesFewLayers = 23, kLanesPerLayer = 1984, kLanesPerLayerMore = 15000;
+void lanes_share(LinearWs &w, int64_t batch, int longest, int mean)
+{
+    w.apart = rows_list_pays(batch, longest) && longest <= kLanesLayers;
+    if (!w.apart) return;
+    if (mean <= kLanesFewLayers) w.lanes_few = kLanesPerLayer * mean + kLanesPerLayerMore * (longest - mean);
+    w.lanes_large = kLanesPerLayer * ((mean + longest) / 2);
+}
+// What the ring kernel deferred, of at most n layers (n_most: the longest chain of all).
 void launch_deferred(const int64_t *d, int64_t batch, int n, Strides st, uint8_t *mask_out, int64_t *peak_out,
-                     int32_t *status_out, const LinearWs &w, int n_rows, const RaggedGroupDev *groups, int n_groups,
-                     hipStream_t stream)
+                     int32_t *status_out, const LinearWs &w, int n_rows, int n_most, const RaggedGroupDev *groups,
+                     int n_groups, hipStream_t stream)
 {
     const bool rows = rows_list_pays(batch, n), part = w.apart;
     if (rows) {
@@ -1357,8 +1367,10 @@ void launch_deferred(const int64_t *d, int64_t batch, int n, Strides st, uint8_t
         hipLaunchKernelGGL(part ? linear_wide_kernel<true> : linear_wide_kernel<false>, dim3(blocks), dim3(kWave), 0, stream, d,
                            n, st.chain, st.pos, mask_out, peak_out, status_out, w, groups, n_groups);
     }
-    // (of so few layers the end of a block never has more than 64 entries live: rows put nothing on the second list either)
-    if (!part) launch_list(d, n, st, mask_out, peak_out, status_out, w, batch, groups, n_groups, nullptr, 0, stream);
+    // (of so few layers the end of a block never has more than 64 entries live: rows put nothing on the second list either,
+    // but a ragged batch's longer chains, which get waves, may be on it)
+    if (!part || n_most != n)
+        launch_list(d, n_most, st, mask_out, peak_out, status_out, w, batch, groups, n_groups, nullptr, 0, stream);
 }
 }  // namespace
 
@@ -1388,7 +1400,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((batch + kWave - 1) / kWave);
-    w.apart = lanes_share(batch, n);
+    lanes_share(w, batch, n, n);
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, stream, w);
     if (st.chain <= kRingMaxChainStride)
         if (n <= kLogMaxLayers)
@@ -1400,7 +1412,7 @@ hipError_t launch_solve_linear(const int64_t *d, int64_t batch, int n, Strides s
     else
         hipLaunchKernelGGL(linear_defer_all_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, stream,
                            batch, w);
-    launch_deferred(d, batch, n, st, mask_out, peak_out, status_out, w, n, nullptr, 0, stream);
+    launch_deferred(d, batch, n, st, mask_out, peak_out, status_out, w, n, n, nullptr, 0, stream);
     return hipGetLastError();
 }
 
@@ -1438,16 +1450,17 @@ hipError_t launch_solve_linear_ragged(const int64_t *d_stage, const RaggedGroupD
                                       void *ws, hipStream_t stream)
 {
     if (batch == 0) return hipSuccess;
-    const int n_groups = t.n_groups, max_layers = t.max_layers;
+    const int n_groups = t.n_groups;
     const bool per_chain = ragged_waves_pay(t);
-    LinearWs w = carve_linear(ws, batch, max_layers);
-    w.apart = lanes_share(batch, max_layers);
+    const int longest = per_chain ? t.lane_longest : t.max_layers;  // of the chains that the lanes may defer
+    LinearWs w = carve_linear(ws, batch, t.max_layers);
+    lanes_share(w, batch, longest, (int)((t.layers - (per_chain ? t.wave_layers : 0)) / batch));
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, stream, w);
     hipLaunchKernelGGL(per_chain ? linear_ring_ragged_kernel<true> : linear_ring_ragged_kernel<false>,
                        dim3((unsigned)(per_chain ? t.linear_waves : t.waves)), dim3(kWave), 0, stream, d_stage, groups,
                        n_groups, mask_stage, peak_stage, status_stage, w);
-    launch_deferred(d_stage, batch, max_layers, Strides{1, 0}, mask_stage, peak_stage, status_stage, w,
-                    deep_ones_alone(t) ? std::min(max_layers, kDeepLayers) : max_layers, groups, n_groups, stream);
+    launch_deferred(d_stage, batch, longest, Strides{1, 0}, mask_stage, peak_stage, status_stage, w,
+                    deep_ones_alone(t) ? std::min(longest, kDeepLayers) : longest, t.max_layers, groups, n_groups, stream);
     return hipGetLastError();
 }
 

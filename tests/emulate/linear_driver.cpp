@@ -56,6 +56,7 @@ void launch_form(Form form, const int64_t *d, const int64_t *off, const int32_t 
     char *const ws = (char *)emu::device_memory(linear_workspace_bytes(batch, n));
     LinearWs w = carve_linear(ws, batch, n);
     w.apart = form == kRowsAndLanes;
+    if (form == kRowsAndLanes) w.lanes_few = w.lanes_large = kLanesPerLayer * n;
     const unsigned lanes = (unsigned)((batch + kWave - 1) / kWave), rows = (unsigned)((batch + kRowsOfWave - 1) / kRowsOfWave);
     hipLaunchKernelGGL(linear_reset_kernel, dim3(1), dim3(1), 0, nullptr, w);
     switch (form) {
