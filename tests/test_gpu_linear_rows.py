@@ -52,7 +52,7 @@ def test_lengths_and_kinds_of_sizes(n):
     check(kinds(n, MORE_THAN_WAVES + 3 * 11, n), chain_major=n % 2 == 1)
 
 
-@pytest.mark.parametrize("n, unrounded", [(16, 3000), (17, 900), (17, 65600), (33, 3000)])
+@pytest.mark.parametrize("n, unrounded", [(16, 3000), (17, 900), (17, 65600), (33, 3000), (130, 900), (130, 3000)])
 def test_what_the_lanes_of_a_larger_batch_leave(n, unrounded):
     """More than 65,536 chains: those that leave the ring kernel's 32 bits or its ring, few (a wave each) and many (rows)."""
     print(f"linear: 65,600 chains of {n} layers, {unrounded} unrounded", flush=True)
@@ -60,7 +60,7 @@ def test_what_the_lanes_of_a_larger_batch_leave(n, unrounded):
     at = np.random.default_rng(n).permutation(65600)[:unrounded]
     d[:, at] += inputs.uniform_aligned_chains(9, n, unrounded, 1, 9) // 4096 * (1 << 30) + 1
     d[:, at[:12]] = kinds(n, 12, 3)
-    d[:, at[12]] = live_entries(n)[:, 0]
+    d[:, at[12:20]] = live_entries(n)  # (of 130 layers more than 64 live: the last kernel's)
     check(d)
     off = np.arange(65601, dtype=np.int64) * (n + 1)
     mask, peak, status = B.ckpt_ragged_solve_linear(torch.from_numpy(inputs.chain_major(d)).cuda().view(-1), off)

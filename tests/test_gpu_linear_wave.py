@@ -74,15 +74,15 @@ def test_long_chains(n):
     check(live_entries(n))
 
 
-@pytest.mark.parametrize("batch", [2560, 2561])
-def test_a_list_of_their_own_where_all_waves_fit_the_chip(batch):
-    d = inputs.uniform_aligned_chains(4, 511, batch, 256, 32768)
-    d[:, 7:9] = live_entries(511)                                                # more than 64 live entries: for the list
-    d[:, batch - 1] = live_entries(511)[:, 0]
+@pytest.mark.parametrize("n, batch", [(2047, 512), (2047, 513), (1279, 1024), (1280, 1024), (2048, 4)])
+def test_a_list_of_their_own_where_all_waves_fit_the_chip(n, batch):
+    d = inputs.uniform_aligned_chains(4, n, batch, 256, 32768)
+    d[:, 1:3] = live_entries(n)                                                  # more than 64 live entries: for the list
+    d[:, batch - 1] = live_entries(n)[:, 0]
     check(d)
 
 
-@pytest.mark.parametrize("batch", [4096, 4097, 16384, 16385])
+@pytest.mark.parametrize("batch", [1024, 1025, 65536, 65537])
 def test_batches_on_both_sides_of_the_rule(batch):
     d = inputs.uniform_aligned_chains(3, 40, batch, 256, 32768)
     d[:, ::9] += 1
@@ -127,7 +127,7 @@ def test_one_size_near_the_largest_value(n):
     check_one_large_size([t.cpu().numpy() for t in B.ckpt_solve_linear(torch.from_numpy(d).cuda())], d, fits)
 
 
-@pytest.mark.parametrize("n,batch", [(3, 4112), (64, 4160), (300, 6160), (20000, 16)])
+@pytest.mark.parametrize("n,batch", [(3, 65552), (64, 65552), (65, 65552), (300, 65552), (20000, 16)])
 def test_one_size_near_the_largest_value_a_lane_per_chain(n, batch):
     d, fits = one_large_size(n)
     d, fits = np.tile(d, (1, batch // 16)), np.tile(fits, batch // 16)
@@ -143,15 +143,19 @@ def test_one_size_near_the_largest_value_in_a_ragged_batch():
     check_one_large_size((mask.reshape(16, 301).T, peak, status), d, fits)
 
 
-def test_long_groups_of_a_ragged_batch():
-    """Groups on both sides of the rule (257 and 4095 layers get waves, 256 and 4096 lanes), with chains that
-    leave either kind, lengths counted on the host and on the device."""
+@pytest.mark.parametrize("short", [0, 262144])
+def test_long_groups_of_a_ragged_batch(short):
+    """Staged (beside `short` chains of one layer), groups on both sides of the rule (257 and 4095 layers get waves, 256 and
+    4096 lanes), with chains that leave either kind; the same chains without the others, which are taken where they lie.
+    Lengths counted on the host and on the device."""
     rng = np.random.default_rng(1)
     lengths = np.concatenate([np.array([256, 257, 257, 1001, 4095, 4096, 300, 300, 300]),
-                              rng.choice([5, 24, 300], size=200)])
+                              rng.choice([5, 24, 300], size=200), np.ones(short, dtype=np.int64)])
     rng.shuffle(lengths)
     d, _, off = inputs.ragged_batch(6, lengths)
-    for c in range(0, len(lengths), 3):
+    for c in range(0, len(lengths), 3 if short == 0 else 1000):
+        d[off[c]:off[c + 1]] += 1
+    for c in np.nonzero(lengths == 300)[0][3:50:3]:
         d[off[c]:off[c + 1]] += 1
     for c in np.nonzero(lengths == 300)[0][:3]:
         d[off[c]:off[c + 1]] = live_entries(300)[:, 0]
@@ -164,11 +168,13 @@ def test_long_groups_of_a_ragged_batch():
         assert np.array_equal(mask.cpu().numpy(), want_mask)
 
 
-@pytest.mark.parametrize("batch", [3000, 12288])
-def test_many_long_chains_of_a_ragged_batch(batch):
-    """Groups of 257 to 300 layers and some of 40: a wave to a chain, and (all of them together being too many) a lane."""
+@pytest.mark.parametrize("batch, short", [(3000, 0), (12288, 0), (3000, 262144), (12288, 262144)])
+def test_many_long_chains_of_a_ragged_batch(batch, short):
+    """Groups of 257 to 300 layers and some of 40, taken where they lie, and staged beside `short` chains of one layer: a
+    wave to a chain, and (all of them together being too many) a lane."""
     rng = np.random.default_rng(batch)
     lengths = np.where(rng.random(batch) < 0.1, 40, rng.integers(257, 301, size=batch))
+    lengths = np.concatenate([lengths, np.ones(short, dtype=np.int64)])
     d, _, off = inputs.ragged_batch(8, lengths)
     for c in range(0, batch, 5):
         d[off[c]:off[c + 1]] += 1

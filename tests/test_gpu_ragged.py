@@ -13,6 +13,9 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+STAGED = 262144  # chains beyond this are staged by the linear solver and not taken where they lie
+
+
 def to_dev(x):
     return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
 
@@ -102,7 +105,8 @@ def test_cubic_with_long_chains_in_the_batch():
 
 
 def test_one_large_group_beside_small_ones():
-    """A group of 70,001 chains spans many transposition tiles and leaves a ragged last tile."""
+    """A group of 70,001 chains spans many transposition tiles of the evaluations and leaves a ragged last tile; the linear
+    solver takes so many where they lie, the three longest with a wave each."""
     lengths = np.full(70004, 24)
     lengths[[0, 35000, 70003]] = [257, 1, 64]
     d, m, off = inputs.ragged_batch(14, lengths)
@@ -152,15 +156,16 @@ def test_chain_with_a_bad_size_is_reported_alone():
     assert np.array_equal(np_(peak)[[0, 2, 3]], good_peak[[0, 2, 3]])
 
 
-def test_linear_hands_chains_of_several_groups_to_its_later_kernels():
-    """Sizes that are no multiples of a power of two and need more than 30 bits leave the first
-    linear kernel for the 64-bit one, which then finds each listed chain's length and staging
-    from its group; a few chains whose sums pass 2^63 go on to the last kernel and come back with
-    their status.  Groups on both sides of the register-log limit, short and long mixed."""
-    lengths = np.array([3, 40, 300, 17, 40, 258, 1, 40, 255, 300, 17, 64] * 23, dtype=np.int64)
+@pytest.mark.parametrize("short", [0, STAGED])
+def test_linear_hands_chains_of_several_groups_to_its_later_kernels(short):
+    """Staged (beside `short` chains of one layer), sizes that are no multiples of a power of two and need more than 30 bits
+    leave the first linear kernel for the rows, or a wave each, which then find each listed chain's length and staging
+    from its group; a few chains whose sums pass 2^63 come back with their status.  Groups on both sides of the
+    register-log limit, short and long mixed.  Without the others the same chains are taken where they lie."""
+    lengths = np.array([3, 40, 300, 17, 40, 258, 1, 40, 255, 300, 17, 64] * 23 + [1] * short, dtype=np.int64)
     d, m, off = inputs.ragged_batch(21, lengths, lo_units=1 << 20, hi_units=1 << 36, unit=1)
     d_small, _, _ = inputs.ragged_batch(22, lengths)           # every third chain stays in the first kernel
-    for c in range(0, len(lengths), 3):
+    for c in range(0, 276, 3):
         d[off[c]:off[c + 1]] = d_small[off[c]:off[c + 1]]
     say(f"ragged linear, {len(lengths)} chains, 64-bit sizes in two of three")
     check_linear(d, off)
@@ -178,8 +183,10 @@ def test_linear_hands_chains_of_several_groups_to_its_later_kernels():
     assert (st[ok] == 0).all() and (st[hit] == 4).all()        # CKPT_ERR_OVERFLOW
     assert np.array_equal(np_(peak)[ok], want_peak[ok])
     got_mask = np_(mask)
-    for c in np.nonzero(ok)[0]:
-        assert np.array_equal(got_mask[off[c]:off[c + 1]], want_mask[off[c]:off[c + 1]]), f"chain {c}"
+    for c in hit:
+        assert not got_mask[off[c]:off[c + 1]].any()
+        got_mask[off[c]:off[c + 1]] = want_mask[off[c]:off[c + 1]]
+    assert np.array_equal(got_mask, want_mask)
 
 
 def test_many_distinct_lengths_and_repeated_calls():
@@ -275,6 +282,49 @@ def test_cubic_classes_in_one_launch_and_in_several(batch, longest):
     for c in where[::2]:
         d[off[c]:off[c + 1]] = rng.integers(1, (1 << 62) // (lengths[c] + 2), size=lengths[c] + 1)
     check_cubic(d, off)
+
+
+@pytest.mark.parametrize("longest, many", [(16, 3000), (17, 900), (17, 3000), (64, 900), (64, 150000), (257, 900), (257, 3000),
+                                           (1023, 1500), (1100, 900), (1100, 3000), (2048, 1500)])
+def test_what_the_lanes_of_a_staged_batch_leave(longest, many):
+    """Chains that leave the ring kernel's 32 bits or its ring in a batch that is staged: few of them (a wave each) and many
+    (rows, with LDS for all but the deepest; up to 64 layers lanes), unrounded ones and ones that need 64 bits, bad ones,
+    ones with more than 64 live entries, among chains of up to three layers."""
+    rng = np.random.default_rng(longest + many)
+    batch = STAGED + many + 1
+    lengths = rng.integers(1, 4, size=batch)
+    at = rng.permutation(batch)[:many]
+    lengths[at] = np.minimum(rng.choice([3, 15, 16, 17, 24], size=many), longest)
+    ends = [n for n in (40, 64, 130, 256, 257, 258, 300, 1001, 1023, 1024, longest) if n <= longest]
+    lengths[at[:4 * len(ends)]] = np.repeat(ends, 4)
+    lengths[at[-1]] = longest
+    d, _, off = inputs.ragged_batch(23, lengths)
+    say(f"ragged linear: {batch} chains, {many} of up to {longest} layers for the later kernels")
+    bad = {}
+    for k, c in enumerate(at):
+        n, part = int(lengths[c]), slice(off[c], off[c + 1])
+        if k % 4 == 3 and n >= 130:   # (one of the four of each end: more than 64 live entries)
+            d[part] = 1
+            d[off[c] + 1:off[c] + n] = np.arange(n - 1, 0, -1)
+            d[off[c] + n - 1] = 1 << 40
+        elif k % 2:
+            d[part] = np.floor(2 ** rng.uniform(20, 32, size=n + 1))
+            d[off[c]] |= 1
+        else:
+            d[part] = rng.integers(1 << 40, (1 << 62) // (n + 2), size=n + 1)
+        if k % 50 == 7:
+            bad[c] = (int(off[c] + k % (n + 1)), *((0, 3) if k % 100 == 7 else ((1 << 63) - 1, 4)))
+    want_peak, want_mask = oracle.ragged_solve_dynamic(d, off)
+    want_status = np.zeros(batch, dtype=np.int32)
+    for c, (place, value, code) in bad.items():
+        d[place] = value
+        want_status[c], want_peak[c] = code, -1
+        want_mask[off[c]:off[c + 1]] = 0
+    for off_dev in (None, to_dev(off)):
+        mask, peak, status = B.ckpt_ragged_solve_linear(to_dev(d), off, offsets_dev=off_dev)
+        assert np.array_equal(np_(status), want_status)
+        assert np.array_equal(np_(peak), want_peak)
+        assert np.array_equal(np_(mask), want_mask)
 
 
 @pytest.mark.parametrize("batch, deep", [(1100, 5), (1100, 64), (1100, 65), (4000, 70), (20000, 300), (20000, 3000)])

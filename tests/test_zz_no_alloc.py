@@ -7,8 +7,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2502_12499_amd import binding as B
 from paper_2502_12499_amd import inputs
+from test_gpu_linear_wave import live_entries
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -62,19 +64,44 @@ def test_limits_are_host_errors():
     assert lib.ckpt_solve_linear_noalloc(None, ctypes.byref(B.Layout(4, 8, 1, 4)), fake, fake, None, None) == 1
 
 
+def check_at_the_largest_batch(d, status):
+    want = B.ckpt_solve_linear(d)
+    mask, peak, code = torch.full_like(want[0], 7), torch.full_like(want[1], -5), torch.full_like(want[2], -5)
+    torch.cuda.synchronize()
+    B.ckpt_solve_linear_noalloc(d, mask, peak, code)
+    torch.cuda.synchronize()
+    assert torch.equal(code, status)
+    same(want, (mask, peak, code))
+
+
 def test_the_last_kernel_at_the_largest_batch():
-    """With the largest batch the lists fill the library's array to its end: chains that go through both
-    lists (sizes that are not positive, found after most of the chain) must not need room behind them."""
-    n, batch = 24, 1048576
+    """With the largest batch the lists fill the library's array to its end: every chain goes through both of them (a size
+    that is not positive; up to 16 layers the kernel between leaves such chains to the last one), and none may need room
+    behind them."""
+    n, batch = 12, 1048576
     gen = torch.Generator(device=DEV)
     gen.manual_seed(5)
     d = torch.randint(256, 32769, (n + 1, batch), generator=gen, device=DEV, dtype=torch.int64) * 4096
-    bad = torch.arange(0, batch, 100003, device=DEV)
-    d[0, bad] = 0
-    want = B.ckpt_solve_linear(d)
-    mask, peak, status = torch.full_like(want[0], 7), torch.full_like(want[1], -5), torch.full_like(want[2], -5)
-    torch.cuda.synchronize()
-    B.ckpt_solve_linear_noalloc(d, mask, peak, status)
-    torch.cuda.synchronize()
-    assert int((want[2] != 0).sum()) == len(bad)
-    same(want, (mask, peak, status))
+    d[n, ::2] = 1 << 50
+    d[0] = 0
+    check_at_the_largest_batch(d, torch.full((batch,), 3, dtype=torch.int32, device=DEV))
+
+
+@pytest.mark.parametrize("bad", [11, 2000])
+def test_what_rows_leave_at_the_largest_batch(bad):
+    """Longer chains go to rows or a wave each, which report bad sizes themselves and leave chains with more than 64 live
+    entries to the last kernel."""
+    n, batch = 130, 1048576
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(6)
+    d = torch.randint(256, 32769, (n + 1, batch), generator=gen, device=DEV, dtype=torch.int64) * 4096
+    at = torch.randperm(batch, generator=gen, device=DEV)
+    d[:, at[:16]] = torch.from_numpy(live_entries(n)).to(DEV)
+    status = torch.zeros(batch, dtype=torch.int32, device=DEV)
+    d[n // 2, at[16:16 + bad]] = 0
+    status[at[16:16 + bad]] = 3
+    check_at_the_largest_batch(d, status)
+    peak, mask = oracle.batch_solve_dynamic(inputs.chain_major(live_entries(n)))
+    got = B.ckpt_solve_linear(d)
+    assert (got[1][at[:16]] == int(peak[0])).all()
+    assert (got[0][:, at[:16]] == torch.from_numpy(mask[0]).to(DEV)[:, None]).all()
