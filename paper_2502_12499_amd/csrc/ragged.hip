@@ -9,6 +9,7 @@
 // the caller's stream.
 #include <vector>
 
+#include "linear_wave.h"
 #include "ragged_plan.h"
 
 namespace ckpt {
@@ -162,9 +163,10 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
             t.tiles2 = at.tiles2 + v[5];
             t.staged = at.staged + v[6];
             const int slot = t.n_groups;
-            groups[slot] = ragged_next_group(t, n, many, &first2);
+            const RaggedGroupDev g = ragged_next_group(t, n, many, &first2);
+            groups[slot] = g;
             tile_first2[slot] = first2;
-            if (groups[slot].first < batch - kLongest && batch - kLongest <= t.chains) totals->rows_longest = n;
+            if (g.first < batch - kLongest && batch - kLongest <= t.chains) totals->rows_longest = n;
         }
         at.n_groups += (int32_t)all[0];
         at.chains += all[1];
@@ -181,24 +183,32 @@ __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint
         own.deep_layers += one.deep_layers;
         own.layers += one.layers;
     }
-#pragma unroll
-    for (int s = kWave / 2; s >= 1; s >>= 1) {
-        own.wave_longest = max(own.wave_longest, __shfl_xor(own.wave_longest, s));
-        own.lane_longest = max(own.lane_longest, __shfl_xor(own.lane_longest, s));
-        own.wave_layers += __shfl_xor(own.wave_layers, s);
-        own.lane_waves += __shfl_xor(own.lane_waves, s);
-        own.deep_chains += __shfl_xor(own.deep_chains, s);
-        own.deep_layers += __shfl_xor(own.deep_layers, s);
-        own.layers += __shfl_xor(own.layers, s);
+    // (what no thread of a wave has is passed over; with shuffles of all of it the launch took 3 us longer)
+    const bool last = threadIdx.x % kWave == kWave - 1;
+    if (__any(own.layers != 0)) {
+        const int64_t all = sum_up_to(own.layers);
+        const int deepest = max_up_to(own.lane_longest);
+        if (last) {
+            atomicAdd(&layers, (unsigned long long)all);
+            atomicMax(&lane_longest, deepest);
+        }
     }
-    if (threadIdx.x % kWave == 0) {
-        atomicMax(&wave_longest, own.wave_longest);
-        atomicMax(&lane_longest, own.lane_longest);
-        atomicAdd(&wave_layers, (unsigned long long)own.wave_layers);
-        atomicAdd(&lane_waves, (unsigned long long)own.lane_waves);
-        atomicAdd(&deep_chains, own.deep_chains);
-        atomicAdd(&deep_layers, (unsigned long long)own.deep_layers);
-        atomicAdd(&layers, (unsigned long long)own.layers);
+    if (__any(own.wave_layers != 0)) {
+        const int64_t all = sum_up_to(own.wave_layers), waves = sum_up_to(own.lane_waves);
+        const int deepest = max_up_to(own.wave_longest);
+        if (last) {
+            atomicAdd(&wave_layers, (unsigned long long)all);
+            atomicAdd(&lane_waves, (unsigned long long)waves);
+            atomicMax(&wave_longest, deepest);
+        }
+    }
+    if (__any(own.deep_layers != 0)) {
+        const int64_t all = sum_up_to(own.deep_layers);
+        const int chains = sum_up_to(own.deep_chains);
+        if (last) {
+            atomicAdd(&deep_layers, (unsigned long long)all);
+            atomicAdd(&deep_chains, chains);
+        }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
