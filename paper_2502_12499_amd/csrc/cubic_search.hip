@@ -415,7 +415,7 @@ __device__ inline uint64_t select_lanes(uint64_t off, uint64_t on, uint64_t mask
 // sums are under way; a window that reaches back beyond Z is finished from two older slices and from the values
 // parked in F (whose sums come from memory: 64 layers a segment are usual in a chain of 4,096).
 // What bounds it is the chain of dependent instructions of a head (about 45, half of them scalar, eight to nine
-// cycles each; a loop of its own for the heads of a slice takes three jumps a head out of it, 7 % at 4,096 layers); a
+// cycles each; a loop of its own for the heads of a slice takes three jumps a head out of it); a
 // form that kept the values in LDS took 1,190 cycles a head, most of it four LDS round trips. P: prefix sums, P[n]
 // below 2^31 or 2^63; F (and head): room for n + 1 + kWave values; RECORD: head[j], a minimal predecessor of j, is
 // written for j = 1..n, F(j) for j < n, and *ties says whether any was one of several.  stop(F(h)) is asked once per
@@ -967,7 +967,7 @@ namespace {
 // twenty, so `finish` takes one pass; it takes whatever is left.  A call is bound by two or three passes in a row, each
 // as long as its slowest wave (a point of many heads).  A point whose F(h) has passed what the best cost seen leaves
 // stops: a small s would have a head at every cell. Measured, with every budget evaluated in brackets: one chain of
-// 4,096 aligned layers 290 us (1,650), of 1,001 of a network 97 (1,200 to 1,490; 480 while the first of equal
+// 4,096 aligned layers 300 us (1,650), of 1,001 of a network 97 (1,200 to 1,490; 480 while the first of equal
 // predecessors was taken and there were always two rounds), of 152 of a network 48 (121 to 137; 90 then); two of 3,115
 // aligned layers 396 (2,215); 100 of 1,001 466 (5,260), unrounded 484 (118,000); 1,000 of 300 600 (3,710), unrounded
 // 685 (34,000).

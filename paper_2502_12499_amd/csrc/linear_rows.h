@@ -5,8 +5,8 @@
 // a DPP operand (row_newbcast), so a position costs nine instructions for four chains at once, no scalar register is
 // passed, and nothing diverges; the work around a block (about 150 instructions) falls on 16 positions instead of 64.
 // Values are 32-bit integers, or doubles as exact 53-bit integers (one instruction for a sum, a maximum or a comparison;
-// an int64 maximum is three): where the sizes, divided by their common power of two, need more than that, where a
-// queue outgrows its row, or a size is not positive, the chain is left to the form of a wave per chain.
+// a 64-bit maximum is three), or unsigned 64-bit integers where the sizes, divided by their common power of two, need
+// them.  Where a queue outgrows its row, or a size is not positive, the chain is left to the form of a wave per chain.
 //
 // What bounds it is issue again, and alone on a SIMD the wait states around DPP operands: 72 ns a position (32 bits;
 // 105 in doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 61 us (66 with a move for

@@ -159,8 +159,8 @@ template <> constexpr double kBeyond<double> = (double)((int64_t)1 << 52);  // (
 template <> constexpr uint64_t kBeyond<uint64_t> = (uint64_t)1 << 63;       // (twice as much fits: every checked chain)
 
 // Turns the order around: the smallest of values is what the largest of these is turned back.
-template <class S> __device__ inline S turned(S v) { return ~v; }
-__device__ inline double turned(double v) { return -v; }
+template <class S> __device__ inline S turned(S v) { return -v; }
+__device__ inline uint64_t turned(uint64_t v) { return ~v; }
 
 constexpr int kQueueBytes = 2048;
 // Bytes of LDS: the queue while it is put together, the steps of a chain.

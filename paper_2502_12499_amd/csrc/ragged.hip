@@ -112,10 +112,9 @@ __device__ inline void block_exclusive_sums(int64_t (&v)[kSums], int64_t (&total
 
 // One workgroup: the lengths in tiles of kCountThreads, a length per thread.  Most of the 65,535 possible lengths do
 // not occur, so the tiles that hold none are found first (every thread reads its length of every tile up to the longest
-// that was counted, the loads in flight together; 13 us with 1,001 layers at most, 18 through all 64 tiles) and passed
-// over; in a tile that holds some, every thread adds up what its group contributes to the totals and, knowing the
-// totals before it, writes the group's descriptor.  (A thread per stretch of 64 lengths, each walked twice, took 65
-// us; this takes 16.)
+// that was counted, the loads in flight together) and passed over; in a tile that holds some, every thread adds up what its
+// group contributes to the totals and, knowing the totals before it, writes the group's descriptor.  13 us with 1,001
+// layers at most; 18 where all 64 tiles are looked at, 65 with a thread per stretch of 64 lengths, each walked twice.
 __global__ __launch_bounds__(kCountThreads) void ragged_layout_kernel(const uint32_t *__restrict__ hist,
                                                                       int64_t batch, RaggedGroupDev *__restrict__ groups,
                                                                       int64_t *__restrict__ tile_first2,
@@ -472,7 +471,7 @@ int ragged_run(int which, const int64_t *d, const uint8_t *mask_in, const int64_
     const int n_groups = p.t.n_groups;
     if (which == CKPT_CALL_SOLVE_CUBIC && p.t.max_layers <= kSearchMaxLayers) {
         // Short chains are solved one by one where they lie: nothing is grouped, staged or put back (1,000
-        // chains of 2 to 152 layers: 0.25 ms; group after group, 136 of them, it took 6.7 ms).
+        // chains of 2 to 152 layers: 0.11 ms; group after group, 136 of them, it took 6.7 ms).
         if (!offsets_dev) {
             if (hipMemcpyAsync(base + w.off, offsets_host, (size_t)(batch + 1) * 8, hipMemcpyHostToDevice, stream) !=
                     hipSuccess ||

@@ -54,8 +54,8 @@
 //        loops.  What it cannot take goes on the second list, or is done by the wave.
 //   list kernel     one wave per chain of the second list (lane 0 works),
 //        64-bit values, stacks of full capacity n+1 in LDS (n <= 2047) or in
-//        the workspace.  Correct for any input, and the only writer of error
-//        statuses.
+//        the workspace.  Correct for any input.  (Error statuses are written
+//        here and by the form of a wave per chain.)
 #include "ckpt_internal.h"
 #include "linear_rows.h"
 #include "linear_wave.h"
@@ -618,7 +618,9 @@ __device__ __forceinline__ bool wave_chain(const int64_t *__restrict__ dp, const
             }
         }
     };
-    if (n < 4 * kWave) pass(std::integral_constant<int, 4>());
+    // (the hint only says which pass lies out of line: without it one chain of 152 layers 9.3 us instead of 8.9, 997 of
+    // 1,001 57.3 instead of 56.2)
+    if (__builtin_expect(n < 4 * kWave, 0)) pass(std::integral_constant<int, 4>());
     else pass(std::integral_constant<int, 16>());
     bits = lane_value(bits_up_to(bits), kWave - 1);
     sum = lane_value(sum_up_to(sum), kWave - 1);
@@ -1246,8 +1248,11 @@ __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__
 // kernel's lanes beyond.  Waves and rows, us: 1,001 layers, 1,024 chains 62 and 79, 2,048 chains 100 and 82, unrounded
 // ones 131 and 115, 204 and 121.  Rows and lanes at 65,536 chains: 64 layers 49 and 51 (unrounded, which the lanes try
 // in 32 bits first, 72 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at
-// 131,072 aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD four waves, or one up to
-// 16,384 chains: 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than those.
+// 131,072 aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD three waves (four end at 1,023
+// layers), or one up to 16,384 chains: 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than
+// those.  Rows take the same time whatever the sizes are; lanes take less where all chains move alike, so 65,536 chains
+// whose layers are all of one size are slower by rows: 64 layers 43 us (28 by lanes), 256 138 (84), 1,001 581 (385).
+// 16,384 of them are not: 15 (26), 47 (79), 192 (352).
 static_assert(kLongest <= 1024, "fewer than the chains of a batch that takes rows");
 constexpr int64_t kWaveBatch = 1024, kRowsFewBatch = 16384, kRowsBatch = 65536;
 constexpr int kRowsFewMaxLayers = 4095, kRowsMaxLayers = 1279;
