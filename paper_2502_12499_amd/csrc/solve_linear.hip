@@ -44,8 +44,8 @@
 //        the chain's mask_out slot i.  A final forward sweep turns them into the mask.
 //        A lane defers its chain when a ring fills, the values outgrow 30 bits,
 //        a step exceeds 255 positions, or a size is not positive: it appends
-//        the chain to a list in the workspace, those with sizes of 2^44 and more from the list's end if lanes and
-//        rows are to share it.
+//        the chain to a list in the workspace, those with large sizes from the list's end if lanes and rows are to
+//        share it.
 //   rows and waves  few chains, and what the ring kernel leaves of many: four chains to a wave (linear_rows.h) or one
 //        (linear_wave.h), in 32-bit integers, doubles or 64-bit integers.  Chains they cannot take either (more than 64
 //        entries live) go on a second list.
@@ -82,7 +82,7 @@ constexpr int kLdsStackMaxN = 2047;
 constexpr int kWaveMaxLayers = 16383;  // of the wave kernel: 34 KB of LDS
 
 struct LinearWs {
-    int32_t *count;   // [3] chains deferred by the ring kernel, without and with a size of 2^44 or more (one 64-bit word to a
+    int32_t *count;   // [3] chains deferred by the ring kernel, without and with a large size (one 64-bit word to a
                       // wave that has both), and chains deferred again by the kernels after it (first 256 bytes)
     int32_t *list;    // [batch] the first; the last from the end backwards
     int32_t *list2;   // [batch] the second
@@ -506,11 +506,65 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
         for (int u = 0; u < kChunk; ++u) rows[u] = ahead[u];
     }
 
-    const bool file = live && defer, is_large = w.apart && large >> 12 != 0;
-    const uint64_t filed = __builtin_amdgcn_ballot_w64(file);
-    if (filed != 0) {
-        const uint64_t large_ones = __builtin_amdgcn_ballot_w64(file && is_large), others = filed & ~large_ones;
-        const int first = __builtin_ctzll((unsigned long long)filed);
+    const auto results = [&] {
+        peak_out[c] = (int64_t)((uint64_t)Mi << sh);
+        if (status_out) status_out[c] = CKPT_OK;
+        if constexpr (LOG_REGS) {
+            // forward sweep over the steps in the registers: position i = n-1 - (8k + u), ascending.
+            // Rows are addressed by a scalar base that moves up one row per position, plus the lane's
+            // offset; only the first chunk taken (the last one filled) can reach below position 0.
+            int cur = 0;
+            auto sweep_chunk = [&](const int ks, const bool guarded) {
+                const uint32_t w0 = logA[ks], w1 = logB[ks];
+                const int ilow = n - 1 - (kChunk * ks + kChunk - 1);  // the chunk's lowest position (below 0 if guarded)
+                uint8_t *rowp = mbase + (int64_t)ilow * pstride;      // wave-uniform; one row up per position
+#pragma unroll
+                for (int u = kChunk - 1; u >= 0; --u, rowp += pstride) {
+                    const int i = ilow + (kChunk - 1 - u);
+                    if (guarded && i < 0) continue;
+                    const uint32_t step = ((u < 4 ? w0 : w1) >> (8 * (u & 3))) & 255u;
+                    const bool on = i == cur;
+                    cur = on ? i + 1 + (int)step : cur;
+                    rowp[moff] = on ? 1 : 0;
+                }
+            };
+            int k = chunk - 1;
+            if (k >= 0) sweep_chunk(__builtin_amdgcn_readfirstlane(k), true);
+            for (--k; k >= 0; --k) sweep_chunk(__builtin_amdgcn_readfirstlane(k), false);
+            mp[(int64_t)n * pstride] = 1;
+            return;
+        }
+        // forward sweep: replace the parked steps by the mask (once they have all landed)
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        int cur = 0;
+        constexpr int kSweep = 32;  // rows in flight per lane in this sweep, which does nothing but wait for them
+        for (int k0 = 0; k0 <= n; k0 += kSweep) {
+            uint8_t b[kSweep];
+#pragma unroll
+            for (int u = 0; u < kSweep; ++u) b[u] = (k0 + u) <= n ? mp[(int64_t)(k0 + u) * pstride] : 0;
+#pragma unroll
+            for (int u = 0; u < kSweep; ++u) {
+                const int k = k0 + u;
+                const bool on = k == cur;
+                if (on) cur = k + 1 + b[u];
+                b[u] = on ? 1 : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kSweep; ++u)
+                if ((k0 + u) <= n) mp[(int64_t)(k0 + u) * pstride] = b[u];
+        }
+    };
+    if (live && !defer) results();
+    // (after the results: in front of them they wait for the atomic, 172 us instead of 160 for 1,048,576 chains of 16 layers
+    // with one in fifty deferred)
+    if (!w.apart) {
+        if (live && defer) w.list[atomicAdd(w.count, 1)] = (int32_t)(c + list_base);
+    } else if (__builtin_amdgcn_ballot_w64(live && defer) != 0) {
+        // (about the size from which on a chain of so many layers needs 64 bits: 2^48 of 17, 2^46 of 64)
+        const bool file = live && defer, is_large = large >> (__clz(n + 1) - 11) != 0;
+        const uint64_t large_ones = __builtin_amdgcn_ballot_w64(file && is_large);
+        const uint64_t others = __builtin_amdgcn_ballot_w64(file && !is_large);
+        const int first = __builtin_ctzll((unsigned long long)(large_ones | others));
         const int many_large = (int)__popcll((unsigned long long)large_ones), many = (int)__popcll((unsigned long long)others);
         unsigned long long at = 0;
         if (lane == first) {
@@ -523,53 +577,6 @@ __device__ __forceinline__ void linear_ring_wave(const int64_t *__restrict__ d, 
         const uint64_t before = (1ull << lane) - 1;
         if (file && is_large) w.list_end[-1 - at_large - (int)__popcll((unsigned long long)(large_ones & before))] = (int32_t)(c + list_base);
         if (file && !is_large) w.list[at_other + (int)__popcll((unsigned long long)(others & before))] = (int32_t)(c + list_base);
-    }
-    if (!live || defer) return;
-    peak_out[c] = (int64_t)((uint64_t)Mi << sh);
-    if (status_out) status_out[c] = CKPT_OK;
-    if constexpr (LOG_REGS) {
-        // forward sweep over the steps in the registers: position i = n-1 - (8k + u), ascending.
-        // Rows are addressed by a scalar base that moves up one row per position, plus the lane's
-        // offset; only the first chunk taken (the last one filled) can reach below position 0.
-        int cur = 0;
-        auto sweep_chunk = [&](const int ks, const bool guarded) {
-            const uint32_t w0 = logA[ks], w1 = logB[ks];
-            const int ilow = n - 1 - (kChunk * ks + kChunk - 1);  // the chunk's lowest position (below 0 if guarded)
-            uint8_t *rowp = mbase + (int64_t)ilow * pstride;      // wave-uniform; one row up per position
-#pragma unroll
-            for (int u = kChunk - 1; u >= 0; --u, rowp += pstride) {
-                const int i = ilow + (kChunk - 1 - u);
-                if (guarded && i < 0) continue;
-                const uint32_t step = ((u < 4 ? w0 : w1) >> (8 * (u & 3))) & 255u;
-                const bool on = i == cur;
-                cur = on ? i + 1 + (int)step : cur;
-                rowp[moff] = on ? 1 : 0;
-            }
-        };
-        int k = chunk - 1;
-        if (k >= 0) sweep_chunk(__builtin_amdgcn_readfirstlane(k), true);
-        for (--k; k >= 0; --k) sweep_chunk(__builtin_amdgcn_readfirstlane(k), false);
-        mp[(int64_t)n * pstride] = 1;
-        return;
-    }
-    // forward sweep: replace the parked steps by the mask (once they have all landed)
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-    int cur = 0;
-    constexpr int kSweep = 32;  // rows in flight per lane in this sweep, which does nothing but wait for them
-    for (int k0 = 0; k0 <= n; k0 += kSweep) {
-        uint8_t b[kSweep];
-#pragma unroll
-        for (int u = 0; u < kSweep; ++u) b[u] = (k0 + u) <= n ? mp[(int64_t)(k0 + u) * pstride] : 0;
-#pragma unroll
-        for (int u = 0; u < kSweep; ++u) {
-            const int k = k0 + u;
-            const bool on = k == cur;
-            if (on) cur = k + 1 + b[u];
-            b[u] = on ? 1 : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < kSweep; ++u)
-            if ((k0 + u) <= n) mp[(int64_t)(k0 + u) * pstride] = b[u];
     }
 }
 
