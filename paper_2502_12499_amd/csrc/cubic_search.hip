@@ -767,6 +767,560 @@ struct SearchWs {
 
 __global__ void cubic_search_reset_kernel(SearchWs w) { *w.count = 0; }
 
+// ---------------------------------------------------------------------------
+// many short chains: a row of lanes per chain
+// ---------------------------------------------------------------------------
+
+// A search needs few evaluations if each round knows the last one's: a chain of 64 unrounded layers is settled by 29 with
+// eight points a round (4.5 rounds), by 85 with 64 (2.4 rounds).  Where there are chains enough to fill the chip, a wave
+// therefore takes kWave / G of them, G lanes each, and the rounds of all run side by side.
+//   What an evaluation tells.  A pass for s finds the window start of every cell, and with it the largest budget up to s
+// (c is the same there) and the smallest one above it: the sums that just fit a window and those that just do not.  So a
+// point costs what its budget costs, an interval without a budget in it is closed without a look, and every round closes
+// at least one budget of every open interval at its upper end.
+//   The state of a chain is one open interval for each of its lanes: the one below the lane's point.  G points in m open
+// intervals, at least one in each, one of them at its upper end, leave at most G: nothing is ever put aside.
+//   The pass.  As in lane_cost the window minimum is that of suffix minima, but positions are taken in blocks of four,
+// whose values stay in registers: what of the block under way lies in the window is joined by comparing the sums, and L1
+// and L2 are written once a block has been filled, so that nothing has to be cleared or lowered cell by cell.  L2 is lowered
+// from the first block that any lane still reads.  The window starts of a block do not depend on values.  They come from a
+// table over the range of the prefix sums, slots of one width: the first position at or above the slot's lower end, then
+// three sums tested at once.  (Moving a start on from that of the cell before takes as many turns as the lane that moves
+// farthest: 2.8 instead of 1.3 at eight unrounded chains a wave.)  Table, sums and minima are read a block ahead each.
+// What bounds it: issue, about 145 vector and 24 LDS instructions a block of four cells, and the two waves on a SIMD that
+// the LDS space leaves (20 KB a wave at 64 layers); the rounds of a wave are those of its slowest chain (5.3 and 6.4 of 4.5
+// and 5.0).  65,536 chains of 64 layers, unrounded 0.70 ms (a wave a chain: 1.29), aligned 0.55 (1.11).
+constexpr int kRowBlk = 4;
+constexpr int kRowSlots = 4;   // slots of the table per layer
+constexpr int kRowsMaxLayers = 128;
+constexpr int kRowsOf8Layers = 72;
+
+__host__ __device__ inline int row_blocks(int n) { return (n + kRowBlk - 1) / kRowBlk; }
+// Prefix sums from position -1 on, with the padding that what is read ahead sees.
+__host__ __device__ inline int row_sums(int n) { return (row_blocks(n) + 4) * kRowBlk + 2; }
+// The slots of a chain, four more so that those of the chains of a wave lie in banks of their own.
+__host__ __device__ inline int row_slots(int n) { return n * kRowSlots + 4 * kRowSlots; }
+// Positions whose minima a lane keeps: those of all windows, and of longer chains those of nearly all (the windows up to the
+// best cost reach over 37 layers in one of a hundred chains of 64 unrounded layers, over 50 of 128; over 60 in one of ten
+// networks of 128).  What it saves is waves in flight: 65,536 aligned chains of 64 layers 756 us with a ring of 64, 557 with
+// 40; 128 layers with 72, 60, 48: aligned 2.0, 1.7, 1.5 ms, networks 2.3, 2.7, 3.6 ms (5.1 and 4.1 with a wave a chain).
+__host__ __device__ inline int row_ring(int n)
+{
+    const int most = row_blocks(n) * kRowBlk, a = 32 + n / 8, b = 12 + 3 * n / 8;
+    const int some = ((a > b ? a : b) + kRowBlk - 1) / kRowBlk * kRowBlk;
+    return most < some ? most : some;
+}
+__host__ __device__ inline size_t rows_lds_bytes(int n, int chains, int ring)
+{
+    const size_t per_lane = ring + ring / kRowBlk, per_chain = (size_t)row_sums(n) + row_blocks(n) * kRowBlk;
+    return ((per_lane + 1) * kWave + per_chain * chains) * 4 + (size_t)row_slots(n) * chains;
+}
+
+template <int G>
+struct RowsLds {
+    static constexpr int kChains = kWave / G;
+    int ring;
+    uint32_t *L2;  // [ring / kRowBlk][kWave] minimum of the full blocks behind one
+    uint32_t *L1;  // [ring][kWave] minimum from a position to the end of its block
+    uint32_t *P;   // [row_sums(n)][kChains] d_1 + .. + d_k + span + 1 from k = -1 on (0 there), padded with the last
+    uint32_t *F;   // [blocks * kRowBlk][kChains] the values of the last pass
+    int *slot;     // [kWave]
+    uint8_t *T;    // [kChains][row_slots(n)] the first position at or above a slot's lower end
+    __device__ RowsLds(unsigned char *base, int n, int ring) : ring(ring)
+    {
+        L2 = (uint32_t *)base;
+        L1 = L2 + ring / kRowBlk * kWave;
+        P = L1 + ring * kWave;
+        F = P + (size_t)row_sums(n) * kChains;
+        slot = (int *)(F + (size_t)row_blocks(n) * kRowBlk * kChains);
+        T = (uint8_t *)(slot + kWave);
+    }
+};
+
+// ---- across the G lanes of a row ----
+
+constexpr int kDppSwap1 = 0xb1, kDppSwap2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+template <int CTRL>
+__device__ inline uint32_t dpp_of(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false); }
+template <int CTRL>
+__device__ inline uint64_t dpp_of(uint64_t v)
+{
+    return ((uint64_t)dpp_of<CTRL>((uint32_t)(v >> 32)) << 32) | dpp_of<CTRL>((uint32_t)v);
+}
+template <int CTRL>
+__device__ inline float dpp_of(float v) { return __uint_as_float(dpp_of<CTRL>(__float_as_uint(v))); }
+
+// v joined over the row, for all of its lanes (the mirrors stand for swaps by 4 and 8: what they exchange is the same in
+// all lanes of a quad, of half a row)
+template <int G, typename V, typename Join>
+__device__ inline V row_all(V v, Join join)
+{
+    static_assert(G == 8 || G == 16 || G == 64, "rows that the operations across lanes have");
+    v = join(v, dpp_of<kDppSwap1>(v));
+    v = join(v, dpp_of<kDppSwap2>(v));
+    v = join(v, dpp_of<kDppHalfMirror>(v));
+    if constexpr (G > 8) v = join(v, dpp_of<kDppMirror>(v));
+    if constexpr (G > 16) {
+        v = join(v, __shfl_xor(v, 16, kWave));
+        v = join(v, __shfl_xor(v, 32, kWave));
+    }
+    return v;
+}
+template <int G, typename V>
+__device__ inline V row_min(V v) { return row_all<G>(v, [](V a, V b) { return a < b ? a : b; }); }
+template <int G, typename V>
+__device__ inline V row_sum(V v) { return row_all<G>(v, [](V a, V b) { return a + b; }); }
+
+// v joined with those of the lanes before, where 0 changes nothing
+template <int CTRL, int ROW_MASK>
+__device__ inline uint32_t dpp_or_0(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false); }
+template <int CTRL, int ROW_MASK>
+__device__ inline uint64_t dpp_or_0(uint64_t v)
+{
+    return ((uint64_t)dpp_or_0<CTRL, ROW_MASK>((uint32_t)(v >> 32)) << 32) | dpp_or_0<CTRL, ROW_MASK>((uint32_t)v);
+}
+template <int G, typename V, typename Join>
+__device__ inline V row_scan(V v, Join join)
+{
+    const int i = threadIdx.x % G;
+    const auto step = [&](V from, int k) { v = join(v, G >= 16 || i >= k ? from : (V)0); };
+    step(dpp_or_0<kDppRowShr1, 0xf>(v), 1);
+    step(dpp_or_0<kDppRowShr2, 0xf>(v), 2);
+    step(dpp_or_0<kDppRowShr4, 0xf>(v), 4);
+    if constexpr (G > 8) step(dpp_or_0<kDppRowShr8, 0xf>(v), 8);
+    if constexpr (G > 16) {
+        step(dpp_or_0<kDppRowBcast15, 0xa>(v), 16);
+        step(dpp_or_0<kDppRowBcast31, 0xc>(v), 32);
+    }
+    return v;
+}
+
+// F_s(n) without the size at the end.  FLAT: the prefix sums are those in full; else they are modulo 2^32, and values are cut
+// to 2^31.  `record`: the values go to m.F.  `slack`: how far the largest budget up to s lies below it; `gap`: minus how far the next one lies above (or
+// a value that is not negative if there is none).  `cut`: a window reached back beyond the ring and was cut off there, so
+// that the result is what F_s(n) does not exceed.
+template <bool FLAT, int G>
+__device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool record, const int n, const uint32_t first,
+                                              const uint32_t s, const int shift, uint32_t &slack, uint32_t &gap, bool &cut)
+{
+    typedef uint32_t U;
+    typedef int32_t I;
+    constexpr int C = kWave / G;
+    constexpr U kMax = ~0u, kCap = 1u << 31;
+    const int lane = threadIdx.x, row = lane / G, nb = row_blocks(n);
+    const int ring = m.ring, ring_blocks = ring / kRowBlk;
+    const U *const P = m.P + row;   // P[(k + 1) * C]: the sum at position k
+    const uint8_t *const T = m.T + row * row_slots(n);
+    U least = kMax, most = 0, far = 0;
+    U p[kRowBlk][4];
+    // three sums from a window's start on against where the window may begin
+    const auto test = [&](int &l, const U e, const U p0, const U p1, const U p2) {
+        U t0, t1, t2;
+        if constexpr (FLAT) {  // (the difference and the comparison are one instruction)
+            l += __builtin_sub_overflow(p0, e, &t0) ? 1 : 0;
+            l += __builtin_sub_overflow(p1, e, &t1) ? 1 : 0;
+            l += __builtin_sub_overflow(p2, e, &t2) ? 1 : 0;
+        } else {
+            t0 = p0 - e; t1 = p1 - e; t2 = p2 - e;
+            l += (int)((I)t0 < 0) + (int)((I)t1 < 0) + (int)((I)t2 < 0);
+        }
+        far |= t2;
+        U a = t0 < t1 ? t0 : t1, z = t0 > t1 ? t0 : t1;
+        a = a < t2 ? a : t2;
+        z = z > t2 ? z : t2;
+        least = a < least ? a : least;
+        most = z > most ? z : most;
+    };
+    const auto sums = [&](const int (&l)[kRowBlk]) {
+#pragma unroll
+        for (int u = 0; u < kRowBlk; ++u) {
+            const U *const at = P + l[u] * C;
+            p[u][0] = at[0]; p[u][1] = at[C]; p[u][2] = at[2 * C]; p[u][3] = at[3 * C];
+        }
+    };
+    const auto move_on = [&](const U (&e)[kRowBlk], int (&l)[kRowBlk]) {
+        far = 0;
+#pragma unroll
+        for (int u = 0; u < kRowBlk; ++u) {
+            const U tm = p[u][0] - e[u];
+            most = tm > most ? tm : most;
+            test(l[u], e[u], p[u][1], p[u][2], p[u][3]);
+        }
+        while (__builtin_expect(__builtin_amdgcn_ballot_w64((I)far < 0) != 0, 0)) {
+            far = 0;
+            sums(l);
+#pragma unroll
+            for (int u = 0; u < kRowBlk; ++u) test(l[u], e[u], p[u][1], p[u][2], p[u][3]);
+        }
+    };
+    // a window that begins at e holds the position with this sum
+    const auto holds = [&](U sum, U e) { return FLAT ? sum >= e : (I)(sum - e) >= 0; };
+    // the sums that block b's positions end in, and where the windows of the cells behind them may begin
+    const auto load = [&](U (&x)[kRowBlk], int b) {
+#pragma unroll
+        for (int u = 0; u < kRowBlk; ++u) x[u] = P[(b * kRowBlk + u + 1) * C];
+    };
+    // (modulo 2^32 the sums wrap now and then as they ascend; the table is that of the sums in full)
+    U wraps = 0, latest = 0;
+    const auto table = [&](const U (&x)[kRowBlk], U (&e)[kRowBlk], int (&l)[kRowBlk]) {
+#pragma unroll
+        for (int u = 0; u < kRowBlk; ++u) {
+            e[u] = x[u] - s;
+            if constexpr (FLAT) {
+                l[u] = T[(uint32_t)(e[u] >> shift)];
+            } else {
+                wraps += x[u] < latest ? 1 : 0;
+                latest = x[u];
+                l[u] = T[(uint32_t)((((uint64_t)wraps << 32 | x[u]) - s) >> shift)];
+            }
+        }
+    };
+    // In turn b: the sums x that block b's positions end in and those of the two blocks behind it, where the windows of the
+    // cells behind each may begin (e), their starts l, for the next block what the table says of them.  Block b has slot b %
+    // kTurns of each: the turns are written out, so that nothing is moved from one to the next.
+    constexpr int kTurns = 4;
+    int l[kTurns][kRowBlk] = {};
+    U x[kTurns][kRowBlk], e[kTurns][kRowBlk];
+    load(x[0], 0);
+    load(x[1], 1);
+    load(x[2], 2);
+    table(x[0], e[0], l[0]);
+    table(x[1], e[1], l[1]);
+    sums(l[0]);
+    move_on(e[0], l[0]);
+    U f[kRowBlk + 1], edge = e[0][0] - 1;  // edge: the sum at the last position before the block (before the first: out)
+    f[kRowBlk] = first;
+    int low = 0;                           // the first block that holds a window's start
+    int turn = 0;                          // the last multiple of `ring`
+    cut = false;
+    U *const L1 = m.L1 + lane, *const L2 = m.L2 + lane;
+    const auto block = [&](const int b, auto r) {
+        constexpr int r0 = decltype(r)::value, r1 = (r0 + 1) % kTurns, r2 = (r0 + 2) % kTurns, r3 = (r0 + 3) % kTurns;
+        f[0] = f[kRowBlk];
+        const int back = (b - ring_blocks) * kRowBlk;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(l[r0][0] < back) != 0, 0)) {
+            cut |= l[r0][0] < back;
+#pragma unroll
+            for (int u = 0; u < kRowBlk; ++u) l[r0][u] = l[r0][u] > back ? l[r0][u] : back;
+        }
+        U la[kRowBlk], lc[kRowBlk];
+#pragma unroll
+        for (int u = 0; u < kRowBlk; ++u) {
+            // (a position before the turn's beginning: below 0, so the larger one as a number without a sign)
+            const unsigned near = (unsigned)(l[r0][u] - turn), far_end = near + (unsigned)ring, at = near < far_end ? near : far_end;
+            la[u] = L1[at * kWave];
+            lc[u] = L2[at / kRowBlk * kWave];
+        }
+        sums(l[r1]);
+        table(x[r2], e[r2], l[r2]);
+        load(x[r3], b + 3);  // (past the last block: the padding)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kRowBlk; ++u) {
+            const U from = e[r0][u];
+            U w = la[u] < lc[u] ? la[u] : lc[u];
+            w = f[u] < w ? f[u] : w;
+            w = holds(edge, from) ? w : f[u];
+#pragma unroll
+            for (int k = 0; k < u; ++k) {
+                const U v = holds(x[r0][k], from) ? f[k] : kMax;
+                w = v < w ? v : w;
+            }
+            f[u + 1] = ((u + 1 < kRowBlk ? x[r0][(u + 1) % kRowBlk] : x[r1][0]) - x[r0][u]) + w;
+            if (!FLAT) f[u + 1] = f[u + 1] < kCap ? f[u + 1] : kCap;
+        }
+        if (record) {
+#pragma unroll
+            for (int u = 0; u < kRowBlk; ++u) m.F[(b * kRowBlk + u) * C + row] = f[u];
+        }
+        U whole = f[kRowBlk - 1];
+        const int spot = b - turn / kRowBlk;
+        U *const here = L1 + spot * kRowBlk * kWave;
+        here[(kRowBlk - 1) * kWave] = whole;
+#pragma unroll
+        for (int u = kRowBlk - 2; u >= 0; --u) {
+            whole = f[u] < whole ? f[u] : whole;
+            here[u * kWave] = whole;
+        }
+        move_on(e[r1], l[r1]);
+        // (cell after cell a start only moves on)
+        if (__builtin_amdgcn_ballot_w64(l[r1][0] < (low + 1) * kRowBlk) == 0) ++low;
+        low = low > b + 1 - ring_blocks ? low : b + 1 - ring_blocks;
+        for (int q = b - 1, at = spot; q >= low; --q) {
+            at = at > 0 ? at - 1 : ring_blocks - 1;
+            lds_min(L2 + at * kWave, whole);
+        }
+        L2[spot * kWave] = kMax;
+        turn += spot + 1 == ring_blocks ? ring : 0;
+        edge = x[r0][kRowBlk - 1];
+    };
+    for (int b = 0;; b += kTurns) {
+        block(b, std::integral_constant<int, 0>());
+        if (b + 1 >= nb) break;
+        block(b + 1, std::integral_constant<int, 1>());
+        if (b + 2 >= nb) break;
+        block(b + 2, std::integral_constant<int, 2>());
+        if (b + 3 >= nb) break;
+        block(b + 3, std::integral_constant<int, 3>());
+        if (b + 4 >= nb) break;
+    }
+    slack = least;
+    gap = most;
+    const int last = (n - 1) % kRowBlk;
+    return last == 0 ? f[1] : last == 1 ? f[2] : last == 2 ? f[3] : f[4];
+}
+
+// The cost of a feasible set by the lane of the best of G greedy walks (see greedy_bound), half an octave to an octave
+// between their limits.
+template <int G>
+__device__ inline uint64_t rows_bound(const float *size, const int n, const float all)
+{
+    constexpr int C = kWave / G;
+    const int i = threadIdx.x % G;
+    const float limit = all * exp2f(-0.5f - (float)i * (5.6f / G));
+    const float *const d = size + threadIdx.x / G;
+    float kept = d[0] + d[n * C], seg = 0.0f, longest = 0.0f;
+    const auto layer = [&](const float x) {
+        const float to = seg + x;
+        const bool fits = to <= limit;
+        kept += fits ? 0.0f : x;
+        seg = fits ? to : 0.0f;
+        longest = fmaxf(longest, seg);
+    };
+    constexpr int kAtOnce = 8;
+    int k = 1;
+    for (; k + kAtOnce <= n; k += kAtOnce) {
+        float x[kAtOnce];
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) x[j] = d[(k + j) * C];
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) layer(x[j]);
+    }
+    for (; k < n; ++k) layer(d[k * C]);
+    const float cost = (kept + longest) * (1.0f + 1.0f / 4096.0f);
+    return (uint64_t)(double)__uint_as_float(row_min<G>(__float_as_uint(cost))) + 1;
+}
+
+// Chain c of each row where `valid`, n <= MOST.  True if it is left, with nothing written: 32 bits do not hold its values, or
+// the ring its windows.
+template <int G, int MOST>
+__device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const int64_t c, const bool valid, const int n,
+                                            const int64_t cstride, const int64_t pstride, uint8_t *__restrict__ mask_out,
+                                            int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
+                                            int32_t *__restrict__ status_out, const int ring)
+{
+    typedef uint32_t U;
+    typedef int32_t I;
+    constexpr int C = kWave / G;
+    const RowsLds<G> m(search_lds, n, ring);
+    const int lane = threadIdx.x, row = lane / G, i = lane % G;
+    const int64_t *const dp = d + c * cstride;
+    // the sizes, a lane's one after the other
+    constexpr int PER = MOST / G + 1;
+    const int per = (n + G) / G, k0 = i * per;
+    uint64_t own[PER], sum = 0, bits = 0, high = 0, mx = 0;
+    bool bad = false;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        own[q] = 0;
+        if (q < per) own[q] = k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const uint64_t x = own[q];
+        bad |= q < per && k0 + q <= n && (int64_t)x <= 0;
+        bits |= x;
+        high += x >> 32;
+        sum += x;
+        mx = x > mx ? x : mx;
+    }
+    const uint64_t d_first = (uint64_t)dp[0], d_last = (uint64_t)dp[(int64_t)n * pstride];
+    const uint64_t upto = row_scan<G>(sum, [](uint64_t a, uint64_t b) { return a + b; }), before = upto - sum;
+    sum = row_sum<G>(sum);
+    high = row_sum<G>(high);
+    bits = row_all<G>(bits, [](uint64_t a, uint64_t b) { return a | b; });
+    mx = ~row_min<G>(~mx);
+    bad = row_min<G>((uint32_t)!bad) == 0;
+    const int32_t status = bad ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
+    const int shift = bits ? __ffsll((unsigned long long)bits) - 1 : 0;
+    const uint64_t total = sum >> shift, d0 = d_first >> shift, dn = d_last >> shift, ends = d0 + dn;
+    const uint64_t all = status == CKPT_OK ? total - ends : 0, largest = mx >> shift;
+    float *const size = (float *)m.L1;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (q < per && k0 + q <= n) size[(k0 + q) * C + row] = (float)(own[q] >> shift);
+    __syncthreads();
+    uint64_t bound = rows_bound<G>(size, n, (float)all);
+    bound = bound < total ? bound : total;
+    bound = bound > ends ? bound : ends;
+    uint64_t span = all < bound - ends ? all : bound - ends;
+    // The differences of sums modulo 2^32 that are looked at: a window and the two sizes behind its start, or four sizes.
+    const bool narrow = bound < (1ull << 31) - 1 && span + 2 * largest < (1ull << 31) && kRowBlk * largest < (1ull << 31);
+    bool solved = valid && status == CKPT_OK && narrow, beyond = false;  // beyond: windows reach back beyond the ring
+    const bool flat = !solved || total + span + 1 < (1ull << 32);
+    if (!solved) span = 0;
+    if (__builtin_amdgcn_ballot_w64(solved) == 0 && __builtin_amdgcn_ballot_w64(valid && status != CKPT_OK) == 0)
+        return valid;
+    // The prefix sums, of a chain that is left out 1 everywhere, and the table: position k is the first one of the slots
+    // behind that of the one before, up to its own; bytes up to a word's beginning, words, bytes.
+    __syncthreads();
+    const uint64_t end = solved ? all + span + 1 : 1;
+    int slot_shift = 0;
+    while ((end >> slot_shift) >= (uint64_t)(n * kRowSlots)) ++slot_shift;
+    {
+        uint8_t *const T = m.T + row * row_slots(n);
+        uint64_t run = before;
+        int at = i == 0 ? 0 : solved && k0 < n ? (int)(((run >> shift) - d0 + span + 1) >> slot_shift) + 1 : 2;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int k = k0 + q;
+            run += own[q];
+            const uint64_t here = solved ? (run >> shift) - d0 + span + 1 : 1;
+            int to = -1;
+            if (q < per && k < n) {
+                m.P[(k + 1) * C + row] = (U)here;
+                to = (int)(here >> slot_shift);
+            }
+            const int words = (at + 3) & ~3, rest = (to + 1) & ~3;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                if (at + j <= to && at + j < words) T[at + j] = (uint8_t)k;
+                if (rest + j <= to && rest + j >= at) T[rest + j] = (uint8_t)k;
+            }
+            for (int word = words; word + 3 <= to; word += 4) *(uint32_t *)(T + word) = (uint32_t)k * 0x01010101u;
+            at = to + 1;
+        }
+    }
+    for (int k = n + i; k < row_sums(n) - 1; k += G) m.P[(k + 1) * C + row] = (U)end;
+    if (i == 0) m.P[row] = 0;
+    const bool all_flat = __builtin_amdgcn_ballot_w64(!flat) == 0;
+    __syncthreads();
+    const U first = solved ? (U)d0 : 0, tail = solved ? (U)dn : 0;
+    // s = 0 makes every layer a checkpoint
+    U ub = (U)bound, best_cost = total <= bound ? (U)total : std::numeric_limits<U>::max(), best_s = 0;
+    // a point, what its interval begins above, and whether that is what the neighbour's point leaves
+    const auto split = [](U lo, U wide, int k, int of) {
+        const U part = (U)((float)wide * (float)k / (float)of);
+        return k >= of || part > wide ? lo + wide : lo + part;
+    };
+    U s = split(0, (U)span, i + 1, G), lo = 0;
+    bool leftmost = i == 0;
+    bool settled = false, cut;
+    U value;
+    for (int round = 0;; ++round) {
+        U slack, gap;
+        if (all_flat) value = rows_pass<true>(m, settled, n, first, s, slot_shift, slack, gap, cut);
+        else value = rows_pass<false>(m, settled, n, first, s, slot_shift, slack, gap, cut);
+        if (settled) break;
+        const U at = s - slack, least = value + tail, cost = at + least;
+        const U low_cost = row_min<G>(cost), low_at = row_min<G>(cost == low_cost ? at : std::numeric_limits<U>::max());
+        if (low_cost <= ub && (low_cost < best_cost || (low_cost == best_cost && low_at < best_s))) {
+            best_cost = low_cost;
+            best_s = low_at;
+            ub = low_cost;
+        }
+        // what is left below the point: above what the neighbour's says of its next budget, and up to where the best cost is
+        // reached
+        const U above = (I)gap < 0 ? s - gap - 1 : std::numeric_limits<I>::max();
+        const U left = (U)__shfl_up(above, 1, kWave);
+        const I from = (I)(leftmost ? lo : left);
+        // (a point whose windows were cut says nothing of itself and those below it.  The first round may have such, for its
+        // bound is a rough one; where a later one has, the best cost allows them, and the chain is left to a wave of its own)
+        const U floor = cut ? first + tail : least;
+        const I room = floor > ub ? -1 : (I)(ub - floor), last = cut ? (I)at : (I)at - 1, top = last < room ? last : room;
+        const uint64_t cuts = __builtin_amdgcn_ballot_w64(cut && round > 0 && at + first + tail <= ub);
+        beyond |= ((cuts >> (row * G)) & (~0ull >> (kWave - G))) != 0;
+        solved &= !beyond;
+        const bool open = solved && top > from;
+        const uint64_t opens = __builtin_amdgcn_ballot_w64(open);
+        if (opens == 0) {  // one more pass, for the canonical set: the values for the best budget
+            settled = true;
+            s = best_s;
+            continue;
+        }
+        // the next points: one for each interval, the others by width; what is left over goes to the last one
+        const float wide = open ? (float)(top - from) : 0.0f;
+        const float whole = row_sum<G>(wide);
+        const int many = row_sum<G>((uint32_t)open);
+        const int mine = open ? 1 + (int)(wide / whole * (float)(G - many) * 0.9999f) : 0;
+        const int upto_here = (int)row_scan<G>((uint32_t)mine, [](uint32_t a, uint32_t b) { return a + b; });
+        m.slot[lane] = 0;
+        __syncthreads();
+        if (open) m.slot[row * G + upto_here - mine] = i;
+        __syncthreads();
+        const int owner = (int)row_scan<G>((uint32_t)m.slot[lane], [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+        // (a chain without an open interval goes on with its best point, closed)
+        const int src = row * G + owner;
+        const U o_lo = (U)__shfl(from, src, kWave), o_top = (U)__shfl(top, src, kWave);
+        const int o_end = __shfl(upto_here, src, kWave), o_many = __shfl(mine, src, kWave);
+        const int k = i - (o_end - o_many);
+        const int all_points = (int)row_sum<G>((uint32_t)mine);
+        const int of = o_end == all_points ? G - (o_end - o_many) : o_many;
+        leftmost = many == 0 || k == 0;
+        lo = many == 0 ? best_s : o_lo;
+        s = many == 0 ? best_s : split(o_lo, o_top - o_lo, k + 1, of);
+        __syncthreads();
+    }
+    beyond |= cut;
+    __syncthreads();
+    // from n the first minimal predecessor in the window
+    uint64_t mine = 0;
+    const U *const P = m.P + row, *const F = m.F + row;
+    constexpr int kLook = G == 8 ? 2 : 1;  // positions a lane looks at together: a window holds some ten
+    for (int j = n;;) {                    // (value: the least F in the window of j, which is F of its predecessor)
+        if (j % G == i) mine |= 1ull << (j / G);
+        if (__builtin_amdgcn_ballot_w64(j > 0) == 0) break;
+        const U e = P[(j > 0 ? j : 1) * C] - best_s;
+        int pred = n, top = j - 1;
+        for (bool more = j > 0;;) {
+            int first_here = n;
+            for (int k = 0; k < kLook; ++k) {
+                const int h = top - k * G - i, at = h > 0 ? h : 0;
+                const U sum = P[(at + 1) * C], fh = F[at * C];
+                // (up to the first that is not in the window: farther sums may be beyond what a difference tells)
+                const uint64_t ins = __builtin_amdgcn_ballot_w64(more && h >= 0 && (I)(sum - e) >= 0);
+                const uint64_t outs = ~(ins >> (row * G)) & (~0ull >> (kWave - G));
+                more = outs == 0;
+                const int many = more ? G : __ffsll((unsigned long long)outs) - 1;
+                first_here = i < many && fh == value ? h : first_here;
+            }
+            const int found = (int)row_min<G>((uint32_t)first_here);
+            pred = found < pred ? found : pred;
+            top -= kLook * G;
+            if (__builtin_amdgcn_ballot_w64(more) == 0) break;
+        }
+        if (j > 0) {
+            j = pred < j ? pred : j - 1;  // (there is one)
+            value -= j > 0 ? P[(j + 1) * C] - P[j * C] : 0;
+        }
+    }
+    if (!valid) return false;
+    if (status == CKPT_OK && (!narrow || beyond)) return true;
+    if (status != CKPT_OK) mine = 0;
+    uint8_t *const mp = mask_out + c * cstride;
+    for (int k = i, q = 0; k <= n; k += G, ++q) mp[(int64_t)k * pstride] = (uint8_t)((mine >> q) & 1);
+    if (i == 0) {
+        peak_out[c] = status == CKPT_OK ? (int64_t)((uint64_t)best_cost << shift) : -1;
+        if (budget_out) budget_out[c] = status == CKPT_OK ? (int64_t)((uint64_t)best_s << shift) : -1;
+        if (status_out) status_out[c] = status;
+    }
+    return false;
+}
+
+template <int G, int MOST>
+__global__ __launch_bounds__(kWave) void cubic_rows_kernel(const int64_t *__restrict__ d, int64_t batch, int n, int64_t cstride,
+                                                           int64_t pstride, int ring, uint8_t *__restrict__ mask_out,
+                                                           int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
+                                                           int32_t *__restrict__ status_out, SearchWs w)
+{
+    const int64_t c = (int64_t)xcd_blocked(blockIdx.x, gridDim.x) * (kWave / G) + threadIdx.x / G;
+    const bool valid = c < batch;
+    const bool left = search_rows<G, MOST>(d, valid ? c : batch - 1, valid, n, cstride, pstride, mask_out, peak_out, budget_out,
+                                           status_out, ring);
+    if (left && threadIdx.x % G == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
+}
+
 // Every chain of the batch; WIDE false: those that need 64 bits go on the list.
 template <bool WIDE>
 __global__ __launch_bounds__(kWave) void cubic_search_kernel(const int64_t *__restrict__ d, int n, int64_t cstride,
@@ -793,7 +1347,7 @@ __global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t 
     const int count = *w.count;
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
         const int64_t c = w.list[item];
-        (void)search_one<false, true>(d + c * cstride, pstride, n, mask_out + c * cstride, pstride, peak_out + c,
+        (void)search_one<true, true>(d + c * cstride, pstride, n, mask_out + c * cstride, pstride, peak_out + c,
                                       budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr, ~0u);
         __syncthreads();
     }
@@ -844,7 +1398,8 @@ hipError_t raise_search_lds_limit()
     return raise_lds_limit(search_lds_raised,
                            {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
                             (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel,
-                            (const void *)cubic_search_ragged_wide_kernel},
+                            (const void *)cubic_search_ragged_wide_kernel, (const void *)cubic_rows_kernel<8, kRowsOf8Layers>,
+                            (const void *)cubic_rows_kernel<16, kRowsMaxLayers>},
                            search_lds_bytes(kSearchMaxLayers, 8));
 }
 
@@ -852,6 +1407,12 @@ hipError_t raise_search_lds_limit()
 // chains that need 64 bits follow in a second one; fewer chains do not fill the chip either way.
 constexpr int64_t kSearchSplitFrom = 1024;
 constexpr int kSearchWideBlocks = 1024;
+// A row of lanes per chain from here on: 8,192 chains of 16, 64 and 128 layers, unrounded 45, 173 and 546 us (a wave a chain:
+// 48, 198, 845), aligned 38, 111, 315 (46, 173, 703); at 4,096 chains the longer ones only, 39, 156, 400 (34, 121, 463).
+// Eight lanes rather than sixteen where that leaves waves enough, up to the length whose LDS leaves a SIMD two of them:
+// 65,536 aligned chains of 64 layers 552 us (646), of 90 1,030 (907); 8,192 of 64 153 (108).
+constexpr int64_t kRowsFrom = 8192, kRowsLongFrom = 4096, kRowsOf8From = 16384;
+constexpr int kRowsLong = 96;
 // (a launch has fewer than 2^32 threads)
 constexpr int64_t kMostWavesOfALaunch = 1 << 25;
 // Waves of this much LDS that the chip holds (LDS is handed out in units of 1,280 bytes).
@@ -889,7 +1450,19 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
     }
     const dim3 grid((unsigned)batch), block(kWave);
     const SearchWs w{(int32_t *)ws, (int32_t *)((char *)ws + 256)};
-    if (batch < kSearchSplitFrom) {
+    if (batch >= (n > kRowsLong ? kRowsLongFrom : kRowsFrom) && n <= kRowsMaxLayers) {
+        const int ring = row_ring(n);
+        hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
+        const auto rows = [&](auto lanes, auto most) {
+            constexpr int G = decltype(lanes)::value, C = kWave / G;
+            hipLaunchKernelGGL((cubic_rows_kernel<G, decltype(most)::value>), dim3((unsigned)((batch + C - 1) / C)), block, rows_lds_bytes(n, C, ring),
+                               stream, d, batch, n, st.chain, st.pos, ring, mask_out, peak_out, budget_out, status_out, w);
+        };
+        if (batch >= kRowsOf8From && n <= kRowsOf8Layers) rows(std::integral_constant<int, 8>(), std::integral_constant<int, kRowsOf8Layers>());
+        else rows(std::integral_constant<int, 16>(), std::integral_constant<int, kRowsMaxLayers>());
+        hipLaunchKernelGGL(cubic_search_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(n, 8), stream, d,
+                           n, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);
+    } else if (batch < kSearchSplitFrom) {
         hipLaunchKernelGGL(cubic_search_kernel<true>, grid, block, search_lds_bytes(n, 8), stream, d, n, st.chain, st.pos,
                            mask_out, peak_out, budget_out, status_out, w);
     } else {

@@ -89,6 +89,9 @@ inline int dpp(int old, int x, int control, int row_mask)
     if (control > 0x110 && control < 0x120) from = lane() - (control - 0x110) >= row * 16 ? lane() - (control - 0x110) : -1;
     if (control > 0x100 && control < 0x110) from = lane() + (control - 0x100) < row * 16 + 16 ? lane() + (control - 0x100) : -1;
     if (control >= 0x150 && control < 0x160) from = row * 16 + (control - 0x150);
+    if (control < 0x100) from = lane() / 4 * 4 + ((control >> (2 * (lane() % 4))) & 3);
+    if (control == 0x140) from = lane() ^ 15;
+    if (control == 0x141) from = lane() ^ 7;
     if (control == 0x142) from = row * 16 - 1;
     if (control == 0x143) from = row > 1 ? 31 : -1;
     return from < 0 || !((row_mask >> row) & 1) ? old : (int)(uint32_t)v[from];

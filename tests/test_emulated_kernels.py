@@ -30,6 +30,8 @@ def source(name, tmp_path):
     text = replaced(text, r"extern __shared__ [^;]*;", f"#define {lds} (({kind} *)emu::dynamic_lds)")
     if name == "cubic_search":
         text = replaced(text, r"    uint32_t r;\n    asm\(\"v_cndmask_b32[^;]*;\n    return r;", "    return (mask >> emu::lane()) & 1 ? on : off;")
+        # (lanes that do the same read a ring's row together, before one of them writes it)
+        text = replaced(text, r"        U whole = f\[kRowBlk - 1\];\n", "        (void)emu::ballot(true);\n        U whole = f[kRowBlk - 1];\n")
     if name == "solve_linear":
         text = ring_in_c(text)
         # (the lanes of a row read the step together, before one of them marks it)
@@ -108,6 +110,11 @@ def run_driver(driver, sources, tmp_path):
 def test_the_search_on_the_cpu(tmp_path):
     source("cubic_search", tmp_path)  # (the driver includes it: it also calls what has no entry point)
     run_driver("search_driver", [], tmp_path)
+
+
+def test_the_search_with_a_row_of_lanes_per_chain_on_the_cpu(tmp_path):
+    source("cubic_search", tmp_path)
+    run_driver("rows_driver", [], tmp_path)
 
 
 def test_the_linear_solver_on_the_cpu(tmp_path):

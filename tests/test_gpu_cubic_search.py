@@ -51,6 +51,34 @@ def test_batches_on_both_sides_of_the_split(batch):
     check(d)
 
 
+@pytest.mark.parametrize("n,batch", [(1, 8192), (2, 8193), (5, 16385), (36, 16391), (37, 8199), (63, 16384), (64, 8195), (72, 16387),
+                                     (73, 16386), (96, 8197), (97, 4099), (120, 4096), (128, 8198)])
+def test_rows_of_lanes(n, batch):
+    """Batches whose chains have rows of 8 or 16 lanes each: lengths around a block, a ring and the lanes' shares; a wave's
+    chains of every kind side by side, chains that are left to a wave each and bad ones among them."""
+    rng = np.random.default_rng(n)
+    print(f"rows of lanes: n = {n}, batch = {batch}", flush=True)
+    kinds = [inputs.uniform_aligned_chains(n, n, 61, 256, 32768), inputs.log_uniform_chains(n, n, 61),
+             np.stack([network(n, k)[:, 0] if n > 4 else np.full(n + 1, k + 1) for k in range(61)], 1),
+             rng.integers(1 << 24, 1 << 26, size=(n + 1, 19)), rng.integers(1, 4, size=(n + 1, 7)),
+             np.full((n + 1, 1), 7), rng.integers(1, (1 << 62) // (n + 2), size=(n + 1, 3)),
+             (1 << rng.integers(0, 40, size=(n + 1, 5)))]
+    d = np.concatenate([k.astype(np.int64) for k in kinds], axis=1)
+    d = d[:, rng.permutation(d.shape[1])]
+    some = d.shape[1]
+    want_peak, want_mask, want_s = oracle.batch_solve_static(inputs.chain_major(d))
+    at = np.arange(batch) % some
+    d = d[:, at]
+    d[n // 2, 7::1009] = 0
+    bad = d.min(0) <= 0
+    mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d)).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(status.cpu().numpy(), np.where(bad, 3, 0))
+    assert np.array_equal(peak.cpu().numpy(), np.where(bad, -1, want_peak[at]))
+    assert np.array_equal(budget.cpu().numpy(), np.where(bad, -1, want_s[at]))
+    assert np.array_equal(mask.cpu().numpy().T, np.where(bad[:, None], 0, want_mask[at]))
+
+
 def test_bad_chains_are_reported_alone():
     d = inputs.uniform_aligned_chains(4, 30, 1100, 256, 32768)
     dc = inputs.chain_major(d)
