@@ -792,8 +792,9 @@ __global__ void cubic_search_reset_kernel(SearchWs w) { *w.count = 0; }
 // and 5.0).  65,536 chains of 64 layers, unrounded 0.70 ms (a wave a chain: 1.29), aligned 0.55 (1.11).
 constexpr int kRowBlk = 4;
 constexpr int kRowSlots = 4;   // slots of the table per layer
-constexpr int kRowsMaxLayers = 128;
-constexpr int kRowsOf8Layers = 72;
+constexpr int kRowsMaxLayers = 256;  // (a position is a byte of the table)
+static_assert(kRowsMaxLayers == kSearchMaxLayers, "every chain of the search has rows that fit it");
+constexpr int kRowsOf8Layers = 72, kRowsOf16Layers = 128;
 
 __host__ __device__ inline int row_blocks(int n) { return (n + kRowBlk - 1) / kRowBlk; }
 // Prefix sums from position -1 on, with the padding that what is read ahead sees.
@@ -897,15 +898,16 @@ __device__ inline V row_scan(V v, Join join)
 }
 
 // F_s(n) without the size at the end.  FLAT: the prefix sums are those in full; else they are modulo 2^32, and values are cut
-// to 2^31.  `record`: the values go to m.F.  `slack`: how far the largest budget up to s lies below it; `gap`: minus how far the next one lies above (or
-// a value that is not negative if there is none).  `cut`: a window reached back beyond the ring and was cut off there, so
+// to 2^31.  `record`: the values go to m.F.  `over`: no difference of sums that is not negative is larger, and every negative
+// one is as a number without a sign.  `slack`: how far the largest budget up to s lies below it; `gap`: minus how far the next
+// one lies above (not above `over` if there is none).  `cut`: a window reached back beyond the ring and was cut off there, so
 // that the result is what F_s(n) does not exceed.
 template <bool FLAT, int G>
 __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool record, const int n, const uint32_t first,
-                                              const uint32_t s, const int shift, uint32_t &slack, uint32_t &gap, bool &cut)
+                                              const uint32_t s, const uint32_t over, const int shift, uint32_t &slack, uint32_t &gap,
+                                              bool &cut)
 {
     typedef uint32_t U;
-    typedef int32_t I;
     constexpr int C = kWave / G;
     constexpr U kMax = ~0u, kCap = 1u << 31;
     const int lane = threadIdx.x, row = lane / G, nb = row_blocks(n);
@@ -923,9 +925,9 @@ __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool re
             l += __builtin_sub_overflow(p2, e, &t2) ? 1 : 0;
         } else {
             t0 = p0 - e; t1 = p1 - e; t2 = p2 - e;
-            l += (int)((I)t0 < 0) + (int)((I)t1 < 0) + (int)((I)t2 < 0);
+            l += (int)(t0 > over) + (int)(t1 > over) + (int)(t2 > over);
         }
-        far |= t2;
+        far = t2 > far ? t2 : far;
         U a = t0 < t1 ? t0 : t1, z = t0 > t1 ? t0 : t1;
         a = a < t2 ? a : t2;
         z = z > t2 ? z : t2;
@@ -947,7 +949,7 @@ __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool re
             most = tm > most ? tm : most;
             test(l[u], e[u], p[u][1], p[u][2], p[u][3]);
         }
-        while (__builtin_expect(__builtin_amdgcn_ballot_w64((I)far < 0) != 0, 0)) {
+        while (__builtin_expect(__builtin_amdgcn_ballot_w64(far > over) != 0, 0)) {
             far = 0;
             sums(l);
 #pragma unroll
@@ -955,7 +957,7 @@ __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool re
         }
     };
     // a window that begins at e holds the position with this sum
-    const auto holds = [&](U sum, U e) { return FLAT ? sum >= e : (I)(sum - e) >= 0; };
+    const auto holds = [&](U sum, U e) { return FLAT ? sum >= e : sum - e <= over; };
     // the sums that block b's positions end in, and where the windows of the cells behind them may begin
     const auto load = [&](U (&x)[kRowBlk], int b) {
 #pragma unroll
@@ -1155,8 +1157,10 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
     bound = bound < total ? bound : total;
     bound = bound > ends ? bound : ends;
     uint64_t span = all < bound - ends ? all : bound - ends;
-    // The differences of sums modulo 2^32 that are looked at: a window and the two sizes behind its start, or four sizes.
-    const bool narrow = bound < (1ull << 31) - 1 && span + 2 * largest < (1ull << 31) && kRowBlk * largest < (1ull << 31);
+    // What is looked at of differences of sums modulo 2^32: up to a window, or the size at its start, and two sizes more; down
+    // to four sizes below 0.
+    const uint64_t reach = (span > largest ? span : largest) + 2 * largest;
+    const bool narrow = bound < (1ull << 31) - 1 && largest < (1ull << 31) && reach + 4 * largest < (1ull << 32);
     bool solved = valid && status == CKPT_OK && narrow, beyond = false;  // beyond: windows reach back beyond the ring
     const bool flat = !solved || total + span + 1 < (1ull << 32);
     if (!solved) span = 0;
@@ -1196,7 +1200,7 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
     if (i == 0) m.P[row] = 0;
     const bool all_flat = __builtin_amdgcn_ballot_w64(!flat) == 0;
     __syncthreads();
-    const U first = solved ? (U)d0 : 0, tail = solved ? (U)dn : 0;
+    const U first = solved ? (U)d0 : 0, tail = solved ? (U)dn : 0, over = solved ? (U)reach : 0;
     // s = 0 makes every layer a checkpoint
     U ub = (U)bound, best_cost = total <= bound ? (U)total : std::numeric_limits<U>::max(), best_s = 0;
     // a point, what its interval begins above, and whether that is what the neighbour's point leaves
@@ -1210,8 +1214,8 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
     U value;
     for (int round = 0;; ++round) {
         U slack, gap;
-        if (all_flat) value = rows_pass<true>(m, settled, n, first, s, slot_shift, slack, gap, cut);
-        else value = rows_pass<false>(m, settled, n, first, s, slot_shift, slack, gap, cut);
+        if (all_flat) value = rows_pass<true>(m, settled, n, first, s, over, slot_shift, slack, gap, cut);
+        else value = rows_pass<false>(m, settled, n, first, s, over, slot_shift, slack, gap, cut);
         if (settled) break;
         const U at = s - slack, least = value + tail, cost = at + least;
         const U low_cost = row_min<G>(cost), low_at = row_min<G>(cost == low_cost ? at : std::numeric_limits<U>::max());
@@ -1222,8 +1226,8 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
         }
         // what is left below the point: above what the neighbour's says of its next budget, and up to where the best cost is
         // reached
-        const U above = (I)gap < 0 ? s - gap - 1 : std::numeric_limits<I>::max();
-        const U left = (U)__shfl_up(above, 1, kWave);
+        const U above = gap > over ? s - gap - 1 : std::numeric_limits<I>::max();
+        const U left = (U)__shfl_up(above < (U)std::numeric_limits<I>::max() ? above : (U)std::numeric_limits<I>::max(), 1, kWave);
         const I from = (I)(leftmost ? lo : left);
         // (a point whose windows were cut says nothing of itself and those below it.  The first round may have such, for its
         // bound is a rough one; where a later one has, the best cost allows them, and the chain is left to a wave of its own)
@@ -1279,7 +1283,7 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
                 const int h = top - k * G - i, at = h > 0 ? h : 0;
                 const U sum = P[(at + 1) * C], fh = F[at * C];
                 // (up to the first that is not in the window: farther sums may be beyond what a difference tells)
-                const uint64_t ins = __builtin_amdgcn_ballot_w64(more && h >= 0 && (I)(sum - e) >= 0);
+                const uint64_t ins = __builtin_amdgcn_ballot_w64(more && h >= 0 && sum - e <= over);
                 const uint64_t outs = ~(ins >> (row * G)) & (~0ull >> (kWave - G));
                 more = outs == 0;
                 const int many = more ? G : __ffsll((unsigned long long)outs) - 1;
@@ -1399,7 +1403,7 @@ hipError_t raise_search_lds_limit()
                            {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
                             (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel,
                             (const void *)cubic_search_ragged_wide_kernel, (const void *)cubic_rows_kernel<8, kRowsOf8Layers>,
-                            (const void *)cubic_rows_kernel<16, kRowsMaxLayers>},
+                            (const void *)cubic_rows_kernel<16, kRowsOf16Layers>, (const void *)cubic_rows_kernel<16, kRowsMaxLayers>},
                            search_lds_bytes(kSearchMaxLayers, 8));
 }
 
@@ -1407,12 +1411,14 @@ hipError_t raise_search_lds_limit()
 // chains that need 64 bits follow in a second one; fewer chains do not fill the chip either way.
 constexpr int64_t kSearchSplitFrom = 1024;
 constexpr int kSearchWideBlocks = 1024;
-// A row of lanes per chain from here on: 8,192 chains of 16, 64 and 128 layers, unrounded 45, 173 and 546 us (a wave a chain:
-// 48, 198, 845), aligned 38, 111, 315 (46, 173, 703); at 4,096 chains the longer ones only, 39, 156, 400 (34, 121, 463).
+// A row of lanes per chain from here on: 8,192 chains of 16, 64 and 128 layers, unrounded 45, 173 and 460 us (a wave a chain:
+// 48, 198, 842), aligned 38, 111, 333 (46, 173, 703); at 4,096 chains the longer ones only, 39, 156, 331 (34, 121, 463), and
+// where a wave a chain leaves a CU three or two waves, beyond 128 layers, at 2,048: of 152 and 256 layers unrounded 448 and
+// 1,207 (599, 1,554), aligned 219 and 399 (335, 844), networks 284 and 469 (330, 758).
 // Eight lanes rather than sixteen where that leaves waves enough, up to the length whose LDS leaves a SIMD two of them:
 // 65,536 aligned chains of 64 layers 552 us (646), of 90 1,030 (907); 8,192 of 64 153 (108).
-constexpr int64_t kRowsFrom = 8192, kRowsLongFrom = 4096, kRowsOf8From = 16384;
-constexpr int kRowsLong = 96;
+constexpr int64_t kRowsOf8From = 16384;
+inline int64_t rows_from(int n) { return n > 128 ? 2048 : n > 96 ? 4096 : 8192; }
 // (a launch has fewer than 2^32 threads)
 constexpr int64_t kMostWavesOfALaunch = 1 << 25;
 // Waves of this much LDS that the chip holds (LDS is handed out in units of 1,280 bytes).
@@ -1450,7 +1456,7 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
     }
     const dim3 grid((unsigned)batch), block(kWave);
     const SearchWs w{(int32_t *)ws, (int32_t *)((char *)ws + 256)};
-    if (batch >= (n > kRowsLong ? kRowsLongFrom : kRowsFrom) && n <= kRowsMaxLayers) {
+    if (batch >= rows_from(n)) {
         const int ring = row_ring(n);
         hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
         const auto rows = [&](auto lanes, auto most) {
@@ -1459,6 +1465,7 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
                                stream, d, batch, n, st.chain, st.pos, ring, mask_out, peak_out, budget_out, status_out, w);
         };
         if (batch >= kRowsOf8From && n <= kRowsOf8Layers) rows(std::integral_constant<int, 8>(), std::integral_constant<int, kRowsOf8Layers>());
+        else if (n <= kRowsOf16Layers) rows(std::integral_constant<int, 16>(), std::integral_constant<int, kRowsOf16Layers>());
         else rows(std::integral_constant<int, 16>(), std::integral_constant<int, kRowsMaxLayers>());
         hipLaunchKernelGGL(cubic_search_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(n, 8), stream, d,
                            n, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);

@@ -56,6 +56,7 @@ void check(const char *what, const std::vector<Sizes> &chains, int ring = 0)
 {
     const int n = (int)chains[0].size() - 1;
     if (ring == 0) ring = row_ring(n);
+    if (rows_lds_bytes(n, kWave / G, ring) > kDefaultLdsLimit) return;
     const int64_t batch = (int64_t)chains.size(), n1 = n + 1;
     Sizes good;
     std::vector<int> want_status;
@@ -106,7 +107,7 @@ template <int G>
 void all_kinds()
 {
     const int64_t top = INT64_MAX;
-    for (const int n : {1, 2, 3, 4, 5, 8, 9, 24, 63, 64, 65, 100, 128}) {
+    for (const int n : {1, 2, 3, 4, 5, 8, 9, 24, 63, 64, 65, 100, 128, 129, 256}) {
         std::vector<Sizes> chains = {uniform(n, 1, 1000000), uniform(n, 1, 3), spread(n, 12), spread(n, 22), uniform(n, 7, 7), with(uniform(n, 1, 9), n / 2, 0)};
         for (const int k : {0, n}) {
             chains.push_back(with(uniform(n, 100, 100), k, 1ll << 29));

@@ -52,7 +52,7 @@ def test_batches_on_both_sides_of_the_split(batch):
 
 
 @pytest.mark.parametrize("n,batch", [(1, 8192), (2, 8193), (5, 16385), (36, 16391), (37, 8199), (63, 16384), (64, 8195), (72, 16387),
-                                     (73, 16386), (96, 8197), (97, 4099), (120, 4096), (128, 8198)])
+                                     (73, 16386), (96, 8197), (97, 4099), (120, 4096), (128, 8198), (129, 2048), (200, 2051), (256, 2063)])
 def test_rows_of_lanes(n, batch):
     """Batches whose chains have rows of 8 or 16 lanes each: lengths around a block, a ring and the lanes' shares; a wave's
     chains of every kind side by side, chains that are left to a wave each and bad ones among them."""
