@@ -4,14 +4,14 @@
 // most 16 entries of it live when a block ends.  What a lane has to tell its chain goes through the row broadcast of
 // a DPP operand (row_newbcast), so a position costs nine instructions for four chains at once, no scalar register is
 // passed, and nothing diverges; the work around a block (about 150 instructions) falls on 16 positions instead of 64.
-// Values are 32-bit integers, or doubles as exact 53-bit integers (one instruction for a sum, a maximum or a comparison;
-// a 64-bit maximum is three), or unsigned 64-bit integers where the sizes, divided by their common power of two, need
-// them.  Where a queue outgrows its row, or a size is not positive, the chain is left to the form of a wave per chain.
+// Values are unsigned 32-bit integers, or doubles as exact 53-bit integers (one instruction for a sum, a maximum or a
+// comparison; a 64-bit maximum is three), or unsigned 64-bit integers where the sizes, divided by their common power of
+// two, need them.  Where a queue outgrows its row, or a size is not positive, the chain is left to the form of a wave per chain.
 //
 // What bounds it is issue again, and alone on a SIMD the wait states around DPP operands: 72 ns a position (32 bits;
-// 105 in doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 61 us (66 with a move for
-// each half of a double), where a lane per chain took 137 (a try in 32 bits, then 64-bit integers with a queue in LDS,
-// 1.8 us a position).
+// 105 in doubles) with one wave there, 150 with four.  65,536 chains of 64 unrounded layers 45 us (62 in
+// doubles, 66 with a move for each half of one), where a lane per chain took 137 (a try in 32 bits, then 64-bit integers
+// with a queue in LDS, 1.8 us a position).
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -79,18 +79,36 @@ __device__ __forceinline__ void unrolled(const F f)  // f(FROM), .., f(TO - 1)
     }
 }
 
-// (sum(d) + max(d)) >> shift of a chain stays below.
+// (sum(d) + max(d)) >> shift of a chain stays below, and with it every M(j) and U(i,j); kRowTop stands for no M.  32 bits
+// take all but the last two values, so nothing may be added to the top: chains of 64 unrounded layers of up to 256 MiB need
+// 2^31 to 2^32, and took doubles while 32 bits ended at 2^30 (65,536 of them 62 us, now 45; aligned ones 44 both ways).  A
+// wave's own form (linear_wave.h) does with 2^30: 997 chains of 1,001 aligned layers took 61.2 us this way, 60.4 so, and
+// unrounded batches of its size gained nothing.
 template <class S> constexpr uint64_t kRowBeyond = (uint64_t)kBeyond<S>;
+template <> constexpr uint64_t kRowBeyond<uint32_t> = UINT32_MAX - 1;
+template <class S> constexpr S kRowTop = (S)kRowBeyond<S>;
+template <> constexpr uint32_t kRowTop<uint32_t> = UINT32_MAX;
+// M(j) from B(j) and d_j, no less than the top where the weight is the top.  (32 bits: an addition that saturates.)
+template <class S> __device__ inline S settled_M(S B, S weight) { return B + weight; }
+__device__ inline uint32_t settled_M(uint32_t B, uint32_t weight)
+{
+    const uint32_t M = B + weight;
+    return M < B ? UINT32_MAX : M;
+}
+// The -T(j) of no entry: its U, the largest size + T(i) - T(j), is more than any M, or, in 32 bits, than those of most
+// chains: 2^31 and what of the block lies above i.  (It only says when to stop looking.)
+template <class S> __device__ inline S row_no_T(S) { return kRowTop<S>; }
+__device__ inline uint32_t row_no_T(uint32_t base) { return 0x80000000u - base; }
 constexpr int kRowsQueueBytes = 2048;
 __host__ __device__ inline size_t rows_lds_bytes(int n) { return kRowsQueueBytes + (size_t)kRowsOfWave * ((size_t)n + 1) * 2; }
 
 // Sizes come from `load` (scaled; of the lane's own chain, of n layers), the chosen steps go to the row's nxt.
-// Returns M(0), or a negative value if the row's queue was too short.  Rows of several lengths start together, each
+// Returns M(0), or (S)-1 if the row's queue was too short.  Rows of several lengths start together, each
 // with its last block; one that has come to its first position runs along on sizes that no lane takes.
 template <class S, class Load>
 __device__ __forceinline__ S rows_steps(const Load load, const int n, unsigned char *lds, uint16_t *nxt)
 {
-    constexpr S kTop = (S)kRowBeyond<S>;
+    constexpr S kTop = kRowTop<S>;
     struct alignas(16) Entry { S M, minus_T, G; int32_t back; };
     static_assert(sizeof(Entry) * kWave <= kRowsQueueBytes, "the queue's place in LDS");
     const int lane = threadIdx.x % kWave, l = lane % kRow;
@@ -102,7 +120,7 @@ __device__ __forceinline__ S rows_steps(const Load load, const int n, unsigned c
     // the queue: lane p of the row its entry p from the head, M(j), -T(j), G = the largest size from the block's end to
     // j - 1, hi - j; beyond the entries an M that is no minimum, with a U that ends the search
     const S last = load(n);
-    S qM = l == 0 ? last : kTop, q_minus_T = l == 0 ? (S)0 : kTop, qG = 0;
+    S qM = l == 0 ? last : kTop, q_minus_T = l == 0 ? (S)0 : row_no_T(last), qG = 0;
     int q_back = -1;
     S base = last;  // T(hi)
     S result = -1;
@@ -146,11 +164,11 @@ __device__ __forceinline__ S rows_steps(const Load load, const int n, unsigned c
         const S weight = is ? d : kTop;
         unrolled<0, kRow>([&](auto k) {
             constexpr int m = decltype(k)::value;
-            const S v = top_of(table[m], row_value<m>((S)(B + weight)));
+            const S v = top_of(table[m], row_value<m>(settled_M(B, weight)));
             back = v <= B ? m : back;
             B = least_of(v, B);
         });
-        const S M = B + weight;
+        const S M = settled_M(B, weight);
         if (is) nxt[hi - l] = (uint16_t)(hi - back);
         if (__builtin_amdgcn_ballot_w64(hi >= 0 && hi < kRow) != 0) {
             const S first = __shfl(M, lane - l + (hi & (kRow - 1)), kWave);
@@ -180,12 +198,12 @@ __device__ __forceinline__ S rows_steps(const Load load, const int n, unsigned c
         __syncthreads();
         const Entry e = queue[l];
         __syncthreads();
+        base += row_value<kRow - 1>(sums);
         const bool live = l < entries_now;
         qM = live ? e.M : kTop;
-        q_minus_T = live ? e.minus_T : kTop;
+        q_minus_T = live ? e.minus_T : row_no_T(base);
         qG = live ? e.G : (S)0;
         q_back = e.back;
-        base += row_value<kRow - 1>(sums);
     }
 }
 

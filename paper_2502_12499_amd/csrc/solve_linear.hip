@@ -1112,10 +1112,12 @@ __device__ __forceinline__ bool rows_chains(const int64_t *__restrict__ dp, cons
     if (__builtin_amdgcn_ballot_w64(fits) != 0) {
         if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<double>) != 0)
             peak = (int64_t)rows_steps<uint64_t>([&](int k) { return at(k); }, n, lds, nxt);
-        else if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<int32_t>) != 0)
+        else if (__builtin_amdgcn_ballot_w64(fits && most >= kRowBeyond<uint32_t>) != 0)
             peak = (int64_t)rows_steps<double>([&](int k) { return (double)(int64_t)at(k); }, n, lds, nxt);
-        else
-            peak = rows_steps<int32_t>([&](int k) { return (int32_t)at(k); }, n, lds, nxt);
+        else {
+            const uint32_t m0 = rows_steps<uint32_t>([&](int k) { return (uint32_t)at(k); }, n, lds, nxt);
+            peak = m0 == UINT32_MAX ? -1 : (int64_t)m0;
+        }
     }
     const bool done = fits && peak >= 0;
     // the set: from one checkpoint to the next, each step marked where it lies
@@ -1254,7 +1256,7 @@ __global__ __launch_bounds__(kWave, 4) void linear_flat_kernel(const int64_t *__
 // A wave per chain up to 1,024 chains, one for each SIMD of the chip; four chains to a wave up to 65,536, and the ring
 // kernel's lanes beyond.  Waves and rows, us: 1,001 layers, 1,024 chains 62 and 79, 2,048 chains 100 and 82, unrounded
 // ones 131 and 115, 204 and 121.  Rows and lanes at 65,536 chains: 64 layers 49 and 51 (unrounded, which the lanes try
-// in 32 bits first, 72 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at
+// in 32 bits first, 55 and 137), 256 layers 154 and 170 (251 and 482), 1,001 layers 610 and 723 (1,004 and 2,950); at
 // 131,072 aligned ones 88 and 56 for 64 layers.  The LDS of the steps has to leave a SIMD three waves (four end at 1,023
 // layers), or one up to 16,384 chains: 16,384 of 3,000 layers 0.89 ms, 2.0 with lanes, but 65,536 of 2,047 5 % slower than
 // those.  Rows take the same time whatever the sizes are; lanes take less where all chains move alike, so 65,536 chains
@@ -1268,7 +1270,7 @@ inline bool rows_fit(int64_t batch, int n)
     return batch > kWaveBatch && (batch <= kRowsFewBatch ? n <= kRowsFewMaxLayers : batch <= kRowsBatch && n <= kRowsMaxLayers);
 }
 // Rows also take what the ring kernel leaves of larger batches (unrounded sizes: all of it), where that kernel's form
-// in 64 bits, a lane per chain, is slower: 131,072 unrounded chains of 64 layers 202 us (267), 262,144 of 1,001 5.6 ms
+// in 64 bits, a lane per chain, is slower: 131,072 unrounded chains of 64 layers 168 us (267), 262,144 of 1,001 5.6 ms
 // (8.8), but of 12 layers 142 us (130) and of 3,000 28.8 ms (27.5).
 inline bool rows_list_pays(int64_t batch, int n)
 {

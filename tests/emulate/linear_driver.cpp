@@ -222,6 +222,19 @@ std::vector<Sizes> kinds(int n)
 int main()
 {
     for (const int n : {1, 2, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 100, 130, 257, 330}) check("kinds of sizes", kinds(n), kEqualLengths);
+    // sum(d) + max(d) in the upper half of 32 bits, and on both sides of what they take
+    std::vector<Sizes> all;
+    for (const int n : {3, 15, 16, 17, 47, 64, 65, 100}) {
+        std::vector<Sizes> chains;
+        for (const int k : {0, 1, n / 2, n - 1, n})
+            for (int less = 0; less < 5; ++less) {
+                chains.push_back(up_to(n, k, (1ll << 32) - less));
+                chains.push_back(with(uniform(n, 1, ((1ll << 32) - 8) / (n + 2)), k, (1ll << 32) / (n + 2) - less));
+            }
+        check("the upper half of 32 bits", chains, kEqualLengths);
+        all.insert(all.end(), chains.begin(), chains.end());
+    }
+    check("the upper half of 32 bits, ragged", all, {kFlatWaves, kFlatRows, kFlatFewRows, kStaged});
     // ever fewer trailing zeros towards the front, with sizes up to the lanes' limit of 2^24 before and after each of them
     for (const int n : {9, 12, 17, 24}) {
         std::vector<Sizes> chains;

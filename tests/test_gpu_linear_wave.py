@@ -68,6 +68,25 @@ def test_ends_of_blocks_and_limits_of_the_values(n):
             check(d)
 
 
+@pytest.mark.parametrize("n, batch", [(3, 60), (16, 1100), (17, 60), (63, 60), (64, 1100), (64, 65600), (65, 1100), (100, 60), (300, 1100)])
+def test_the_upper_half_of_32_bits(n, batch):
+    """sum(d) + max(d) between 2**31 and 2**32, and on both sides of 2**32 - 2, from where on values are wider: a wave per
+    chain, rows, and rows of what the lanes leave."""
+    rng = np.random.default_rng(n * batch)
+    d = rng.integers((1 << 31) // (n + 1), (1 << 32) // (n + 2), size=(n + 1, batch)).astype(np.int64)
+    for c in range(0, batch, 3):
+        at, most = int(rng.integers(0, n + 1)), (1 << 32) - int(rng.integers(0, 6))
+        if c % 2:  # one size is half of it
+            d[:, c] = rng.integers(1, max(2, most // (4 * n)), size=n + 1)
+        d[at, c] = 0
+        d[at, c] = (most - int(d[:, c].sum())) // 2
+        if 2 * int(d[at, c]) + int(d[:, c].sum()) - int(d[at, c]) < most:
+            d[(at + 1) % (n + 1), c] += 1
+    assert d.min() > 0
+    print(f"linear, upper half of 32 bits: n = {n}, batch = {batch}", flush=True)
+    check(d, chain_major=n % 2 == 1)
+
+
 @pytest.mark.parametrize("n", [2047, 2048, 3000])
 def test_long_chains(n):
     check(inputs.uniform_aligned_chains(n, n, 2, 256, 32768))
