@@ -41,8 +41,8 @@ extern __shared__ __align__(16) unsigned char search_lds[];
 // LDS space leaves (20 KB a wave at 64 layers in 32 bits): 310 cycles a cell of 64 points alone, 390 with two
 // waves.  The loads a cell depends on are issued a cell ahead (the predecessor j-1 always lies in the window
 // and is joined from its register), those that the window's start depends on two.
-// 65,536 chains of 64 layers of unrounded sizes: 1.28 ms, where evaluating all 2,017 budgets of each with
-// a queue per lane took 31.2 ms; one chain of 152 layers 88 us (129 us).
+// Batches below rows_from(): 4,096 chains of 64 layers of unrounded sizes 124 us, one chain of 152 layers 88 us (129 us with
+// a queue per lane for every budget); 65,536 of 64 layers took 1.28 ms so (31.2), and 0.68 with rows.
 //
 // Arithmetic.  UB, the cost of a feasible set, bounds the optimum, so a value of F above UB may
 // be cut off at any number above UB: with UB < 2^31 (sizes divided by their common power of two) 32
