@@ -1645,11 +1645,15 @@ __device__ inline uint64_t block_min(uint64_t v, uint64_t *room)
     return wave_min_u64(v);
 }
 
+// One workgroup a chain.  What bounds it is issue: sixteen waves on a CU, four to a SIMD, so an instruction of all costs
+// sixteen cycles.  Hence waves without sizes do nothing but their segment length, no thread looks at more than its `per`
+// sizes, the waves' results are joined in the lanes of a row, and the only division is that by a unit that is no power of two.
 __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64_t *__restrict__ d, int n, int64_t cstride,
                                                                      int64_t pstride, int points, int waves, LongWs w)
 {
     constexpr int kWaves = kTableThreads / kWave;
-    __shared__ uint64_t room[kWaves], part[5][kWaves];
+    static_assert(kWaves == 16, "a row of lanes holds the waves' values");
+    __shared__ uint64_t room[kWaves], part[4][kWaves];
     __shared__ float bound_of[kBounds];
     __shared__ uint64_t ends2[2];
     float *const prefix = (float *)search_lds;  // [n + 1] of the interior sizes
@@ -1657,48 +1661,51 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int64_t *dp = d + c * cstride;
     const int per = (n + kTableThreads) / kTableThreads, k0 = tid * per;  // a thread takes `per` sizes in a row
-    uint64_t x[kTablePer];
-    uint64_t bits = 0, high = 0, sum = 0, mx = 0, bad = 0;
+    const bool holds = __builtin_amdgcn_readfirstlane(wave) * kWave * per <= n;
+    const auto either = [](uint64_t a, uint64_t b) { return a | b; };
+    uint64_t x[kTablePer] = {};
+    uint64_t bits = 0, high = 0, sum = 0, mx = 0;
+    if (holds) {
 #pragma unroll
-    for (int q = 0; q < kTablePer; ++q) x[q] = q < per && k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
+        for (int q = 0; q < kTablePer; ++q) {
+            if (q >= per) break;
+            x[q] = k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
+        }
+    }
     for (int k = tid; k < seen_slots(n); k += kTableThreads) w.seen[c * seen_slots(n) + k] = 0;
     for (int k = tid; k < 2 * waves; k += kTableThreads) w.found[c * 2 * waves + k] = ~0ull;
+    if (holds) {
 #pragma unroll
-    for (int q = 0; q < kTablePer; ++q) {
-        bad |= (q < per && k0 + q <= n && (int64_t)x[q] <= 0) ? 1 : 0;
-        bits |= x[q];
-        high += x[q] >> 32;
-        sum += x[q];
-        mx = x[q] > mx ? x[q] : mx;
+        for (int q = 0; q < kTablePer; ++q) {
+            if (q >= per) break;
+            bits |= k0 + q > n || (int64_t)x[q] > 0 ? x[q] : 1ull << 63;  // (no size that is positive has that bit)
+            high += x[q] >> 32;
+            sum += x[q];
+            mx = x[q] > mx ? x[q] : mx;
+        }
+        bits = row_all<kWave>(bits, either);
+        high = row_sum<kWave>(high);
+        sum = row_sum<kWave>(sum);
+        mx = ~wave_min_u64(~mx);
     }
-#pragma unroll
-    for (int k = kWave / 2; k >= 1; k >>= 1) {
-        bits |= (uint64_t)__shfl_xor((long long)bits, k, kWave);
-        high += (uint64_t)__shfl_xor((long long)high, k, kWave);
-        sum += (uint64_t)__shfl_xor((long long)sum, k, kWave);
-    }
-    mx = ~wave_min_u64(~mx);
-    bad = __any(bad != 0) ? 1 : 0;
     if (lane == 0) {
-        part[0][wave] = bits; part[1][wave] = high; part[2][wave] = sum; part[3][wave] = mx; part[4][wave] = bad;
+        part[0][wave] = bits; part[1][wave] = high; part[2][wave] = sum; part[3][wave] = mx;
     }
     __syncthreads();
-    bits = high = sum = mx = bad = 0;
-    for (int k = 0; k < kWaves; ++k) {
-        bits |= part[0][k];
-        high += part[1][k];
-        sum += part[2][k];
-        mx = part[3][k] > mx ? part[3][k] : mx;
-        bad |= part[4][k];
-    }
+    bits = lane63_u64(row_all<kWaves>(part[0][lane % kWaves], either));
+    high = lane63_u64(row_sum<kWaves>(part[1][lane % kWaves]));
+    sum = lane63_u64(row_sum<kWaves>(part[2][lane % kWaves]));
+    mx = ~lane63_u64(row_min<kWaves>(~part[3][lane % kWaves]));
     LongMeta m = {};
-    m.status = bad ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
+    m.status = bits >> 63 ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
     if (m.status != CKPT_OK) {
         if (tid == 0) w.meta[c] = m;
         return;
     }
     uint64_t unit = bits & (0 - bits);
-    if ((sum + mx) / unit >= (1ull << 31)) {
+    const int shift = __ffsll((unsigned long long)unit) - 1;
+    m.narrow = (sum + mx) >> shift < (1ull << 31);
+    if (!m.narrow) {
         // Euclid on all sizes at once: the smallest remainder of any size takes the divisor's place until none is left
         uint64_t g = mx;
 #pragma unroll
@@ -1706,10 +1713,13 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
         g = block_min(g, room);
         for (int turn = 0; turn < 12 && g > unit; ++turn) {  // (not settled by then: small divisors do not help)
             uint64_t r = ~0ull;
+            if (holds) {
 #pragma unroll
-            for (int q = 0; q < kTablePer; ++q) {
-                const uint64_t rest = x[q] % g;
-                r = rest != 0 && rest < r ? rest : r;
+                for (int q = 0; q < kTablePer; ++q) {
+                    if (q >= per) break;
+                    const uint64_t rest = x[q] % g;
+                    r = rest != 0 && rest < r ? rest : r;
+                }
             }
             r = block_min(r, room);
             if (r == ~0ull) {
@@ -1720,35 +1730,42 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
         }
     }
     m.unit = unit;
-    m.narrow = (sum + mx) / unit < (1ull << 31);
     const bool pow2 = (unit & (unit - 1)) == 0;
-    const int shift = __ffsll((unsigned long long)unit) - 1;
+    if (!pow2) m.narrow = (sum + mx) / unit < (1ull << 31);  // (the largest power of two is the first)
     uint64_t *const P64 = (uint64_t *)w.P + c * (n + 1);
     uint32_t *const P32 = (uint32_t *)P64;
-    uint64_t mine = 0;
+    uint64_t mine = 0, incl = 0;
+    if (holds) {
+        if (pow2) {
 #pragma unroll
-    for (int q = 0; q < kTablePer; ++q) {
-        x[q] = pow2 ? x[q] >> shift : x[q] / unit;
-        mine += x[q];
+            for (int q = 0; q < kTablePer; ++q) x[q] >>= shift;
+        } else {
+#pragma unroll
+            for (int q = 0; q < kTablePer; ++q) {
+                if (q >= per) break;
+                x[q] /= unit;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kTablePer; ++q) mine += x[q];
+        incl = wave_scan_u64(mine);
     }
-    const uint64_t incl = wave_scan_u64(mine);
     __syncthreads();
     if (lane == kWave - 1) room[wave] = incl;
     if (tid == 0) ends2[0] = x[0];
     __syncthreads();
-    uint64_t run = incl - mine, total = 0;
-    for (int k = 0; k < kWaves; ++k) {
-        run += k < wave ? room[k] : 0;
-        total += room[k];
-    }
+    const uint64_t of_wave = room[lane % kWaves], total = lane63_u64(row_sum<kWaves>(of_wave));
+    if (holds) {
+        uint64_t run = incl - mine + lane63_u64(row_sum<kWaves>(lane % kWaves < wave ? of_wave : 0));
 #pragma unroll
-    for (int q = 0; q < kTablePer; ++q) {
-        const int k = k0 + q;
-        if (q >= per || k > n) break;
-        run += x[q];
-        if (m.narrow) P32[k] = (uint32_t)run; else P64[k] = run;
-        prefix[k] = bound_prefix(run, ends2[0]);
-        if (k == n) ends2[1] = x[q];
+        for (int q = 0; q < kTablePer; ++q) {
+            const int k = k0 + q;
+            if (q >= per || k > n) break;
+            run += x[q];
+            if (m.narrow) P32[k] = (uint32_t)run; else P64[k] = run;
+            prefix[k] = bound_prefix(run, ends2[0]);
+            if (k == n) ends2[1] = x[q];
+        }
     }
     __syncthreads();
     // a bound from 16 segment lengths, one to a wave (see bound_prefix)
@@ -1763,9 +1780,9 @@ __global__ __launch_bounds__(kTableThreads) void search_table_kernel(const int64
         if (lane == 0) bound_of[wave] = bound_cost(kept, length, all, n);
     }
     __syncthreads();
+    if (wave != 0) return;
+    const float low = row_min<kBounds>(bound_of[lane % kBounds]);
     if (tid != 0) return;
-    float low = bound_of[0];
-    for (int k = 1; k < kBounds; ++k) low = fminf(low, bound_of[k]);
     uint64_t ub = ends + (uint64_t)(double)low + 1;
     ub = ub < total ? ub : total;
     m.ub = ub;
