@@ -198,6 +198,23 @@ def test_long_chains(n):
     check(heavy_ends)
 
 
+@pytest.mark.parametrize("n", [191, 192, 193, 959, 960, 1023, 1024, 1025, 1087, 1088])
+def test_the_last_wave_of_the_table_that_holds_sizes(n):
+    """The waves and threads that a chain's sizes end in: its last size alone there, a common divisor of all sizes that it
+    alone takes away, 64-bit arithmetic, and a chain whose last size alone is bad."""
+    rng = np.random.default_rng(n)
+    d = rng.integers(1, 1000, size=(n + 1, 4)).astype(np.int64)
+    d[:, 1] *= 3 * (1 << 30) + 9                    # 32 bits once divided
+    d[:, 2] *= 3 * (1 << 30) + 9
+    d[n, 2] += 1                                    # not so
+    d[n, 3] = 1 << 40
+    print(f"cubic search, table: n = {n}", flush=True)
+    check(d, chain_major=n % 2 == 1)
+    d[n, 1], d[n, 3] = 0, -(1 << 40)
+    status = B.ckpt_solve_cubic(torch.from_numpy(d).cuda())[3].cpu().tolist()
+    assert [s == 0 for s in status] == [True, False, True, False]
+
+
 @pytest.mark.parametrize("n", [64, 142, 200, 257, 300, 640])
 def test_sizes_at_the_ends_that_outweigh_the_rest(n):
     """The size in front, or the last one, 2^20 to 2^50 times the interior sizes: neither is part of any budget."""
