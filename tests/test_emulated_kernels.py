@@ -30,8 +30,6 @@ def source(name, tmp_path):
     text = replaced(text, r"extern __shared__ [^;]*;", f"#define {lds} (({kind} *)emu::dynamic_lds)")
     if name == "cubic_search":
         text = replaced(text, r"    uint32_t r;\n    asm\(\"v_cndmask_b32[^;]*;\n    return r;", "    return (mask >> emu::lane()) & 1 ? on : off;")
-        # (lanes that do the same read a ring's row together, before one of them writes it)
-        text = replaced(text, r"        U whole = f\[kRowBlk - 1\];\n", "        (void)emu::ballot(true);\n        U whole = f[kRowBlk - 1];\n")
     if name == "solve_linear":
         text = ring_in_c(text)
         # (the lanes of a row read the step together, before one of them marks it)
