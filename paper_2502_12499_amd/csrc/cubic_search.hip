@@ -765,7 +765,7 @@ struct SearchWs {
     int32_t *list;   // [batch]
 };
 
-__global__ void cubic_search_reset_kernel(SearchWs w) { *w.count = 0; }
+__global__ void cubic_search_reset_kernel(SearchWs w) { w.count[threadIdx.x] = 0; }
 
 // ---------------------------------------------------------------------------
 // many short chains: a row of lanes per chain
@@ -801,9 +801,9 @@ __host__ __device__ inline int row_blocks(int n) { return (n + kRowBlk - 1) / kR
 __host__ __device__ inline int row_sums(int n) { return (row_blocks(n) + 4) * kRowBlk + 2; }
 // The slots of a chain, four more so that those of the chains of a wave lie in banks of their own.
 __host__ __device__ inline int row_slots(int n) { return n * kRowSlots + 4 * kRowSlots; }
-// Positions whose minima a lane keeps: those of all windows, and of longer chains those of nearly all (the windows up to the
-// best cost reach over 37 layers in one of a hundred chains of 64 unrounded layers, over 50 of 128; over 60 in one of ten
-// networks of 128).  What it saves is waves in flight: 65,536 aligned chains of 64 layers 756 us with a ring of 64, 557 with
+// Positions whose minima a lane keeps: those of all windows, and of longer chains those of nearly all of most kinds (the windows
+// up to the best cost reach over 37 layers in one of a hundred chains of 64 unrounded layers, over 50 of 128; over 60 in one of
+// ten networks of 128; where the layers in front outweigh the rest, over nearly all: see RowsLeft::kFar).  What it saves is waves in flight: 65,536 aligned chains of 64 layers 756 us with a ring of 64, 557 with
 // 40; 128 layers with 72, 60, 48: aligned 2.0, 1.7, 1.5 ms, networks 2.3, 2.7, 3.6 ms (5.1 and 4.1 with a wave a chain).
 __host__ __device__ inline int row_ring(int n)
 {
@@ -1073,8 +1073,8 @@ __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool re
     return last == 0 ? f[1] : last == 1 ? f[2] : last == 2 ? f[3] : f[4];
 }
 
-// The cost of a feasible set by the lane of the best of G greedy walks (see greedy_bound), half an octave to an octave
-// between their limits.
+// The cost of a feasible set without the sizes at the ends, by the lane of the best of G greedy walks (see greedy_bound), half
+// an octave to an octave between their limits.
 template <int G>
 __device__ inline uint64_t rows_bound(const float *size, const int n, const float all)
 {
@@ -1082,7 +1082,7 @@ __device__ inline uint64_t rows_bound(const float *size, const int n, const floa
     const int i = threadIdx.x % G;
     const float limit = all * exp2f(-0.5f - (float)i * (5.6f / G));
     const float *const d = size + threadIdx.x / G;
-    float kept = d[0] + d[n * C], seg = 0.0f, longest = 0.0f;
+    float kept = 0.0f, seg = 0.0f, longest = 0.0f;
     const auto layer = [&](const float x) {
         const float to = seg + x;
         const bool fits = to <= limit;
@@ -1104,59 +1104,110 @@ __device__ inline uint64_t rows_bound(const float *size, const int n, const floa
     return (uint64_t)(double)__uint_as_float(row_min<G>(__float_as_uint(cost))) + 1;
 }
 
-// Chain c of each row where `valid`, n <= MOST.  True if it is left, with nothing written: 32 bits do not hold its values, or
-// the ring its windows.
+// A chain is expected to be far, one whose windows reach beyond the ring, if a window that does holds no more than this share
+// of the span: the best cost lies at 0.3 to 0.4 of it for unrounded sizes, 0.7 to 0.8 for networks, 0.95 for sizes that fall from
+// layer to layer.  (Taken so, of 64 layers, 0 to 2 % of aligned and unrounded chains and networks, 74 % of networks whose
+// pictures are all halved in the first third; 0, 0 and 74 % are.)
+constexpr float kFarShare = 0.75f;
+
+// What a row knows of its chain before the search.
 template <int G, int MOST>
-__device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const int64_t c, const bool valid, const int n,
-                                            const int64_t cstride, const int64_t pstride, uint8_t *__restrict__ mask_out,
-                                            int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
-                                            int32_t *__restrict__ status_out, const int ring)
+struct RowChain {
+    static constexpr int PER = MOST / G + 1;
+    int per, k0;                // the lane's sizes: how many, and the first one's position
+    uint64_t own[PER], before;  // ... and the sum of those before
+    int32_t status;
+    int shift;
+    uint64_t d0, dn, total, all, largest;  // scaled: the sizes at the ends, all sizes, the interior ones, the largest
+    uint64_t span;                         // no budget beyond it can be optimal
+    // (n <= MOST; size: LDS for a float a layer and chain)
+    __device__ __forceinline__ RowChain(const int64_t *__restrict__ dp, const int n, const int64_t pstride, float *const size)
+    {
+        constexpr int C = kWave / G;
+        const int row = threadIdx.x / G, i = threadIdx.x % G;
+        per = (n + G) / G;
+        k0 = i * per;
+        uint64_t sum = 0, bits = 0, high = 0, mx = 0;
+        bool bad = false;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            own[q] = 0;
+            if (q < per) own[q] = k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const uint64_t x = own[q];
+            bad |= q < per && k0 + q <= n && (int64_t)x <= 0;
+            bits |= x;
+            high += x >> 32;
+            sum += x;
+            mx = x > mx ? x : mx;
+        }
+        const uint64_t d_first = (uint64_t)dp[0], d_last = (uint64_t)dp[(int64_t)n * pstride];
+        before = row_scan<G>(sum, [](uint64_t a, uint64_t b) { return a + b; }) - sum;
+        sum = row_sum<G>(sum);
+        high = row_sum<G>(high);
+        bits = row_all<G>(bits, [](uint64_t a, uint64_t b) { return a | b; });
+        mx = ~row_min<G>(~mx);
+        bad = row_min<G>((uint32_t)!bad) == 0;
+        status = bad ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
+        shift = bits ? __ffsll((unsigned long long)bits) - 1 : 0;
+        total = sum >> shift;
+        d0 = d_first >> shift;
+        dn = d_last >> shift;
+        all = status == CKPT_OK ? total - d0 - dn : 0;
+        largest = mx >> shift;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (q < per && k0 + q <= n) size[(k0 + q) * C + row] = (float)(own[q] >> shift);
+        __syncthreads();
+        span = rows_bound<G>(size, n, (float)all);
+        span = span < all ? span : all;
+    }
+    // Is it expected to be far?  (sums: as size)
+    __device__ __forceinline__ bool far(const int n, const int ring, float *const sums) const
+    {
+        constexpr int C = kWave / G;
+        const int row = threadIdx.x / G, i = threadIdx.x % G;
+        uint64_t run = before;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            run += own[q];
+            if (q < per && k0 + q <= n) sums[(k0 + q) * C + row] = (float)(run >> shift);
+        }
+        __syncthreads();
+        // the least sum that a window beyond the ring has, one that ends in a block's first position
+        float least = std::numeric_limits<float>::max();
+        for (int b = ring / kRowBlk + 1 + i; b < row_blocks(n); b += G)
+            least = fminf(least, sums[b * kRowBlk * C + row] - sums[(b * kRowBlk - ring - 1) * C + row]);
+        least = row_all<G>(least, [](float a, float b) { return fminf(a, b); });
+        return status == CKPT_OK && least <= kFarShare * (float)span;
+    }
+};
+
+// Why a row leaves its chain, with nothing written: the ring does not hold its windows, or 32 bits its values.
+enum class RowsLeft { kNone, kFar, kWide };
+
+// Chain c of each row where `valid`, n <= MOST.
+template <int G, int MOST>
+__device__ __forceinline__ RowsLeft search_rows(const int64_t *__restrict__ d, const int64_t c, const bool valid, const int n,
+                                                const int64_t cstride, const int64_t pstride, uint8_t *__restrict__ mask_out,
+                                                int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
+                                                int32_t *__restrict__ status_out, const int ring)
 {
     typedef uint32_t U;
     typedef int32_t I;
-    constexpr int C = kWave / G;
+    constexpr int C = kWave / G, PER = RowChain<G, MOST>::PER;
     const RowsLds<G> m(search_lds, n, ring);
     const int lane = threadIdx.x, row = lane / G, i = lane % G;
-    const int64_t *const dp = d + c * cstride;
-    // the sizes, a lane's one after the other
-    constexpr int PER = MOST / G + 1;
-    const int per = (n + G) / G, k0 = i * per;
-    uint64_t own[PER], sum = 0, bits = 0, high = 0, mx = 0;
-    bool bad = false;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        own[q] = 0;
-        if (q < per) own[q] = k0 + q <= n ? (uint64_t)dp[(int64_t)(k0 + q) * pstride] : 0;
-    }
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const uint64_t x = own[q];
-        bad |= q < per && k0 + q <= n && (int64_t)x <= 0;
-        bits |= x;
-        high += x >> 32;
-        sum += x;
-        mx = x > mx ? x : mx;
-    }
-    const uint64_t d_first = (uint64_t)dp[0], d_last = (uint64_t)dp[(int64_t)n * pstride];
-    const uint64_t upto = row_scan<G>(sum, [](uint64_t a, uint64_t b) { return a + b; }), before = upto - sum;
-    sum = row_sum<G>(sum);
-    high = row_sum<G>(high);
-    bits = row_all<G>(bits, [](uint64_t a, uint64_t b) { return a | b; });
-    mx = ~row_min<G>(~mx);
-    bad = row_min<G>((uint32_t)!bad) == 0;
-    const int32_t status = bad ? CKPT_ERR_SIZE : chain_overflows(sum, high, mx) ? CKPT_ERR_OVERFLOW : CKPT_OK;
-    const int shift = bits ? __ffsll((unsigned long long)bits) - 1 : 0;
-    const uint64_t total = sum >> shift, d0 = d_first >> shift, dn = d_last >> shift, ends = d0 + dn;
-    const uint64_t all = status == CKPT_OK ? total - ends : 0, largest = mx >> shift;
-    float *const size = (float *)m.L1;
-#pragma unroll
-    for (int q = 0; q < PER; ++q)
-        if (q < per && k0 + q <= n) size[(k0 + q) * C + row] = (float)(own[q] >> shift);
-    __syncthreads();
-    uint64_t bound = rows_bound<G>(size, n, (float)all);
-    bound = bound < total ? bound : total;
-    bound = bound > ends ? bound : ends;
-    uint64_t span = all < bound - ends ? all : bound - ends;
+    const RowChain<G, MOST> chain(d + c * cstride, n, pstride, (float *)m.L1);
+    const int per = chain.per, k0 = chain.k0, shift = chain.shift;
+    const auto &own = chain.own;
+    const int32_t status = chain.status;
+    const uint64_t before = chain.before, d0 = chain.d0, dn = chain.dn, total = chain.total, all = chain.all, largest = chain.largest;
+    uint64_t span = chain.span;
+    const uint64_t bound = d0 + dn + span;
     // What is looked at of differences of sums modulo 2^32: up to a window, or the size at its start, and two sizes more; down
     // to four sizes below 0.
     const uint64_t reach = (span > largest ? span : largest) + 2 * largest;
@@ -1165,7 +1216,7 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
     const bool flat = !solved || total + span + 1 < (1ull << 32);
     if (!solved) span = 0;
     if (__builtin_amdgcn_ballot_w64(solved) == 0 && __builtin_amdgcn_ballot_w64(valid && status != CKPT_OK) == 0)
-        return valid;
+        return valid ? RowsLeft::kWide : RowsLeft::kNone;
     // The prefix sums, of a chain that is left out 1 everywhere, and the table: position k is the first one of the slots
     // behind that of the one before, up to its own; bytes up to a word's beginning, words, bytes.
     __syncthreads();
@@ -1299,8 +1350,8 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
             value -= j > 0 ? P[(j + 1) * C] - P[j * C] : 0;
         }
     }
-    if (!valid) return false;
-    if (status == CKPT_OK && (!narrow || beyond)) return true;
+    if (!valid) return RowsLeft::kNone;
+    if (status == CKPT_OK && (!narrow || beyond)) return narrow ? RowsLeft::kFar : RowsLeft::kWide;
     if (status != CKPT_OK) mine = 0;
     uint8_t *const mp = mask_out + c * cstride;
     for (int k = i, q = 0; k <= n; k += G, ++q) mp[(int64_t)k * pstride] = (uint8_t)((mine >> q) & 1);
@@ -1309,20 +1360,110 @@ __device__ __forceinline__ bool search_rows(const int64_t *__restrict__ d, const
         if (budget_out) budget_out[c] = status == CKPT_OK ? (int64_t)((uint64_t)best_s << shift) : -1;
         if (status_out) status_out[c] = status;
     }
-    return false;
+    return RowsLeft::kNone;
 }
 
+// Where the rows may leave chains for their windows (a ring for some of the positions), the call is
+//   cubic_rows_sample_kernel  how many of some chains are expected to be far;
+//   cubic_rows_kernel         if those are few: the rows, with what they leave done by the same wave or on lists; else nothing;
+//   cubic_search_far_kernel   a wave a chain, in 32 bits: the listed far chains if they are many, or all chains;
+//   cubic_search_wide_kernel  ... in 64 bits: those that need them, and the listed far chains if they are few.
+// Far chains cost the rows their rounds and a wave its search, so a batch of many is better left to waves altogether: 65,536
+// chains of 64 layers that fall from one to the next 1.13 ms, 2.8 with rows first and then 64-bit arithmetic for the far ones;
+// 4,096 of 256 layers 1.29 (4.1).
+// Words of SearchWs::count; its list is followed by one of the far chains, [batch] too.
+constexpr int kCountWide = 0, kCountFar = 1, kHeads = 16, kSampled = 32;
+constexpr int kSamples = 128;  // workgroups, with a byte each from word kSampled on
+constexpr int kXcds = 8;
+
+// Are `from` or more of the sampled chains expected to be far?
+__device__ inline bool mostly_far(const SearchWs w, const int from)
+{
+    static_assert(kSamples / 4 * 2 == kWave, "a wave reads every word twice");
+    uint32_t v = (uint32_t)w.count[kSampled + threadIdx.x % (kSamples / 4)];
+    v = (v & 0xff00ffu) + ((v >> 8) & 0xff00ffu);
+    v = (v & 0xffffu) + (v >> 16);
+    return (int)(row_sum<kWave>(v) / 2) >= from;
+}
+
+// The chains of one wave of every kSamples-th of the batch, anywhere in it (so that no period of the chains matters).  The
+// other words are cleared, which other calls have a launch for.
 template <int G, int MOST>
+__global__ __launch_bounds__(kWave) void cubic_rows_sample_kernel(const int64_t *__restrict__ d, int64_t batch, int n, int64_t cstride,
+                                                                  int64_t pstride, int ring, SearchWs w)
+{
+    constexpr int C = kWave / G;
+    const int64_t waves = (batch + C - 1) / C, any = waves * (int64_t)((blockIdx.x * 2654435761u) >> 16) >> 16;
+    const int64_t c = (waves * blockIdx.x + any) / kSamples * C + threadIdx.x / G;
+    const bool valid = c < batch;
+    const RowChain<G, MOST> chain(d + (valid ? c : batch - 1) * cstride, n, pstride, (float *)search_lds);
+    const uint64_t far = __builtin_amdgcn_ballot_w64(chain.far(n, ring, (float *)search_lds) && valid && threadIdx.x % G == 0);
+    if (threadIdx.x == 0) ((uint8_t *)(w.count + kSampled))[blockIdx.x] = (uint8_t)__popcll((unsigned long long)far);
+    if (blockIdx.x == 0 && threadIdx.x < kSampled) w.count[threadIdx.x] = 0;
+}
+
+// IN_WAVE: a wave goes on with its far chains, one after the other; else they go on their list.
+template <int G, int MOST, bool IN_WAVE>
 __global__ __launch_bounds__(kWave) void cubic_rows_kernel(const int64_t *__restrict__ d, int64_t batch, int n, int64_t cstride,
-                                                           int64_t pstride, int ring, uint8_t *__restrict__ mask_out,
+                                                           int64_t pstride, int ring, int far_from, uint8_t *__restrict__ mask_out,
                                                            int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
                                                            int32_t *__restrict__ status_out, SearchWs w)
 {
+    if (ring < row_blocks(n) * kRowBlk && mostly_far(w, far_from)) return;
     const int64_t c = (int64_t)xcd_blocked(blockIdx.x, gridDim.x) * (kWave / G) + threadIdx.x / G;
     const bool valid = c < batch;
-    const bool left = search_rows<G, MOST>(d, valid ? c : batch - 1, valid, n, cstride, pstride, mask_out, peak_out, budget_out,
-                                           status_out, ring);
-    if (left && threadIdx.x % G == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
+    const RowsLeft left = search_rows<G, MOST>(d, valid ? c : batch - 1, valid, n, cstride, pstride, mask_out, peak_out,
+                                               budget_out, status_out, ring);
+    const bool leads = threadIdx.x % G == 0;
+    if (leads && left == RowsLeft::kWide) w.list[atomicAdd(w.count + kCountWide, 1)] = (int32_t)c;
+    if constexpr (!IN_WAVE) {
+        if (leads && left == RowsLeft::kFar) w.list[batch + atomicAdd(w.count + kCountFar, 1)] = (int32_t)c;
+    } else {
+        for (uint64_t far = __builtin_amdgcn_ballot_w64(leads && left == RowsLeft::kFar); far != 0; far &= far - 1) {
+            const int64_t f = c - threadIdx.x / G + __builtin_ctzll((unsigned long long)far) / G;
+            __syncthreads();
+            const bool done = search_one<true, false>(d + f * cstride, pstride, n, mask_out + f * cstride, pstride, peak_out + f,
+                                                      budget_out ? budget_out + f : nullptr, status_out ? status_out + f : nullptr, ~0u);
+            if (!done && threadIdx.x == 0) w.list[atomicAdd(w.count + kCountWide, 1)] = (int32_t)f;
+        }
+    }
+}
+
+// EACH: a workgroup for every chain of the batch, with or without one to solve.  Else the waves that the chip holds: of an
+// XCD's share, whose neighbours in memory it reads together, they take half one after the other and the rest as they get
+// free.  (All of it as they get free: 8,192 chains of 64 layers 188 us instead of 169, all of it one after the other 201.)
+template <bool EACH>
+__global__ __launch_bounds__(kWave) void cubic_search_far_kernel(const int64_t *__restrict__ d, int64_t batch, int n, int64_t cstride,
+                                                                 int64_t pstride, int far_from, int few, uint8_t *__restrict__ mask_out,
+                                                                 int64_t *__restrict__ peak_out, int64_t *__restrict__ budget_out,
+                                                                 int32_t *__restrict__ status_out, SearchWs w)
+{
+    const bool every = mostly_far(w, far_from);
+    const int count = every ? (int)batch : w.count[kCountFar];
+    if (!every && count <= few) return;
+    const auto solve = [&](const int at) {
+        const int64_t c = every ? at : w.list[batch + at];
+        const bool done = search_one<true, false>(d + c * cstride, pstride, n, mask_out + c * cstride, pstride, peak_out + c,
+                                                  budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr, ~0u);
+        if (!done && threadIdx.x == 0) w.list[atomicAdd(w.count + kCountWide, 1)] = (int32_t)c;
+    };
+    if constexpr (EACH) {
+        const int at = (int)xcd_blocked(blockIdx.x, gridDim.x);
+        if (at < count) solve(at);
+    } else {
+        const int xcd = blockIdx.x % kXcds, share = (count + kXcds - 1) / kXcds, first = share * xcd;
+        const int waves = gridDim.x / kXcds, fixed = share / waves / 2;
+        for (int turn = 0;; ++turn) {
+            int at = turn * waves + blockIdx.x / kXcds;
+            if (turn >= fixed) {
+                if (threadIdx.x == 0) at = fixed * waves + atomicAdd(w.count + kHeads + xcd, 1);
+                at = __builtin_amdgcn_readfirstlane(at);
+            }
+            if (at >= share || first + at >= count) break;
+            solve(first + at);
+            __syncthreads();
+        }
+    }
 }
 
 // Every chain of the batch; WIDE false: those that need 64 bits go on the list.
@@ -1340,17 +1481,17 @@ __global__ __launch_bounds__(kWave) void cubic_search_kernel(const int64_t *__re
     if (!WIDE && !done && threadIdx.x == 0) w.list[atomicAdd(w.count, 1)] = (int32_t)c;
 }
 
-// The listed ones.
-__global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t *__restrict__ d, int n,
+// The listed ones, and the far chains if they are no more than `few`.
+__global__ __launch_bounds__(kWave) void cubic_search_wide_kernel(const int64_t *__restrict__ d, int64_t batch, int n, int few,
                                                                   int64_t cstride, int64_t pstride,
                                                                   uint8_t *__restrict__ mask_out,
                                                                   int64_t *__restrict__ peak_out,
                                                                   int64_t *__restrict__ budget_out,
                                                                   int32_t *__restrict__ status_out, SearchWs w)
 {
-    const int count = *w.count;
+    const int wide = w.count[kCountWide], far = few > 0 ? w.count[kCountFar] : 0, count = wide + (far <= few ? far : 0);
     for (int item = blockIdx.x; item < count; item += gridDim.x) {
-        const int64_t c = w.list[item];
+        const int64_t c = w.list[item < wide ? item : batch + (item - wide)];
         (void)search_one<true, true>(d + c * cstride, pstride, n, mask_out + c * cstride, pstride, peak_out + c,
                                       budget_out ? budget_out + c : nullptr, status_out ? status_out + c : nullptr, ~0u);
         __syncthreads();
@@ -1402,8 +1543,8 @@ hipError_t raise_search_lds_limit()
     return raise_lds_limit(search_lds_raised,
                            {(const void *)cubic_search_kernel<true>, (const void *)cubic_search_kernel<false>,
                             (const void *)cubic_search_wide_kernel, (const void *)cubic_search_ragged_kernel,
-                            (const void *)cubic_search_ragged_wide_kernel, (const void *)cubic_rows_kernel<8, kRowsOf8Layers>,
-                            (const void *)cubic_rows_kernel<16, kRowsOf16Layers>, (const void *)cubic_rows_kernel<16, kRowsMaxLayers>},
+                            (const void *)cubic_search_ragged_wide_kernel, (const void *)cubic_search_far_kernel<true>,
+                            (const void *)cubic_search_far_kernel<false>, (const void *)cubic_rows_kernel<16, kRowsMaxLayers, false>},
                            search_lds_bytes(kSearchMaxLayers, 8));
 }
 
@@ -1419,10 +1560,25 @@ constexpr int kSearchWideBlocks = 1024;
 // 65,536 aligned chains of 64 layers 552 us (646), of 90 1,030 (907); 8,192 of 64 153 (108).
 constexpr int64_t kRowsOf8From = 16384;
 inline int64_t rows_from(int n) { return n > 128 ? 2048 : n > 96 ? 4096 : 8192; }
+// The share of a batch's chains that are expected to be far from which on waves take them all.  Far chains among others add a
+// launch's time to that of the rows, a wave's search at least: 65,536 unrounded chains of 64 layers with one in ten of layers in
+// front that outweigh the rest 0.95 ms (1.27 with a wave a chain), with one in two 1.19 (1.20; 1.6 as rows and waves); 8,192 of
+// them with one in ten 253 us as rows and waves, 200 as waves.
+// A workgroup for every chain up to this many (see there): 2,048 chains of 152 layers 291 us (340 with the waves that the chip
+// holds), 8,192 of 48 layers 134 (148).  Where there is nothing to do that costs 8,192 chains 1 us.
+constexpr int64_t kFarEachMost = 8192;
 // (a launch has fewer than 2^32 threads)
 constexpr int64_t kMostWavesOfALaunch = 1 << 25;
 // Waves of this much LDS that the chip holds (LDS is handed out in units of 1,280 bytes).
 inline int64_t at_once(size_t lds) { return 256 * ((160 << 10) / (int64_t)align_up(lds, 1280)); }
+// The share of a batch's chains that are expected to be far from which on waves take them all.  Far chains among others add to
+// the rows' time a wave's search, a quarter of what all of them take with four turns of waves; with one in ten of layers in
+// front that outweigh the rest, unrounded others and a share of 1/4, 8,192 chains of 64 layers 280 us, 2,048 of 130 487 (so 201
+// and 360; without rows 198 and 361), 65,536 of 64 1.0 ms (1.27 without rows).
+inline float far_share(int64_t batch, int n)
+{
+    return (n <= kRowsOf8Layers ? batch < kRowsOf8From : batch <= 4 * at_once(search_lds_bytes(n, 4))) ? 1.0f / 16 : 1.0f / 4;
+}
 // A ragged batch goes in one launch up to this many turns of it, with the longest chain's LDS for all: the classes one
 // after the other each wait for their slowest wave.  1,000 chains of 2 to 152 layers 114 us (four launches 247), 4,096
 // 194 (335), 8,192 373 (387), 16,384 668 (567); of 2 to 256 layers 4,096 427 (519), 8,192 785 (798), 16,384 1,546
@@ -1457,18 +1613,44 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
     const dim3 grid((unsigned)batch), block(kWave);
     const SearchWs w{(int32_t *)ws, (int32_t *)((char *)ws + 256)};
     if (batch >= rows_from(n)) {
-        const int ring = row_ring(n);
-        hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(1), 0, stream, w);
+        // (far chains that are less than a turn of the wide ones' waves go with those: a launch lasts as long as a chain)
+        const int few = (int)at_once(search_lds_bytes(n, 8));
         const auto rows = [&](auto lanes, auto most) {
-            constexpr int G = decltype(lanes)::value, C = kWave / G;
-            hipLaunchKernelGGL((cubic_rows_kernel<G, decltype(most)::value>), dim3((unsigned)((batch + C - 1) / C)), block, rows_lds_bytes(n, C, ring),
-                               stream, d, batch, n, st.chain, st.pos, ring, mask_out, peak_out, budget_out, status_out, w);
+            constexpr int G = decltype(lanes)::value, MOST = decltype(most)::value, C = kWave / G;
+            constexpr bool kInWave = MOST <= kRowsOf16Layers;
+            const int positions = row_blocks(n) * kRowBlk;
+            const int64_t waves = (batch + C - 1) / C;
+            const size_t one = search_lds_bytes(n, 4);
+            int ring = row_ring(n);
+            size_t lds = rows_lds_bytes(n, C, ring);
+            // A wave goes on with its far chains where the LDS for that leaves as many waves, and a longer ring what of it there
+            // is: 65,536 unrounded chains of 64 layers 665 us (697 with the far ones in a launch), 8,192 150 (180).  Beyond 128
+            // layers that gains nothing: 2,048 networks of 152 302 (292).
+            const bool in_wave = kInWave && ring < positions && (at_once(one) >= at_once(lds) || waves <= at_once(one));
+            if (in_wave) {
+                while (ring < positions && rows_lds_bytes(n, C, ring + kRowBlk) <= one) ring += kRowBlk;
+                lds = std::max(one, rows_lds_bytes(n, C, ring));
+            }
+            const bool whole = ring == positions;  // (no chain is far)
+            if (whole)
+                hipLaunchKernelGGL(cubic_search_reset_kernel, dim3(1), dim3(kSampled), 0, stream, w);
+            else
+                hipLaunchKernelGGL((cubic_rows_sample_kernel<G, MOST>), dim3(kSamples), block, (size_t)(n + 1) * C * 4, stream, d, batch,
+                                   n, st.chain, st.pos, ring, w);
+            const int far_from = (int)(far_share(batch, n) * (float)(kSamples * C));
+            hipLaunchKernelGGL((in_wave ? cubic_rows_kernel<G, MOST, kInWave> : cubic_rows_kernel<G, MOST, false>), dim3((unsigned)waves), block,
+                               lds, stream, d, batch, n, st.chain, st.pos, ring, far_from, mask_out, peak_out, budget_out, status_out, w);
+            if (whole) return;
+            const bool each = batch <= kFarEachMost;
+            hipLaunchKernelGGL(each ? cubic_search_far_kernel<true> : cubic_search_far_kernel<false>,
+                               dim3((unsigned)(each ? batch : at_once(one))), block, one, stream, d, batch, n, st.chain, st.pos, far_from, few,
+                               mask_out, peak_out, budget_out, status_out, w);
         };
         if (batch >= kRowsOf8From && n <= kRowsOf8Layers) rows(std::integral_constant<int, 8>(), std::integral_constant<int, kRowsOf8Layers>());
         else if (n <= kRowsOf16Layers) rows(std::integral_constant<int, 16>(), std::integral_constant<int, kRowsOf16Layers>());
         else rows(std::integral_constant<int, 16>(), std::integral_constant<int, kRowsMaxLayers>());
         hipLaunchKernelGGL(cubic_search_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(n, 8), stream, d,
-                           n, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);
+                           batch, n, few, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);
     } else if (batch < kSearchSplitFrom) {
         hipLaunchKernelGGL(cubic_search_kernel<true>, grid, block, search_lds_bytes(n, 8), stream, d, n, st.chain, st.pos,
                            mask_out, peak_out, budget_out, status_out, w);
@@ -1477,7 +1659,7 @@ hipError_t launch_cubic_search(const int64_t *d, int64_t batch, int n, Strides s
         hipLaunchKernelGGL(cubic_search_kernel<false>, grid, block, search_lds_bytes(n, 4), stream, d, n, st.chain,
                            st.pos, mask_out, peak_out, budget_out, status_out, w);
         hipLaunchKernelGGL(cubic_search_wide_kernel, dim3(kSearchWideBlocks), block, search_lds_bytes(n, 8), stream, d,
-                           n, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);
+                           batch, n, 0, st.chain, st.pos, mask_out, peak_out, budget_out, status_out, w);
     }
     return hipGetLastError();
 }

@@ -79,6 +79,58 @@ def test_rows_of_lanes(n, batch):
     assert np.array_equal(mask.cpu().numpy().T, np.where(bad[:, None], 0, want_mask[at]))
 
 
+def front_heavy(n, seed, batch):
+    """Layers in front that outweigh the rest: sizes that fall from layer to layer, pictures halved in the first third, a few
+    large layers before many small ones."""
+    rng = np.random.default_rng(seed)
+    k = np.arange(n + 1)[:, None]
+    falls = 2.0 ** 27 * (0.8 + 0.15 * rng.random(batch)) ** k * (0.7 + 0.6 * rng.random((n + 1, batch)))
+    ends = np.sort(1 + rng.random((4, batch)) * n / 3, axis=0)
+    halved = (k[:, :, None] >= ends.T[None]).sum(2)
+    pyramid = rng.integers(8, 208, size=batch) * 802816.0 / 2.0 ** halved
+    small = np.where(k < 5, rng.integers(1 << 20, 1 << 21, size=(n + 1, batch)), rng.integers(1024, 5120, size=(n + 1, batch)))
+    at = np.arange(batch) % 3
+    return np.maximum(np.where(at == 0, falls, np.where(at == 1, pyramid, small)).astype(np.int64), 1)
+
+
+@pytest.mark.parametrize("share", ["all", "tenth", "half in front"])
+@pytest.mark.parametrize("n,batch", [(44, 8192), (64, 8197), (72, 16390), (100, 4099), (152, 2051), (152, 9001), (256, 2048)])
+def test_windows_beyond_the_ring(n, batch, share):
+    """Chains that the rows leave to waves: of the whole batch, of some, side by side with others or not; bad ones and ones that
+    need 64 bits among them."""
+    print(f"windows beyond the ring: n = {n}, batch = {batch}, {share}", flush=True)
+    rng = np.random.default_rng(n + batch)
+    far, near = front_heavy(n, n, 30), inputs.log_uniform_chains(n, n, 29)
+    wide = rng.integers(1, (1 << 62) // (n + 2), size=(n + 1, 2))
+    kinds = np.concatenate([far, near, wide], axis=1).astype(np.int64)
+    want_peak, want_mask, want_s = oracle.batch_solve_static(inputs.chain_major(kinds))
+    c = np.arange(batch)
+    is_far = {"all": c >= 0, "tenth": c % 10 == 3, "half in front": c < batch // 2}[share]
+    at = np.where(is_far, c % 30, 30 + c % 29)
+    at[5::997] = 59 + c[5::997] % 2
+    d = kinds[:, at]
+    d[n // 2, 7::1009] = 0
+    bad = d.min(0) <= 0
+    mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d)).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(status.cpu().numpy(), np.where(bad, 3, 0))
+    assert np.array_equal(peak.cpu().numpy(), np.where(bad, -1, want_peak[at]))
+    assert np.array_equal(budget.cpu().numpy(), np.where(bad, -1, want_s[at]))
+    assert np.array_equal(mask.cpu().numpy().T, np.where(bad[:, None], 0, want_mask[at]))
+
+
+@pytest.mark.parametrize("n", [152, 256])
+def test_windows_beyond_the_ring_take_no_longer_than_a_wave_a_chain(n):
+    """2,047 chains have a wave each, twice as many would have rows: with the rows' rounds before them and in the arithmetic of
+    64 bits they took 5.7 and 5.8 times as long, not 1.7 and 1.8 times."""
+    d = np.tile(front_heavy(n, n, 89), 46)[:, :4094]
+    once, twice = (torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (d[:, :2047], d))
+    ws = torch.empty(B.workspace_bytes(B.CALL_SOLVE_CUBIC, B.layout_of(twice)), dtype=torch.uint8, device="cuda")
+    few, many = (shortest_us(lambda: B.ckpt_solve_cubic(x, workspace=ws)) for x in (once, twice))
+    print(f"{few:.0f} and {many:.0f} us", flush=True)
+    assert many < 2.6 * few
+
+
 def test_bad_chains_are_reported_alone():
     d = inputs.uniform_aligned_chains(4, 30, 1100, 256, 32768)
     dc = inputs.chain_major(d)
