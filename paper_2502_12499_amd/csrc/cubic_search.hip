@@ -956,8 +956,9 @@ __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool re
             for (int u = 0; u < kRowBlk; ++u) test(l[u], e[u], p[u][1], p[u][2], p[u][3]);
         }
     };
-    // a window that begins at e holds the position with this sum
-    const auto holds = [&](U sum, U e) { return FLAT ? sum >= e : sum - e <= over; };
+    // the window of the cell behind the sum x, which begins at e = x - s, holds the position with this sum (no more than four
+    // sizes below x, or out)
+    const auto holds = [&](U sum, U e, U x) { return FLAT ? sum >= e : x - sum <= s; };
     // the sums that block b's positions end in, and where the windows of the cells behind them may begin
     const auto load = [&](U (&x)[kRowBlk], int b) {
 #pragma unroll
@@ -1023,10 +1024,10 @@ __device__ __forceinline__ uint32_t rows_pass(const RowsLds<G> &m, const bool re
             const U from = e[r0][u];
             U w = la[u] < lc[u] ? la[u] : lc[u];
             w = f[u] < w ? f[u] : w;
-            w = holds(edge, from) ? w : f[u];
+            w = holds(edge, from, x[r0][u]) ? w : f[u];
 #pragma unroll
             for (int k = 0; k < u; ++k) {
-                const U v = holds(x[r0][k], from) ? f[k] : kMax;
+                const U v = holds(x[r0][k], from, x[r0][u]) ? f[k] : kMax;
                 w = v < w ? v : w;
             }
             f[u + 1] = ((u + 1 < kRowBlk ? x[r0][(u + 1) % kRowBlk] : x[r1][0]) - x[r0][u]) + w;
@@ -1208,10 +1209,12 @@ __device__ __forceinline__ RowsLeft search_rows(const int64_t *__restrict__ d, c
     const uint64_t before = chain.before, d0 = chain.d0, dn = chain.dn, total = chain.total, all = chain.all, largest = chain.largest;
     uint64_t span = chain.span;
     const uint64_t bound = d0 + dn + span;
-    // What is looked at of differences of sums modulo 2^32: up to a window, or the size at its start, and two sizes more; down
-    // to four sizes below 0.
+    // What is looked at of differences from where a window may begin, modulo 2^32: up to a window, or the size at its start, and
+    // two sizes more; down to a slot, which is no wider than the largest size, and a size below 0.  (Every chain that the form
+    // of a wave takes in 32 bits fits.  65,536 chains of 16 layers, one of some 650 MB, others of up to 8, all odd, 95 us; with
+    // four sizes below 0 they were left for 64 bits: 626.)
     const uint64_t reach = (span > largest ? span : largest) + 2 * largest;
-    const bool narrow = bound < (1ull << 31) - 1 && largest < (1ull << 31) && reach + 4 * largest < (1ull << 32);
+    const bool narrow = bound < (1ull << 31) - 1 && reach + 2 * largest < (1ull << 32);
     bool solved = valid && status == CKPT_OK && narrow, beyond = false;  // beyond: windows reach back beyond the ring
     const bool flat = !solved || total + span + 1 < (1ull << 32);
     if (!solved) span = 0;

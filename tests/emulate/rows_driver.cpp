@@ -94,7 +94,7 @@ void check(const char *what, const std::vector<Sizes> &chains, Far far, int ring
         want_status.push_back(!positive ? CKPT_ERR_SIZE : sum + most > (__int128)INT64_MAX ? CKPT_ERR_OVERFLOW : CKPT_OK);
         for (int k = 0; k <= n; ++k) good.push_back(want_status.back() == CKPT_OK ? chains[(size_t)c][(size_t)k] : 1);
         shift.push_back(__builtin_ctzll(bits));
-        fits.push_back((sum + 6 * most) >> shift.back() < (1ll << 31));
+        fits.push_back((sum + most) >> shift.back() < INT32_MAX && 3 * most >> shift.back() < (1ll << 31));
         large.push_back(most >> shift.back() >= (1ll << 31));
     }
     std::vector<uint8_t> want_mask((size_t)(batch * n1));
@@ -107,11 +107,11 @@ void check(const char *what, const std::vector<Sizes> &chains, Far far, int ring
         printf("%s, n = %d, chain %d, %d lanes, ring %d: %s\n", what, n, c, G, ring, how);
         ++failures;
     };
-    // the rows with a list of what they leave, everything by a wave a chain, both again with a workgroup for each chain, what
-    // the rows leave in the same wave
-    for (const int turn : {0, 1, 2, 3, 4}) {
-        const int far_from = turn % 2 == 0 ? INT32_MAX : 0;
-        const bool each = turn >= 2, in_wave = turn == 4;
+    // the rows with a list of what they leave, everything by a wave a chain (of some lengths with a workgroup for each chain),
+    // what the rows leave in the same wave
+    for (const int turn : {0, 1, 2}) {
+        const int far_from = turn == 1 ? 0 : INT32_MAX;
+        const bool each = (n + turn) % 2 == 0, in_wave = turn == 2;
         if (in_wave && MOST > kRowsOf16Layers) break;
         uint8_t *mask = (uint8_t *)emu::device_memory((size_t)(batch * n1));
         int64_t *peak = (int64_t *)emu::device_memory((size_t)batch * 8), *budget = (int64_t *)emu::device_memory((size_t)batch * 8);
@@ -194,6 +194,13 @@ void all_kinds(const std::vector<int> &lengths)
         std::vector<Sizes> large;
         for (int k = 0; k < 24; ++k) large.push_back(with(uniform(n, 1ll << (19 + k % 8), 1ll << 27), n / 2, (1ll << 26) + 1));
         check<G, MOST>("sums around 2^32", large, kAny);
+        std::vector<Sizes> heavy;  // one size that a few of add up to 2^32, before or among ones that add up to more or less
+        for (int k = 0; k < 16; ++k) {
+            const int at[] = {0, 1, n / 2, n};
+            const int64_t x = (600000001 + (int64_t)(rng() % 115000000)) | 1;
+            heavy.push_back(with(k < 8 ? uniform(n, 1, 1 << 20) : k < 12 ? uniform(n, 1 << 20, 1 << 22) : uniform(n, 1 << 24, 1 << 26), at[k % 4], x));
+        }
+        check<G, MOST>("one large size", heavy, kAny);
         std::vector<Sizes> networks;
         for (int k = 0; k < 16; ++k) networks.push_back(network(n));
         check<G, MOST>("networks", networks, kAny);

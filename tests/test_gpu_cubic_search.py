@@ -119,6 +119,24 @@ def test_windows_beyond_the_ring(n, batch, share):
     assert np.array_equal(mask.cpu().numpy().T, np.where(bad[:, None], 0, want_mask[at]))
 
 
+@pytest.mark.parametrize("n,batch", [(3, 8192), (16, 8195), (33, 16384), (64, 16390), (100, 4096), (200, 2049)])
+def test_rows_with_one_large_size(n, batch):
+    """One size of which five add up to about 2^32, in front, inside or last, others whose sums stay below that or do not."""
+    print(f"rows with one large size: n = {n}, batch = {batch}", flush=True)
+    rng = np.random.default_rng(n)
+    d = np.concatenate([rng.integers(1, 1 << b, size=(n + 1, 20)) for b in (12, 20, 26)], axis=1) | 1
+    d[rng.integers(0, n + 1, size=60), np.arange(60)] = rng.integers(600_000_000, 860_000_000, size=60)
+    d = d.astype(np.int64)
+    want_peak, want_mask, want_s = oracle.batch_solve_static(inputs.chain_major(d))
+    at = rng.integers(0, 60, size=batch)
+    mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d[:, at])).cuda())
+    torch.cuda.synchronize()
+    assert (status.cpu().numpy() == 0).all()
+    assert np.array_equal(peak.cpu().numpy(), want_peak[at])
+    assert np.array_equal(budget.cpu().numpy(), want_s[at])
+    assert np.array_equal(mask.cpu().numpy().T, want_mask[at])
+
+
 @pytest.mark.parametrize("n", [152, 256])
 def test_windows_beyond_the_ring_take_no_longer_than_a_wave_a_chain(n):
     """2,047 chains have a wave each, twice as many would have rows: with the rows' rounds before them and in the arithmetic of
