@@ -42,7 +42,7 @@ extern __shared__ __align__(16) unsigned char search_lds[];
 // waves.  The loads a cell depends on are issued a cell ahead (the predecessor j-1 always lies in the window
 // and is joined from its register), those that the window's start depends on two.
 // Batches below rows_from(): 4,096 chains of 64 layers of unrounded sizes 124 us, one chain of 152 layers 88 us (129 us with
-// a queue per lane for every budget); 65,536 of 64 layers took 1.28 ms so (31.2), and 0.68 with rows.
+// a queue per lane for every budget); 65,536 of 64 layers took 1.28 ms so (31.2), and 0.66 with rows.
 //
 // Arithmetic.  UB, the cost of a feasible set, bounds the optimum, so a value of F above UB may
 // be cut off at any number above UB: with UB < 2^31 (sizes divided by their common power of two) 32
@@ -789,7 +789,7 @@ __global__ void cubic_search_reset_kernel(SearchWs w) { w.count[threadIdx.x] = 0
 // farthest: 2.8 instead of 1.3 at eight unrounded chains a wave.)  Table, sums and minima are read a block ahead each.
 // What bounds it: issue, about 145 vector and 24 LDS instructions a block of four cells, and the two waves on a SIMD that
 // the LDS space leaves (20 KB a wave at 64 layers); the rounds of a wave are those of its slowest chain (5.3 and 6.4 of 4.5
-// and 5.0).  65,536 chains of 64 layers, unrounded 0.70 ms (a wave a chain: 1.29), aligned 0.55 (1.11).
+// and 5.0).  65,536 chains of 64 layers, unrounded 0.66 ms (a wave a chain: 1.28), aligned 0.54 (1.10).
 constexpr int kRowBlk = 4;
 constexpr int kRowSlots = 4;   // slots of the table per layer
 constexpr int kRowsMaxLayers = 256;  // (a position is a byte of the table)
@@ -803,8 +803,9 @@ __host__ __device__ inline int row_sums(int n) { return (row_blocks(n) + 4) * kR
 __host__ __device__ inline int row_slots(int n) { return n * kRowSlots + 4 * kRowSlots; }
 // Positions whose minima a lane keeps: those of all windows, and of longer chains those of nearly all of most kinds (the windows
 // up to the best cost reach over 37 layers in one of a hundred chains of 64 unrounded layers, over 50 of 128; over 60 in one of
-// ten networks of 128; where the layers in front outweigh the rest, over nearly all: see RowsLeft::kFar).  What it saves is waves in flight: 65,536 aligned chains of 64 layers 756 us with a ring of 64, 557 with
-// 40; 128 layers with 72, 60, 48: aligned 2.0, 1.7, 1.5 ms, networks 2.3, 2.7, 3.6 ms (5.1 and 4.1 with a wave a chain).
+// ten networks of 128; where the layers in front outweigh the rest, over nearly all: see RowsLeft::kFar).  What it saves is
+// waves in flight: 65,536 aligned chains of 64 layers 756 us with a ring of 64, 541 with 40; 128 layers with 72, 60, 48: aligned
+// 2.0, 1.7, 1.5 ms (5.1 with a wave a chain), networks, of which 60 leave one in ten and fewer leave more, 2.2 with 60 (4.1).
 __host__ __device__ inline int row_ring(int n)
 {
     const int most = row_blocks(n) * kRowBlk, a = 32 + n / 8, b = 12 + 3 * n / 8;
@@ -1555,12 +1556,13 @@ hipError_t raise_search_lds_limit()
 // chains that need 64 bits follow in a second one; fewer chains do not fill the chip either way.
 constexpr int64_t kSearchSplitFrom = 1024;
 constexpr int kSearchWideBlocks = 1024;
-// A row of lanes per chain from here on: 8,192 chains of 16, 64 and 128 layers, unrounded 45, 173 and 460 us (a wave a chain:
-// 48, 198, 842), aligned 38, 111, 333 (46, 173, 703); at 4,096 chains the longer ones only, 39, 156, 331 (34, 121, 463), and
-// where a wave a chain leaves a CU three or two waves, beyond 128 layers, at 2,048: of 152 and 256 layers unrounded 448 and
-// 1,207 (599, 1,554), aligned 219 and 399 (335, 844), networks 284 and 469 (330, 758).
-// Eight lanes rather than sixteen where that leaves waves enough, up to the length whose LDS leaves a SIMD two of them:
-// 65,536 aligned chains of 64 layers 552 us (646), of 90 1,030 (907); 8,192 of 64 153 (108).
+// A row of lanes per chain from here on: 8,192 chains of 16, 64 and 128 layers, unrounded 45, 150 and 472 us (a wave a chain:
+// 50, 199, 839), aligned 39, 115, 346 (49, 172, 702); at 4,096 chains the longer ones only, 39, 156, 341 (34, 121, 459), and
+// where a wave a chain leaves a CU three or two waves, beyond 128 layers, at 2,048: of 152 and 256 layers unrounded 460 and
+// 1,221 (598, 1,542), aligned 227 and 413 (331, 846), networks 293 and 479 (331, 759).
+// Eight lanes rather than sixteen where that leaves waves enough, up to 72 layers (a CU holds eight of those waves up to 68,
+// then seven): 65,536 aligned chains of 64 layers 541 us (646), of 72 layers 666 and unrounded 836 (760, 1,025), 16,384 of those
+// 264 and 326 (239, 371); 65,536 aligned of 90 1,030 (907); 8,192 of 64 153 (115).
 constexpr int64_t kRowsOf8From = 16384;
 inline int64_t rows_from(int n) { return n > 128 ? 2048 : n > 96 ? 4096 : 8192; }
 // The share of a batch's chains that are expected to be far from which on waves take them all.  Far chains among others add a
@@ -1577,7 +1579,7 @@ inline int64_t at_once(size_t lds) { return 256 * ((160 << 10) / (int64_t)align_
 // The share of a batch's chains that are expected to be far from which on waves take them all.  Far chains among others add to
 // the rows' time a wave's search, a quarter of what all of them take with four turns of waves; with one in ten of layers in
 // front that outweigh the rest, unrounded others and a share of 1/4, 8,192 chains of 64 layers 280 us, 2,048 of 130 487 (so 201
-// and 360; without rows 198 and 361), 65,536 of 64 1.0 ms (1.27 without rows).
+// and 366; without rows 198 and 360), 65,536 of 64 1.0 ms (1.27 without rows).
 inline float far_share(int64_t batch, int n)
 {
     return (n <= kRowsOf8Layers ? batch < kRowsOf8From : batch <= 4 * at_once(search_lds_bytes(n, 4))) ? 1.0f / 16 : 1.0f / 4;

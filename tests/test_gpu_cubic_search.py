@@ -111,12 +111,13 @@ def test_windows_beyond_the_ring(n, batch, share):
     d = kinds[:, at]
     d[n // 2, 7::1009] = 0
     bad = d.min(0) <= 0
-    mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d)).cuda())
+    major = n in (44, 100)
+    mask, peak, budget, status = B.ckpt_solve_cubic(torch.from_numpy(np.ascontiguousarray(d.T if major else d)).cuda(), chain_major=major)
     torch.cuda.synchronize()
     assert np.array_equal(status.cpu().numpy(), np.where(bad, 3, 0))
     assert np.array_equal(peak.cpu().numpy(), np.where(bad, -1, want_peak[at]))
     assert np.array_equal(budget.cpu().numpy(), np.where(bad, -1, want_s[at]))
-    assert np.array_equal(mask.cpu().numpy().T, np.where(bad[:, None], 0, want_mask[at]))
+    assert np.array_equal(mask.cpu().numpy() if major else mask.cpu().numpy().T, np.where(bad[:, None], 0, want_mask[at]))
 
 
 @pytest.mark.parametrize("n,batch", [(3, 8192), (16, 8195), (33, 16384), (64, 16390), (100, 4096), (200, 2049)])
